@@ -158,6 +158,12 @@ __device__ __forceinline__ int64_t gstride() {
   return int64_t(gridDim.x) * blockDim.x;
 }
 
+// The error latch as other blocks of the running kernel left it (a plain
+// load may be served from a stale line of this die's cache).
+__device__ __forceinline__ int latch_now(const int* err) {
+  return __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // ---- deterministic block reductions ---------------------------------------
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll

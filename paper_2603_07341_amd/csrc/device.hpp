@@ -23,10 +23,12 @@ constexpr uint64_t kEmpty = ~0ull;       // free hash slot
 // further latches kErrTableFull (the step is repeated with a larger
 // table), so every key of a completed table lies within kMaxProbe slots of
 // its home and a lookup can stop there.  At the load factors the host
-// keeps (at most 1/2) sequences this long do not occur; when a set outgrows
-// its estimate the table fills up and the latch fires early instead of
-// after a walk through the whole table.
-constexpr uint64_t kMaxProbe = 4096;
+// keeps (at most 1/2; 0.69 for the densest tuning) the longest sequence of
+// 10^7..10^9 keys is 80..330 slots (ln n / (a - 1 - ln a) at load a), so
+// sequences this long do not occur; when a set outgrows its estimate the
+// table fills up and the latch fires at a load near 0.85 instead of after
+// a walk through the whole table.
+constexpr uint64_t kMaxProbe = 512;
 constexpr uint32_t kCand = 0x80000000u;  // ref names a candidate, not a row
 constexpr uint32_t kNone = 0xFFFFFFFFu;  // no slot / no column
 // Distance byte of a row that is a hole: a row of an in-place step's set
@@ -45,6 +47,7 @@ enum : int {
   kErrCap = 32,        // a realization's new set exceeds the state cap
   kErrChunks = 64,     // a round's frontier needs more candidate chunks
   kErrInput = 128,     // a given key is out of range or repeated
+  kErrOver = 256,      // the rows found so far already exceed the state cap
 };
 
 // Model constants passed by value to every kernel.

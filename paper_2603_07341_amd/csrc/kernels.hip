@@ -384,16 +384,22 @@ __global__ void k_round_prep(StepCtl* ctl, int r, int chunk, int last, int D,
   ctl->r_rows = uint32_t(rows);
   ctl->r_ncand = uint32_t(rows * D);
   ctl->r_ntiles = uint32_t(cdiv(rows * D, kBlock));
-  if (chunk == 0) ctl->r_ncur = ctl->fstart[r];
+  if (chunk == 0) {
+    ctl->r_ncur = ctl->fstart[r];
+    ctl->r_own = ctl->fstart[r];
+  }
   ctl->r_total = 0;
 }
 
 // The chunk's new rows join the set; after the last chunk they close
-// frontier r.
+// frontier r.  More than load_rows rows (0: no limit) latch kErrTableFull:
+// the table can still be enlarged, and a round's inserts or the last
+// lookups in a table beyond that load cost more than the repeated step.
 __global__ void k_round_finish(StepCtl* ctl, int r, int last, int64_t cap,
-                               int* err) {
+                               int64_t load_rows, int* err) {
   if (*err) return;
   int64_t n = int64_t(ctl->r_ncur) + ctl->r_total;
+  if (load_rows > 0 && n > load_rows) atomicOr(err, kErrTableFull);
   if (n > cap) {
     atomicOr(err, kErrCapacity);
     n = cap;
@@ -415,20 +421,28 @@ __global__ void k_round_finish(StepCtl* ctl, int r, int last, int64_t cap,
 //   key owned by c2      c_ref = c2 (column linked after the commit)
 // Candidates are processed in tiles of one block; the owners of each tile
 // are counted into tile_cnt so that new rows are numbered by a scan.
+// row_limit > 0 (state cap): once the rows found so far exceed it, kErrOver
+// is latched.  A block stops at its next tile once anything is latched, so
+// a set that outgrows the table or the cap ends the round there: under a
+// binding cap (4x4x4 lattice, ten-word keys, cap 2e6) the uncut ball's
+// inserts into an overfull table took 0.6-0.9 s per step before.
 constexpr uint32_t kOwner = 0xFFFFFFFEu;
 
 template <int W>
 __global__ void __launch_bounds__(kBlock)
     k_expand_probe(DevModel m, const uint64_t* keys, const uint64_t* pay,
-                   const StepCtl* ctl, int64_t cap, uint64_t* table,
+                   StepCtl* ctl, int64_t row_limit, uint64_t* table,
                    uint64_t mask, uint32_t* c_slot, uint32_t* c_ref,
                    uint32_t* tile_cnt, int32_t* col, int* err) {
+  __shared__ int stop[2];  // latch seen at this tile, by parity of the tile
   if (*err) return;
   const int D = m.D;
   const int64_t f0 = ctl->r_f0, nc = ctl->r_ncand;
   const int64_t ntiles = cdiv(nc, kBlock);
-  for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+  int par = 0;
+  for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x, par ^= 1) {
     const int64_t c = tile * kBlock + threadIdx.x;
+    if (threadIdx.x == 0) stop[par] = latch_now(err);
     uint32_t owner = 0;
     if (c < nc) {
       const int64_t p = f0 + c / D;
@@ -493,7 +507,13 @@ __global__ void __launch_bounds__(kBlock)
     }
     uint32_t tot;
     block_excl_scan(owner, &tot);
-    if (threadIdx.x == 0) tile_cnt[tile] = tot;
+    if (threadIdx.x == 0) {
+      tile_cnt[tile] = tot;
+      if (row_limit > 0 && tot &&
+          int64_t(atomicAdd(&ctl->r_own, tot)) + tot > row_limit)
+        atomicOr(err, kErrOver);
+    }
+    if (stop[par]) return;  // written before the scan's barriers
   }
 }
 
@@ -1347,7 +1367,8 @@ void rehash_rows(const DevModel& m, int Wi, const Side& n, uint32_t* midx,
 void expand_round(const DevModel& m, int Wi, int prec, const Side& n, int r,
                   StepCtl* ctl, int64_t cap, int64_t est, uint64_t* table,
                   uint64_t mask, const RoundBufs& rb, int32_t* col, void* phi,
-                  int chunks, int* err, hipStream_t s) {
+                  int chunks, int64_t row_limit, int64_t load_rows, int* err,
+                  hipStream_t s) {
   const int D = m.D;
   const int64_t nc_bound = std::min<int64_t>(rb.cand_cap, est * D);
   const int g = grid_for(nc_bound);
@@ -1355,8 +1376,8 @@ void expand_round(const DevModel& m, int Wi, int prec, const Side& n, int r,
   const int last = q == chunks - 1 ? 1 : 0;
   k_round_prep<<<1, 1, 0, s>>>(ctl, r, q, last, D, rb.cand_cap, err);
   PACES_DISPATCH_W(Wi, k_expand_probe<WW><<<g, kBlock, 0, s>>>(
-                           m, n.keys, n.pay, ctl, cap, table, mask, rb.c_slot,
-                           rb.c_ref, rb.tile_cnt, col, err));
+                           m, n.keys, n.pay, ctl, row_limit, table, mask,
+                           rb.c_slot, rb.c_ref, rb.tile_cnt, col, err));
   const int gt = tiles_for(cdiv(nc_bound, kBlock));
   k_scan_reduce<<<gt, kBlock, 0, s>>>(rb.tile_cnt, &ctl->r_ntiles, rb.scan_tmp,
                                       err);
@@ -1376,7 +1397,7 @@ void expand_round(const DevModel& m, int Wi, int prec, const Side& n, int r,
                              (float2*)phi, err));
   }
   k_expand_link<<<g, kBlock, 0, s>>>(D, ctl, cap, rb.c_ref, rb.crow, col, err);
-  k_round_finish<<<1, 1, 0, s>>>(ctl, r, last, cap, err);
+  k_round_finish<<<1, 1, 0, s>>>(ctl, r, last, cap, load_rows, err);
   }
 }
 

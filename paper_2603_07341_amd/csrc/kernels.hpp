@@ -42,6 +42,8 @@ struct StepCtl {
   // r_rows) of the frontier; r_ncur the rows of the set so far
   uint32_t r_f0, r_rows, r_ncand, r_ntiles, r_ncur, r_total;
   uint32_t r_need;                    // chunks the largest round needs
+  uint32_t r_own;                     // rows of the set, counted during a
+                                      // round (state cap of one realization)
   uint32_t kmax;                      // largest K over realizations
   uint32_t nrec;                      // steps recorded (R records each)
   // expansion from the previous step's graph (warm.hpp): new states of
@@ -130,10 +132,13 @@ void rehash_rows(const DevModel& m, int Wi, const Side& n, uint32_t* midx,
 // the previous ones added); a frontier larger than that latches kErrChunks
 // with the chunk count it needs in ctl->r_need.
 // est: host estimate of the new set's rows, used only to size grids.
+// row_limit: rows beyond which the round latches kErrOver; load_rows: rows
+// beyond which it latches kErrTableFull (0: no such limit).
 void expand_round(const DevModel& m, int Wi, int prec, const Side& n, int r,
                   StepCtl* ctl, int64_t cap, int64_t est, uint64_t* table,
                   uint64_t mask, const RoundBufs& rb, int32_t* col, void* phi,
-                  int chunks, int* err, hipStream_t s);
+                  int chunks, int64_t row_limit, int64_t load_rows, int* err,
+                  hipStream_t s);
 // Exclusive scan of cnt[0, *ntiles) (at most `bound` entries) into base,
 // the total into *total; tmp holds scan_tmp_words(bound) words.
 void tile_scan(const uint32_t* cnt, const uint32_t* ntiles, int64_t bound,

@@ -326,6 +326,7 @@ struct paces_sim {
   int warm_np = 0;         // partial blocks of the dropped weight
   int warm_nmass = 0;      // the step's folded weight partials
   int64_t nlive = 0;       // live rows of side cur; nS is its row range
+  int64_t nprev = 0;       // live rows before the last step
   bool has_holes = false;  // side cur has holes (nlive < nS)
   uint32_t* dcount = nullptr;  // [1] a count read back by the host
 
@@ -821,6 +822,7 @@ paces_status upload_state(paces_sim* s, int64_t n,
   }
   s->nS = n;
   s->nlive = n;
+  s->nprev = 0;
   s->has_holes = false;
   s->h.n_old = uint32_t(n);
   s->graph_ok = false;  // no columns yet: the next step expands from scratch
@@ -870,6 +872,15 @@ void stage_select(paces_sim* s, bool counted, hipStream_t st,
                s->nS, s->has_holes, s->scan_tmp, s->err, st);
 }
 
+// Rows at which the rounds of an attempt stop because the ball of the full
+// selection is certainly over the state cap (0: no such limit).  One
+// realization only: the first cut's q comes from the last record, so the
+// ball's size is not needed then; an attempt from a cut selection counts
+// its whole ball, which the next q depends on.
+int64_t over_limit(const paces_sim* s, const FrozenStep* fz) {
+  return !fz && !s->cap_active && s->m->R == 1 ? s->p.max_states : 0;
+}
+
 // expand + merge + build of the columns from the previous step's graph, in
 // place: k rounds of the breadth-first search (found states take holes or
 // rows past the range), the new set's sizes with the state-cap check, then
@@ -884,8 +895,8 @@ void stage_expand_warm(paces_sim* s, int64_t est, hipStream_t st) {
   Stage sg(s, PACES_STAGE_EXPAND, st);
   for (int r = 1; r <= k; ++r)
     warm_round(dm, Wi, s->prec, c, r, s->ctl, s->cap, s->nS, est, s->table,
-               s->tmask, s->rb, s->wb, s->scan_tmp, s->vec[s->ipsi], s->err,
-               st);
+               s->tmask, s->rb, s->wb, s->scan_tmp, s->vec[s->ipsi],
+               over_limit(s, nullptr), s->err, st);
   warm_sizes(dm, c, k, s->ctl, est, s->p.max_states, s->ball, s->err, st);
   s->warm_np = warm_commit(dm, Wi, s->prec, c, k, s->ctl, s->nS, est,
                            s->table, s->tmask, s->wb, s->vec[s->ipsi],
@@ -917,10 +928,15 @@ void stage_expand(paces_sim* s, int64_t est, hipStream_t st,
     insert_rows(dm, Wi, s->prec, so, sn, s->midx, s->ctl, s->table, s->tmask,
                 s->cnt, s->vec[s->ipsi], s->vec[s->iphi], s->err, st);
   }
+  // a table that can still be enlarged is left at half load before further
+  // inserts and at three quarters before the last frontier's lookups
+  const bool more = s->tmask < s->tmask_alloc;
+  const int64_t slots = int64_t(s->tmask + 1);
   for (int r = 1; r <= k; ++r)
     expand_round(dm, Wi, s->prec, sn, r, s->ctl, s->cap, est, s->table,
-                 s->tmask, s->rb, sn.col, s->vec[s->iphi], s->chunks, s->err,
-                 st);
+                 s->tmask, s->rb, sn.col, s->vec[s->iphi], s->chunks,
+                 over_limit(s, fz),
+                 !more ? 0 : (r < k ? slots / 2 : slots / 4 * 3), s->err, st);
   lookup_last(dm, Wi, sn, k, s->ctl, est, s->table, s->tmask, sn.col, s->cap,
               s->err, st);
   if (s->p.max_states > 0)
@@ -1341,8 +1357,14 @@ constexpr double kRelayout = 0.1;
 
 // An expansion from scratch probes only as much of the table as the step
 // needs (load factor at most 2^-table_shift for a new set up to the
-// estimate); the table clear costs with it.
+// estimate); the table clear costs with it.  While the set grows by more
+// than half per step (a run's first steps: three- to eightfold), the last
+// step's factor is taken as the next one's: clearing a table too large once
+// costs microseconds, a repeated expansion the whole round again.
 void cold_table_mask(paces_sim* s, int64_t est) {
+  if (s->nprev > 0 && s->nlive > s->nprev + s->nprev / 2)
+    est = std::max(est, std::min(s->cap, s->nlive * std::min<int64_t>(
+                                             s->nlive / s->nprev + 1, 8)));
   uint64_t P = 1024;
   while (P < (uint64_t(est) << s->tune.table_shift) && P <= s->tmask_alloc)
     P <<= 1;
@@ -1431,6 +1453,7 @@ void finish_step(paces_sim* s, const FrozenStep* fz) {
   s->last_warm = s->warm_step;
   s->graph_ok = true;
   s->h = c;
+  s->nprev = s->nlive;
   s->nS = c.n_new;
   s->nlive = s->warm_step ? int64_t(c.n_live) : int64_t(c.n_new);
   s->has_holes = s->nlive < s->nS;
@@ -1472,16 +1495,18 @@ bool warm_after_latch(paces_sim* s, int e, hipStream_t st) {
     std::swap(s->ipsi, s->iphi);
     s->swapped = false;
   }
-  if (e != kErrCap) s->graph_ok = false;
+  if (e != kErrCap && e != kErrOver) s->graph_ok = false;
   return false;
 }
 
-// An attempt from scratch that ran out of rows under the state cap of one
-// realization, before any cut: the capacity holds the cap, so the ball is
-// over it, and the first cut (q from the last record) needs no ball count.
-// The step is cut instead of growing the rows for a ball it will not keep.
+// An attempt whose rows passed the state cap of one realization before any
+// cut (kErrOver), or one from scratch that ran out of rows (the capacity
+// holds the cap, so the ball is over it): the first cut (q from the last
+// record) needs no ball count.  The step is cut instead of growing the rows
+// for a ball it will not keep.
 bool overflow_over_cap(const paces_sim* s, int e, bool was_warm,
                        const FrozenStep* fz) {
+  if (e & kErrOver) return true;
   return e == kErrCapacity && !was_warm && !fz && !s->cap_active &&
          s->m->R == 1 && s->p.max_states > 0 && s->cap >= s->p.max_states;
 }
@@ -1497,7 +1522,9 @@ paces_status handle_latch(paces_sim* s, int e, hipStream_t st) {
   }
   if (e & kErrTableFull) {
     if (s->tmask < s->tmask_alloc) {
-      s->tmask = 2 * s->tmask + 1;
+      // a set that outgrew its estimate: four times the slots, so that one
+      // repeat does where the set grows fivefold in a step
+      s->tmask = std::min(4 * s->tmask + 3, s->tmask_alloc);
       return PACES_OK;
     }
     return grow(s, 2 * s->cap, s->cap + s->cap / 4, st);
@@ -1562,11 +1589,10 @@ paces_status do_step(paces_sim* s, hipStream_t st,
       cold_table_mask(s, est);
       continue;
     }
-    if (overflow_over_cap(s, e, was_warm, fz)) {
+    if (overflow_over_cap(s, e, was_warm, fz))
       ST_TRY(cap_select(s, st, true));
-      continue;
-    }
-    ST_TRY(handle_latch(s, e, st));
+    else
+      ST_TRY(handle_latch(s, e, st));
     if (s->warm_step && !s->graph_ok) {
       s->warm_step = false;
       cold_table_mask(s, est);
@@ -1670,6 +1696,7 @@ paces_status restore_snapshot(paces_sim* s, const Snapshot& z,
   s->h = z.h;
   s->nS = z.n;
   s->nlive = z.n;
+  s->nprev = 0;
   s->has_holes = false;
   s->fresh = z.fresh;
   s->launched = z.launched;
@@ -2594,7 +2621,8 @@ paces_status paces_run_stage(paces_sim* s, int32_t stage, void* hip_stream) {
         ST_TRY(read_latch(s, st, &e));
         if (!e) break;
         drop_pending(s);
-        const int retry = kErrTableFull | kErrCapacity | kErrChunks | kErrCap;
+        const int retry = kErrTableFull | kErrCapacity | kErrChunks |
+                          kErrCap | kErrOver;
         if (attempt >= 40 || (e & ~retry)) {
           s->staged_next = 0;
           return check_latch_code(s, e);

@@ -276,6 +276,7 @@ __global__ void k_warm_prep(StepCtl* ctl, int r, int D, int64_t cand_cap,
   ctl->r_ntiles = uint32_t(cdiv(nc, kBlock));
   ctl->r_ncur = ctl->n_staged;
   ctl->r_total = 0;
+  ctl->r_own = ctl->nM + ctl->n_staged;
 }
 
 // Key of candidate c and its parent's row: a live row (from wlist) or the
@@ -310,18 +311,23 @@ __device__ __forceinline__ bool warm_cand(const DevModel& m,
 // candidate whose compare-and-swap fills an empty slot owns the key (probe
 // distance into c_slot), counted per tile of candidates.  Tombstones are
 // passed over and never claimed, so removing the staged entries restores
-// the table.
+// the table.  row_limit > 0 (state cap): M and the states found so far
+// exceeding it latch kErrOver; a block stops at its next tile once anything
+// is latched (as in the rounds of an expansion from scratch).
 template <int W>
 __global__ void __launch_bounds__(kBlock)
-    k_warm_probe(DevModel m, int r, const StepCtl* ctl, Side c,
+    k_warm_probe(DevModel m, int r, StepCtl* ctl, int64_t row_limit, Side c,
                  const uint32_t* freel, const uint64_t* wlist,
                  uint64_t* table, uint64_t mask, uint32_t* c_slot,
                  uint32_t* c_ref, uint32_t* tile_cnt, int* err) {
+  __shared__ int stop[2];  // latch seen at this tile, by parity of the tile
   if (*err) return;
   const int64_t nc = ctl->r_ncand, noc = ctl->w_noc, f0 = ctl->w_f0;
   const int64_t ntiles = cdiv(nc, kBlock);
-  for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+  int par = 0;
+  for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x, par ^= 1) {
     const int64_t cand = tile * kBlock + threadIdx.x;
+    if (threadIdx.x == 0) stop[par] = latch_now(err);
     uint32_t owner = 0;
     if (cand < nc) {
       uint64_t k[W];
@@ -382,7 +388,13 @@ __global__ void __launch_bounds__(kBlock)
     }
     uint32_t tot;
     block_excl_scan(owner, &tot);
-    if (threadIdx.x == 0) tile_cnt[tile] = tot;
+    if (threadIdx.x == 0) {
+      tile_cnt[tile] = tot;
+      if (row_limit > 0 && tot &&
+          int64_t(atomicAdd(&ctl->r_own, tot)) + tot > row_limit)
+        atomicOr(err, kErrOver);
+    }
+    if (stop[par]) return;  // written before the scan's barriers
   }
 }
 
@@ -665,8 +677,8 @@ void warm_begin(const DevModel& m, StepCtl* ctl, const uint32_t* midx,
 void warm_round(const DevModel& m, int Wi, int prec, const Side& c, int r,
                 StepCtl* ctl, int64_t cap, int64_t n_old, int64_t est,
                 uint64_t* table, uint64_t mask, const RoundBufs& rb,
-                const WarmBufs& wb, uint32_t* scan_tmp, void* psi, int* err,
-                hipStream_t s) {
+                const WarmBufs& wb, uint32_t* scan_tmp, void* psi,
+                int64_t row_limit, int* err, hipStream_t s) {
   const int D = m.D;
   const int go = tiles_for(n_old);
 #define PACES_WARM_OLD(WRITE)                                                 \
@@ -691,8 +703,8 @@ void warm_round(const DevModel& m, int Wi, int prec, const Side& c, int r,
   const int64_t nc_bound = std::min<int64_t>(rb.cand_cap, (n_old + est) * D);
   const int g = grid_for(nc_bound);
   PACES_DISPATCH_W(Wi, k_warm_probe<WW><<<g, kBlock, 0, s>>>(
-                           m, r, ctl, c, wb.freel, wb.wlist, table, mask,
-                           rb.c_slot, rb.c_ref, rb.tile_cnt, err));
+                           m, r, ctl, row_limit, c, wb.freel, wb.wlist, table,
+                           mask, rb.c_slot, rb.c_ref, rb.tile_cnt, err));
   tile_scan(rb.tile_cnt, &ctl->r_ntiles, cdiv(nc_bound, kBlock), rb.scan_tmp,
             rb.tile_base, &ctl->r_total, err, s);
   if (prec == 64) {

@@ -65,12 +65,13 @@ void warm_begin(const DevModel& m, StepCtl* ctl, const uint32_t* midx,
 // table; the first of each new key becomes the state's row (the next hole,
 // else the next row past the range): key, payload, distance kNewRow | r,
 // amplitude 0.  A row past cap latches kErrCapacity; more candidates than
-// the buffers hold latch kErrChunks.
+// the buffers hold latch kErrChunks; M and the found states together
+// beyond row_limit (0: none) latch kErrOver.
 void warm_round(const DevModel& m, int Wi, int prec, const Side& c, int r,
                 StepCtl* ctl, int64_t cap, int64_t n_old, int64_t est,
                 uint64_t* table, uint64_t mask, const RoundBufs& rb,
-                const WarmBufs& wb, uint32_t* scan_tmp, void* psi, int* err,
-                hipStream_t s);
+                const WarmBufs& wb, uint32_t* scan_tmp, void* psi,
+                int64_t row_limit, int* err, hipStream_t s);
 // Sizes after the search: the row range n_new and the live rows n_live;
 // live rows per realization into ball (with max_states > 0, a realization
 // above it latches kErrCap).
