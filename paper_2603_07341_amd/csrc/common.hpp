@@ -238,6 +238,76 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v,
   return base + x - v;
 }
 
+// ---- positions from per-block sums ------------------------------------------
+// A counting kernel runs on at most kSumBlocks blocks, block b over one
+// contiguous run of tiles (tile_run), and leaves one sum per block.  The
+// kernel that needs positions runs on the same grid and adds the sums of
+// the blocks before its own by itself: at most 2048 words, served by the
+// caches, for about 1 us of latency, where a scan between the two took
+// three more launches of 2-7 us each.
+constexpr int kSumBlocks = kMaxSums;
+
+struct TileRun {
+  int64_t t0, t1;
+};
+__device__ __forceinline__ TileRun tile_run(int64_t ntiles, int g) {
+  const int64_t per = cdiv(ntiles, g);
+  const int64_t a = int64_t(blockIdx.x) * per, b = a + per;
+  return {a < ntiles ? a : ntiles, b < ntiles ? b : ntiles};
+}
+__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor((unsigned long long)v, o);
+  return v;
+}
+// Sum of sums[0, b) for every lane; the sum of all g to *total.
+__device__ __forceinline__ uint64_t sums_before(const uint32_t* sums, int g,
+                                                int b, uint64_t* total) {
+  __shared__ uint64_t s[2][kBlock / 64];
+  uint64_t before = 0, all = 0;
+  for (int i = threadIdx.x; i < g; i += kBlock) {
+    const uint32_t v = sums[i];
+    all += v;
+    before += i < b ? v : 0u;
+  }
+  before = wave_sum_u64(before);
+  all = wave_sum_u64(all);
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  __syncthreads();
+  if (lane == 0) {
+    s[0][wid] = before;
+    s[1][wid] = all;
+  }
+  __syncthreads();
+  before = all = 0;
+  for (int w = 0; w < kBlock / 64; ++w) {
+    before += s[0][w];
+    all += s[1][w];
+  }
+  *total = all;
+  return before;
+}
+// Exclusive scan of sums[0, g) into pre (LDS, g entries); returns the total.
+__device__ __forceinline__ uint32_t sums_scan(const uint32_t* sums, int g,
+                                              uint32_t* pre) {
+  uint32_t carry = 0;
+  for (int c = 0; c < g; c += kBlock) {
+    const int i = c + threadIdx.x;
+    uint32_t tot;
+    const uint32_t off = block_excl_scan(i < g ? sums[i] : 0u, &tot) + carry;
+    if (i < g) pre[i] = off;
+    carry += tot;
+  }
+  __syncthreads();
+  return carry;
+}
+// Grid for tiles of `per_tile` items over at most `bound` items.
+inline int sum_grid(int64_t bound, int64_t per_tile) {
+  int64_t g = cdiv(bound, per_tile);
+  if (g < 1) g = 1;
+  return int(g > kSumBlocks ? kSumBlocks : g);
+}
+
 // Per-realization integer counters (deterministic: integer sums commute):
 // LDS bins per block, one global add per nonzero bin.
 __device__ __forceinline__ void count_flush(int R, uint32_t* lds,

@@ -108,8 +108,10 @@ __global__ void __launch_bounds__(kBlock)
   }
 }
 
-__global__ void k_begin_step(StepCtl* ctl, int* err, uint32_t* cnt, int n) {
-  for (int i = threadIdx.x; i < n; i += blockDim.x) cnt[i] = 0u;
+__global__ void k_begin_step(StepCtl* ctl, int* err, uint32_t* cnt,
+                             uint32_t* ball, int R) {
+  for (int i = threadIdx.x; i < 2 * R; i += blockDim.x) cnt[i] = 0u;
+  for (int i = threadIdx.x; i < R; i += blockDim.x) ball[i] = 0u;
   if (threadIdx.x == 0) {
     *err = 0;
     ctl->fstart[0] = 0;
@@ -117,86 +119,22 @@ __global__ void k_begin_step(StepCtl* ctl, int* err, uint32_t* cnt, int n) {
     ctl->n_new = 0;
     ctl->kmax = 0;
     ctl->r_need = 0;
+    ctl->r_own = 0;
+    ctl->c_max = 0;
+    ctl->n_staged = 0;
+    ctl->gstart[0] = 0;
+    ctl->gstart[1] = 0;
+    ctl->nfree = 0;
     ctl->w_moved = 0;  // an in-place step has not committed
-  }
-}
-
-// ---- scan over a device-sized array ----------------------------------------
-// Tile t covers elements [t*kTile, (t+1)*kTile); element t*kTile + q*kBlock
-// + lane belongs to lane `lane` (q = 0..kItems-1), so every load of the block
-// is one contiguous run of kBlock elements.  Blocks stride over tiles.
-__global__ void __launch_bounds__(kBlock)
-    k_scan_reduce(const uint32_t* in, const uint32_t* nptr, uint32_t* bsum,
-                  const int* err) {
-  if (*err) return;
-  const int64_t n = *nptr, ntiles = cdiv(n, kTile);
-  for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-    uint32_t v = 0;
-#pragma unroll
-    for (int q = 0; q < kItems; ++q) {
-      const int64_t e = t * kTile + q * kBlock + threadIdx.x;
-      if (e < n) v += in[e];
-    }
-    uint32_t tot;
-    block_excl_scan(v, &tot);
-    if (threadIdx.x == 0) bsum[t] = tot;
-  }
-}
-
-// Single block: exclusive scan of the tile sums in place; the grand total
-// goes to *out1 (and *out2 when given).  Each lane takes kScanRun
-// consecutive sums per pass, so one pass covers kBlock * kScanRun tiles.
-constexpr int kScanRun = 16;
-__global__ void __launch_bounds__(kBlock)
-    k_scan_bsum(uint32_t* bsum, const uint32_t* nptr, uint32_t* out1,
-                uint32_t* out2, const int* err) {
-  if (*err) return;
-  const int64_t nb = cdiv(int64_t(*nptr), kTile);
-  uint32_t carry = 0;
-  for (int64_t c = 0; c < nb; c += int64_t(kBlock) * kScanRun) {
-    const int64_t e0 = c + int64_t(threadIdx.x) * kScanRun;
-    uint32_t v[kScanRun];
-    uint32_t sum = 0;
-#pragma unroll
-    for (int j = 0; j < kScanRun; ++j) {
-      v[j] = e0 + j < nb ? bsum[e0 + j] : 0u;
-      sum += v[j];
-    }
-    uint32_t tot;
-    uint32_t off = block_excl_scan(sum, &tot) + carry;
-#pragma unroll
-    for (int j = 0; j < kScanRun; ++j) {
-      if (e0 + j < nb) bsum[e0 + j] = off;
-      off += v[j];
-    }
-    carry += tot;
-  }
-  if (threadIdx.x == 0) {
-    *out1 = carry;
-    if (out2) *out2 = carry;
-  }
-}
-
-__global__ void __launch_bounds__(kBlock)
-    k_scan_apply(const uint32_t* in, const uint32_t* nptr,
-                 const uint32_t* bsum, uint32_t* out, const int* err) {
-  if (*err) return;
-  const int64_t n = *nptr, ntiles = cdiv(n, kTile);
-  for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-    uint32_t run = bsum[t];
-#pragma unroll
-    for (int q = 0; q < kItems; ++q) {
-      const int64_t e = t * kTile + q * kBlock + threadIdx.x;
-      const uint32_t v = e < n ? in[e] : 0u;
-      uint32_t tot;
-      const uint32_t off = block_excl_scan(v, &tot) + run;
-      if (e < n) out[e] = off;
-      run += tot;
-    }
+    ctl->w_tomb = 0;
+    ctl->w_drop = 0;
   }
 }
 
 // ---- select -----------------------------------------------------------------
+// A tile is kTile rows; element t*kTile + q*kBlock + lane belongs to lane
+// `lane` (q = 0..kItems-1), so every load of the block is one contiguous run
+// and the bits of a wave's 64 rows are one ballot.
 
 // Rows that are holes (dist == kHole, left by dropped rows of in-place
 // steps) are never selected; dist may be null (no holes).
@@ -204,76 +142,79 @@ __device__ __forceinline__ bool is_hole(const uint8_t* dist, int64_t e) {
   return dist && dist[e] == kHole;
 }
 
-template <typename Amp>
-__global__ void __launch_bounds__(kBlock)
-    k_select_count(const Amp* psi, const uint8_t* dist, const StepCtl* ctl,
-                   double th2, uint32_t* bsum) {
-  const int64_t n = ctl->n_old, ntiles = cdiv(n, kTile);
-  for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-    uint32_t v = 0;
-#pragma unroll
-    for (int q = 0; q < kItems; ++q) {
-      const int64_t e = t * kTile + q * kBlock + threadIdx.x;
-      if (e < n && weight(psi[e]) >= th2 && !is_hole(dist, e)) ++v;
-    }
-    uint32_t tot;
-    block_excl_scan(v, &tot);
-    if (threadIdx.x == 0) bsum[t] = tot;
-  }
+// The bits of the wave's 64 rows from e on (lane 0's row a multiple of 64).
+__device__ __forceinline__ void put_bits(uint64_t* bits, int64_t e, int64_t n,
+                                         bool keep) {
+  const uint64_t b = __ballot(keep);
+  if ((threadIdx.x & 63) == 0 && e < n) bits[e >> 6] = b;
 }
 
-// Selected rows are written in ascending order: tile offset from the scan,
-// then one block scan per run of kBlock rows.
 template <typename Amp>
 __global__ void __launch_bounds__(kBlock)
-    k_select_write(const Amp* psi, const uint8_t* dist, const StepCtl* ctl,
-                   double th2, const uint32_t* bsum, uint32_t* midx) {
-  const int64_t n = ctl->n_old, ntiles = cdiv(n, kTile);
-  for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-    uint32_t run = bsum[t];
+    k_select_bits(const Amp* psi, const uint8_t* dist, const StepCtl* ctl,
+                  double th2, uint64_t* bits, uint32_t* sums) {
+  const int64_t n = ctl->n_old;
+  const TileRun run = tile_run(cdiv(n, kTile), gridDim.x);
+  uint32_t v = 0;
+  for (int64_t t = run.t0; t < run.t1; ++t) {
 #pragma unroll
     for (int q = 0; q < kItems; ++q) {
       const int64_t e = t * kTile + q * kBlock + threadIdx.x;
       const bool keep = e < n && weight(psi[e]) >= th2 && !is_hole(dist, e);
-      uint32_t tot;
-      const uint32_t off = block_excl_scan(keep ? 1u : 0u, &tot) + run;
-      if (keep) midx[off] = uint32_t(e);
-      run += tot;
+      put_bits(bits, e, n, keep);
+      v += keep ? 1u : 0u;
     }
   }
+  uint32_t tot;
+  block_excl_scan(v, &tot);
+  if (threadIdx.x == 0) sums[blockIdx.x] = tot;
 }
 
-// Selection given as one flag per old row (state cap): same tile layout.
+// Selection given as one flag per old row (state cap).
 __global__ void __launch_bounds__(kBlock)
-    k_flag_count(const uint8_t* keep, const StepCtl* ctl, uint32_t* bsum) {
-  const int64_t n = ctl->n_old, ntiles = cdiv(n, kTile);
-  for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-    uint32_t v = 0;
-#pragma unroll
-    for (int q = 0; q < kItems; ++q) {
-      const int64_t e = t * kTile + q * kBlock + threadIdx.x;
-      if (e < n && keep[e]) ++v;
-    }
-    uint32_t tot;
-    block_excl_scan(v, &tot);
-    if (threadIdx.x == 0) bsum[t] = tot;
-  }
-}
-
-__global__ void __launch_bounds__(kBlock)
-    k_flag_write(const uint8_t* keep, const StepCtl* ctl,
-                 const uint32_t* bsum, uint32_t* midx) {
-  const int64_t n = ctl->n_old, ntiles = cdiv(n, kTile);
-  for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-    uint32_t run = bsum[t];
+    k_flag_bits(const uint8_t* keep, const StepCtl* ctl, uint64_t* bits,
+                uint32_t* sums) {
+  const int64_t n = ctl->n_old;
+  const TileRun run = tile_run(cdiv(n, kTile), gridDim.x);
+  uint32_t v = 0;
+  for (int64_t t = run.t0; t < run.t1; ++t) {
 #pragma unroll
     for (int q = 0; q < kItems; ++q) {
       const int64_t e = t * kTile + q * kBlock + threadIdx.x;
       const bool k = e < n && keep[e];
+      put_bits(bits, e, n, k);
+      v += k ? 1u : 0u;
+    }
+  }
+  uint32_t tot;
+  block_excl_scan(v, &tot);
+  if (threadIdx.x == 0) sums[blockIdx.x] = tot;
+}
+
+// The selected rows ascending: the sums of the blocks before, then one block
+// scan per run of kBlock rows.  Reads a bit per row where it read the
+// amplitude before (16 bytes): 43 us of a step at 1.5e7 rows.
+__global__ void __launch_bounds__(kBlock)
+    k_select_write(const uint64_t* bits, StepCtl* ctl, const uint32_t* sums,
+                   uint32_t* midx, const int* err) {
+  if (*err) return;
+  const int64_t n = ctl->n_old;
+  const TileRun run = tile_run(cdiv(n, kTile), gridDim.x);
+  uint64_t total;
+  uint32_t at = uint32_t(sums_before(sums, gridDim.x, blockIdx.x, &total));
+  if (gtid() == 0) {
+    ctl->nM = uint32_t(total);
+    ctl->fstart[1] = uint32_t(total);
+  }
+  for (int64_t t = run.t0; t < run.t1; ++t) {
+#pragma unroll
+    for (int q = 0; q < kItems; ++q) {
+      const int64_t e = t * kTile + q * kBlock + threadIdx.x;
+      const bool k = e < n && ((bits[e >> 6] >> (e & 63)) & 1u);
       uint32_t tot;
-      const uint32_t off = block_excl_scan(k ? 1u : 0u, &tot) + run;
+      const uint32_t off = block_excl_scan(k ? 1u : 0u, &tot) + at;
       if (k) midx[off] = uint32_t(e);
-      run += tot;
+      at += tot;
     }
   }
 }
@@ -320,8 +261,8 @@ __global__ void __launch_bounds__(kBlock)
     k_insert_rows(DevModel m, const uint64_t* keys_o, const uint64_t* pay_o,
                   const uint64_t* tot_o, const uint32_t* midx,
                   const uint32_t* nptr, int64_t n_fixed, uint64_t* keys_n,
-                  uint64_t* pay_n, uint64_t* tot_n, uint64_t* table,
-                  uint64_t mask, uint32_t* cnt_r, const Amp* psi_o, Amp* phi,
+                  uint64_t* pay_n, uint64_t* tot_n, uint8_t* dist_n,
+                  uint64_t* table, uint64_t mask, uint32_t* cnt_r, const Amp* psi_o, Amp* phi,
                   int* err) {
   __shared__ uint32_t bins[kMaxReal];
   if (*err) return;
@@ -341,6 +282,7 @@ __global__ void __launch_bounds__(kBlock)
     } else {
       load_key<W>(keys_n, i, k);
     }
+    if (dist_n) dist_n[i] = 0;
     const uint64_t h = key_hash<W>(m, k);
     const uint64_t mine = (uint64_t(hash_tag(h)) << 32) | uint64_t(i);
     uint64_t s = h & mask;
@@ -360,52 +302,17 @@ __global__ void __launch_bounds__(kBlock)
 }
 
 // ---- expansion round --------------------------------------------------------
-// Parameters of chunk `chunk` of round r: parents [f0 + chunk * per,
-// f0 + (chunk + 1) * per) of frontier r-1 = [f0, f1), per = cand_cap / D.
-// The first chunk starts the row count of the round at fstart[r]; the last
-// one enqueued latches kErrChunks when parents are left over.
-__global__ void k_round_prep(StepCtl* ctl, int r, int chunk, int last, int D,
-                             int64_t cand_cap, int* err) {
-  if (*err) return;
-  const int64_t f0 = ctl->fstart[r - 1], f1 = ctl->fstart[r];
-  const int64_t per = cand_cap / D;
-  const int64_t start = f0 + int64_t(chunk) * per;
-  int64_t rows = f1 - start;
-  if (rows < 0) rows = 0;
-  if (rows > per) {
-    if (last) {
-      atomicOr(err, kErrChunks);
-      const uint32_t need = uint32_t(cdiv(f1 - f0, per));
-      if (need > ctl->r_need) ctl->r_need = need;
-    }
-    rows = per;
-  }
-  ctl->r_f0 = uint32_t(start < f1 ? start : f1);
-  ctl->r_rows = uint32_t(rows);
-  ctl->r_ncand = uint32_t(rows * D);
-  ctl->r_ntiles = uint32_t(cdiv(rows * D, kBlock));
-  if (chunk == 0) {
-    ctl->r_ncur = ctl->fstart[r];
-    ctl->r_own = ctl->fstart[r];
-  }
-  ctl->r_total = 0;
-}
-
-// The chunk's new rows join the set; after the last chunk they close
-// frontier r.  More than load_rows rows (0: no limit) latch kErrTableFull:
-// the table can still be enlarged, and a round's inserts or the last
-// lookups in a table beyond that load cost more than the repeated step.
-__global__ void k_round_finish(StepCtl* ctl, int r, int last, int64_t cap,
-                               int64_t load_rows, int* err) {
-  if (*err) return;
-  int64_t n = int64_t(ctl->r_ncur) + ctl->r_total;
-  if (load_rows > 0 && n > load_rows) atomicOr(err, kErrTableFull);
-  if (n > cap) {
-    atomicOr(err, kErrCapacity);
-    n = cap;
-  }
-  ctl->r_ncur = uint32_t(n);
-  if (last) ctl->fstart[r + 1] = uint32_t(n);
+// Chunk `chunk` of round r: parents [f0, f0 + rows) with f0 = fstart[r-1] +
+// chunk * per, per = cand_cap / D, of frontier r-1 = [fstart[r-1],
+// fstart[r]).  rows > per: parents are left over for further chunks.
+struct Chunk {
+  int64_t f0, rows;
+};
+__device__ __forceinline__ Chunk round_chunk(const StepCtl* ctl, int r,
+                                             int chunk, int64_t per) {
+  const int64_t f1 = ctl->fstart[r];
+  const int64_t start = int64_t(ctl->fstart[r - 1]) + int64_t(chunk) * per;
+  return {start < f1 ? start : f1, start < f1 ? f1 - start : 0};
 }
 
 // Probe: insert-if-absent of candidate c = (parent f0 + c / D, slot c % D).
@@ -417,10 +324,13 @@ __global__ void k_round_finish(StepCtl* ctl, int r, int last, int64_t cap,
 //   structural zero      col = -1
 //   key already a row    col = that row
 //   owner                c_ref = kOwner, c_slot = probe distance of the
-//                        claimed slot from the key's home
-//   key owned by c2      c_ref = c2 (column linked after the commit)
-// Candidates are processed in tiles of one block; the owners of each tile
-// are counted into tile_cnt so that new rows are numbered by a scan.
+//                        claimed slot from the key's home, and the owner's
+//                        rank in its tile << 16
+//   key owned by c2      c_ref = c2 (column linked by the commit)
+// A block takes a contiguous run of tiles of kBlock candidates; tile_base
+// holds the block's owners before the tile, sums the block's owners, so that
+// the commit numbers the new rows without a scan in between (a round was
+// eight launches before, two now).
 // row_limit > 0 (state cap): once the rows found so far exceed it, kErrOver
 // is latched.  A block stops at its next tile once anything is latched, so
 // a set that outgrows the table or the cap ends the round there: under a
@@ -431,27 +341,42 @@ constexpr uint32_t kOwner = 0xFFFFFFFEu;
 template <int W>
 __global__ void __launch_bounds__(kBlock)
     k_expand_probe(DevModel m, const uint64_t* keys, const uint64_t* pay,
-                   StepCtl* ctl, int64_t row_limit, uint64_t* table,
-                   uint64_t mask, uint32_t* c_slot, uint32_t* c_ref,
-                   uint32_t* tile_cnt, int32_t* col, int* err) {
+                   StepCtl* ctl, int r, int chunk, int last, int64_t cand_cap,
+                   int64_t row_limit, uint64_t* table, uint64_t mask,
+                   uint32_t* c_slot, uint32_t* c_ref, uint32_t* tile_base,
+                   uint32_t* sums, int32_t* col, int* err) {
   __shared__ int stop[2];  // latch seen at this tile, by parity of the tile
   if (*err) return;
   const int D = m.D;
-  const int64_t f0 = ctl->r_f0, nc = ctl->r_ncand;
-  const int64_t ntiles = cdiv(nc, kBlock);
+  const int64_t per = cand_cap / D;
+  const Chunk ch = round_chunk(ctl, r, chunk, per);
+  if (ch.rows > per && last) {
+    if (gtid() == 0) {
+      atomicOr(err, kErrChunks);
+      const uint32_t need =
+          uint32_t(cdiv(int64_t(ctl->fstart[r]) - ctl->fstart[r - 1], per));
+      if (need > ctl->r_need) ctl->r_need = need;
+    }
+    return;
+  }
+  const int64_t f0 = ch.f0, nc = (ch.rows < per ? ch.rows : per) * D;
+  if (gtid() == 0 && uint32_t(nc) > ctl->c_max) ctl->c_max = uint32_t(nc);
+  const int64_t nM = ctl->nM;
+  const TileRun run = tile_run(cdiv(nc, kBlock), gridDim.x);
+  uint32_t own = 0;
   int par = 0;
-  for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x, par ^= 1) {
+  for (int64_t tile = run.t0; tile < run.t1; ++tile, par ^= 1) {
     const int64_t c = tile * kBlock + threadIdx.x;
     if (threadIdx.x == 0) stop[par] = latch_now(err);
-    uint32_t owner = 0;
+    uint32_t owner = 0, dist = 0;
     if (c < nc) {
       const int64_t p = f0 + c / D;
       const int s = int(c % D);
-      uint64_t par[W], k[W];
-      load_key<W>(keys, p, par);
+      uint64_t par_k[W], k[W];
+      load_key<W>(keys, p, par_k);
       const uint64_t py = pay[p];
       uint32_t rref = kNone;
-      if (!slot_target<W>(m, par, py, s, k)) {
+      if (!slot_target<W>(m, par_k, py, s, k)) {
         col[p * D + s] = -1;
       } else {
         const uint64_t h = key_hash<W>(m, k);
@@ -469,7 +394,7 @@ __global__ void __launch_bounds__(kBlock)
                                            (unsigned long long)mine);
             if (old == kEmpty) {
               rref = kOwner;
-              c_slot[c] = uint32_t(probes);
+              dist = uint32_t(probes);
               owner = 1;
               done = true;
               break;
@@ -477,10 +402,10 @@ __global__ void __launch_bounds__(kBlock)
             e = old;
           }
           if (uint32_t(e >> 32) == tag) {
-            const uint32_t r = uint32_t(e);
+            const uint32_t rr = uint32_t(e);
             bool same;
-            if (r & kCand) {
-              const int64_t c2 = int64_t(r & ~kCand);
+            if (rr & kCand) {
+              const int64_t c2 = int64_t(rr & ~kCand);
               uint64_t par2[W], k2[W];
               load_key<W>(keys, f0 + c2 / D, par2);
               slot_target<W>(m, par2, pay[f0 + c2 / D], int(c2 % D), k2);
@@ -488,13 +413,13 @@ __global__ void __launch_bounds__(kBlock)
 #pragma unroll
               for (int q = 0; q < W; ++q) same &= (k2[q] == k[q]);
             } else {
-              same = key_eq<W>(k, keys + int64_t(r) * W);
+              same = key_eq<W>(k, keys + int64_t(rr) * W);
             }
             if (same) {
-              if (r & kCand)
-                rref = r & ~kCand;
+              if (rr & kCand)
+                rref = rr & ~kCand;
               else
-                col[p * D + s] = int32_t(r);
+                col[p * D + s] = int32_t(rr);
               done = true;
               break;
             }
@@ -506,60 +431,90 @@ __global__ void __launch_bounds__(kBlock)
       c_ref[c] = rref;
     }
     uint32_t tot;
-    block_excl_scan(owner, &tot);
+    const uint32_t rank = block_excl_scan(owner, &tot);
+    if (owner) c_slot[c] = dist | (rank << 16);
     if (threadIdx.x == 0) {
-      tile_cnt[tile] = tot;
+      tile_base[tile] = own;
       if (row_limit > 0 && tot &&
-          int64_t(atomicAdd(&ctl->r_own, tot)) + tot > row_limit)
+          nM + int64_t(atomicAdd(&ctl->r_own, tot)) + tot > row_limit)
         atomicOr(err, kErrOver);
     }
+    own += tot;
     if (stop[par]) return;  // written before the scan's barriers
   }
+  if (threadIdx.x == 0) sums[blockIdx.x] = own;
 }
 
-// Owners append their key as a new row: row = n_cur + tile base + rank of
-// the owner inside its tile.  The table slot is pointed at the row.
+// Owners append their key as a new row: row = rows so far + owners of the
+// blocks before + owners of the tiles before + rank in the tile; the table
+// slot is pointed at the row.  A candidate whose key another one owns takes
+// that one's row.  Same grid as the probe.  Block 0 closes the chunk (after
+// the last one, frontier r); more than load_rows rows (0: no limit) latch
+// kErrTableFull: the table can still be enlarged, and a round's inserts or
+// the last lookups in a table beyond that load cost more than the repeated
+// step.
 template <int W, typename Amp>
 __global__ void __launch_bounds__(kBlock)
-    k_expand_commit(DevModel m, uint64_t* keys, uint64_t* pay, uint64_t* tot,
-                    const StepCtl* ctl, int64_t cap, uint64_t* table,
-                    uint64_t mask, const uint32_t* c_slot, const uint32_t* c_ref,
-                    const uint32_t* tile_base, uint32_t* crow, int32_t* col,
-                    Amp* phi, int* err) {
+    k_expand_commit(DevModel m, Side n, StepCtl* ctl, int r, int chunk,
+                    int last, int64_t cand_cap, int64_t cap, int64_t load_rows,
+                    uint64_t* table, uint64_t mask, const uint32_t* c_slot,
+                    const uint32_t* c_ref, const uint32_t* tile_base,
+                    const uint32_t* sums, int32_t* col, Amp* phi, int* err) {
+  __shared__ uint32_t pre[kSumBlocks];
   if (*err) return;
   const int D = m.D;
-  const int64_t f0 = ctl->r_f0, nc = ctl->r_ncand, n_cur = ctl->r_ncur;
-  const int64_t ntiles = cdiv(nc, kBlock);
-  for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+  const int64_t per = cand_cap / D;
+  const Chunk ch = round_chunk(ctl, r, chunk, per);
+  const int64_t f0 = ch.f0, nc = (ch.rows < per ? ch.rows : per) * D;
+  const int64_t n_cur = chunk == 0 ? ctl->fstart[r] : ctl->r_cur[chunk & 1];
+  const int64_t ntiles = cdiv(nc, kBlock), tiles_per = cdiv(ntiles, gridDim.x);
+  const uint32_t total = sums_scan(sums, gridDim.x, pre);
+  if (gtid() == 0) {
+    int64_t now = n_cur + total;
+    if (load_rows > 0 && now > load_rows) atomicOr(err, kErrTableFull);
+    if (now > cap) {
+      atomicOr(err, kErrCapacity);
+      now = cap;
+    }
+    ctl->r_cur[(chunk + 1) & 1] = uint32_t(now);
+    if (last) ctl->fstart[r + 1] = uint32_t(now);
+  }
+  const TileRun run = tile_run(ntiles, gridDim.x);
+  for (int64_t tile = run.t0; tile < run.t1; ++tile) {
     const int64_t c = tile * kBlock + threadIdx.x;
-    const bool own = c < nc && c_ref[c] == kOwner;
-    uint32_t tot_in_tile;
-    const uint32_t rank = block_excl_scan(own ? 1u : 0u, &tot_in_tile);
-    if (!own) continue;
+    if (c >= nc) continue;
+    const uint32_t ref = c_ref[c];
+    if (ref == kNone) continue;
     const int64_t p = f0 + c / D;
     const int s = int(c % D);
-    const int64_t row = n_cur + tile_base[tile] + rank;
-    if (row >= cap) {
-      atomicOr(err, kErrCapacity);
-      crow[c] = kNone;
+    if (ref != kOwner) {
+      const int64_t t2 = int64_t(ref) / kBlock;
+      const int64_t row = n_cur + pre[t2 / tiles_per] + tile_base[t2] +
+                          (c_slot[ref] >> 16);
+      col[p * D + s] = row < cap ? int32_t(row) : -1;
+      continue;
+    }
+    const uint32_t sl = c_slot[c];
+    const int64_t row = n_cur + pre[blockIdx.x] + tile_base[tile] + (sl >> 16);
+    if (row >= cap) {  // latched by block 0
       col[p * D + s] = -1;
       continue;
     }
     uint64_t par[W], k[W];
-    load_key<W>(keys, p, par);
-    const uint64_t py = pay[p];
+    load_key<W>(n.keys, p, par);
+    const uint64_t py = n.pay[p];
     slot_target<W>(m, par, py, s, k);
-    store_key<W>(keys, row, k);
+    store_key<W>(n.keys, row, k);
     uint64_t np, nt;
-    slot_row_info<W>(m, k, py, tot[p], s, np, nt);
-    pay[row] = np;
-    tot[row] = nt;
+    slot_row_info<W>(m, k, py, n.tot[p], s, np, nt);
+    n.pay[row] = np;
+    n.tot[row] = nt;
+    n.dist[row] = uint8_t(r);
     // the slot holds (tag | candidate); the tag and the home follow from
     // the key, so the entry is rewritten without reading it back
     const uint64_t h = key_hash<W>(m, k);
-    table[((h & mask) + c_slot[c]) & mask] =
+    table[((h & mask) + (sl & 0xFFFFu)) & mask] =
         (uint64_t(hash_tag(h)) << 32) | uint64_t(row);
-    crow[c] = uint32_t(row);
     col[p * D + s] = int32_t(row);
     Amp z;
     z.x = 0;
@@ -568,31 +523,23 @@ __global__ void __launch_bounds__(kBlock)
   }
 }
 
-// Candidates whose key another candidate owns take that candidate's row.
-__global__ void __launch_bounds__(kBlock)
-    k_expand_link(int D, const StepCtl* ctl, int64_t cap, const uint32_t* c_ref,
-                  const uint32_t* crow, int32_t* col, const int* err) {
-  if (*err) return;
-  const int64_t f0 = ctl->r_f0, nc = ctl->r_ncand;
-  for (int64_t c = gtid(); c < nc; c += gstride()) {
-    const uint32_t r = c_ref[c];
-    if (r >= kOwner) continue;  // kOwner or kNone
-    const uint32_t row = crow[r];
-    col[f0 * D + c] = row == kNone ? -1 : int32_t(row);
-  }
-}
-
 template <int W>
 __global__ void __launch_bounds__(kBlock)
     k_lookup_cols(DevModel m, const uint64_t* keys, const uint64_t* pay,
                   StepCtl* ctl, int k, const uint64_t* table, uint64_t mask,
-                  int32_t* col, int64_t cap, const int* err) {
+                  int32_t* col, int64_t max_states, uint32_t* ball, int* err) {
   if (*err) return;
   const int D = m.D;
   const int64_t f0 = ctl->fstart[k];
   const int64_t f1 = ctl->fstart[k + 1];
   const int64_t nc = (f1 - f0) * D;
-  if (gtid() == 0) ctl->n_new = uint32_t(f1);
+  if (gtid() == 0) {
+    ctl->n_new = uint32_t(f1);
+    if (max_states > 0) {
+      ball[0] = uint32_t(f1);
+      if (f1 > max_states) atomicOr(err, kErrCap);
+    }
+  }
   for (int64_t c = gtid(); c < nc; c += gstride()) {
     const int64_t p = f0 + c / D;
     const int s = int(c % D);
@@ -1015,19 +962,20 @@ constexpr int kRegBins = 16;
 
 // Norm, exciton populations, row counts and (batched) energy of psi per
 // realization as per-block partials.  Rows are visited in the select
-// kernels' tile layout, so the same pass also counts, per tile, the rows
-// the next step will select.
+// kernels' tile layout, so the same pass also leaves the next step's
+// selection (bits and per-block sums).
 template <typename R>
 __global__ void __launch_bounds__(kBlock)
     k_pop_norm(int N, int Rn, double th2, const StepCtl* ctl,
                const typename VecT<R>::T* psi, const uint64_t* pay,
                const uint8_t* dist,
                const double* e_row, double* n2_part, double* en_part,
-               double* pop_part, uint32_t* sel_bsum, uint32_t* cnt_s,
-               const int* err) {
+               double* pop_part, uint64_t* sel_bits, uint32_t* sel_sums,
+               uint32_t* cnt_s, const int* err) {
   extern __shared__ double lds[];
   if (*err) return;
-  const int64_t n = ctl->n_new, ntiles = cdiv(n, kTile);
+  const int64_t n = ctl->n_new;
+  const TileRun run = tile_run(cdiv(n, kTile), gridDim.x);
   const bool priv = Rn == 1 && N <= kPrivBins;
   // up to kRegBins sites: each thread sums its rows' weights per site in
   // registers and adds them to its lane's LDS bins once at the end
@@ -1048,16 +996,16 @@ __global__ void __launch_bounds__(kBlock)
   }
   __syncthreads();
   double n2 = 0;
-  uint32_t rows = 0;
-  for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-    uint32_t keep = 0;
+  uint32_t rows = 0, kept = 0;
+  for (int64_t t = run.t0; t < run.t1; ++t) {
 #pragma unroll
     for (int q = 0; q < kItems; ++q) {
       const int64_t e = t * kTile + q * kBlock + threadIdx.x;
+      bool keep = false;
       if (e < n && !is_hole(dist, e)) {
         const double w = weight(psi[e]);
         const uint64_t p = pay[e];
-        keep += w >= th2 ? 1u : 0u;
+        keep = w >= th2;
         if (Rn == 1) {
           n2 += w;
           ++rows;
@@ -1078,10 +1026,14 @@ __global__ void __launch_bounds__(kBlock)
           if (e_row) atomicAdd(&en_lds[r], e_row[e]);
         }
       }
+      put_bits(sel_bits, e, n, keep);
+      kept += keep ? 1u : 0u;
     }
+  }
+  {
     uint32_t tot;
-    block_excl_scan(keep, &tot);
-    if (threadIdx.x == 0) sel_bsum[t] = tot;
+    block_excl_scan(kept, &tot);
+    if (threadIdx.x == 0) sel_sums[blockIdx.x] = tot;
   }
   if (regs) {
 #pragma unroll
@@ -1270,7 +1222,7 @@ int supported_words(int W) {
   return 0;
 }
 
-int64_t scan_tmp_words(int64_t n) { return cdiv(n, kTile) + 16; }
+int64_t sel_bit_words(int64_t n) { return cdiv(n, 64) + 1; }
 
 void fill_u64(uint64_t* p, int64_t n, uint64_t v, hipStream_t s) {
   if (n <= 0) return;
@@ -1299,129 +1251,100 @@ void check_set(const DevModel& m, int Wi, const uint64_t* keys, int64_t n,
                            m, keys, n, table, mask, err));
 }
 
-void begin_step(StepCtl* ctl, int* err, uint32_t* cnt, int R,
+void begin_step(StepCtl* ctl, int* err, uint32_t* cnt, uint32_t* ball, int R,
                 hipStream_t s) {
-  k_begin_step<<<1, kBlock, 0, s>>>(ctl, err, cnt, 2 * R);
+  k_begin_step<<<1, kBlock, 0, s>>>(ctl, err, cnt, ball, R);
 }
 
-void select_rows(int prec, const void* psi, const uint8_t* dist, double th2,
-                 bool select_all, bool counted, StepCtl* ctl, uint32_t* midx,
-                 uint32_t* tmp, int64_t cap, int* err, hipStream_t s) {
-  if (select_all) {
-    k_select_all<<<grid_for(cap), kBlock, 0, s>>>(ctl, midx);
-    return;
-  }
-  const int g = tiles_for(cap);
-  if (!counted) {
-    if (prec == 64)
-      k_select_count<double2><<<g, kBlock, 0, s>>>((const double2*)psi, dist, ctl, th2, tmp);
-    else
-      k_select_count<float2><<<g, kBlock, 0, s>>>((const float2*)psi, dist, ctl, th2, tmp);
-  }
-  k_scan_bsum<<<1, kBlock, 0, s>>>(tmp, &ctl->n_old, &ctl->nM, &ctl->fstart[1],
-                                   err);
+int select_bits(int prec, const void* psi, const uint8_t* dist, double th2,
+                const StepCtl* ctl, const Sums& sm, int64_t n, hipStream_t s) {
+  const int g = sum_grid(n, kTile);
   if (prec == 64)
-    k_select_write<double2><<<g, kBlock, 0, s>>>((const double2*)psi, dist, ctl, th2, tmp, midx);
+    k_select_bits<double2><<<g, kBlock, 0, s>>>((const double2*)psi, dist, ctl,
+                                                th2, sm.bits, sm.sel);
   else
-    k_select_write<float2><<<g, kBlock, 0, s>>>((const float2*)psi, dist, ctl, th2, tmp, midx);
+    k_select_bits<float2><<<g, kBlock, 0, s>>>((const float2*)psi, dist, ctl,
+                                               th2, sm.bits, sm.sel);
+  return g;
 }
 
-void select_flags(const uint8_t* keep, StepCtl* ctl, uint32_t* midx,
-                  uint32_t* tmp, int64_t cap, int* err, hipStream_t s) {
-  const int g = tiles_for(cap);
-  k_flag_count<<<g, kBlock, 0, s>>>(keep, ctl, tmp);
-  k_scan_bsum<<<1, kBlock, 0, s>>>(tmp, &ctl->n_old, &ctl->nM, &ctl->fstart[1],
-                                   err);
-  k_flag_write<<<g, kBlock, 0, s>>>(keep, ctl, tmp, midx);
+int flag_bits(const uint8_t* keep, const StepCtl* ctl, const Sums& sm,
+              int64_t n, hipStream_t s) {
+  const int g = sum_grid(n, kTile);
+  k_flag_bits<<<g, kBlock, 0, s>>>(keep, ctl, sm.bits, sm.sel);
+  return g;
+}
+
+void select_write(StepCtl* ctl, const Sums& sm, int grid, uint32_t* midx,
+                  const int* err, hipStream_t s) {
+  k_select_write<<<grid, kBlock, 0, s>>>(sm.bits, ctl, sm.sel, midx, err);
+}
+
+void select_all(StepCtl* ctl, uint32_t* midx, int64_t n, hipStream_t s) {
+  k_select_all<<<grid_for(n), kBlock, 0, s>>>(ctl, midx);
 }
 
 void insert_rows(const DevModel& m, int Wi, int prec, const Side& o,
                  const Side& n, const uint32_t* midx, const StepCtl* ctl,
-                 uint64_t* table, uint64_t mask, uint32_t* cnt_m,
-                 const void* psi_o, void* phi, int* err, hipStream_t s) {
-  const int g = grid_for(int64_t(mask + 1) / 2);
+                 int64_t bound, uint64_t* table, uint64_t mask,
+                 uint32_t* cnt_m, const void* psi_o, void* phi, int* err,
+                 hipStream_t s) {
+  const int g = grid_for(bound);
   if (prec == 64) {
     PACES_DISPATCH_W(Wi, k_insert_rows<WW, double2><<<g, kBlock, 0, s>>>(
                              m, o.keys, o.pay, o.tot, midx, &ctl->nM, 0,
-                             n.keys, n.pay, n.tot, table, mask, cnt_m,
+                             n.keys, n.pay, n.tot, n.dist, table, mask, cnt_m,
                              (const double2*)psi_o, (double2*)phi, err));
   } else {
     PACES_DISPATCH_W(Wi, k_insert_rows<WW, float2><<<g, kBlock, 0, s>>>(
                              m, o.keys, o.pay, o.tot, midx, &ctl->nM, 0,
-                             n.keys, n.pay, n.tot, table, mask, cnt_m,
+                             n.keys, n.pay, n.tot, n.dist, table, mask, cnt_m,
                              (const float2*)psi_o, (float2*)phi, err));
   }
 }
 
-void rehash_rows(const DevModel& m, int Wi, const Side& n, uint32_t* midx,
-                 int64_t rows, uint64_t* table, uint64_t mask, int* err,
-                 hipStream_t s) {
-  (void)midx;
+void rehash_rows(const DevModel& m, int Wi, const Side& n, int64_t rows,
+                 uint64_t* table, uint64_t mask, int* err, hipStream_t s) {
   if (rows <= 0) return;
   PACES_DISPATCH_W(Wi, k_insert_rows<WW, double2><<<grid_for(rows), kBlock, 0, s>>>(
                            m, nullptr, nullptr, nullptr, nullptr, nullptr,
-                           rows, n.keys, n.pay, n.tot, table, mask, nullptr,
-                           nullptr, nullptr, err));
+                           rows, n.keys, n.pay, n.tot, n.dist, table, mask,
+                           nullptr, nullptr, nullptr, err));
 }
 
 void expand_round(const DevModel& m, int Wi, int prec, const Side& n, int r,
                   StepCtl* ctl, int64_t cap, int64_t est, uint64_t* table,
-                  uint64_t mask, const RoundBufs& rb, int32_t* col, void* phi,
-                  int chunks, int64_t row_limit, int64_t load_rows, int* err,
-                  hipStream_t s) {
-  const int D = m.D;
-  const int64_t nc_bound = std::min<int64_t>(rb.cand_cap, est * D);
-  const int g = grid_for(nc_bound);
+                  uint64_t mask, const RoundBufs& rb, const Sums& sm,
+                  int32_t* col, void* phi, int chunks, int64_t row_limit,
+                  int64_t load_rows, int* err, hipStream_t s) {
+  const int g = sum_grid(std::min<int64_t>(rb.cand_cap, est * m.D), kBlock);
   for (int q = 0; q < chunks; ++q) {
-  const int last = q == chunks - 1 ? 1 : 0;
-  k_round_prep<<<1, 1, 0, s>>>(ctl, r, q, last, D, rb.cand_cap, err);
-  PACES_DISPATCH_W(Wi, k_expand_probe<WW><<<g, kBlock, 0, s>>>(
-                           m, n.keys, n.pay, ctl, row_limit, table, mask,
-                           rb.c_slot, rb.c_ref, rb.tile_cnt, col, err));
-  const int gt = tiles_for(cdiv(nc_bound, kBlock));
-  k_scan_reduce<<<gt, kBlock, 0, s>>>(rb.tile_cnt, &ctl->r_ntiles, rb.scan_tmp,
-                                      err);
-  k_scan_bsum<<<1, kBlock, 0, s>>>(rb.scan_tmp, &ctl->r_ntiles, &ctl->r_total,
-                                   nullptr, err);
-  k_scan_apply<<<gt, kBlock, 0, s>>>(rb.tile_cnt, &ctl->r_ntiles, rb.scan_tmp,
-                                     rb.tile_base, err);
-  if (prec == 64) {
-    PACES_DISPATCH_W(Wi, k_expand_commit<WW, double2><<<g, kBlock, 0, s>>>(
-                             m, n.keys, n.pay, n.tot, ctl, cap, table, mask,
-                             rb.c_slot, rb.c_ref, rb.tile_base, rb.crow, col,
-                             (double2*)phi, err));
-  } else {
-    PACES_DISPATCH_W(Wi, k_expand_commit<WW, float2><<<g, kBlock, 0, s>>>(
-                             m, n.keys, n.pay, n.tot, ctl, cap, table, mask,
-                             rb.c_slot, rb.c_ref, rb.tile_base, rb.crow, col,
-                             (float2*)phi, err));
+    const int last = q == chunks - 1 ? 1 : 0;
+    PACES_DISPATCH_W(Wi, k_expand_probe<WW><<<g, kBlock, 0, s>>>(
+                             m, n.keys, n.pay, ctl, r, q, last, rb.cand_cap,
+                             row_limit, table, mask, rb.c_slot, rb.c_ref,
+                             rb.tile_base, sm.own, col, err));
+    if (prec == 64) {
+      PACES_DISPATCH_W(Wi, k_expand_commit<WW, double2><<<g, kBlock, 0, s>>>(
+                               m, n, ctl, r, q, last, rb.cand_cap, cap,
+                               load_rows, table, mask, rb.c_slot, rb.c_ref,
+                               rb.tile_base, sm.own, col, (double2*)phi, err));
+    } else {
+      PACES_DISPATCH_W(Wi, k_expand_commit<WW, float2><<<g, kBlock, 0, s>>>(
+                               m, n, ctl, r, q, last, rb.cand_cap, cap,
+                               load_rows, table, mask, rb.c_slot, rb.c_ref,
+                               rb.tile_base, sm.own, col, (float2*)phi, err));
+    }
   }
-  k_expand_link<<<g, kBlock, 0, s>>>(D, ctl, cap, rb.c_ref, rb.crow, col, err);
-  k_round_finish<<<1, 1, 0, s>>>(ctl, r, last, cap, load_rows, err);
-  }
-}
-
-void tile_scan(const uint32_t* cnt, const uint32_t* ntiles, int64_t bound,
-               uint32_t* tmp, uint32_t* base, uint32_t* total, int* err,
-               hipStream_t s) {
-  const int gt = tiles_for(bound);
-  k_scan_reduce<<<gt, kBlock, 0, s>>>(cnt, ntiles, tmp, err);
-  k_scan_bsum<<<1, kBlock, 0, s>>>(tmp, ntiles, total, nullptr, err);
-  k_scan_apply<<<gt, kBlock, 0, s>>>(cnt, ntiles, tmp, base, err);
-}
-
-void tile_sums_scan(uint32_t* bsum, const uint32_t* nrows, uint32_t* total,
-                    int* err, hipStream_t s) {
-  k_scan_bsum<<<1, kBlock, 0, s>>>(bsum, nrows, total, nullptr, err);
 }
 
 void lookup_last(const DevModel& m, int Wi, const Side& n, int k,
                  StepCtl* ctl, int64_t est, const uint64_t* table,
-                 uint64_t mask, int32_t* col, int64_t cap, int* err,
-                 hipStream_t s) {
+                 uint64_t mask, int32_t* col, int64_t max_states,
+                 uint32_t* ball, int* err, hipStream_t s) {
   PACES_DISPATCH_W(Wi, k_lookup_cols<WW><<<grid_for(est * m.D), kBlock, 0, s>>>(
-                           m, n.keys, n.pay, ctl, k, table, mask, col, cap,
-                           err));
+                           m, n.keys, n.pay, ctl, k, table, mask, col,
+                           max_states, ball, err));
 }
 
 int part_grid(int64_t rows) { return grid_for(rows); }
@@ -1529,7 +1452,7 @@ int pop_norm(int prec, int N, int R, double th2, int64_t est,
              const StepCtl* ctl, const void* psi, const uint64_t* pay,
              const uint8_t* dist,
              const double* e_row, double* n2_part, double* en_part,
-             double* pop_part, uint32_t* sel_bsum, uint32_t* cnt_s, int* err,
+             double* pop_part, const Sums& sm, uint32_t* cnt_s, int* err,
              hipStream_t s) {
   const bool priv = R == 1 && N <= kPrivBins;
   const size_t lds = sizeof(double) * ((priv ? N * 64 : R * N) + 3 * R);
@@ -1540,11 +1463,11 @@ int pop_norm(int prec, int N, int R, double th2, int64_t est,
   if (prec == 64)
     k_pop_norm<double><<<g, kBlock, lds, s>>>(
         N, R, th2, ctl, (const double2*)psi, pay, dist, e_row, n2_part, en_part,
-        pop_part, sel_bsum, cnt_s, err);
+        pop_part, sm.bits, sm.sel, cnt_s, err);
   else
     k_pop_norm<float><<<g, kBlock, lds, s>>>(
         N, R, th2, ctl, (const float2*)psi, pay, dist, e_row, n2_part, en_part,
-        pop_part, sel_bsum, cnt_s, err);
+        pop_part, sm.bits, sm.sel, cnt_s, err);
   return g;
 }
 

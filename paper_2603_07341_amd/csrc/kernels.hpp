@@ -19,6 +19,7 @@ constexpr int kPartBlocks = 2048;  // grid of the population reduction
 constexpr int kMaxPartials = 1 << 18;  // per-block partials of row kernels
 constexpr int kObsFields = 12;
 constexpr int kMaxReal = 256;      // disorder realizations per sim
+constexpr int kMaxSums = 2048;     // blocks of a kernel that leaves sums
 
 // Chebyshev expansion of exp(-i H dt) on [E_min, E_max], computed on the
 // device from the Gershgorin bounds of the step.
@@ -38,38 +39,45 @@ struct StepCtl {
   uint32_t nM;                        // selected rows
   uint32_t fstart[kMaxRounds + 2];    // frontier r: [fstart[r], fstart[r+1])
   uint32_t n_new;                     // rows of the new set
-  // current chunk of the current expansion round: parents [r_f0, r_f0 +
-  // r_rows) of the frontier; r_ncur the rows of the set so far
-  uint32_t r_f0, r_rows, r_ncand, r_ntiles, r_ncur, r_total;
-  uint32_t r_need;                    // chunks the largest round needs
-  uint32_t r_own;                     // rows of the set, counted during a
-                                      // round (state cap of one realization)
+  // expansion from scratch: rows of the set before chunk q of a round
+  // (q > 0) in r_cur[q & 1]; chunks the largest round needs
+  uint32_t r_cur[2], r_need;
+  uint32_t r_own;                     // states found so far, counted while a
+                                      // round runs (state cap of one
+                                      // realization only)
+  uint32_t c_max;                     // candidates of the largest round
   uint32_t kmax;                      // largest K over realizations
   uint32_t nrec;                      // steps recorded (R records each)
-  // expansion from the previous step's graph (warm.hpp): new states of
-  // round r are rows [gstart[r], gstart[r+1]) of the new set; w_noc
-  // candidates of the round come from old rows, the rest from the new
-  // states of the round before (first row w_f0); w_nkeep old rows stay;
-  // w_moved is set once the hash table holds the new rows; w_tomb counts
-  // the table entries of dropped rows turned into tombstones by this step
+  // expansion from the previous step's graph (warm.hpp): states found in
+  // round r are numbers [gstart[r], gstart[r+1]) of the n_staged found in
+  // all; the current round has r_ncand candidates, the first w_noc of them
+  // from old rows; w_moved is set once the step has committed; w_tomb
+  // counts the table entries of dropped rows turned into tombstones by this
+  // step, w_drop the rows dropped
   uint32_t gstart[kMaxRounds + 2];
-  uint32_t n_staged, w_noc, w_f0, w_nkeep, w_moved, w_tomb;
+  uint32_t n_staged, r_ncand, w_noc, w_moved, w_tomb, w_drop;
   // in-place steps: holes of the set at the step's start (the free list's
-  // length) and the set's live rows after the step (n_new is its row range)
-  uint32_t nfree, n_live;
+  // length); n_new is the set's row range
+  uint32_t nfree;
   double t;                           // time after the last completed step
 };
 
 // Buffers of one expansion round.
 struct RoundBufs {
-  uint32_t* c_slot;     // [cand] probe distance of owning candidates from
-                        // the key's home slot (below kMaxProbe)
+  uint32_t* c_slot;     // [cand] of an owning candidate: probe distance from
+                        // the key's home slot (below kMaxProbe); from
+                        // scratch also its rank in its tile << 16
   uint32_t* c_ref;      // [cand] outcome of the probe
-  uint32_t* crow;       // [cand] row of owning candidates
-  uint32_t* tile_cnt;   // [cand / 256] owners per tile of candidates
-  uint32_t* tile_base;  // [cand / 256] exclusive scan of tile_cnt
-  uint32_t* scan_tmp;
+  uint32_t* tile_base;  // [cand / 256] owners of the block before the tile
   int64_t cand_cap;     // candidates the buffers hold
+};
+
+// Per-block sums of the counting kernels (kSumBlocks words each), kept
+// apart where two are in use at a time, and one bit per row: the next
+// step's selection.
+struct Sums {
+  uint32_t *sel, *hole, *old_, *own, *rows;
+  uint64_t* bits;
 };
 
 // Row arrays of one set.  col (ELL columns, D per row) and dist (distance
@@ -84,7 +92,8 @@ struct Side {
 };
 
 int supported_words(int W);  // internal word count >= W, or 0
-int64_t scan_tmp_words(int64_t n);
+// Words of the selection's bits for n rows.
+int64_t sel_bit_words(int64_t n);
 
 void fill_u64(uint64_t* p, int64_t n, uint64_t v, hipStream_t s);
 // One empty dispatch (kernel k_mark) on the stream.
@@ -103,31 +112,37 @@ void check_set(const DevModel& m, int Wi, const uint64_t* keys, int64_t n,
                hipStream_t s);
 
 // Start of a step: clear the latch, reset the counters (cnt: 2R
-// per-realization row counts, |M_r| then |S_r|).
-void begin_step(StepCtl* ctl, int* err, uint32_t* cnt, int R, hipStream_t s);
-// Rows of ctl->n_old with weight >= th2 that are not holes (dist may be
-// null), ascending, into midx; ctl->nM.
-// select_all: the first step takes every row.
-// counted: tmp already holds the per-tile counts (from pop_norm).
-void select_rows(int prec, const void* psi, const uint8_t* dist, double th2,
-                 bool select_all, bool counted, StepCtl* ctl, uint32_t* midx,
-                 uint32_t* tmp, int64_t cap, int* err, hipStream_t s);
-// Rows of ctl->n_old with keep[row] != 0, ascending, into midx; ctl->nM.
-void select_flags(const uint8_t* keep, StepCtl* ctl, uint32_t* midx,
-                  uint32_t* tmp, int64_t cap, int* err, hipStream_t s);
+// per-realization row counts, |M_r| then |S_r|; ball: R).
+void begin_step(StepCtl* ctl, int* err, uint32_t* cnt, uint32_t* ball, int R,
+                hipStream_t s);
+// The selection over rows [0, ctl->n_old) as bits and per-block sums
+// (pop_norm leaves the same for the next step): rows with weight >= th2
+// that are not holes (dist may be null), or rows with keep[row] != 0.
+// n: bound of the row count for the grid, which is returned.
+int select_bits(int prec, const void* psi, const uint8_t* dist, double th2,
+                const StepCtl* ctl, const Sums& sm, int64_t n, hipStream_t s);
+int flag_bits(const uint8_t* keep, const StepCtl* ctl, const Sums& sm,
+              int64_t n, hipStream_t s);
+// The selected rows ascending into midx, their number into ctl->nM; grid:
+// that of the kernel that left the bits.  select_all: every row.
+void select_write(StepCtl* ctl, const Sums& sm, int grid, uint32_t* midx,
+                  const int* err, hipStream_t s);
+void select_all(StepCtl* ctl, uint32_t* midx, int64_t n, hipStream_t s);
 // Rows 0..nM-1 of the new side are M; inserted into the cleared table.
-// phi (may be null) receives their amplitudes from psi_o.
+// phi (may be null) receives their amplitudes from psi_o.  Their distance
+// bytes become 0.  bound: of nM, for the grid.
 void insert_rows(const DevModel& m, int Wi, int prec, const Side& o,
                  const Side& n, const uint32_t* midx, const StepCtl* ctl,
-                 uint64_t* table, uint64_t mask, uint32_t* cnt_m,
-                 const void* psi_o, void* phi, int* err, hipStream_t s);
-// Rebuild the table from rows [0, n) of a side (after growth).
-void rehash_rows(const DevModel& m, int Wi, const Side& n, uint32_t* midx,
-                 int64_t rows, uint64_t* table, uint64_t mask, int* err,
+                 int64_t bound, uint64_t* table, uint64_t mask,
+                 uint32_t* cnt_m, const void* psi_o, void* phi, int* err,
                  hipStream_t s);
+// Rows [0, rows) of a side into the cleared table, their distance bytes 0
+// (dist may be null).
+void rehash_rows(const DevModel& m, int Wi, const Side& n, int64_t rows,
+                 uint64_t* table, uint64_t mask, int* err, hipStream_t s);
 // Expansion round r (1..k): frontier r-1 emits its slots; new rows are
-// appended and become frontier r.  Writes the parents' ELL columns and
-// zeroes phi of the new rows.  The frontier is taken in `chunks` chunks of
+// appended and become frontier r.  Writes the parents' ELL columns, zeroes
+// phi of the new rows and sets their distance bytes to r.  The frontier is taken in `chunks` chunks of
 // at most cand_cap / D parents each (one after another, each sees the rows
 // the previous ones added); a frontier larger than that latches kErrChunks
 // with the chunk count it needs in ctl->r_need.
@@ -136,24 +151,15 @@ void rehash_rows(const DevModel& m, int Wi, const Side& n, uint32_t* midx,
 // beyond which it latches kErrTableFull (0: no such limit).
 void expand_round(const DevModel& m, int Wi, int prec, const Side& n, int r,
                   StepCtl* ctl, int64_t cap, int64_t est, uint64_t* table,
-                  uint64_t mask, const RoundBufs& rb, int32_t* col, void* phi,
-                  int chunks, int64_t row_limit, int64_t load_rows, int* err,
-                  hipStream_t s);
-// Exclusive scan of cnt[0, *ntiles) (at most `bound` entries) into base,
-// the total into *total; tmp holds scan_tmp_words(bound) words.
-void tile_scan(const uint32_t* cnt, const uint32_t* ntiles, int64_t bound,
-               uint32_t* tmp, uint32_t* base, uint32_t* total, int* err,
-               hipStream_t s);
-// In place: bsum holds one count per tile of kTile rows over *nrows rows
-// (written by a kernel of the select layout); exclusive scan, total into
-// *total.
-void tile_sums_scan(uint32_t* bsum, const uint32_t* nrows, uint32_t* total,
-                    int* err, hipStream_t s);
-// Columns of frontier k (lookup only); sets ctl->n_new.
+                  uint64_t mask, const RoundBufs& rb, const Sums& sm,
+                  int32_t* col, void* phi, int chunks, int64_t row_limit,
+                  int64_t load_rows, int* err, hipStream_t s);
+// Columns of frontier k (lookup only); sets ctl->n_new.  max_states > 0
+// (one realization): the row count into ball[0], kErrCap beyond it.
 void lookup_last(const DevModel& m, int Wi, const Side& n, int k,
                  StepCtl* ctl, int64_t est, const uint64_t* table,
-                 uint64_t mask, int32_t* col, int64_t cap, int* err,
-                 hipStream_t s);
+                 uint64_t mask, int32_t* col, int64_t max_states,
+                 uint32_t* ball, int* err, hipStream_t s);
 // Number of per-block partials written by a kernel over `rows` rows.
 int part_grid(int64_t rows);
 // Returns the number of mass partials written.  tmap (may be null) gets
@@ -189,12 +195,13 @@ int cheb_term(const DevModel& m, int prec, int kk, bool energy, bool mid,
               void* b1, double* e_part, double* e_row, int* err,
               hipEvent_t ev_a, hipEvent_t ev_b, hipStream_t s);
 // |psi|^2 and exciton populations as per-block partials (returns their
-// count, at most kPartBlocks), plus the next step's select counts.
+// count, at most kPartBlocks), plus the next step's selection as bits and
+// per-block sums (that count is the grid select_write needs).
 int pop_norm(int prec, int N, int R, double th2, int64_t est,
              const StepCtl* ctl, const void* psi, const uint64_t* pay,
              const uint8_t* dist,
              const double* e_row, double* n2_part, double* en_part,
-             double* pop_part, uint32_t* sel_bsum, uint32_t* cnt_s, int* err,
+             double* pop_part, const Sums& sm, uint32_t* cnt_s, int* err,
              hipStream_t s);
 // <psi0|psi> per realization; p0map (may be null) gets the row of every
 // initial state, -1 if absent.

@@ -303,7 +303,9 @@ struct paces_sim {
   uint64_t tmask = 0;        // probe mask of the current step
   uint64_t tmask_alloc = 0;  // allocated table size - 1
   uint32_t* midx = nullptr;
-  uint32_t* scan_tmp = nullptr;  // select
+  uint32_t* sums_block = nullptr;  // per-block sums of the counting kernels
+  Sums sm{};
+  int sel_grid = 1;  // blocks of the kernel that left the selection in sm
   RoundBufs rb{};
   int chunks = 1;  // candidate chunks per expansion round
 
@@ -325,6 +327,9 @@ struct paces_sim {
                               // until the capacity changes)
   int warm_np = 0;         // partial blocks of the dropped weight
   int warm_nmass = 0;      // the step's folded weight partials
+  int64_t gest = 0;        // rows the launches over the new set are sized
+                           // for, and candidates those of a round
+  int64_t gcand = 0;
   int64_t nlive = 0;       // live rows of side cur; nS is its row range
   int64_t nprev = 0;       // live rows before the last step
   bool has_holes = false;  // side cur has holes (nlive < nS)
@@ -395,7 +400,7 @@ struct paces_sim {
   int64_t nS = 0;
   bool fresh = true;
   bool have_sets = false;   // M / frontiers / phi describe the last step
-  bool counts_valid = false;  // scan_tmp holds the next select's counts
+  bool counts_valid = false;  // sm holds the next step's selection
   int launched = 32;        // Clenshaw launches enqueued per step
   int K_last = 0;
   int k_last = 0;           // neighbour order of the last step
@@ -417,7 +422,7 @@ struct paces_sim {
   // What enqueueing a step leaves on the host (buffer roles, partial
   // counts); a graph replay sets it as its capture did.
   struct HostFx {
-    int ipsi, iphi, warm_np, warm_nmass;
+    int ipsi, iphi, warm_np, warm_nmass, sel_grid;
     bool swapped;
   };
   struct GraphEntry {
@@ -500,7 +505,7 @@ void free_rows(paces_sim* s) {
   s->wb.wmask = nullptr;
   s->graph_ok = false;
   s->midx = nullptr;
-  s->scan_tmp = nullptr;
+  s->sm.bits = nullptr;
   s->e_row = nullptr;
   s->kry.clear();
   dfree(s->table);
@@ -516,15 +521,11 @@ void free_cand(paces_sim* s) {
 
 paces_status alloc_cand(paces_sim* s, int64_t want) {
   free_cand(s);
-  const int64_t tiles = want / 256 + 2;
   Pieces pc;
   pc.add(&s->rb.c_slot, want);
   pc.add(&s->rb.c_ref, want);
-  pc.add(&s->rb.crow, want);
   pc.add(&s->wb.wlist, want);
-  pc.add(&s->rb.tile_cnt, tiles);
-  pc.add(&s->rb.tile_base, tiles);
-  pc.add(&s->rb.scan_tmp, scan_tmp_words(tiles));
+  pc.add(&s->rb.tile_base, want / 256 + 2);
   ST_TRY(pc.carve(&s->cand_block));
   s->cand_bytes = pc.total();
   s->rb.cand_cap = want;
@@ -553,7 +554,7 @@ void drop_graphs(paces_sim* s) {
   s->graphs.clear();
 }
 
-// Largest candidate buffer (entries, 20 bytes each plus tile counts); a
+// Largest candidate buffer (entries, 16 bytes each plus tile counts); a
 // round with more candidates runs in chunks of this size.
 constexpr int64_t kCandMax = int64_t(1) << 29;
 
@@ -575,7 +576,8 @@ size_t carried_bytes(const paces_sim* s) {
 struct RowBlock {
   Side sd[2]{};
   void* vec[4] = {nullptr, nullptr, nullptr, nullptr};
-  uint32_t *midx = nullptr, *scan = nullptr;
+  uint32_t* midx = nullptr;
+  uint64_t* bits = nullptr;
   uint32_t* freel = nullptr;
   uint16_t* wmask = nullptr;
   double* erow = nullptr;
@@ -600,7 +602,7 @@ struct RowBlock {
     pc.add(&midx, cap);
     pc.add(&freel, cap);
     pc.add(&wmask, cap);
-    pc.add(&scan, scan_tmp_words(cap));
+    pc.add(&bits, sel_bit_words(cap));
     if (m->R > 1) pc.add(&erow, cap);
     for (auto& v : kry) pc.add_bytes(&v, size_t(cap) * s->A);
   }
@@ -618,7 +620,7 @@ bool fits_device(const paces_sim* s, int64_t cap) {
   const double margin = double(size_t(2) << 30) + 0.02 * double(tot);
   const double block = double(RowBlock(s, cap).pc.total());
   const int64_t want = cand_want(s->m, cap);
-  const double cand = want > s->rb.cand_cap ? 20.0 * double(want)
+  const double cand = want > s->rb.cand_cap ? 16.1 * double(want)
                                             : double(s->cand_bytes);
   const bool capbuf = s->p.q_nom > 0 || s->p.max_states > 0;
   const double temp = double(s->nS) * double(carried_bytes(s));
@@ -665,7 +667,7 @@ paces_status grow(paces_sim* s, int64_t new_cap, int64_t min_cap,
     if (s->has_holes) {
       uint32_t* idx = reinterpret_cast<uint32_t*>(park + kb + 16 * size_t(n) + ab);
       rows_at_distance(m->Wi, o.keys, o.dist, s->nS, -1, nullptr, idx,
-                       s->dcount, s->scan_tmp, st);
+                       s->dcount, s->sm.rows, st);
       gather_rows(m->Wi, s->A, o, s->vec[s->ipsi], idx, n,
                   reinterpret_cast<uint64_t*>(park),
                   reinterpret_cast<uint64_t*>(park + kb),
@@ -743,7 +745,7 @@ paces_status grow(paces_sim* s, int64_t new_cap, int64_t min_cap,
   s->wb.wmask = nb.wmask;
   s->graph_ok = false;  // columns and table are rebuilt by the next step
   s->midx = nb.midx;
-  s->scan_tmp = nb.scan;
+  s->sm.bits = nb.bits;
   s->e_row = nb.erow;
   s->kry = nb.kry;
   s->cap = new_cap;
@@ -856,20 +858,27 @@ int step_order(const paces_sim* s, const FrozenStep* fz) {
 void stage_select(paces_sim* s, bool counted, hipStream_t st,
                   const FrozenStep* fz) {
   const int R = s->m->R;
-  begin_step(s->ctl, s->err, s->cnt, R, st);
+  const int64_t n_old = std::min(bucket(s->nS), s->cap);
+  begin_step(s->ctl, s->err, s->cnt, s->ball, R, st);
   Stage sg(s, PACES_STAGE_SELECT, st);
-  if (fz)
+  if (fz) {
     adj_set_frozen(s->ctl, s->cnt, uint32_t(fz->nM), s->err, st);
-  else if (s->cap_active)
-    select_flags(s->keep, s->ctl, s->midx, s->scan_tmp,
-                 std::min(bucket(s->nS), s->cap), s->err, st);
-  else
-    select_rows(s->prec, s->vec[s->ipsi], s->side[s->cur].dist, s->th2,
-                s->fresh, counted, s->ctl, s->midx, s->scan_tmp,
-                std::min(bucket(s->nS), s->cap), s->err, st);
+    return;
+  }
+  if (s->fresh && !s->cap_active) {
+    select_all(s->ctl, s->midx, n_old, st);
+    return;
+  }
+  if (s->cap_active)
+    s->sel_grid = flag_bits(s->keep, s->ctl, s->sm, n_old, st);
+  else if (!counted)
+    s->sel_grid = select_bits(s->prec, s->vec[s->ipsi], s->side[s->cur].dist,
+                              s->th2, s->ctl, s->sm, n_old, st);
   if (s->warm_step)
-    warm_begin(s->m->dm, s->ctl, s->midx, s->side[s->cur], s->wb, s->cnt,
-               s->nS, s->has_holes, s->scan_tmp, s->err, st);
+    warm_begin(s->m->dm, s->ctl, s->sm, s->sel_grid, s->side[s->cur], s->wb,
+               s->cnt, n_old, s->has_holes, s->err, st);
+  else
+    select_write(s->ctl, s->sm, s->sel_grid, s->midx, s->err, st);
 }
 
 // Rows at which the rounds of an attempt stop because the ball of the full
@@ -893,14 +902,18 @@ void stage_expand_warm(paces_sim* s, int64_t est, hipStream_t st) {
   const int k = s->p.k;
   const Side c = s->side[s->cur];
   Stage sg(s, PACES_STAGE_EXPAND, st);
+  const int64_t n_old = std::min(bucket(s->nS), s->cap);
   for (int r = 1; r <= k; ++r)
-    warm_round(dm, Wi, s->prec, c, r, s->ctl, s->cap, s->nS, est, s->table,
-               s->tmask, s->rb, s->wb, s->scan_tmp, s->vec[s->ipsi],
+    warm_round(dm, Wi, s->prec, c, r, s->ctl, s->cap, n_old, s->gcand,
+               s->table, s->tmask, s->rb, s->wb, s->sm, s->vec[s->ipsi],
                over_limit(s, nullptr), s->err, st);
-  warm_sizes(dm, c, k, s->ctl, est, s->p.max_states, s->ball, s->err, st);
-  s->warm_np = warm_commit(dm, Wi, s->prec, c, k, s->ctl, s->nS, est,
-                           s->table, s->tmask, s->wb, s->vec[s->ipsi],
-                           s->mass_part, s->err, st);
+  if (s->p.max_states > 0)
+    warm_cap_check(dm, c, k, s->ctl, est, s->p.max_states, s->ball, s->err,
+                   st);
+  s->warm_np = warm_commit(dm, Wi, s->prec, c, k, s->ctl, n_old,
+                           std::max<int64_t>(s->gcand / dm.D, 256), s->table,
+                           s->tmask, s->wb, s->vec[s->ipsi], s->mass_part,
+                           s->err, st);
 }
 
 // expand + merge + build of the columns: M into the cleared table, k
@@ -923,10 +936,10 @@ void stage_expand(paces_sim* s, int64_t est, hipStream_t st,
       (void)hipMemcpyAsync(sn.keys, fz->mkeys, size_t(fz->nM) * Wi * 8,
                            hipMemcpyDeviceToDevice, st);
     row_info(dm, Wi, sn.keys, fz->nM, sn.pay, sn.tot, st);
-    rehash_rows(dm, Wi, sn, nullptr, fz->nM, s->table, s->tmask, s->err, st);
+    rehash_rows(dm, Wi, sn, fz->nM, s->table, s->tmask, s->err, st);
   } else {
-    insert_rows(dm, Wi, s->prec, so, sn, s->midx, s->ctl, s->table, s->tmask,
-                s->cnt, s->vec[s->ipsi], s->vec[s->iphi], s->err, st);
+    insert_rows(dm, Wi, s->prec, so, sn, s->midx, s->ctl,
+                std::min(bucket(s->nS), s->cap), s->table, s->tmask, s->cnt, s->vec[s->ipsi], s->vec[s->iphi], s->err, st);
   }
   // a table that can still be enlarged is left at half load before further
   // inserts and at three quarters before the last frontier's lookups
@@ -934,14 +947,13 @@ void stage_expand(paces_sim* s, int64_t est, hipStream_t st,
   const int64_t slots = int64_t(s->tmask + 1);
   for (int r = 1; r <= k; ++r)
     expand_round(dm, Wi, s->prec, sn, r, s->ctl, s->cap, est, s->table,
-                 s->tmask, s->rb, sn.col, s->vec[s->iphi], s->chunks,
+                 s->tmask, s->rb, s->sm, sn.col, s->vec[s->iphi], s->chunks,
                  over_limit(s, fz),
                  !more ? 0 : (r < k ? slots / 2 : slots / 4 * 3), s->err, st);
-  lookup_last(dm, Wi, sn, k, s->ctl, est, s->table, s->tmask, sn.col, s->cap,
-              s->err, st);
-  if (s->p.max_states > 0)
+  lookup_last(dm, Wi, sn, k, s->ctl, est, s->table, s->tmask, sn.col,
+              dm.R == 1 ? s->p.max_states : 0, s->ball, s->err, st);
+  if (s->p.max_states > 0 && dm.R > 1)
     cap_check(dm, s->ctl, sn.pay, est, s->p.max_states, s->ball, s->err, st);
-  dist_of_rounds(s->ctl, k, sn.dist, est, st);
 }
 
 // transfer: old amplitudes into phi, discarded weight.
@@ -1087,8 +1099,9 @@ void stage_observe(paces_sim* s, int64_t est, hipStream_t st,
   const int n_pop = pop_norm(s->prec, m->N, R, s->th2, est, s->ctl,
                              s->vec[s->ib0], sn.pay, sn.dist,
                              want_e && R > 1 && !krylov ? s->e_row : nullptr,
-                             s->n2_part, s->en_part, s->pop_part, s->scan_tmp,
+                             s->n2_part, s->en_part, s->pop_part, s->sm,
                              s->cnt + R, s->err, st);
+  s->sel_grid = n_pop;
   autocorr(dm, m->Wi, s->prec, s->keys0, s->amps0, s->n0, s->table, s->tmask,
            sn.keys, s->vec[s->ib0], s->a2, fz ? fz->p0map : s->p0_last,
            s->err, st);
@@ -1109,9 +1122,9 @@ void enqueue_step(paces_sim* s, int64_t est, bool counted, hipStream_t st,
   stage_select(s, counted, st, fz);
   stage_expand(s, est, st, fz);
   stage_transfer(s, st, fz, L);
-  stage_build(s, est, st);
-  stage_propagate(s, est, st, L);
-  stage_observe(s, est, st, fz, L);
+  stage_build(s, s->gest, st);
+  stage_propagate(s, s->gest, st, L);
+  stage_observe(s, s->gest, st, fz, L);
 }
 
 // Replay the captured graph of this step's launch sequence, capturing it
@@ -1125,7 +1138,7 @@ paces_status launch_step_graph(paces_sim* s, int64_t est, bool counted,
       s->launched, s->K_last, est, std::min(bucket(s->nS), s->cap),
       int64_t(s->tmask), s->tune.term_rows, s->p.krylov_order,
       s->p.taylor_order, s->chunks, s->warm_step ? 1 : 0,
-      s->has_holes ? 1 : 0};
+      s->has_holes ? 1 : 0, s->gest, s->gcand, s->sel_grid};
   for (auto& g : s->graphs)
     if (g.key == key) {
       g.used = ++s->graph_clock;
@@ -1135,6 +1148,7 @@ paces_status launch_step_graph(paces_sim* s, int64_t est, bool counted,
       s->warm_np = g.fx.warm_np;
       s->warm_nmass = g.fx.warm_nmass;
       s->swapped = g.fx.swapped;
+      s->sel_grid = g.fx.sel_grid;
       return PACES_OK;
     }
   if (!s->cap_stream)
@@ -1159,7 +1173,7 @@ paces_status launch_step_graph(paces_sim* s, int64_t est, bool counted,
     s->graphs.erase(old);
   }
   const paces_sim::HostFx fx{s->ipsi, s->iphi, s->warm_np, s->warm_nmass,
-                             s->swapped};
+                             s->sel_grid, s->swapped};
   s->graphs.push_back({key, exec, ++s->graph_clock, fx});
   HIP_TRY(hipGraphLaunch(exec, st));
   return PACES_OK;
@@ -1204,8 +1218,7 @@ paces_status qnom_select(paces_sim* s, hipStream_t st) {
   s->nM_full = s->nlive;
   if (s->has_holes) {
     rows_at_distance(m->Wi, c.keys, c.dist, s->nS, -1, nullptr, s->midx_full,
-                     s->dcount, s->scan_tmp, st);
-    s->counts_valid = false;
+                     s->dcount, s->sm.rows, st);
   } else {
     iota_u32(s->midx_full, s->nS, st);
   }
@@ -1249,7 +1262,12 @@ paces_status cap_select(paces_sim* s, hipStream_t st, bool over) {
   if (!s->cap_active) {
     ST_TRY(cap_buffers(s));
     s->nM_full = s->h_ctl->nM;
-    if (s->nM_full > 0)
+    if (s->nM_full > 0 && s->warm_step)
+      // an in-place attempt keeps M as the rows at distance 0
+      rows_at_distance(m->Wi, s->side[s->cur].keys, s->side[s->cur].dist,
+                       s->nS, 0, nullptr, s->midx_full, s->dcount, s->sm.rows,
+                       st);
+    else if (s->nM_full > 0)
       HIP_TRY(hipMemcpyAsync(s->midx_full, s->midx, size_t(s->nM_full) * 4,
                              hipMemcpyDeviceToDevice, st));
     s->cap_nM.assign(cnt.begin(), cnt.end());
@@ -1418,6 +1436,12 @@ paces_status prepare_step(paces_sim* s, hipStream_t st, bool frozen,
   s->cap_active = false;
   if (s->p.q_nom > 0 && !s->fresh && !frozen) ST_TRY(qnom_select(s, st));
   *est_out = est;
+  // kernels stride over the device's counts, so launches are sized for what
+  // a step usually holds (an eighth more rows, twice the candidates and
+  // found states of the last step), not for the most the buffers allow
+  s->gest = s->warm_step ? std::min(est, bucket(s->nS + s->nS / 8 + 512)) : est;
+  s->gcand = bucket(s->last_warm ? 2 * int64_t(s->h.c_max) + 2048
+                                 : (s->nS + est) * s->m->D);
   return PACES_OK;
 }
 
@@ -1455,7 +1479,8 @@ void finish_step(paces_sim* s, const FrozenStep* fz) {
   s->h = c;
   s->nprev = s->nlive;
   s->nS = c.n_new;
-  s->nlive = s->warm_step ? int64_t(c.n_live) : int64_t(c.n_new);
+  s->nlive = s->warm_step ? s->nlive + c.n_staged - c.w_drop
+                          : int64_t(c.n_new);
   s->has_holes = s->nlive < s->nS;
   s->cur = s->nside;
   std::swap(s->ipsi, s->ib0);
@@ -1548,8 +1573,8 @@ paces_status do_step(paces_sim* s, hipStream_t st,
                          !s->cap_active;
     if (tail_only) {
       clear_latch(s->err, st);
-      stage_propagate(s, est, st, tail);
-      stage_observe(s, est, st, nullptr, tail);
+      stage_propagate(s, s->gest, st, tail);
+      stage_observe(s, s->gest, st, nullptr, tail);
     } else if (graph && attempt == 0) {
       ST_TRY(launch_step_graph(s, est, counted, st));
     } else {
@@ -1646,8 +1671,7 @@ paces_status take_snapshot(paces_sim* s, Snapshot& z, hipStream_t st) {
     uint32_t* idx = nullptr;
     ST_TRY(dalloc(&idx, s->nlive));
     rows_at_distance(m->Wi, c.keys, c.dist, s->nS, -1, nullptr, idx,
-                     s->dcount, s->scan_tmp, st);
-    s->counts_valid = false;
+                     s->dcount, s->sm.rows, st);
     gather_rows(m->Wi, s->A, c, s->vec[s->ipsi], idx, s->nlive, z.keys,
                 z.pay, z.tot, z.psi, st);
     HIP_TRY(hipStreamSynchronize(st));
@@ -1820,8 +1844,7 @@ paces_status adj_keep_m(paces_sim* s, int64_t nM, hipStream_t st) {
     const Side& c = s->side[s->cur];
     uint32_t got = 0;
     rows_at_distance(Wi, c.keys, c.dist, s->nS, 0, R.mkeys + R.mused * Wi,
-                     nullptr, s->dcount, s->scan_tmp, st);
-    s->counts_valid = false;
+                     nullptr, s->dcount, s->sm.rows, st);
     HIP_TRY(hipMemcpyAsync(&got, s->dcount, 4, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (int64_t(got) != nM)
@@ -2054,9 +2077,10 @@ paces_status expmv_run(const paces_model* m, int64_t n, const uint64_t* keys,
   set_begin(ctl, err, n, st);
   row_info(dm, m->Wi, sd.keys, n, sd.pay, sd.tot, st);
   fill_u64(table, int64_t(L.P), kEmpty, st);
-  rehash_rows(dm, m->Wi, sd, nullptr, n, table, mask, err, st);
+  rehash_rows(dm, m->Wi, sd, n, table, mask, err, st);
   check_set(dm, m->Wi, sd.keys, n, table, mask, err, st);
-  lookup_last(dm, m->Wi, sd, 0, ctl, n, table, mask, col, n, err, st);
+  lookup_last(dm, m->Wi, sd, 0, ctl, n, table, mask, col, 0, nullptr, err,
+              st);
   bounds_and_coef(dm, sd, col, n, n, ctl, dt, 1e-16, kMaxTerms, kMaxTerms,
                   part, cc, err, st);
   StepCtl hc{};
@@ -2123,8 +2147,7 @@ paces_status export_rows(paces_sim* s, const void* vec, uint64_t* keys,
     if (!r) r = dev_alloc(reinterpret_cast<void**>(&ga), size_t(n) * s->A);
     if (!r) {
       rows_at_distance(m->Wi, c.keys, c.dist, s->nS, -1, nullptr, idx,
-                       s->dcount, s->scan_tmp, st);
-      s->counts_valid = false;
+                       s->dcount, s->sm.rows, st);
       gather_rows(m->Wi, s->A, c, vec, idx, n, gk, nullptr, nullptr, ga, st);
       ksrc = gk;
       asrc = ga;
@@ -2481,6 +2504,7 @@ paces_status paces_init_state(const paces_model* m, const paces_run_params* p,
       dalloc(&s->cc, R) || dalloc(&s->a2, 2 * R) || dalloc(&s->cnt, 2 * R) ||
       dalloc(&s->mass_tot, R) || dalloc(&s->p0_last, nt) ||
       dalloc(&s->ball, R) || dalloc(&s->dcount, 1) ||
+      dalloc(&s->sums_block, 5 * kMaxSums) ||
       dalloc(&s->keys0, nt * m->Wi) ||
       dalloc(&s->amps0, 2 * nt))
     return cleanup(PACES_E_OOM);
@@ -2497,6 +2521,11 @@ paces_status paces_init_state(const paces_model* m, const paces_run_params* p,
        dalloc(&s->lz_part, 3 * std::max<int64_t>(kLzGrid1,
                                                  int64_t(kPartBlocks) * R))))
     return cleanup(PACES_E_OOM);
+  s->sm.sel = s->sums_block;
+  s->sm.hole = s->sm.sel + kMaxSums;
+  s->sm.old_ = s->sm.hole + kMaxSums;
+  s->sm.own = s->sm.old_ + kMaxSums;
+  s->sm.rows = s->sm.own + kMaxSums;
   double* q = s->parts;
   s->mass_part = q;  q += sz_mass;
   s->e_part = q;     q += sz_e;
@@ -2546,6 +2575,7 @@ paces_status paces_free_sim(paces_sim* s) {
   dfree(s->p0_last);
   dfree(s->ball);
   dfree(s->dcount);
+  dfree(s->sums_block);
   if (s->cap_block) dev_free(s->cap_block);
   dfree(s->cap_hist);
   dfree(s->cap_mode);
@@ -2662,7 +2692,7 @@ paces_status paces_run_stage(paces_sim* s, int32_t stage, void* hip_stream) {
     case PACES_STAGE_BUILD:
       // the number of series launches is set from the coefficients below
       s->launched = kMaxTerms;
-      stage_build(s, s->staged_est, st);
+      stage_build(s, s->gest, st);
       break;
     case PACES_STAGE_PROPAGATE: {
       int e = 0;
@@ -2673,11 +2703,11 @@ paces_status paces_run_stage(paces_sim* s, int32_t stage, void* hip_stream) {
         return check_latch_code(s, e);
       }
       s->launched = std::max(1, int(s->h_ctl->kmax));
-      stage_propagate(s, s->staged_est, st, L);
+      stage_propagate(s, s->gest, st, L);
       break;
     }
     case PACES_STAGE_OBSERVE: {
-      stage_observe(s, s->staged_est, st, nullptr, L);
+      stage_observe(s, s->gest, st, nullptr, L);
       HIP_TRY(hipStreamSynchronize(st));
       s->staged_next = 0;
       const int e = *s->h_err;
@@ -2826,8 +2856,7 @@ paces_status paces_get_set(paces_sim* s, int32_t which, int32_t round,
     uint32_t got = 0;
     ST_TRY(dalloc(&gathered, s->nS * m->Wi));
     rows_at_distance(m->Wi, c.keys, c.dist, s->nS, d, gathered, nullptr,
-                     s->dcount, s->scan_tmp, st);
-    s->counts_valid = false;
+                     s->dcount, s->sm.rows, st);
     if (hipMemcpyAsync(&got, s->dcount, 4, hipMemcpyDeviceToHost, st) !=
             hipSuccess ||
         hipStreamSynchronize(st) != hipSuccess) {

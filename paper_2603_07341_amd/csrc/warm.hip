@@ -1,11 +1,11 @@
 // warm.hip -- the in-place step from the previous step's graph on gfx950
 // (the method and its invariants are described in warm.hpp).
 //
-// Rows are walked in tiles of kTile rows (one distance byte each, the
-// columns of the frontier rows), so the search inside the set streams its
-// arrays; only slots that leave the set, and the slots of states new to
-// it, reach the hash table.  Found states are numbered by tile scans, so
-// the rows a step gives them are the same in every run.
+// The search inside the set streams the rows' distance bytes and the
+// columns of the frontier rows; only slots that leave the set, and the slots
+// of states new to it, reach the hash table.  Found states are numbered in
+// the order of their candidates.  A round is four launches; its counts stay
+// per block between them (common.hpp), and every block adds up what it needs.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -47,6 +47,12 @@ __device__ __forceinline__ int64_t found_row(int64_t q, const StepCtl* ctl,
                                              const uint32_t* freel) {
   const int64_t nf = ctl->nfree;
   return q < nf ? int64_t(freel[q]) : int64_t(ctl->n_old) + (q - nf);
+}
+
+// Row range of the set after the found states took their rows.
+__device__ __forceinline__ int64_t new_range(const StepCtl* ctl) {
+  const int64_t extra = int64_t(ctl->n_staged) - ctl->nfree;
+  return int64_t(ctl->n_old) + (extra > 0 ? extra : 0);
 }
 
 // Row of key k in the table (plain or staged entry; tombstones and
@@ -91,192 +97,272 @@ __device__ __forceinline__ int64_t warm_slot(const uint64_t* table,
   return -1;
 }
 
+// ---- rows by distance byte --------------------------------------------------
+// The search finds its rows by their distance bytes.  A block takes tiles of
+// kBlock * vb rows, vb bytes per lane in one load (vb 16 for sets that fill
+// the chip with tiles of 4096 rows, 4 and 1 below so that every CU has a
+// tile), and collects the matching rows of a tile in LDS in ascending order;
+// then every lane works on a listed row.  With one row per lane and iteration
+// (one byte load each, most of them not matching) the four rounds of a ring16
+// step at 1.5e7 rows took 340 us.
+constexpr int kMaxVb = 16;
+
+// Bit 8b+7 of the result is set where byte b of x equals d.
+__device__ __forceinline__ uint32_t match4(uint32_t x, uint8_t d) {
+  x ^= uint32_t(d) * 0x01010101u;
+  x = ~(((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x | 0x7F7F7F7Fu);
+  x >>= 7;
+  return (x & 1u) | ((x >> 7) & 2u) | ((x >> 14) & 4u) | ((x >> 21) & 8u);
+}
+
+// Which of the rows [e0, e0 + vb), e0 a multiple of vb, below n have
+// distance byte d.
+__device__ __forceinline__ uint32_t match_rows(const uint8_t* dist, int64_t e0,
+                                               int64_t n, int vb, uint8_t d) {
+  if (e0 >= n) return 0u;
+  uint32_t hit;
+  if (vb == 16) {
+    const uint4 v = *reinterpret_cast<const uint4*>(dist + e0);
+    hit = match4(v.x, d) | (match4(v.y, d) << 4) | (match4(v.z, d) << 8) |
+          (match4(v.w, d) << 12);
+  } else if (vb == 4) {
+    hit = match4(*reinterpret_cast<const uint32_t*>(dist + e0), d);
+  } else {
+    hit = dist[e0] == d ? 1u : 0u;
+  }
+  const int64_t left = n - e0;
+  return left < vb ? hit & ((1u << left) - 1u) : hit;
+}
+
+// The tile's rows (from row t * kBlock * vb on) with distance byte d, as
+// offsets in the tile, ascending, into list (LDS); returns their number.
+// Ends with a barrier.
+__device__ __forceinline__ uint32_t list_rows(const uint8_t* dist, int64_t t,
+                                              int64_t n, int vb, uint8_t d,
+                                              uint16_t* list) {
+  uint32_t hit = match_rows(dist, (t * kBlock + threadIdx.x) * vb, n, vb, d);
+  uint32_t tot;
+  uint32_t off = block_excl_scan(__popc(hit), &tot);
+  while (hit) {
+    const int b = __ffs(hit) - 1;
+    hit &= hit - 1;
+    list[off++] = uint16_t(threadIdx.x * vb + b);
+  }
+  __syncthreads();
+  return tot;
+}
+
+inline int rows_per_lane(int64_t n) {
+  return n >= int64_t(kBlock) * 16 * 256 ? 16 : n >= kBlock * 4 * 128 ? 4 : 1;
+}
+
 // ---- start ------------------------------------------------------------------
-// kHole stays, every other byte becomes kFar (bytes past n_old of the last
-// word belong to rows past the range, which a step writes before reading).
+// Distance bytes of the step from the selection's bits: 0 on M, kFar on the
+// other live rows, kHole kept; 16 rows per lane.  (Bytes past n_old of the
+// last group belong to rows past the range, which a step writes before
+// reading.)  |M| from the selection's sums, per realization by counting; the
+// holes of each block into hole_sums (null: the set has none).  This took
+// three launches before (fill, index list, mark).
 __global__ void __launch_bounds__(kBlock)
-    k_warm_fill(uint8_t* dist, const StepCtl* ctl, const int* err) {
+    k_warm_select(DevModel m, StepCtl* ctl, const uint64_t* bits,
+                  const uint32_t* sel_sums, int sel_grid, const uint64_t* pay,
+                  uint8_t* dist, uint32_t* cnt_m, uint32_t* hole_sums,
+                  const int* err) {
+  __shared__ uint32_t bins[kMaxReal];
   if (*err) return;
-  uint32_t* d4 = reinterpret_cast<uint32_t*>(dist);
-  const int64_t n4 = cdiv(int64_t(ctl->n_old), 4);
-  for (int64_t i = gtid(); i < n4; i += gstride()) {
-    const uint32_t v = d4[i];
-    uint32_t o = 0;
+  if (m.R > 1) {
+    for (int r = threadIdx.x; r < m.R; r += blockDim.x) bins[r] = 0;
+    __syncthreads();
+  }
+  const int64_t n = ctl->n_old;
+  const TileRun run = tile_run(cdiv(n, kBlock * 16), gridDim.x);
+  uint32_t holes = 0;
+  for (int64_t t = run.t0; t < run.t1; ++t) {
+    const int64_t e0 = (t * kBlock + threadIdx.x) * 16;
+    if (e0 >= n) continue;
+    const uint4 v = *reinterpret_cast<const uint4*>(dist + e0);
+    uint32_t sel = reinterpret_cast<const uint16_t*>(bits)[e0 >> 4];
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    uint32_t o[4], hmask = 0;
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const uint32_t byte = (v >> (8 * b)) & 0xFFu;
-      o |= (byte == kHole ? uint32_t(kHole) : uint32_t(kFar)) << (8 * b);
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t hole = match4(w[q], kHole);
+      hmask |= hole << (4 * q);
+      uint32_t x = 0;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        const uint32_t byte = (hole >> b) & 1u             ? kHole
+                              : (sel >> (4 * q + b)) & 1u ? 0u
+                                                          : uint32_t(kFar);
+        x |= byte << (8 * b);
+      }
+      o[q] = x;
     }
-    d4[i] = o;
+    *reinterpret_cast<uint4*>(dist + e0) = make_uint4(o[0], o[1], o[2], o[3]);
+    const int64_t left = n - e0;
+    holes += __popc(left < 16 ? hmask & ((1u << left) - 1u) : hmask);
+    if (m.R > 1)
+      while (sel) {
+        const int b = __ffs(sel) - 1;
+        sel &= sel - 1;
+        atomicAdd(&bins[pay_real(pay[e0 + b])], 1u);
+      }
+  }
+  if (hole_sums) {
+    uint32_t tot;
+    block_excl_scan(holes, &tot);
+    if (threadIdx.x == 0) hole_sums[blockIdx.x] = tot;
+  }
+  if (blockIdx.x == 0) {
+    uint64_t total;
+    sums_before(sel_sums, sel_grid, 0, &total);
+    if (threadIdx.x == 0) {
+      ctl->nM = uint32_t(total);
+      if (m.R == 1) cnt_m[0] = uint32_t(total);
+    }
+  }
+  if (m.R > 1) count_flush(m.R, bins, cnt_m);
+}
+
+// The holes ascending (same grid as k_warm_select).
+__global__ void __launch_bounds__(kBlock)
+    k_warm_holes(StepCtl* ctl, const uint8_t* dist, const uint32_t* sums,
+                 uint32_t* freel, const int* err) {
+  __shared__ uint16_t list[kBlock * kMaxVb];
+  if (*err) return;
+  const int64_t n = ctl->n_old;
+  const TileRun run = tile_run(cdiv(n, kBlock * 16), gridDim.x);
+  uint64_t total;
+  uint64_t at = sums_before(sums, gridDim.x, blockIdx.x, &total);
+  if (gtid() == 0) ctl->nfree = uint32_t(total);
+  for (int64_t t = run.t0; t < run.t1; ++t) {
+    const uint32_t tot = list_rows(dist, t, n, 16, kHole, list);
+    for (uint32_t i = threadIdx.x; i < tot; i += kBlock)
+      freel[at + i] = uint32_t(t * kBlock * 16 + list[i]);
+    at += tot;
   }
 }
 
 // Rows of [0, n) with a given distance byte (d >= 0) or live (d < 0),
-// counted per tile of the select layout, then written in row order.
+// counted per block in the select layout, then written in row order.
 __device__ __forceinline__ bool dist_hit(uint8_t v, int d) {
   return d < 0 ? v != kHole : v == uint8_t(d);
 }
 
 __global__ void __launch_bounds__(kBlock)
-    k_dist_count(const uint8_t* dist, const uint32_t* nptr, int d,
-                 uint32_t* bsum) {
-  const int64_t n = *nptr, ntiles = cdiv(n, kTile);
-  for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-    uint32_t v = 0;
+    k_dist_count(const uint8_t* dist, int64_t n, int d, uint32_t* sums) {
+  const TileRun run = tile_run(cdiv(n, kTile), gridDim.x);
+  uint32_t v = 0;
+  for (int64_t t = run.t0; t < run.t1; ++t) {
 #pragma unroll
     for (int q = 0; q < kItems; ++q) {
       const int64_t e = t * kTile + q * kBlock + threadIdx.x;
       if (e < n && dist_hit(dist[e], d)) ++v;
     }
-    uint32_t tot;
-    block_excl_scan(v, &tot);
-    if (threadIdx.x == 0) bsum[t] = tot;
   }
+  uint32_t tot;
+  block_excl_scan(v, &tot);
+  if (threadIdx.x == 0) sums[blockIdx.x] = tot;
 }
 
 __global__ void __launch_bounds__(kBlock)
-    k_dist_write(int Wi, const uint64_t* keys, const uint8_t* dist,
-                 const uint32_t* nptr, int d, const uint32_t* bsum,
-                 uint64_t* out, uint32_t* rows) {
-  const int64_t n = *nptr, ntiles = cdiv(n, kTile);
-  for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-    uint32_t run = bsum[t];
+    k_dist_write(int Wi, const uint64_t* keys, const uint8_t* dist, int64_t n,
+                 int d, const uint32_t* sums, uint32_t* count, uint64_t* out,
+                 uint32_t* rows) {
+  const TileRun run = tile_run(cdiv(n, kTile), gridDim.x);
+  uint64_t total;
+  uint64_t at = sums_before(sums, gridDim.x, blockIdx.x, &total);
+  if (gtid() == 0) *count = uint32_t(total);
+  for (int64_t t = run.t0; t < run.t1; ++t) {
 #pragma unroll 1
     for (int q = 0; q < kItems; ++q) {
       const int64_t e = t * kTile + q * kBlock + threadIdx.x;
       const bool hit = e < n && dist_hit(dist[e], d);
       uint32_t tot;
-      const uint32_t off = block_excl_scan(hit ? 1u : 0u, &tot) + run;
-      run += tot;
+      const uint64_t off = block_excl_scan(hit ? 1u : 0u, &tot) + at;
+      at += tot;
       if (!hit) continue;
       if (rows) rows[off] = uint32_t(e);
       if (out)
-        for (int w = 0; w < Wi; ++w)
-          out[int64_t(off) * Wi + w] = keys[e * Wi + w];
+        for (int w = 0; w < Wi; ++w) out[off * Wi + w] = keys[e * Wi + w];
     }
-  }
-}
-
-__global__ void __launch_bounds__(kBlock)
-    k_warm_mark(DevModel m, StepCtl* ctl, const uint32_t* midx,
-                const uint64_t* pay, uint8_t* dist, uint32_t* cnt_m,
-                int holes, const int* err) {
-  __shared__ uint32_t bins[kMaxReal];
-  if (*err) return;
-  const int64_t nM = ctl->nM;
-  if (m.R == 1) {
-    // one realization: |M| is the selection's count (cnt_m was cleared by
-    // the step's start)
-    for (int64_t i = gtid(); i < nM; i += gstride()) dist[midx[i]] = 0;
-    if (gtid() == 0) cnt_m[0] = uint32_t(nM);
-  } else {
-    for (int r = threadIdx.x; r < m.R; r += blockDim.x) bins[r] = 0;
-    __syncthreads();
-    for (int64_t i = gtid(); i < nM; i += gstride()) {
-      const uint32_t r = midx[i];
-      dist[r] = 0;
-      atomicAdd(&bins[pay_real(pay[r])], 1u);
-    }
-    count_flush(m.R, bins, cnt_m);
-  }
-  if (gtid() == 0) {
-    if (!holes) ctl->nfree = 0;
-    ctl->n_staged = 0;
-    ctl->gstart[0] = 0;
-    ctl->gstart[1] = 0;
-    ctl->w_noc = 0;
-    ctl->w_nkeep = 0;
-    ctl->w_moved = 0;
-    ctl->w_tomb = 0;
-    ctl->n_live = 0;
   }
 }
 
 // ---- a round ----------------------------------------------------------------
-// Live rows at distance r-1, in the select tile layout.  Count pass:
-// columns mark their rows at distance r (unless nearer; every writer
-// writes r, and no row at distance r-1 is written in round r), the slots
-// whose neighbour lies outside the set go to wmask and are counted per
-// tile.  Write pass: those slots as candidates, in tile order.  Holes and
-// found states never match r-1.
-template <bool WRITE, int D>
+// Live rows at distance r-1.  Count pass: columns mark their rows at
+// distance r (unless nearer; every writer writes r, and no row at distance
+// r-1 is written in round r), the slots whose neighbour lies outside the set
+// go to wmask and are counted per block.  Holes and found states never match
+// r-1.
+template <int D>
 __global__ void __launch_bounds__(kBlock)
-    k_warm_old(DevModel m, int r, const StepCtl* ctl, const uint64_t* pay,
-               const int32_t* col, uint8_t* dist, uint16_t* wmask,
-               uint32_t* bsum, uint64_t* wlist, int64_t cand_cap, int* err) {
+    k_warm_count(DevModel m, int r, int vb, const StepCtl* ctl,
+                 const uint64_t* pay, const int32_t* col, uint8_t* dist,
+                 uint16_t* wmask, uint32_t* sums, const int* err) {
+  __shared__ uint16_t list[kBlock * kMaxVb];
   if (*err) return;
-  const uint8_t front = uint8_t(r - 1);
-  const int64_t n = ctl->n_old, ntiles = cdiv(n, kTile);
-  for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-    uint32_t run = WRITE ? bsum[t] : 0u, cnt = 0;
-#pragma unroll 1
-    for (int q = 0; q < kItems; ++q) {
-      const int64_t e = t * kTile + q * kBlock + threadIdx.x;
+  const int64_t n = ctl->n_old, tile = int64_t(kBlock) * vb;
+  const TileRun run = tile_run(cdiv(n, tile), gridDim.x);
+  uint32_t cnt = 0;
+  for (int64_t t = run.t0; t < run.t1; ++t) {
+    const uint32_t tot = list_rows(dist, t, n, vb, uint8_t(r - 1), list);
+    for (uint32_t i = threadIdx.x; i < tot; i += kBlock) {
+      const int64_t e = t * tile + list[i];
+      const uint64_t p = pay[e];
+      int32_t cs[D];
+      load_cols<D>(col + e * D, cs);
       uint32_t msk = 0;
-      if (e < n && dist[e] == front) {
-        if (WRITE) {
-          msk = wmask[e];
-        } else {
-          const uint64_t p = pay[e];
-          int32_t cs[D];
-          load_cols<D>(col + e * D, cs);
 #pragma unroll
-          for (int s = 0; s < D; ++s) {
-            const int32_t c = cs[s];
-            if (c >= 0) {
-              if (dist[c] > r) dist[c] = uint8_t(r);
-            } else if (slot_live(m, p, s)) {
-              msk |= 1u << s;
-            }
-          }
-          wmask[e] = uint16_t(msk);
+      for (int s = 0; s < D; ++s) {
+        const int32_t c = cs[s];
+        if (c >= 0) {
+          if (dist[c] > r) dist[c] = uint8_t(r);
+        } else if (slot_live(m, p, s)) {
+          msk |= 1u << s;
         }
       }
-      const uint32_t nb = __popc(msk);
-      if (WRITE) {
-        uint32_t tot;
-        uint64_t off = uint64_t(block_excl_scan(nb, &tot)) + run;
-        run += tot;
-        while (msk) {
-          const int s = __ffs(msk) - 1;
-          msk &= msk - 1;
-          if (int64_t(off) < cand_cap)
-            wlist[off] = (uint64_t(e) << 8) | uint64_t(s);
-          else
-            atomicOr(err, kErrChunks);
-          ++off;
-        }
-      } else {
-        cnt += nb;
-      }
-    }
-    if (!WRITE) {
-      uint32_t tot;
-      block_excl_scan(cnt, &tot);
-      if (threadIdx.x == 0) bsum[t] = tot;
+      wmask[e] = uint16_t(msk);
+      cnt += __popc(msk);
     }
   }
+  uint32_t tot;
+  block_excl_scan(cnt, &tot);
+  if (threadIdx.x == 0) sums[blockIdx.x] = tot;
 }
 
-// Candidates of round r: w_noc from live rows, then every slot of the
-// states found in round r-1; the round's states are numbered from
-// n_staged on.
-__global__ void k_warm_prep(StepCtl* ctl, int r, int D, int64_t cand_cap,
-                            int* err) {
+// Write pass (same grid): those slots as candidates, in row order.
+__global__ void __launch_bounds__(kBlock)
+    k_warm_list(int r, int vb, const StepCtl* ctl, const uint8_t* dist,
+                const uint16_t* wmask, const uint32_t* sums, uint64_t* wlist,
+                int64_t cand_cap, int* err) {
+  __shared__ uint16_t list[kBlock * kMaxVb];
   if (*err) return;
-  const int64_t noc = ctl->w_noc;
-  const int64_t nf = int64_t(ctl->gstart[r]) - ctl->gstart[r - 1];
-  int64_t nc = noc + nf * D;
-  if (nc > cand_cap) {
-    atomicOr(err, kErrChunks);
-    nc = 0;
+  const int64_t n = ctl->n_old, tile = int64_t(kBlock) * vb;
+  const TileRun run = tile_run(cdiv(n, tile), gridDim.x);
+  uint64_t total;
+  uint64_t at = sums_before(sums, gridDim.x, blockIdx.x, &total);
+  if (sums[blockIdx.x] == 0) return;
+  for (int64_t t = run.t0; t < run.t1; ++t) {
+    const uint32_t tot = list_rows(dist, t, n, vb, uint8_t(r - 1), list);
+    for (uint32_t i0 = 0; i0 < tot; i0 += kBlock) {
+      const uint32_t i = i0 + threadIdx.x;
+      const int64_t e = i < tot ? t * tile + list[i] : 0;
+      uint32_t msk = i < tot ? wmask[e] : 0u;
+      uint32_t c;
+      uint64_t off = at + block_excl_scan(__popc(msk), &c);
+      at += c;
+      while (msk) {
+        const int s = __ffs(msk) - 1;
+        msk &= msk - 1;
+        if (int64_t(off) < cand_cap)
+          wlist[off] = (uint64_t(e) << 8) | uint64_t(s);
+        else
+          atomicOr(err, kErrChunks);
+        ++off;
+      }
+    }
   }
-  ctl->w_f0 = ctl->gstart[r - 1];
-  ctl->r_ncand = uint32_t(nc);
-  ctl->r_ntiles = uint32_t(cdiv(nc, kBlock));
-  ctl->r_ncur = ctl->n_staged;
-  ctl->r_total = 0;
-  ctl->r_own = ctl->nM + ctl->n_staged;
 }
 
 // Key of candidate c and its parent's row: a live row (from wlist) or the
@@ -309,7 +395,9 @@ __device__ __forceinline__ bool warm_cand(const DevModel& m,
 // candidate.  A key found as a live row marks it at distance r; a key
 // found staged or claimed by another candidate needs nothing; the
 // candidate whose compare-and-swap fills an empty slot owns the key (probe
-// distance into c_slot), counted per tile of candidates.  Tombstones are
+// distance into c_slot), counted per block.  Candidates of round r: w_noc
+// from live rows (the count pass's sums), then every slot of the states
+// found in round r-1.  Tombstones are
 // passed over and never claimed, so removing the staged entries restores
 // the table.  row_limit > 0 (state cap): M and the states found so far
 // exceeding it latch kErrOver; a block stops at its next tile once anything
@@ -318,14 +406,28 @@ template <int W>
 __global__ void __launch_bounds__(kBlock)
     k_warm_probe(DevModel m, int r, StepCtl* ctl, int64_t row_limit, Side c,
                  const uint32_t* freel, const uint64_t* wlist,
+                 const uint32_t* old_sums, int old_grid, int64_t cand_cap,
                  uint64_t* table, uint64_t mask, uint32_t* c_slot,
-                 uint32_t* c_ref, uint32_t* tile_cnt, int* err) {
+                 uint32_t* c_ref, uint32_t* sums, int* err) {
   __shared__ int stop[2];  // latch seen at this tile, by parity of the tile
   if (*err) return;
-  const int64_t nc = ctl->r_ncand, noc = ctl->w_noc, f0 = ctl->w_f0;
-  const int64_t ntiles = cdiv(nc, kBlock);
+  uint64_t total;
+  sums_before(old_sums, old_grid, 0, &total);
+  const int64_t noc = int64_t(total), f0 = ctl->gstart[r - 1], nM = ctl->nM;
+  const int64_t nc = noc + (int64_t(ctl->gstart[r]) - f0) * m.D;
+  if (nc > cand_cap) {
+    if (gtid() == 0) atomicOr(err, kErrChunks);
+    return;
+  }
+  if (gtid() == 0) {
+    ctl->w_noc = uint32_t(noc);
+    ctl->r_ncand = uint32_t(nc);
+    if (uint32_t(nc) > ctl->c_max) ctl->c_max = uint32_t(nc);
+  }
+  const TileRun run = tile_run(cdiv(nc, kBlock), gridDim.x);
+  uint32_t own = 0;
   int par = 0;
-  for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x, par ^= 1) {
+  for (int64_t tile = run.t0; tile < run.t1; ++tile, par ^= 1) {
     const int64_t cand = tile * kBlock + threadIdx.x;
     if (threadIdx.x == 0) stop[par] = latch_now(err);
     uint32_t owner = 0;
@@ -388,36 +490,44 @@ __global__ void __launch_bounds__(kBlock)
     }
     uint32_t tot;
     block_excl_scan(owner, &tot);
-    if (threadIdx.x == 0) {
-      tile_cnt[tile] = tot;
-      if (row_limit > 0 && tot &&
-          int64_t(atomicAdd(&ctl->r_own, tot)) + tot > row_limit)
-        atomicOr(err, kErrOver);
-    }
+    own += tot;
+    if (threadIdx.x == 0 && row_limit > 0 && tot &&
+        nM + int64_t(atomicAdd(&ctl->r_own, tot)) + tot > row_limit)
+      atomicOr(err, kErrOver);
     if (stop[par]) return;  // written before the scan's barriers
   }
+  if (threadIdx.x == 0) sums[blockIdx.x] = own;
 }
 
-// Owners take their rows (numbered by the tile scan): key, payload,
-// totals, distance kNewRow | r, amplitude 0; their table slot points at
-// the row, staged.
+// Owners take their rows, numbered by the owners of the blocks before and
+// a scan per tile (same grid as the probe): key, payload, totals, distance
+// kNewRow | r, amplitude 0; their table slot points at the row, staged.
 template <int W, typename Amp>
 __global__ void __launch_bounds__(kBlock)
-    k_warm_commit(DevModel m, int r, const StepCtl* ctl, int64_t cap, Side c,
+    k_warm_commit(DevModel m, int r, StepCtl* ctl, int64_t cap, Side c,
                   const uint32_t* freel, const uint64_t* wlist,
                   uint64_t* table, uint64_t mask, const uint32_t* c_slot,
-                  const uint32_t* c_ref, const uint32_t* tile_base, Amp* psi,
+                  const uint32_t* c_ref, const uint32_t* sums, Amp* psi,
                   int* err) {
   if (*err) return;
-  const int64_t nc = ctl->r_ncand, noc = ctl->w_noc, f0 = ctl->w_f0;
-  const int64_t n_cur = ctl->r_ncur, ntiles = cdiv(nc, kBlock);
-  for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+  const int64_t nc = ctl->r_ncand, noc = ctl->w_noc, f0 = ctl->gstart[r - 1];
+  const TileRun run = tile_run(cdiv(nc, kBlock), gridDim.x);
+  uint64_t total;
+  int64_t at = ctl->gstart[r] +
+               int64_t(sums_before(sums, gridDim.x, blockIdx.x, &total));
+  if (gtid() == 0) {
+    ctl->n_staged = uint32_t(ctl->gstart[r] + total);
+    ctl->gstart[r + 1] = ctl->n_staged;
+  }
+  if (sums[blockIdx.x] == 0) return;
+  for (int64_t tile = run.t0; tile < run.t1; ++tile) {
     const int64_t cand = tile * kBlock + threadIdx.x;
     const bool own = cand < nc && c_ref[cand] == kOwnerW;
     uint32_t tot_in_tile;
-    const uint32_t rank = block_excl_scan(own ? 1u : 0u, &tot_in_tile);
+    const int64_t num = at + block_excl_scan(own ? 1u : 0u, &tot_in_tile);
+    at += tot_in_tile;
     if (!own) continue;
-    const int64_t row = found_row(n_cur + tile_base[tile] + rank, ctl, freel);
+    const int64_t row = found_row(num, ctl, freel);
     if (row >= cap) {
       atomicOr(err, kErrCapacity);
       continue;
@@ -442,38 +552,18 @@ __global__ void __launch_bounds__(kBlock)
   }
 }
 
-__global__ void k_warm_finish(StepCtl* ctl, int r, const int* err) {
-  if (*err) return;
-  const uint32_t n = ctl->r_ncur + ctl->r_total;
-  ctl->n_staged = n;
-  ctl->gstart[r + 1] = n;
-}
-
-// ---- sizes ------------------------------------------------------------------
-__global__ void k_warm_range(StepCtl* ctl, int R, uint32_t* ball,
-                             const int* err) {
-  if (*err) return;
-  const int64_t extra = int64_t(ctl->n_staged) - ctl->nfree;
-  ctl->n_new = uint32_t(int64_t(ctl->n_old) + (extra > 0 ? extra : 0));
-  ctl->n_live = 0;
-  for (int r = 0; r < R; ++r) ball[r] = 0u;
-}
-
-// Live rows of the new set, in total and per realization (counted only
-// when per_real).  A thread reads the distances of 16 rows at once (the
-// array's allocation is a multiple of 256 bytes, so the last group stays
-// inside it).
+// ---- sizes (state cap) --------------------------------------------------------
+// Live rows of the new set per realization.  A thread reads the distances
+// of 16 rows at once (the array's allocation is a multiple of 256 bytes, so
+// the last group stays inside it).
 __global__ void __launch_bounds__(kBlock)
-    k_warm_live(DevModel m, int k, StepCtl* ctl, const uint8_t* dist,
-                const uint64_t* pay, int per_real, uint32_t* ball,
-                const int* err) {
+    k_warm_live(DevModel m, int k, const StepCtl* ctl, const uint8_t* dist,
+                const uint64_t* pay, uint32_t* ball, const int* err) {
   __shared__ uint32_t bins[kMaxReal];
   if (*err) return;
-  if (per_real) {
-    for (int r = threadIdx.x; r < m.R; r += blockDim.x) bins[r] = 0;
-    __syncthreads();
-  }
-  const int64_t n = ctl->n_new, n16 = cdiv(n, 16);
+  for (int r = threadIdx.x; r < m.R; r += blockDim.x) bins[r] = 0;
+  __syncthreads();
+  const int64_t n = new_range(ctl), n16 = cdiv(n, 16);
   const uint4* d16 = reinterpret_cast<const uint4*>(dist);
   uint32_t live = 0;
   for (int64_t g = gtid(); g < n16; g += gstride()) {
@@ -484,13 +574,15 @@ __global__ void __launch_bounds__(kBlock)
       const int64_t e = g * 16 + q;
       if (e >= n || !kept(uint8_t(w[q >> 2] >> (8 * (q & 3))), k)) continue;
       ++live;
-      if (per_real) atomicAdd(&bins[pay_real(pay[e])], 1u);
+      if (m.R > 1) atomicAdd(&bins[pay_real(pay[e])], 1u);
     }
   }
-  uint32_t tot;
-  block_excl_scan(live, &tot);
-  if (threadIdx.x == 0 && tot) atomicAdd(&ctl->n_live, tot);
-  if (per_real) count_flush(m.R, bins, ball);
+  if (m.R == 1) {
+    uint32_t tot;
+    block_excl_scan(live, &tot);
+    if (threadIdx.x == 0) bins[0] = tot;
+  }
+  count_flush(m.R, bins, ball);
 }
 
 __global__ void k_warm_cap_over(int R, int64_t max_states,
@@ -501,51 +593,94 @@ __global__ void k_warm_cap_over(int R, int64_t max_states,
 }
 
 // ---- the commit -------------------------------------------------------------
-// Live rows the search did not reach become holes: weight into the
-// partials, amplitude 0, table entry a tombstone, columns of the row and
-// of its neighbours toward it -1, distance kHole.
+// First every block's share of the old rows: those the search did not reach
+// become holes (weight into the partials, amplitude 0, table entry a
+// tombstone, columns of the row and of its neighbours toward it -1, distance
+// kHole).  Then its share of the found states' slots: distance r, table
+// entry plain (lane of slot 0), columns by lookup.  An edge is seen from
+// both ends as slots s and s ^ 1, so a found state also sets the column of a
+// live row toward it (that row had -1 there: the state was outside the old
+// set); between two found states both ends write the same values.  The two
+// parts need no order between blocks: a lookup may still find a row that is
+// being dropped, whose distance byte (kFar or kHole) says so, and they write
+// different columns.
 template <int W, typename Amp>
 __global__ void __launch_bounds__(kBlock)
-    k_warm_drop(DevModel m, int k, StepCtl* ctl, Side c, uint64_t* table,
-                uint64_t mask, Amp* psi, double* mass_part, const int* err) {
+    k_warm_settle(DevModel m, int k, StepCtl* ctl, Side c,
+                  const uint32_t* freel, uint64_t* table, uint64_t mask,
+                  Amp* psi, double* mass_part, const int* err) {
   __shared__ double bins[kMaxReal];
+  __shared__ uint16_t list[kBlock * kMaxVb];
   if (*err) return;
-  if (gtid() == 0) ctl->w_moved = 1;
+  if (gtid() == 0) {
+    ctl->w_moved = 1;
+    ctl->n_new = uint32_t(new_range(ctl));
+  }
   const int R = m.R, D = m.D;
   if (R > 1) {
     for (int r = threadIdx.x; r < R; r += blockDim.x) bins[r] = 0.0;
     __syncthreads();
   }
   const int64_t nold = ctl->n_old;
+  const TileRun run = tile_run(cdiv(nold, kBlock * 16), gridDim.x);
   double lost = 0;
-  uint32_t tombs = 0;
-  for (int64_t e = gtid(); e < nold; e += gstride()) {
-    if (c.dist[e] != kFar) continue;
-    const Amp v = psi[e];
-    if (R > 1)
-      atomicAdd(&bins[pay_real(c.pay[e])], weight(v));
-    else
-      lost += weight(v);
-    Amp z;
-    z.x = 0;
-    z.y = 0;
-    psi[e] = z;
-    uint64_t key[W];
-    load_key<W>(c.keys, e, key);
-    const int64_t sl =
-        warm_slot<W>(table, mask, key, key_hash<W>(m, key), uint32_t(e));
-    if (sl >= 0) {
-      table[sl] = kTomb;
-      ++tombs;
+  uint32_t tombs = 0, drops = 0;
+  for (int64_t t = run.t0; t < run.t1; ++t) {
+    const uint32_t tot = list_rows(c.dist, t, nold, 16, kFar, list);
+    drops += tot;
+    for (uint32_t i = threadIdx.x; i < tot; i += kBlock) {
+      const int64_t e = t * kBlock * 16 + list[i];
+      const Amp v = psi[e];
+      if (R > 1)
+        atomicAdd(&bins[pay_real(c.pay[e])], weight(v));
+      else
+        lost += weight(v);
+      Amp z;
+      z.x = 0;
+      z.y = 0;
+      psi[e] = z;
+      uint64_t key[W];
+      load_key<W>(c.keys, e, key);
+      const int64_t sl =
+          warm_slot<W>(table, mask, key, key_hash<W>(m, key), uint32_t(e));
+      if (sl >= 0) {
+        table[sl] = kTomb;
+        ++tombs;
+      }
+      for (int s = 0; s < D; ++s) {
+        const int32_t nb = c.col[e * D + s];
+        // a neighbour that stays (within k) loses its column toward e; one
+        // dropped too clears its own
+        if (nb >= 0 && c.dist[nb] <= k) c.col[int64_t(nb) * D + (s ^ 1)] = -1;
+        c.col[e * D + s] = -1;
+      }
+      c.dist[e] = kHole;
     }
-    for (int s = 0; s < D; ++s) {
-      const int32_t nb = c.col[e * D + s];
-      // a neighbour that stays (within k) loses its column toward e; one
-      // dropped too clears its own
-      if (nb >= 0 && c.dist[nb] <= k) c.col[int64_t(nb) * D + (s ^ 1)] = -1;
-      c.col[e * D + s] = -1;
+  }
+  const int64_t ns = ctl->n_staged;
+  for (int64_t t = gtid(); t < ns * D; t += gstride()) {
+    const int64_t q = t / D;
+    const int s = int(t % D);
+    const int64_t row = found_row(q, ctl, freel);
+    uint64_t par[W], kk[W];
+    load_key<W>(c.keys, row, par);
+    if (s == 0) {
+      const uint64_t h = key_hash<W>(m, par);
+      const int64_t sl = warm_slot<W>(table, mask, par, h,
+                                      kStaged | uint32_t(row));
+      if (sl >= 0)
+        table[sl] = (uint64_t(hash_tag(h)) << 32) | uint64_t(row);
+      c.dist[row] = uint8_t(c.dist[row] & ~kNewRow);
     }
-    c.dist[e] = kHole;
+    int32_t out = -1;
+    if (slot_target<W>(m, par, c.pay[row], s, kk)) {
+      const int64_t f = warm_find<W>(table, mask, c.keys, kk, key_hash<W>(m, kk));
+      if (f >= 0 && kept(c.dist[f], k)) {
+        out = int32_t(f);
+        c.col[f * D + (s ^ 1)] = int32_t(row);
+      }
+    }
+    c.col[row * D + s] = out;
   }
   if (R > 1) {
     __syncthreads();
@@ -557,44 +692,9 @@ __global__ void __launch_bounds__(kBlock)
   }
   uint32_t tot;
   block_excl_scan(tombs, &tot);
-  if (threadIdx.x == 0 && tot) atomicAdd(&ctl->w_tomb, tot);
-}
-
-// States found this step: distance r, table entry plain (lane of slot 0),
-// columns by lookup.  An edge is seen from both ends as slots s and s ^ 1,
-// so a found state also sets the column of a live row toward it (that row
-// had -1 there: the state was outside the old set); between two found
-// states both ends write the same values.
-template <int W>
-__global__ void __launch_bounds__(kBlock)
-    k_warm_fix(DevModel m, const StepCtl* ctl, Side c, const uint32_t* freel,
-               uint64_t* table, uint64_t mask, const int* err) {
-  if (*err) return;
-  const int D = m.D;
-  const int64_t ns = ctl->n_staged;
-  for (int64_t t = gtid(); t < ns * D; t += gstride()) {
-    const int64_t q = t / D;
-    const int s = int(t % D);
-    const int64_t row = found_row(q, ctl, freel);
-    uint64_t par[W], k[W];
-    load_key<W>(c.keys, row, par);
-    if (s == 0) {
-      const uint64_t h = key_hash<W>(m, par);
-      const int64_t sl = warm_slot<W>(table, mask, par, h,
-                                      kStaged | uint32_t(row));
-      if (sl >= 0)
-        table[sl] = (uint64_t(hash_tag(h)) << 32) | uint64_t(row);
-      c.dist[row] = uint8_t(c.dist[row] & ~kNewRow);
-    }
-    int32_t out = -1;
-    if (slot_target<W>(m, par, c.pay[row], s, k)) {
-      const int64_t f = warm_find<W>(table, mask, c.keys, k, key_hash<W>(m, k));
-      if (f >= 0) {
-        out = int32_t(f);
-        c.col[f * D + (s ^ 1)] = int32_t(row);
-      }
-    }
-    c.col[row * D + s] = out;
+  if (threadIdx.x == 0 && drops) {
+    atomicAdd(&ctl->w_tomb, tot);
+    atomicAdd(&ctl->w_drop, drops);
   }
 }
 
@@ -616,16 +716,6 @@ __global__ void __launch_bounds__(kBlock)
   for (int64_t e = gtid(); e < n; e += gstride()) {
     const uint8_t d = dist[e];
     if (d >= kNewRow && d < kHole) dist[e] = kHole;
-  }
-}
-
-__global__ void __launch_bounds__(kBlock)
-    k_dist_rounds(const StepCtl* ctl, int k, uint8_t* dist) {
-  const int64_t n = ctl->n_new;
-  for (int64_t e = gtid(); e < n; e += gstride()) {
-    int r = 0;
-    while (r < k && e >= int64_t(ctl->fstart[r + 1])) ++r;
-    dist[e] = uint8_t(r);
   }
 }
 
@@ -656,99 +746,81 @@ __global__ void __launch_bounds__(kBlock)
 
 // ---- host wrappers ----------------------------------------------------------
 
-void warm_begin(const DevModel& m, StepCtl* ctl, const uint32_t* midx,
+void warm_begin(const DevModel& m, StepCtl* ctl, const Sums& sm, int sel_grid,
                 const Side& c, const WarmBufs& wb, uint32_t* cnt_m,
-                int64_t n_old, bool holes, uint32_t* scan_tmp, int* err,
-                hipStream_t s) {
-  k_warm_fill<<<grid_for(cdiv(n_old, 4)), kBlock, 0, s>>>(c.dist, ctl, err);
-  if (holes) {
-    // holes, ascending, into the free list
-    const int g = tiles_for(n_old);
-    k_dist_count<<<g, kBlock, 0, s>>>(c.dist, &ctl->n_old, int(kHole),
-                                      scan_tmp);
-    tile_sums_scan(scan_tmp, &ctl->n_old, &ctl->nfree, err, s);
-    k_dist_write<<<g, kBlock, 0, s>>>(1, nullptr, c.dist, &ctl->n_old,
-                                      int(kHole), scan_tmp, nullptr, wb.freel);
-  }
-  k_warm_mark<<<grid_for(n_old), kBlock, 0, s>>>(m, ctl, midx, c.pay, c.dist,
-                                                  cnt_m, holes ? 1 : 0, err);
+                int64_t n_old, bool holes, int* err, hipStream_t s) {
+  const int g = sum_grid(n_old, kBlock * 16);
+  k_warm_select<<<g, kBlock, 0, s>>>(m, ctl, sm.bits, sm.sel, sel_grid, c.pay,
+                                     c.dist, cnt_m, holes ? sm.hole : nullptr,
+                                     err);
+  if (holes)
+    k_warm_holes<<<g, kBlock, 0, s>>>(ctl, c.dist, sm.hole, wb.freel, err);
 }
 
 void warm_round(const DevModel& m, int Wi, int prec, const Side& c, int r,
-                StepCtl* ctl, int64_t cap, int64_t n_old, int64_t est,
+                StepCtl* ctl, int64_t cap, int64_t n_old, int64_t n_cand,
                 uint64_t* table, uint64_t mask, const RoundBufs& rb,
-                const WarmBufs& wb, uint32_t* scan_tmp, void* psi,
+                const WarmBufs& wb, const Sums& sm, void* psi,
                 int64_t row_limit, int* err, hipStream_t s) {
-  const int D = m.D;
-  const int go = tiles_for(n_old);
-#define PACES_WARM_OLD(WRITE)                                                 \
-  switch (D) {                                                                \
-    case 4: k_warm_old<WRITE, 4><<<go, kBlock, 0, s>>>(PACES_WARM_OLD_ARGS); break;   \
-    case 6: k_warm_old<WRITE, 6><<<go, kBlock, 0, s>>>(PACES_WARM_OLD_ARGS); break;   \
-    case 8: k_warm_old<WRITE, 8><<<go, kBlock, 0, s>>>(PACES_WARM_OLD_ARGS); break;   \
-    case 10: k_warm_old<WRITE, 10><<<go, kBlock, 0, s>>>(PACES_WARM_OLD_ARGS); break; \
-    case 12: k_warm_old<WRITE, 12><<<go, kBlock, 0, s>>>(PACES_WARM_OLD_ARGS); break; \
-    case 14: k_warm_old<WRITE, 14><<<go, kBlock, 0, s>>>(PACES_WARM_OLD_ARGS); break; \
-    default: break;                                                           \
+  const int vb = rows_per_lane(n_old);
+  const int go = sum_grid(n_old, int64_t(kBlock) * vb);
+#define PACES_WARM_COUNT(DT)                                               \
+  k_warm_count<DT><<<go, kBlock, 0, s>>>(m, r, vb, ctl, c.pay, c.col, c.dist, \
+                                         wb.wmask, sm.old_, err)
+  switch (m.D) {
+    case 4: PACES_WARM_COUNT(4); break;
+    case 6: PACES_WARM_COUNT(6); break;
+    case 8: PACES_WARM_COUNT(8); break;
+    case 10: PACES_WARM_COUNT(10); break;
+    case 12: PACES_WARM_COUNT(12); break;
+    case 14: PACES_WARM_COUNT(14); break;
+    default: break;
   }
-#define PACES_WARM_OLD_ARGS \
-  m, r, ctl, c.pay, c.col, c.dist, wb.wmask, scan_tmp, wb.wlist, rb.cand_cap, err
-  PACES_WARM_OLD(false)
-  tile_sums_scan(scan_tmp, &ctl->n_old, &ctl->w_noc, err, s);
-  PACES_WARM_OLD(true)
-#undef PACES_WARM_OLD_ARGS
-#undef PACES_WARM_OLD
-  k_warm_prep<<<1, 1, 0, s>>>(ctl, r, D, rb.cand_cap, err);
-  // candidates: at most the set's slots plus the new states'
-  const int64_t nc_bound = std::min<int64_t>(rb.cand_cap, (n_old + est) * D);
-  const int g = grid_for(nc_bound);
+#undef PACES_WARM_COUNT
+  k_warm_list<<<go, kBlock, 0, s>>>(r, vb, ctl, c.dist, wb.wmask, sm.old_,
+                                    wb.wlist, rb.cand_cap, err);
+  const int g = sum_grid(std::min(rb.cand_cap, n_cand), kBlock);
   PACES_DISPATCH_W(Wi, k_warm_probe<WW><<<g, kBlock, 0, s>>>(
-                           m, r, ctl, row_limit, c, wb.freel, wb.wlist, table,
-                           mask, rb.c_slot, rb.c_ref, rb.tile_cnt, err));
-  tile_scan(rb.tile_cnt, &ctl->r_ntiles, cdiv(nc_bound, kBlock), rb.scan_tmp,
-            rb.tile_base, &ctl->r_total, err, s);
+                           m, r, ctl, row_limit, c, wb.freel, wb.wlist,
+                           sm.old_, go, rb.cand_cap, table, mask, rb.c_slot,
+                           rb.c_ref, sm.own, err));
   if (prec == 64) {
     PACES_DISPATCH_W(Wi, k_warm_commit<WW, double2><<<g, kBlock, 0, s>>>(
                              m, r, ctl, cap, c, wb.freel, wb.wlist, table,
-                             mask, rb.c_slot, rb.c_ref, rb.tile_base,
+                             mask, rb.c_slot, rb.c_ref, sm.own,
                              (double2*)psi, err));
   } else {
     PACES_DISPATCH_W(Wi, k_warm_commit<WW, float2><<<g, kBlock, 0, s>>>(
                              m, r, ctl, cap, c, wb.freel, wb.wlist, table,
-                             mask, rb.c_slot, rb.c_ref, rb.tile_base,
+                             mask, rb.c_slot, rb.c_ref, sm.own,
                              (float2*)psi, err));
   }
-  k_warm_finish<<<1, 1, 0, s>>>(ctl, r, err);
 }
 
-void warm_sizes(const DevModel& m, const Side& c, int k, StepCtl* ctl,
-                int64_t est, int64_t max_states, uint32_t* ball, int* err,
-                hipStream_t s) {
-  k_warm_range<<<1, 1, 0, s>>>(ctl, m.R, ball, err);
-  const int per_real = (m.R > 1 || max_states > 0) ? 1 : 0;
+void warm_cap_check(const DevModel& m, const Side& c, int k, StepCtl* ctl,
+                    int64_t est, int64_t max_states, uint32_t* ball, int* err,
+                    hipStream_t s) {
   // 16 rows per thread and one count added to the total per block
   k_warm_live<<<std::min(grid_for(cdiv(est, 16)), 512), kBlock, 0, s>>>(
-      m, k, ctl, c.dist, c.pay, per_real, ball, err);
-  if (max_states > 0)
-    k_warm_cap_over<<<1, 1, 0, s>>>(m.R, max_states, ball, err);
+      m, k, ctl, c.dist, c.pay, ball, err);
+  k_warm_cap_over<<<1, 1, 0, s>>>(m.R, max_states, ball, err);
 }
 
 int warm_commit(const DevModel& m, int Wi, int prec, const Side& c, int k,
-                StepCtl* ctl, int64_t n_old, int64_t est, uint64_t* table,
+                StepCtl* ctl, int64_t n_old, int64_t n_found, uint64_t* table,
                 uint64_t mask, const WarmBufs& wb, void* psi,
                 double* mass_part, int* err, hipStream_t s) {
-  const int g = std::min(grid_for(n_old), kPartBlocks);
+  const int g = std::min(std::max(sum_grid(n_old, kBlock * 16),
+                                  grid_for(n_found * m.D)), kPartBlocks);
   if (prec == 64) {
-    PACES_DISPATCH_W(Wi, k_warm_drop<WW, double2><<<g, kBlock, 0, s>>>(
-                             m, k, ctl, c, table, mask, (double2*)psi,
-                             mass_part, err));
+    PACES_DISPATCH_W(Wi, k_warm_settle<WW, double2><<<g, kBlock, 0, s>>>(
+                             m, k, ctl, c, wb.freel, table, mask,
+                             (double2*)psi, mass_part, err));
   } else {
-    PACES_DISPATCH_W(Wi, k_warm_drop<WW, float2><<<g, kBlock, 0, s>>>(
-                             m, k, ctl, c, table, mask, (float2*)psi,
-                             mass_part, err));
+    PACES_DISPATCH_W(Wi, k_warm_settle<WW, float2><<<g, kBlock, 0, s>>>(
+                             m, k, ctl, c, wb.freel, table, mask,
+                             (float2*)psi, mass_part, err));
   }
-  PACES_DISPATCH_W(Wi, k_warm_fix<WW><<<grid_for(est * m.D), kBlock, 0, s>>>(
-                           m, ctl, c, wb.freel, table, mask, err));
   return g;
 }
 
@@ -763,34 +835,21 @@ void warm_unstage(const StepCtl* ctl, const Side& c, const WarmBufs& wb,
     k_warm_unstage_rows<<<grid_for(n_old), kBlock, 0, s>>>(c.dist, n_old);
 }
 
-void dist_of_rounds(const StepCtl* ctl, int k, uint8_t* dist, int64_t est,
-                    hipStream_t s) {
-  k_dist_rounds<<<grid_for(est), kBlock, 0, s>>>(ctl, k, dist);
-}
-
 void dist_fill(uint8_t* dist, int64_t n, uint8_t v, hipStream_t s) {
   if (n > 0) k_dist_fill<<<grid_for(n), kBlock, 0, s>>>(dist, n, v);
 }
 
 void rows_at_distance(int Wi, const uint64_t* keys, const uint8_t* dist,
                       int64_t n, int d, uint64_t* out, uint32_t* rows,
-                      uint32_t* count, uint32_t* tmp, hipStream_t s) {
+                      uint32_t* count, uint32_t* sums, hipStream_t s) {
   if (n <= 0) {
     k_u32_set<<<1, 1, 0, s>>>(count, 0);
     return;
   }
-  const int g = tiles_for(n);
-  // the kernels read the row count from device memory: the last word of
-  // tmp, past the tile sums; the word before it is a clear latch for the
-  // scan, which skips its work when its latch is set (the sim's own may
-  // hold the error of a step that is being repeated)
-  uint32_t* nrows = tmp + scan_tmp_words(n) - 1;
-  int* clear = reinterpret_cast<int*>(tmp + scan_tmp_words(n) - 2);
-  k_u32_set<<<1, 1, 0, s>>>(nrows, n);
-  k_u32_set<<<1, 1, 0, s>>>(reinterpret_cast<uint32_t*>(clear), 0);
-  k_dist_count<<<g, kBlock, 0, s>>>(dist, nrows, d, tmp);
-  tile_sums_scan(tmp, nrows, count, clear, s);
-  k_dist_write<<<g, kBlock, 0, s>>>(Wi, keys, dist, nrows, d, tmp, out, rows);
+  const int g = sum_grid(n, kTile);
+  k_dist_count<<<g, kBlock, 0, s>>>(dist, n, d, sums);
+  k_dist_write<<<g, kBlock, 0, s>>>(Wi, keys, dist, n, d, sums, count, out,
+                                    rows);
 }
 
 void gather_rows(int Wi, size_t A, const Side& c, const void* psi,

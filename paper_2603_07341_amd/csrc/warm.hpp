@@ -50,14 +50,13 @@ struct WarmBufs {
   uint32_t* freel;  // [rows] holes of the set, ascending
 };
 
-// Distances of the rows in [0, n_old): kHole kept, 0 on M (midx[0, nM)),
-// kFar elsewhere; the holes into freel (ctl->nfree; holes false: the set
-// has none, and the free list is not built); |M| per realization into
-// cnt_m; the step's other counts cleared.
-void warm_begin(const DevModel& m, StepCtl* ctl, const uint32_t* midx,
+// Distances of the rows in [0, n_old): kHole kept, 0 on the selected rows
+// (bits and sums of a kernel on sel_grid blocks), kFar elsewhere; the holes
+// into freel (ctl->nfree; holes false: the set has none, and the free list
+// is not built); ctl->nM and |M| per realization into cnt_m.
+void warm_begin(const DevModel& m, StepCtl* ctl, const Sums& sm, int sel_grid,
                 const Side& c, const WarmBufs& wb, uint32_t* cnt_m,
-                int64_t n_old, bool holes, uint32_t* scan_tmp, int* err,
-                hipStream_t s);
+                int64_t n_old, bool holes, int* err, hipStream_t s);
 // Round r (1..k): live rows at distance r-1 mark their neighbours inside
 // the set at distance r and hand the slots whose neighbour is outside it
 // on as candidates; states found in round r-1 hand on every slot.
@@ -67,25 +66,27 @@ void warm_begin(const DevModel& m, StepCtl* ctl, const uint32_t* midx,
 // amplitude 0.  A row past cap latches kErrCapacity; more candidates than
 // the buffers hold latch kErrChunks; M and the found states together
 // beyond row_limit (0: none) latch kErrOver.
+// n_old, n_cand: estimates of the rows and of a round's candidates, which
+// only size grids.
 void warm_round(const DevModel& m, int Wi, int prec, const Side& c, int r,
-                StepCtl* ctl, int64_t cap, int64_t n_old, int64_t est,
+                StepCtl* ctl, int64_t cap, int64_t n_old, int64_t n_cand,
                 uint64_t* table, uint64_t mask, const RoundBufs& rb,
-                const WarmBufs& wb, uint32_t* scan_tmp, void* psi,
+                const WarmBufs& wb, const Sums& sm, void* psi,
                 int64_t row_limit, int* err, hipStream_t s);
-// Sizes after the search: the row range n_new and the live rows n_live;
-// live rows per realization into ball (with max_states > 0, a realization
-// above it latches kErrCap).
-void warm_sizes(const DevModel& m, const Side& c, int k, StepCtl* ctl,
-                int64_t est, int64_t max_states, uint32_t* ball, int* err,
-                hipStream_t s);
+// State cap, before the commit: live rows of the new set per realization
+// into ball; one above max_states latches kErrCap.
+void warm_cap_check(const DevModel& m, const Side& c, int k, StepCtl* ctl,
+                    int64_t est, int64_t max_states, uint32_t* ball, int* err,
+                    hipStream_t s);
 // The commit.  Drop pass: every live row the search did not reach (kFar)
 // becomes a hole (its weight into per-block partials, one double per
 // block or R per block; amplitude 0; table entry a tombstone; its own and
 // its neighbours' columns toward it -1).  Then the found states: distance
 // r, table entry plain, columns by lookup (also the column of a live
-// neighbour toward them).  Returns the number of partial blocks.
+// neighbour toward them).  Sets ctl->n_new.  Returns the number of partial
+// blocks.  n_found: estimate of the found states, for the grid.
 int warm_commit(const DevModel& m, int Wi, int prec, const Side& c, int k,
-                StepCtl* ctl, int64_t n_old, int64_t est, uint64_t* table,
+                StepCtl* ctl, int64_t n_old, int64_t n_found, uint64_t* table,
                 uint64_t mask, const WarmBufs& wb, void* psi,
                 double* mass_part, int* err, hipStream_t s);
 // Before a repeated search: staged and candidate entries of the table back
@@ -94,20 +95,15 @@ int warm_commit(const DevModel& m, int Wi, int prec, const Side& c, int k,
 void warm_unstage(const StepCtl* ctl, const Side& c, const WarmBufs& wb,
                   uint64_t* table, uint64_t mask, int64_t n_old,
                   hipStream_t s);
-// Distance bytes of a set built from scratch: round r of rows [fstart[r],
-// fstart[r+1]) (r = 0..k), so that the set has no holes and its frontiers
-// read like those of an in-place step.
-void dist_of_rounds(const StepCtl* ctl, int k, uint8_t* dist, int64_t est,
-                    hipStream_t s);
 // dist[0, n) = v.
 void dist_fill(uint8_t* dist, int64_t n, uint8_t v, hipStream_t s);
 // Keys of the rows [0, n) whose distance is d (d < 0: every live row), in
 // row order, into out (Wi words each; null: none); their rows into rows
-// (may be null); their count into *count (device).  tmp: scan space of
-// scan_tmp_words(n) words.  Works whatever the sim's latch holds.
+// (may be null); their count into *count (device).  sums: kSumBlocks words.
+// Works whatever the sim's latch holds.
 void rows_at_distance(int Wi, const uint64_t* keys, const uint8_t* dist,
                       int64_t n, int d, uint64_t* out, uint32_t* rows,
-                      uint32_t* count, uint32_t* tmp, hipStream_t s);
+                      uint32_t* count, uint32_t* sums, hipStream_t s);
 // Gather rows idx[0, n) of a set (keys, payload, totals and the amplitude,
 // A bytes each) into dense arrays (any output may be null).
 void gather_rows(int Wi, size_t A, const Side& c, const void* psi,
