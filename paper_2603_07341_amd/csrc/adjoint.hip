@@ -146,7 +146,7 @@ __global__ void __launch_bounds__(kBlock)
   double2* yk = (kk & 1) ? ty1 : ty0;
   double2* yo = (kk & 1) ? ty0 : ty1;
   const bool more = kk + 1 < K;
-  for (int64_t i = gtid(); i < n; i += gstride()) {
+  for (int64_t i = gtid_xcd(); i < n; i += gstride()) {
     const double2 xv = xk[i], yv = yk[i];
     for (int q = 0; q < nq; ++q) {
       const double2 c = cn[q * kMaxTerms + kk];

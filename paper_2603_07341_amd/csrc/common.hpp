@@ -158,6 +158,29 @@ __device__ __forceinline__ int64_t gstride() {
   return int64_t(gridDim.x) * blockDim.x;
 }
 
+// Grid-stride start of the kernels that gather along the ELL columns.
+// Blocks are dealt to the eight XCDs in turn, so neighbouring rows' gathers,
+// which share cache lines, would land in different L2s; here runs of kXcdRun
+// consecutive blocks (8192 rows) go to one XCD instead, while the XCDs still
+// walk the rows side by side (one slice per XCD measured slower: the
+// windows the gathers meet in then lie eight slices apart in the last-level
+// cache).  Middle Clenshaw term, runs of 0 / 4 / 16 / 64 / 256 blocks:
+// ring16 at 1.31e7 rows 260.6 / 253.8 / 250.0 / 252.9 / 256.9 us, complex64
+// at 8.9e6 125.5 / 119.9 / 119.6 / 119.0 / 121.5, the 25-site chain at
+// 1.63e7 360.0 / 350.8 / 347.6 / 342.9 / 350.7, 3x3x3 at 7.1e6
+// 193.8 / 189.8 / 183.8 / 186.2 / 185.3.  Blocks past the last full round of
+// 8 runs keep their place.
+constexpr int kXcds = 8, kXcdRun = 32;
+__device__ __forceinline__ int64_t gtid_xcd() {
+  constexpr unsigned round = kXcds * kXcdRun;
+  unsigned b = blockIdx.x;
+  if (b < gridDim.x / round * round) {
+    const unsigned i = b / kXcds;
+    b = i / kXcdRun * round + b % kXcds * kXcdRun + i % kXcdRun;
+  }
+  return int64_t(b) * blockDim.x + threadIdx.x;
+}
+
 // The error latch as other blocks of the running kernel left it (a plain
 // load may be served from a stale line of this die's cache).
 __device__ __forceinline__ int latch_now(const int* err) {

@@ -69,7 +69,7 @@ __global__ void __launch_bounds__(kBlock)
     __syncthreads();
   }
   double sp = 0, sn = 0, sz = 0;
-  for (int64_t i = gtid(); i < n; i += gstride()) {
+  for (int64_t i = gtid_xcd(); i < n; i += gstride()) {
     const uint64_t p = ld_stream(pay + i);
     const int r = Rn > 1 ? pay_real(p) : 0;
     if (Rn > 1 && !lz_live(st[r], j)) continue;

@@ -163,7 +163,7 @@ __global__ void __launch_bounds__(kBlock)
   for (int q = 0; q < ND; ++q) jv[q] = R(m.J[q]);
   const bool energy = L == 0 && want_energy;
   double esum = 0;
-  for (int64_t i = gtid(); i < n; i += gstride()) {
+  for (int64_t i = gtid_xcd(); i < n; i += gstride()) {
     const uint64_t p = ld_stream(pay + i);
     const TaylorPlan& P = plan[Rn > 1 ? pay_real(p) : 0];
     const int total = P.m * P.s;
