@@ -45,8 +45,7 @@
 namespace paces {
 namespace {
 
-constexpr int kItems = 8;
-constexpr int kTile = kBlock * kItems;
+constexpr int kItems = 8;  // tiles of kBlock rows in flight per block
 // Grid-stride kernels launch at most this many blocks (4M threads, several
 // times what the 256 CUs hold): blocks beyond the work are dispatched only
 // to exit, and with grids sized from a row estimate they cost the
@@ -76,14 +75,6 @@ inline void launch_ev(void (*kern)(K...), int grid, hipStream_t s,
                           0u, K(args)...);
   else
     kern<<<grid, kBlock, 0, s>>>(K(args)...);
-}
-
-// Grid for a kernel striding over tiles of kTile items.
-inline int tiles_for(int64_t bound) {
-  int64_t g = cdiv(bound, kTile);
-  if (g < 1) g = 1;
-  if (g > 2048) g = 2048;
-  return int(g);
 }
 
 // |c|^2 as fl(fl(re*re) + fl(im*im)) in FP64 (FP32 amplitudes widened
@@ -179,6 +170,21 @@ __device__ __forceinline__ int64_t gtid_xcd() {
     b = i / kXcdRun * round + b % kXcds * kXcdRun + i % kXcdRun;
   }
   return int64_t(b) * blockDim.x + threadIdx.x;
+}
+
+// Arrival of one block at the end of a kernel: true in every lane of the
+// block that arrives last, whose reads then see what the others wrote.  The
+// counter is left at zero for the next kernel that uses it.
+__device__ __forceinline__ bool last_block(uint32_t* ticket, uint32_t blocks) {
+  __shared__ int last;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_ACQ_REL,
+                                  __HIP_MEMORY_SCOPE_AGENT) == blocks - 1;
+    if (last) *ticket = 0u;
+  }
+  __syncthreads();
+  return last != 0;
 }
 
 // The error latch as other blocks of the running kernel left it (a plain
@@ -341,12 +347,16 @@ __device__ __forceinline__ void count_flush(int R, uint32_t* lds,
 }
 
 // J_k(x) by its power series sum_j (-1)^j (x/2)^(2j+k) / (j! (j+k)!); for
-// x <= 2 every term shrinks and no cancellation occurs.
+// x <= 2 every term shrinks and no cancellation occurs.  Below 1e-60 the
+// leading factor (which only shrinks, x / 2 <= 1) is taken as zero: far under
+// every tolerance, and without the up to 128 divisions of the high orders.
 __device__ double bessel_series(double x, int k) {
   const double h = 0.5 * x, h2 = h * h;
   double lead = 1.0;
-  for (int q = 1; q <= k; ++q) lead *= h / q;
-  if (lead == 0.0) return 0.0;
+  for (int q = 1; q <= k; ++q) {
+    lead *= h / q;
+    if (lead < 1e-60) return 0.0;
+  }
   double term = lead, sum = lead;
   for (int j = 1; j < 60; ++j) {
     term *= -h2 / (double(j) * double(j + k));

@@ -52,7 +52,10 @@ __global__ void __launch_bounds__(kBlock)
 // runs show in stream order.
 __global__ void k_mark(int tag) { (void)tag; }
 
-__global__ void k_clear_err(int* err) { *err = 0; }
+__global__ void k_clear_err(int* err, StepCtl* ctl) {
+  *err = 0;
+  ctl->ticket = 0;
+}
 
 // ---- a given set of states (stateless propagation) --------------------------
 // Canonical keys of W words to the internal width Wi >= W (leading zero
@@ -128,13 +131,14 @@ __global__ void k_begin_step(StepCtl* ctl, int* err, uint32_t* cnt,
     ctl->w_moved = 0;  // an in-place step has not committed
     ctl->w_tomb = 0;
     ctl->w_drop = 0;
+    ctl->ticket = 0;
   }
 }
 
 // ---- select -----------------------------------------------------------------
-// A tile is kTile rows; element t*kTile + q*kBlock + lane belongs to lane
-// `lane` (q = 0..kItems-1), so every load of the block is one contiguous run
-// and the bits of a wave's 64 rows are one ballot.
+// A tile is kBlock rows, row t * kBlock + lane of lane `lane`, and a block
+// takes kItems of its tiles at a time: every load of the block is one
+// contiguous run, and the bits of a wave's 64 rows are one ballot.
 
 // Rows that are holes (dist == kHole, left by dropped rows of in-place
 // steps) are never selected; dist may be null (no holes).
@@ -154,12 +158,13 @@ __global__ void __launch_bounds__(kBlock)
     k_select_bits(const Amp* psi, const uint8_t* dist, const StepCtl* ctl,
                   double th2, uint64_t* bits, uint32_t* sums) {
   const int64_t n = ctl->n_old;
-  const TileRun run = tile_run(cdiv(n, kTile), gridDim.x);
+  const TileRun run = tile_run(cdiv(n, kBlock), gridDim.x);
   uint32_t v = 0;
-  for (int64_t t = run.t0; t < run.t1; ++t) {
+  for (int64_t t = run.t0; t < run.t1; t += kItems) {
 #pragma unroll
     for (int q = 0; q < kItems; ++q) {
-      const int64_t e = t * kTile + q * kBlock + threadIdx.x;
+      if (t + q >= run.t1) break;
+      const int64_t e = (t + q) * kBlock + threadIdx.x;
       const bool keep = e < n && weight(psi[e]) >= th2 && !is_hole(dist, e);
       put_bits(bits, e, n, keep);
       v += keep ? 1u : 0u;
@@ -175,12 +180,13 @@ __global__ void __launch_bounds__(kBlock)
     k_flag_bits(const uint8_t* keep, const StepCtl* ctl, uint64_t* bits,
                 uint32_t* sums) {
   const int64_t n = ctl->n_old;
-  const TileRun run = tile_run(cdiv(n, kTile), gridDim.x);
+  const TileRun run = tile_run(cdiv(n, kBlock), gridDim.x);
   uint32_t v = 0;
-  for (int64_t t = run.t0; t < run.t1; ++t) {
+  for (int64_t t = run.t0; t < run.t1; t += kItems) {
 #pragma unroll
     for (int q = 0; q < kItems; ++q) {
-      const int64_t e = t * kTile + q * kBlock + threadIdx.x;
+      if (t + q >= run.t1) break;
+      const int64_t e = (t + q) * kBlock + threadIdx.x;
       const bool k = e < n && keep[e];
       put_bits(bits, e, n, k);
       v += k ? 1u : 0u;
@@ -199,17 +205,18 @@ __global__ void __launch_bounds__(kBlock)
                    uint32_t* midx, const int* err) {
   if (*err) return;
   const int64_t n = ctl->n_old;
-  const TileRun run = tile_run(cdiv(n, kTile), gridDim.x);
+  const TileRun run = tile_run(cdiv(n, kBlock), gridDim.x);
   uint64_t total;
   uint32_t at = uint32_t(sums_before(sums, gridDim.x, blockIdx.x, &total));
   if (gtid() == 0) {
     ctl->nM = uint32_t(total);
     ctl->fstart[1] = uint32_t(total);
   }
-  for (int64_t t = run.t0; t < run.t1; ++t) {
+  for (int64_t t = run.t0; t < run.t1; t += kItems) {
 #pragma unroll
     for (int q = 0; q < kItems; ++q) {
-      const int64_t e = t * kTile + q * kBlock + threadIdx.x;
+      if (t + q >= run.t1) break;
+      const int64_t e = (t + q) * kBlock + threadIdx.x;
       const bool k = e < n && ((bits[e >> 6] >> (e & 63)) & 1u);
       uint32_t tot;
       const uint32_t off = block_excl_scan(k ? 1u : 0u, &tot) + at;
@@ -527,9 +534,16 @@ template <int W>
 __global__ void __launch_bounds__(kBlock)
     k_lookup_cols(DevModel m, const uint64_t* keys, const uint64_t* pay,
                   StepCtl* ctl, int k, const uint64_t* table, uint64_t mask,
-                  int32_t* col, int64_t max_states, uint32_t* ball, int* err) {
+                  int32_t* col, int64_t max_states, uint32_t* ball,
+                  const uint64_t* keys0, int64_t n0, int32_t* p0, int* err) {
   if (*err) return;
   const int D = m.D;
+  // rows of the initial states in the new set
+  for (int64_t i = gtid(); i < n0; i += gstride()) {
+    uint64_t key[W];
+    load_key<W>(keys0, i, key);
+    p0[i] = int32_t(table_find<W>(table, mask, keys, key, key_hash<W>(m, key)));
+  }
   const int64_t f0 = ctl->fstart[k];
   const int64_t f1 = ctl->fstart[k + 1];
   const int64_t nc = (f1 - f0) * D;
@@ -727,7 +741,7 @@ __global__ void __launch_bounds__(kBlock)
   if (threadIdx.x == 0) {
     if (K > kcap)
       atomicOr(err, kErrTerms);
-    else if (K > launched)
+    else if (K - 1 > launched)  // launch indices K - 2 .. 0 do the work
       atomicOr(err, kErrNeedTerms);
     atomicMax(&ctl->kmax, uint32_t(K));
     cc->emin = emin;
@@ -736,11 +750,13 @@ __global__ void __launch_bounds__(kBlock)
     cc->b = b;
     cc->alpha = 1.0 / a;
     cc->beta = -b / a;
+    cc->K = K;
+  }
+  if (threadIdx.x == 64) {  // another wave's lane: beside the stores above
     double sn, cs;
     sincos(b * dt, &sn, &cs);
     cc->phase[0] = cs;
     cc->phase[1] = -sn;
-    cc->K = K;
   }
   for (int k = threadIdx.x; k < K && k < kMaxTerms; k += blockDim.x) {
     const double v = (k == 0 ? 1.0 : 2.0) * J[k];
@@ -975,7 +991,7 @@ __global__ void __launch_bounds__(kBlock)
   extern __shared__ double lds[];
   if (*err) return;
   const int64_t n = ctl->n_new;
-  const TileRun run = tile_run(cdiv(n, kTile), gridDim.x);
+  const TileRun run = tile_run(cdiv(n, kBlock), gridDim.x);
   const bool priv = Rn == 1 && N <= kPrivBins;
   // up to kRegBins sites: each thread sums its rows' weights per site in
   // registers and adds them to its lane's LDS bins once at the end
@@ -997,10 +1013,11 @@ __global__ void __launch_bounds__(kBlock)
   __syncthreads();
   double n2 = 0;
   uint32_t rows = 0, kept = 0;
-  for (int64_t t = run.t0; t < run.t1; ++t) {
+  for (int64_t t = run.t0; t < run.t1; t += kItems) {
 #pragma unroll
     for (int q = 0; q < kItems; ++q) {
-      const int64_t e = t * kTile + q * kBlock + threadIdx.x;
+      if (t + q >= run.t1) break;
+      const int64_t e = (t + q) * kBlock + threadIdx.x;
       bool keep = false;
       if (e < n && !is_hole(dist, e)) {
         const double w = weight(psi[e]);
@@ -1049,13 +1066,14 @@ __global__ void __launch_bounds__(kBlock)
       if (all) atomicAdd(&cnt_s[0], all);
     }
     __syncthreads();
-    for (int j = threadIdx.x; j < N; j += blockDim.x) {
-      double v = 0;
-      if (priv)
-        for (int l = 0; l < 64; ++l) v += pop_lds[j * 64 + l];
-      else
-        v = pop_lds[j];
-      pop_part[int64_t(blockIdx.x) * N + j] = v;
+    if (priv) {
+      for (int j = threadIdx.x >> 6; j < N; j += kBlock / 64) {
+        const double v = wave_sum(pop_lds[j * 64 + (threadIdx.x & 63)]);
+        if ((threadIdx.x & 63) == 0) pop_part[int64_t(blockIdx.x) * N + j] = v;
+      }
+    } else {
+      for (int j = threadIdx.x; j < N; j += blockDim.x)
+        pop_part[int64_t(blockIdx.x) * N + j] = pop_lds[j];
     }
   } else {
     __syncthreads();
@@ -1069,120 +1087,26 @@ __global__ void __launch_bounds__(kBlock)
   }
 }
 
-// Second level of a deterministic reduction: block b folds partials
-// b, b + gridDim.x, ... into out[b].
-__global__ void __launch_bounds__(kBlock)
-    k_fold_sum(const double* in, int n, double* out, const int* err) {
-  if (*err) return;
-  double s = 0;
-  for (int i = blockIdx.x + gridDim.x * threadIdx.x; i < n;
-       i += gridDim.x * blockDim.x)
-    s += in[i];
-  s = block_sum(s);
-  if (threadIdx.x == 0) out[blockIdx.x] = s;
-}
-
-// ---- autocorrelation <psi0|psi(t)> ------------------------------------------
-// Block r: the n0 initial states of realization r.
-template <int W, typename Amp>
-__global__ void __launch_bounds__(kBlock)
-    k_autocorr(DevModel m, const uint64_t* keys0, const double* amps0,
-               int64_t n0, const uint64_t* table, uint64_t mask,
-               const uint64_t* keys, const Amp* psi, double* out2,
-               int32_t* p0map, const int* err) {
-  if (*err) return;
-  const int64_t base = int64_t(blockIdx.x) * n0;
-  double re = 0, im = 0;
-  for (int64_t i = base + threadIdx.x; i < base + n0; i += blockDim.x) {
-    uint64_t k[W];
-    load_key<W>(keys0, i, k);
-    const int64_t r = table_find<W>(table, mask, keys, k, key_hash<W>(m, k));
-    if (p0map) p0map[i] = int32_t(r);
-    if (r < 0) continue;
-    const double2 v = widen(psi[r]);
-    const double ar = amps0[2 * i], ai = amps0[2 * i + 1];
-    re += ar * v.x + ai * v.y;  // conj(a0) * v
-    im += ar * v.y - ai * v.x;
-  }
-  re = block_sum(re);
-  im = block_sum(im);
-  if (threadIdx.x == 0) {
-    out2[2 * blockIdx.x] = re;
-    out2[2 * blockIdx.x + 1] = im;
-  }
-}
-
 // ---- observation record -----------------------------------------------------
-// Block (x, r): x < N reduces population (r, x), x = N the scalars of
-// realization r; each folds the per-block partials with a fixed lane
-// mapping.  Records of one step are stored realization after realization.
-__global__ void __launch_bounds__(kBlock)
-    k_obs_final(int N, int Rn, int want_energy, double dt, int n_mass, int n_e,
-                int n_pop, const double* mass_part, const double* n2_part,
-                const double* e_part, const double* en_part,
-                const double* pop_part, const double* a2, const ChebCoef* cc,
-                const StepCtl* ctl, const uint32_t* cnt,
-                const double* mass_tot, double* ring, int rec_doubles,
-                int64_t ring_cap, int* err) {
-  if (*err) return;
-  if (int64_t(ctl->nrec) + 1 > ring_cap) return;  // the host keeps room
-  const int r = blockIdx.y;
-  double* rec = ring + (int64_t(ctl->nrec) * Rn + r) * rec_doubles;
-  if (int(blockIdx.x) < N) {
-    double s = 0;
-    for (int b = threadIdx.x; b < n_pop; b += blockDim.x)
-      s += pop_part[(int64_t(b) * Rn + r) * N + blockIdx.x];
-    s = block_sum(s);
-    if (threadIdx.x == 0) rec[kObsFields + blockIdx.x] = s;
-    return;
-  }
-  double ms = 0, n2 = 0, en = 0;
-  for (int i = threadIdx.x; i < n_mass; i += blockDim.x)
-    ms += mass_part[int64_t(i) * Rn + r];
-  for (int i = threadIdx.x; i < n_pop; i += blockDim.x)
-    n2 += n2_part[int64_t(i) * Rn + r];
-  if (want_energy) {
-    if (Rn == 1)
-      for (int i = threadIdx.x; i < n_e; i += blockDim.x) en += e_part[i];
-    else
-      for (int i = threadIdx.x; i < n_pop; i += blockDim.x)
-        en += en_part[int64_t(i) * Rn + r];
-  }
-  ms = block_sum(ms);
-  n2 = block_sum(n2);
-  en = block_sum(en);
-  if (threadIdx.x == 0) {
-    rec[0] = ctl->t + dt;
-    rec[1] = n2;
-    rec[2] = want_energy ? en : NAN;
-    rec[3] = a2[2 * r];
-    rec[4] = a2[2 * r + 1];
-    rec[5] = ms;
-    rec[6] = mass_tot[r] + ms;
-    rec[7] = double(cnt[Rn + r]);
-    rec[8] = double(cnt[r]);
-    rec[9] = double(cc[r].K);
-    rec[10] = cc[r].emin;
-    rec[11] = cc[r].emax;
-    if (!isfinite(n2)) atomicOr(err, kErrNonFinite);
-  }
-}
-
-// Commit the step on the device: time, cumulative discarded weight per
-// realization, record count and the row count of the current set.
-// The last kernel of a step also mirrors the counts and the error latch into
-// mapped pinned host memory, so the host reads them after one stream
-// synchronisation without copy dispatches.
-__global__ void k_end_step(StepCtl* ctl, int Rn, const double* ring,
-                           int rec_doubles, double* mass_tot, const int* err,
-                           uint32_t* h_ctl, int* h_err) {
-  const int e = *err;
-  if (threadIdx.x == 0 && !e) {
+// Commit of a step on the device: time, cumulative discarded weight per
+// realization, record count and the row count of the current set.  The
+// counts and the error latch are mirrored into mapped pinned host memory, so
+// the host reads them after one stream synchronisation without copy
+// dispatches.
+__device__ __forceinline__ void close_step(StepCtl* ctl, int Rn,
+                                           const double* ring, int rec_doubles,
+                                           double* mass_tot, int e,
+                                           uint32_t* h_ctl, int* h_err) {
+  if (!e) {
     const double* rec = ring + int64_t(ctl->nrec) * Rn * rec_doubles;
-    for (int r = 0; r < Rn; ++r) mass_tot[r] = rec[int64_t(r) * rec_doubles + 6];
-    ctl->t = rec[0];
-    ctl->n_old = ctl->n_new;
-    ctl->nrec += 1;
+    for (int r = threadIdx.x; r < Rn; r += blockDim.x)
+      mass_tot[r] = rec[int64_t(r) * rec_doubles + 6];
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      ctl->t = rec[0];
+      ctl->n_old = ctl->n_new;
+      ctl->nrec += 1;
+    }
   }
   __syncthreads();
   const uint32_t* src = reinterpret_cast<const uint32_t*>(ctl);
@@ -1192,8 +1116,104 @@ __global__ void k_end_step(StepCtl* ctl, int Rn, const double* ring,
   __threadfence_system();
 }
 
-__global__ void k_clear_u32(uint32_t* p, int n) {
-  for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0u;
+// Share of block (x, r) in the records: x < N reduces population (r, x),
+// x = N the scalars of realization r with <psi0|psi(t)> over its n0 initial
+// states (rows p0); each folds the per-block partials with a fixed lane
+// mapping.  Records of one step are stored realization after realization.
+template <typename Amp>
+__device__ __forceinline__ void obs_block(
+    int N, int Rn, int want_energy, double dt, int n_mass, int n_e, int n_pop,
+    const double* mass_part, const double* n2_part, const double* e_part,
+    const double* en_part, const double* pop_part, const double* amps0,
+    int64_t n0, const int32_t* p0, const Amp* psi, const ChebCoef* cc,
+    const StepCtl* ctl, const uint32_t* cnt, const double* mass_tot,
+    double* ring, int rec_doubles, int* err) {
+  const int r = blockIdx.y;
+  double* rec = ring + (int64_t(ctl->nrec) * Rn + r) * rec_doubles;
+  if (int(blockIdx.x) < N) {
+    double s = 0;
+    for (int b = threadIdx.x; b < n_pop; b += blockDim.x)
+      s += pop_part[(int64_t(b) * Rn + r) * N + blockIdx.x];
+    s = block_sum(s);
+    if (threadIdx.x == 0) rec[kObsFields + blockIdx.x] = s;
+  } else {
+    double ms = 0, n2 = 0, en = 0, re = 0, im = 0;
+    for (int i = threadIdx.x; i < n_mass; i += blockDim.x)
+      ms += mass_part[int64_t(i) * Rn + r];
+    for (int i = threadIdx.x; i < n_pop; i += blockDim.x)
+      n2 += n2_part[int64_t(i) * Rn + r];
+    if (want_energy) {
+      if (Rn == 1) {
+        for (int i = threadIdx.x; i < n_e; i += blockDim.x) en += e_part[i];
+      } else {
+        for (int i = threadIdx.x; i < n_pop; i += blockDim.x)
+          en += en_part[int64_t(i) * Rn + r];
+      }
+    }
+    const int64_t base = int64_t(r) * n0;
+    for (int64_t i = base + threadIdx.x; i < base + n0; i += blockDim.x) {
+      const int32_t row = p0[i];
+      if (row < 0) continue;
+      const double2 v = widen(psi[row]);
+      const double ar = amps0[2 * i], ai = amps0[2 * i + 1];
+      re += ar * v.x + ai * v.y;  // conj(a0) * v
+      im += ar * v.y - ai * v.x;
+    }
+    ms = block_sum(ms);
+    n2 = block_sum(n2);
+    en = block_sum(en);
+    re = block_sum(re);
+    im = block_sum(im);
+    if (threadIdx.x == 0) {
+      rec[0] = ctl->t + dt;
+      rec[1] = n2;
+      rec[2] = want_energy ? en : NAN;
+      rec[3] = re;
+      rec[4] = im;
+      rec[5] = ms;
+      rec[6] = mass_tot[r] + ms;
+      rec[7] = double(cnt[Rn + r]);
+      rec[8] = double(cnt[r]);
+      rec[9] = double(cc[r].K);
+      rec[10] = cc[r].emin;
+      rec[11] = cc[r].emax;
+      if (!isfinite(n2)) atomicOr(err, kErrNonFinite);
+    }
+  }
+}
+
+// h_ctl given (one realization): the block that arrives last closes the
+// step.  The sums of the weight and energy partials, <psi0|psi> and the close
+// were four launches of their own before, 3-5 us each.
+template <typename Amp>
+__global__ void __launch_bounds__(kBlock)
+    k_obs_final(int N, int Rn, int want_energy, double dt, int n_mass, int n_e,
+                int n_pop, const double* mass_part, const double* n2_part,
+                const double* e_part, const double* en_part,
+                const double* pop_part, const double* amps0, int64_t n0,
+                const int32_t* p0, const Amp* psi, const ChebCoef* cc,
+                StepCtl* ctl, const uint32_t* cnt, double* mass_tot,
+                double* ring, int rec_doubles, int64_t ring_cap,
+                uint32_t* h_ctl, int* h_err, int* err) {
+  __shared__ int latch;
+  if (threadIdx.x == 0) latch = *err;
+  __syncthreads();
+  if (!latch && int64_t(ctl->nrec) + 1 <= ring_cap)  // the host keeps room
+    obs_block(N, Rn, want_energy, dt, n_mass, n_e, n_pop, mass_part, n2_part,
+              e_part, en_part, pop_part, amps0, n0, p0, psi, cc, ctl, cnt,
+              mass_tot, ring, rec_doubles, err);
+  // every block arrives, also when something is latched
+  if (h_ctl && last_block(&ctl->ticket, gridDim.x * gridDim.y)) {
+    if (threadIdx.x == 0) latch = latch_now(err);
+    __syncthreads();
+    close_step(ctl, Rn, ring, rec_doubles, mass_tot, latch, h_ctl, h_err);
+  }
+}
+
+__global__ void __launch_bounds__(kBlock)
+    k_end_step(StepCtl* ctl, int Rn, const double* ring, int rec_doubles,
+               double* mass_tot, const int* err, uint32_t* h_ctl, int* h_err) {
+  close_step(ctl, Rn, ring, rec_doubles, mass_tot, *err, h_ctl, h_err);
 }
 
 // ---- precision conversion ---------------------------------------------------
@@ -1231,7 +1251,9 @@ void fill_u64(uint64_t* p, int64_t n, uint64_t v, hipStream_t s) {
 
 void mark(int tag, hipStream_t s) { k_mark<<<1, 64, 0, s>>>(tag); }
 
-void clear_latch(int* err, hipStream_t s) { k_clear_err<<<1, 1, 0, s>>>(err); }
+void clear_latch(StepCtl* ctl, int* err, hipStream_t s) {
+  k_clear_err<<<1, 1, 0, s>>>(err, ctl);
+}
 
 void pad_keys(int W, int Wi, const uint64_t* in, uint64_t* out, int64_t n,
               hipStream_t s) {
@@ -1258,7 +1280,7 @@ void begin_step(StepCtl* ctl, int* err, uint32_t* cnt, uint32_t* ball, int R,
 
 int select_bits(int prec, const void* psi, const uint8_t* dist, double th2,
                 const StepCtl* ctl, const Sums& sm, int64_t n, hipStream_t s) {
-  const int g = sum_grid(n, kTile);
+  const int g = sum_grid(n, kBlock);
   if (prec == 64)
     k_select_bits<double2><<<g, kBlock, 0, s>>>((const double2*)psi, dist, ctl,
                                                 th2, sm.bits, sm.sel);
@@ -1270,7 +1292,7 @@ int select_bits(int prec, const void* psi, const uint8_t* dist, double th2,
 
 int flag_bits(const uint8_t* keep, const StepCtl* ctl, const Sums& sm,
               int64_t n, hipStream_t s) {
-  const int g = sum_grid(n, kTile);
+  const int g = sum_grid(n, kBlock);
   k_flag_bits<<<g, kBlock, 0, s>>>(keep, ctl, sm.bits, sm.sel);
   return g;
 }
@@ -1341,10 +1363,11 @@ void expand_round(const DevModel& m, int Wi, int prec, const Side& n, int r,
 void lookup_last(const DevModel& m, int Wi, const Side& n, int k,
                  StepCtl* ctl, int64_t est, const uint64_t* table,
                  uint64_t mask, int32_t* col, int64_t max_states,
-                 uint32_t* ball, int* err, hipStream_t s) {
+                 uint32_t* ball, const uint64_t* keys0, int64_t n0,
+                 int32_t* p0, int* err, hipStream_t s) {
   PACES_DISPATCH_W(Wi, k_lookup_cols<WW><<<grid_for(est * m.D), kBlock, 0, s>>>(
                            m, n.keys, n.pay, ctl, k, table, mask, col,
-                           max_states, ball, err));
+                           max_states, ball, keys0, n0, p0, err));
 }
 
 int part_grid(int64_t rows) { return grid_for(rows); }
@@ -1407,12 +1430,6 @@ void bounds_and_coef(const DevModel& m, const Side& n, const int32_t* col,
                                 ctl, err);
 }
 
-int fold_sum(const double* in, int n, double* out, int* err, hipStream_t s) {
-  const int f = std::max(1, std::min(n, kFold));
-  k_fold_sum<<<f, kBlock, 0, s>>>(in, n, out, err);
-  return f;
-}
-
 int cheb_term(const DevModel& m, int prec, int kk, bool energy, bool mid,
               int64_t est, const StepCtl* ctl, const int32_t* col, int64_t cap,
               const Side& n, const ChebCoef* cc, const void* phi, void* b0,
@@ -1459,7 +1476,7 @@ int pop_norm(int prec, int N, int R, double th2, int64_t est,
   // batched partials hold R * N populations per block: fewer blocks
   // a bounded grid: blocks stride over the tiles, so the per-block work
   // (bins cleared and folded, one count added to the total) is amortised
-  const int g = std::min(tiles_for(est), 1024);
+  const int g = std::min(sum_grid(est, kBlock), 1024);
   if (prec == 64)
     k_pop_norm<double><<<g, kBlock, lds, s>>>(
         N, R, th2, ctl, (const double2*)psi, pay, dist, e_row, n2_part, en_part,
@@ -1471,41 +1488,35 @@ int pop_norm(int prec, int N, int R, double th2, int64_t est,
   return g;
 }
 
-void autocorr(const DevModel& m, int Wi, int prec, const uint64_t* keys0,
-              const double* amps0, int64_t n0, const uint64_t* table,
-              uint64_t mask, const uint64_t* keys, const void* psi,
-              double* out2, int32_t* p0map, int* err, hipStream_t s) {
-  if (prec == 64) {
-    PACES_DISPATCH_W(Wi, k_autocorr<WW, double2><<<m.R, kBlock, 0, s>>>(
-                             m, keys0, amps0, n0, table, mask, keys,
-                             (const double2*)psi, out2, p0map, err));
-  } else {
-    PACES_DISPATCH_W(Wi, k_autocorr<WW, float2><<<m.R, kBlock, 0, s>>>(
-                             m, keys0, amps0, n0, table, mask, keys,
-                             (const float2*)psi, out2, p0map, err));
-  }
-}
-
 void end_step(StepCtl* ctl, int R, const double* ring, int rec_doubles,
               double* mass_tot, int* err, StepCtl* h_ctl_dev, int* h_err_dev,
               hipStream_t s) {
   static_assert(sizeof(StepCtl) % 4 == 0, "StepCtl is copied as 32-bit words");
-  k_end_step<<<1, 64, 0, s>>>(ctl, R, ring, rec_doubles, mass_tot, err,
-                              reinterpret_cast<uint32_t*>(h_ctl_dev),
-                              h_err_dev);
+  k_end_step<<<1, kBlock, 0, s>>>(ctl, R, ring, rec_doubles, mass_tot, err,
+                                  reinterpret_cast<uint32_t*>(h_ctl_dev),
+                                  h_err_dev);
 }
 
-void obs_final(int N, int R, int want_energy, double dt, int n_mass, int n_e,
-               int n_pop, const double* mass_part, const double* n2_part,
-               const double* e_part, const double* en_part,
-               const double* pop_part, const double* a2, const ChebCoef* cc,
-               const StepCtl* ctl, const uint32_t* cnt,
-               const double* mass_tot, double* ring, int rec_doubles,
-               int64_t ring_cap, int* err, hipStream_t s) {
-  k_obs_final<<<dim3(N + 1, R), kBlock, 0, s>>>(
-      N, R, want_energy, dt, n_mass, n_e, n_pop, mass_part, n2_part, e_part,
-      en_part, pop_part, a2, cc, ctl, cnt, mass_tot, ring, rec_doubles,
-      ring_cap, err);
+void obs_final(int prec, int N, int R, int want_energy, double dt, int n_mass,
+               int n_e, int n_pop, const double* mass_part,
+               const double* n2_part, const double* e_part,
+               const double* en_part, const double* pop_part,
+               const double* amps0, int64_t n0, const int32_t* p0,
+               const void* psi, const ChebCoef* cc, StepCtl* ctl,
+               const uint32_t* cnt, double* mass_tot, double* ring,
+               int rec_doubles, int64_t ring_cap, StepCtl* h_ctl_dev,
+               int* h_err_dev, int* err, hipStream_t s) {
+#define PACES_OBS(AMP)                                                        \
+  k_obs_final<AMP><<<dim3(N + 1, R), kBlock, 0, s>>>(                         \
+      N, R, want_energy, dt, n_mass, n_e, n_pop, mass_part, n2_part, e_part,  \
+      en_part, pop_part, amps0, n0, p0, (const AMP*)psi, cc, ctl, cnt,        \
+      mass_tot, ring, rec_doubles, ring_cap,                                  \
+      reinterpret_cast<uint32_t*>(h_ctl_dev), h_err_dev, err)
+  if (prec == 64)
+    PACES_OBS(double2);
+  else
+    PACES_OBS(float2);
+#undef PACES_OBS
 }
 
 void row_info(const DevModel& m, int Wi, const uint64_t* keys, int64_t n,

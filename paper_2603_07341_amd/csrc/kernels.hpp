@@ -59,6 +59,8 @@ struct StepCtl {
   // in-place steps: holes of the set at the step's start (the free list's
   // length); n_new is the set's row range
   uint32_t nfree;
+  uint32_t ticket;                    // blocks of the running kernel that
+                                      // have arrived at its end
   double t;                           // time after the last completed step
 };
 
@@ -98,8 +100,8 @@ int64_t sel_bit_words(int64_t n);
 void fill_u64(uint64_t* p, int64_t n, uint64_t v, hipStream_t s);
 // One empty dispatch (kernel k_mark) on the stream.
 void mark(int tag, hipStream_t s);
-// The error latch cleared on the stream.
-void clear_latch(int* err, hipStream_t s);
+// The error latch (and the arrival counter) cleared on the stream.
+void clear_latch(StepCtl* ctl, int* err, hipStream_t s);
 // A given set of n states as the rows of a step: keys padded from W to Wi
 // words; control counts with frontier 0 = rows [0, n) and the latch
 // cleared; every key valid and distinct (else kErrInput), after the rows
@@ -155,11 +157,13 @@ void expand_round(const DevModel& m, int Wi, int prec, const Side& n, int r,
                   int32_t* col, void* phi, int chunks, int64_t row_limit,
                   int64_t load_rows, int* err, hipStream_t s);
 // Columns of frontier k (lookup only); sets ctl->n_new.  max_states > 0
-// (one realization): the row count into ball[0], kErrCap beyond it.
+// (one realization): the row count into ball[0], kErrCap beyond it.  p0[i]:
+// row of keys0[i], i < n0, or -1.
 void lookup_last(const DevModel& m, int Wi, const Side& n, int k,
                  StepCtl* ctl, int64_t est, const uint64_t* table,
                  uint64_t mask, int32_t* col, int64_t max_states,
-                 uint32_t* ball, int* err, hipStream_t s);
+                 uint32_t* ball, const uint64_t* keys0, int64_t n0,
+                 int32_t* p0, int* err, hipStream_t s);
 // Number of per-block partials written by a kernel over `rows` rows.
 int part_grid(int64_t rows);
 // Returns the number of mass partials written.  tmap (may be null) gets
@@ -182,8 +186,6 @@ void bounds_and_coef(const DevModel& m, const Side& n, const int32_t* col,
 int bounds_part(const DevModel& m, const Side& n, const int32_t* col,
                 int64_t cap, int64_t est, const StepCtl* ctl, double* part,
                 const int* err, hipStream_t s);
-// Fold n per-block partials to at most 256 (deterministic); returns count.
-int fold_sum(const double* in, int n, double* out, int* err, hipStream_t s);
 // Clenshaw launch for index kk (see kernels.hip); buffers b[0], b[1].
 // Returns the number of energy partials (written by the first launch).
 // mid: the launch is expected to be a middle term (selects a kernel name).
@@ -203,12 +205,6 @@ int pop_norm(int prec, int N, int R, double th2, int64_t est,
              const double* e_row, double* n2_part, double* en_part,
              double* pop_part, const Sums& sm, uint32_t* cnt_s, int* err,
              hipStream_t s);
-// <psi0|psi> per realization; p0map (may be null) gets the row of every
-// initial state, -1 if absent.
-void autocorr(const DevModel& m, int Wi, int prec, const uint64_t* keys0,
-              const double* amps0, int64_t n0, const uint64_t* table,
-              uint64_t mask, const uint64_t* keys, const void* psi,
-              double* out2, int32_t* p0map, int* err, hipStream_t s);
 // Commit a successful step on the device: time, discarded weight per
 // realization, record count and the row count of the current set; then
 // mirror *ctl and *err into mapped pinned host memory (device addresses
@@ -217,14 +213,18 @@ void end_step(StepCtl* ctl, int R, const double* ring, int rec_doubles,
               double* mass_tot, int* err, StepCtl* h_ctl_dev, int* h_err_dev,
               hipStream_t s);
 // Reduce partials into observation record ctl->nrec (skipped when an error
-// is latched, so a repeated step records once).
-void obs_final(int N, int R, int want_energy, double dt, int n_mass, int n_e,
-               int n_pop, const double* mass_part, const double* n2_part,
-               const double* e_part, const double* en_part,
-               const double* pop_part, const double* a2, const ChebCoef* cc,
-               const StepCtl* ctl, const uint32_t* cnt,
-               const double* mass_tot, double* ring, int rec_doubles,
-               int64_t ring_cap, int* err, hipStream_t s);
+// is latched, so a repeated step records once); <psi0|psi> per realization
+// from its n0 initial amplitudes and their rows p0 (-1: not in the set).
+// With one realization it then does what end_step does.
+void obs_final(int prec, int N, int R, int want_energy, double dt, int n_mass,
+               int n_e, int n_pop, const double* mass_part,
+               const double* n2_part, const double* e_part,
+               const double* en_part, const double* pop_part,
+               const double* amps0, int64_t n0, const int32_t* p0,
+               const void* psi, const ChebCoef* cc, StepCtl* ctl,
+               const uint32_t* cnt, double* mass_tot, double* ring,
+               int rec_doubles, int64_t ring_cap, StepCtl* h_ctl_dev,
+               int* h_err_dev, int* err, hipStream_t s);
 
 void row_info(const DevModel& m, int Wi, const uint64_t* keys, int64_t n,
               uint64_t* pay, uint64_t* tot, hipStream_t s);

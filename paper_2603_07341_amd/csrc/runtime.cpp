@@ -345,10 +345,8 @@ struct paces_sim {
   double* parts = nullptr;
   double *mass_part = nullptr, *n2_part = nullptr, *e_part = nullptr,
          *en_part = nullptr, *pop_part = nullptr, *bnd_part = nullptr;
-  double *mass_fold = nullptr, *e_fold = nullptr;
   double* e_row = nullptr;     // per-row energy terms (batched sims)
   ChebCoef* cc = nullptr;      // [R]
-  double* a2 = nullptr;        // [R][2]
   uint32_t* cnt = nullptr;     // [2R]: |M_r| then |S_r|
   double* mass_tot = nullptr;  // [R] cumulative discarded weight
 
@@ -913,7 +911,7 @@ void stage_expand_warm(paces_sim* s, int64_t est, hipStream_t st) {
   s->warm_np = warm_commit(dm, Wi, s->prec, c, k, s->ctl, n_old,
                            std::max<int64_t>(s->gcand / dm.D, 256), s->table,
                            s->tmask, s->wb, s->vec[s->ipsi], s->mass_part,
-                           s->err, st);
+                           s->keys0, m->R * s->n0, s->p0_last, s->err, st);
 }
 
 // expand + merge + build of the columns: M into the cleared table, k
@@ -951,7 +949,9 @@ void stage_expand(paces_sim* s, int64_t est, hipStream_t st,
                  over_limit(s, fz),
                  !more ? 0 : (r < k ? slots / 2 : slots / 4 * 3), s->err, st);
   lookup_last(dm, Wi, sn, k, s->ctl, est, s->table, s->tmask, sn.col,
-              dm.R == 1 ? s->p.max_states : 0, s->ball, s->err, st);
+              dm.R == 1 ? s->p.max_states : 0, s->ball, s->keys0,
+              m->R * s->n0, fz && fz->p0map ? fz->p0map : s->p0_last, s->err,
+              st);
   if (s->p.max_states > 0 && dm.R > 1)
     cap_check(dm, s->ctl, sn.pay, est, s->p.max_states, s->ball, s->err, st);
 }
@@ -960,16 +960,12 @@ void stage_expand(paces_sim* s, int64_t est, hipStream_t st,
 void stage_transfer(paces_sim* s, hipStream_t st, const FrozenStep* fz,
                     StepLocals& L) {
   const paces_model* m = s->m;
-  const int R = m->R;
   const Side so = s->side[s->cur], sn = s->side[1 - s->cur];
   Stage sg(s, PACES_STAGE_TRANSFER, st);
   if (s->warm_step && !fz) {
     // the in-place expansion left phi in psi's buffer (kept amplitudes,
     // zeros elsewhere) and the dropped weight in partials
-    L.n_mass = R == 1 ? fold_sum(s->mass_part, s->warm_np, s->mass_fold,
-                                 s->err, st)
-                      : s->warm_np;
-    s->warm_nmass = L.n_mass;
+    L.n_mass = s->warm_nmass = s->warm_np;
     if (!s->swapped) {
       std::swap(s->ipsi, s->iphi);
       s->swapped = true;
@@ -979,13 +975,11 @@ void stage_transfer(paces_sim* s, hipStream_t st, const FrozenStep* fz,
   // rows of M were placed with their amplitudes by the insert; the frozen
   // replay maps every old row
   const int skip = fz ? 0 : (s->cap_active ? 2 : (s->fresh ? 0 : 1));
-  const int np = transfer(m->dm, m->Wi, s->prec, so, s->vec[s->ipsi],
+  L.n_mass = transfer(m->dm, m->Wi, s->prec, so, s->vec[s->ipsi],
                           bucket(s->nS), s->ctl, s->table, s->tmask, sn.keys,
                           s->vec[s->iphi], s->mass_part,
                           fz ? fz->tmap : nullptr, skip, s->th2, s->keep,
                           s->err, st);
-  L.n_mass = R == 1 ? fold_sum(s->mass_part, np, s->mass_fold, s->err, st)
-                    : np;
 }
 
 // build: spectral bounds and the propagator's coefficients or plan (the
@@ -1037,7 +1031,7 @@ void stage_propagate(paces_sim* s, int64_t est, hipStream_t st,
     if (want_e && fixed)
       np = taylor_energy(dm, s->prec, est, s->ctl, sn.col, sn, s->vec[s->ib0],
                          s->e_part, s->e_row, s->err, st);
-    if (want_e && R == 1) L.n_e = fold_sum(s->e_part, np, s->e_fold, s->err, st);
+    if (want_e && R == 1) L.n_e = np;
   } else if (s->p.krylov_order > 0) {
     // Krylov propagator: nk SpMVs with their folds, nk - 1 recurrence
     // passes, the small exponential and the combination into b0
@@ -1081,7 +1075,7 @@ void stage_propagate(paces_sim* s, int64_t est, hipStream_t st,
                      s->vec[s->ib0], s->vec[s->ib1], s->e_part, s->e_row,
                      s->err, kt.a, kt.b, st);
     }
-    if (want_e && R == 1) L.n_e = fold_sum(s->e_part, np, s->e_fold, s->err, st);
+    if (want_e && R == 1) L.n_e = np;
   }
 }
 
@@ -1090,7 +1084,6 @@ void stage_propagate(paces_sim* s, int64_t est, hipStream_t st,
 void stage_observe(paces_sim* s, int64_t est, hipStream_t st,
                    const FrozenStep* fz, const StepLocals& L) {
   const paces_model* m = s->m;
-  const DevModel& dm = m->dm;
   const int R = m->R;
   const Side sn = s->side[s->nside];
   const bool want_e = (s->p.obs_mask & PACES_OBS_ENERGY) != 0;
@@ -1102,18 +1095,22 @@ void stage_observe(paces_sim* s, int64_t est, hipStream_t st,
                              s->n2_part, s->en_part, s->pop_part, s->sm,
                              s->cnt + R, s->err, st);
   s->sel_grid = n_pop;
-  autocorr(dm, m->Wi, s->prec, s->keys0, s->amps0, s->n0, s->table, s->tmask,
-           sn.keys, s->vec[s->ib0], s->a2, fz ? fz->p0map : s->p0_last,
-           s->err, st);
-  obs_final(m->N, R, want_e && !krylov ? 1 : 0, s->p.dt, L.n_mass, L.n_e,
-            n_pop, R == 1 ? s->mass_fold : s->mass_part, s->n2_part,
-            s->e_fold, s->en_part, s->pop_part, s->a2, s->cc, s->ctl, s->cnt,
-            s->mass_tot, s->ring, s->rec_doubles, s->ring_cap, s->err, st);
+  // the Krylov energy goes into the record after it is written, so the step
+  // is closed by a launch of its own there, as it is with several
+  // realizations
+  const bool close = R > 1 || (want_e && krylov);
+  obs_final(s->prec, m->N, R, want_e && !krylov ? 1 : 0, s->p.dt, L.n_mass,
+            L.n_e, n_pop, s->mass_part, s->n2_part, s->e_part, s->en_part,
+            s->pop_part, s->amps0, s->n0,
+            fz && fz->p0map ? fz->p0map : s->p0_last, s->vec[s->ib0], s->cc,
+            s->ctl, s->cnt, s->mass_tot, s->ring, s->rec_doubles, s->ring_cap,
+            close ? nullptr : s->d_hctl, s->d_herr, s->err, st);
   if (want_e && krylov)
     lz_record_energy(R, s->lz_energy, s->ctl, s->ring, s->rec_doubles,
                      s->ring_cap, s->err, st);
-  end_step(s->ctl, R, s->ring, s->rec_doubles, s->mass_tot, s->err, s->d_hctl,
-           s->d_herr, st);
+  if (close)
+    end_step(s->ctl, R, s->ring, s->rec_doubles, s->mass_tot, s->err,
+             s->d_hctl, s->d_herr, st);
 }
 
 void enqueue_step(paces_sim* s, int64_t est, bool counted, hipStream_t st,
@@ -1489,7 +1486,10 @@ void finish_step(paces_sim* s, const FrozenStep* fz) {
   s->fresh = false;
   s->have_sets = true;
   s->K_last = K;
-  s->launched = std::max(4, std::min(K + 2, kMaxTerms));
+  // one launch to spare (a Chebyshev series of K terms takes K - 1): a step
+  // whose series grows further repeats its propagation
+  s->launched = std::max(4, std::min(s->p.taylor_order != 0 ? K + 1 : K,
+                                     kMaxTerms));
   s->acc.rows_steps += double(c.n_new);
   s->counts_valid = true;
   s->cap_active = false;
@@ -1572,7 +1572,7 @@ paces_status do_step(paces_sim* s, hipStream_t st,
     const bool counted = s->counts_valid && attempt == 0 && !fz &&
                          !s->cap_active;
     if (tail_only) {
-      clear_latch(s->err, st);
+      clear_latch(s->ctl, s->err, st);
       stage_propagate(s, s->gest, st, tail);
       stage_observe(s, s->gest, st, nullptr, tail);
     } else if (graph && attempt == 0) {
@@ -2079,8 +2079,8 @@ paces_status expmv_run(const paces_model* m, int64_t n, const uint64_t* keys,
   fill_u64(table, int64_t(L.P), kEmpty, st);
   rehash_rows(dm, m->Wi, sd, n, table, mask, err, st);
   check_set(dm, m->Wi, sd.keys, n, table, mask, err, st);
-  lookup_last(dm, m->Wi, sd, 0, ctl, n, table, mask, col, 0, nullptr, err,
-              st);
+  lookup_last(dm, m->Wi, sd, 0, ctl, n, table, mask, col, 0, nullptr, nullptr,
+              0, nullptr, err, st);
   bounds_and_coef(dm, sd, col, n, n, ctl, dt, 1e-16, kMaxTerms, kMaxTerms,
                   part, cc, err, st);
   StepCtl hc{};
@@ -2499,9 +2499,9 @@ paces_status paces_init_state(const paces_model* m, const paces_run_params* p,
   const int64_t sz_mass = blk, sz_e = R == 1 ? kMaxPartials : 0,
                 sz_bnd = 2 * blk, sz_pop = int64_t(kPartBlocks) * R;
   const int64_t nparts = sz_mass + sz_e + sz_bnd + 2 * sz_pop +
-                         sz_pop * m->N + 2 * 256;
+                         sz_pop * m->N;
   if (dalloc(&s->ctl, 1) || dalloc(&s->err, 1) || dalloc(&s->parts, nparts) ||
-      dalloc(&s->cc, R) || dalloc(&s->a2, 2 * R) || dalloc(&s->cnt, 2 * R) ||
+      dalloc(&s->cc, R) || dalloc(&s->cnt, 2 * R) ||
       dalloc(&s->mass_tot, R) || dalloc(&s->p0_last, nt) ||
       dalloc(&s->ball, R) || dalloc(&s->dcount, 1) ||
       dalloc(&s->sums_block, 5 * kMaxSums) ||
@@ -2532,9 +2532,7 @@ paces_status paces_init_state(const paces_model* m, const paces_run_params* p,
   s->bnd_part = q;   q += sz_bnd;
   s->n2_part = q;    q += sz_pop;
   s->en_part = q;    q += sz_pop;
-  s->pop_part = q;   q += sz_pop * m->N;
-  s->mass_fold = q;  q += 256;
-  s->e_fold = q;
+  s->pop_part = q;
   if (hipMemsetAsync(s->err, 0, 4, st) != hipSuccess ||
       hipMemsetAsync(s->parts, 0, size_t(nparts) * 8, st) != hipSuccess ||
       hipMemsetAsync(s->mass_tot, 0, size_t(R) * 8, st) != hipSuccess ||
@@ -2569,7 +2567,6 @@ paces_status paces_free_sim(paces_sim* s) {
   dfree(s->err);
   dfree(s->parts);
   dfree(s->cc);
-  dfree(s->a2);
   dfree(s->cnt);
   dfree(s->mass_tot);
   dfree(s->p0_last);

@@ -251,12 +251,13 @@ __device__ __forceinline__ bool dist_hit(uint8_t v, int d) {
 
 __global__ void __launch_bounds__(kBlock)
     k_dist_count(const uint8_t* dist, int64_t n, int d, uint32_t* sums) {
-  const TileRun run = tile_run(cdiv(n, kTile), gridDim.x);
+  const TileRun run = tile_run(cdiv(n, kBlock), gridDim.x);
   uint32_t v = 0;
-  for (int64_t t = run.t0; t < run.t1; ++t) {
+  for (int64_t t = run.t0; t < run.t1; t += kItems) {
 #pragma unroll
     for (int q = 0; q < kItems; ++q) {
-      const int64_t e = t * kTile + q * kBlock + threadIdx.x;
+      if (t + q >= run.t1) break;
+      const int64_t e = (t + q) * kBlock + threadIdx.x;
       if (e < n && dist_hit(dist[e], d)) ++v;
     }
   }
@@ -269,14 +270,15 @@ __global__ void __launch_bounds__(kBlock)
     k_dist_write(int Wi, const uint64_t* keys, const uint8_t* dist, int64_t n,
                  int d, const uint32_t* sums, uint32_t* count, uint64_t* out,
                  uint32_t* rows) {
-  const TileRun run = tile_run(cdiv(n, kTile), gridDim.x);
+  const TileRun run = tile_run(cdiv(n, kBlock), gridDim.x);
   uint64_t total;
   uint64_t at = sums_before(sums, gridDim.x, blockIdx.x, &total);
   if (gtid() == 0) *count = uint32_t(total);
-  for (int64_t t = run.t0; t < run.t1; ++t) {
+  for (int64_t t = run.t0; t < run.t1; t += kItems) {
 #pragma unroll 1
     for (int q = 0; q < kItems; ++q) {
-      const int64_t e = t * kTile + q * kBlock + threadIdx.x;
+      if (t + q >= run.t1) break;
+      const int64_t e = (t + q) * kBlock + threadIdx.x;
       const bool hit = e < n && dist_hit(dist[e], d);
       uint32_t tot;
       const uint64_t off = block_excl_scan(hit ? 1u : 0u, &tot) + at;
@@ -608,7 +610,8 @@ template <int W, typename Amp>
 __global__ void __launch_bounds__(kBlock)
     k_warm_settle(DevModel m, int k, StepCtl* ctl, Side c,
                   const uint32_t* freel, uint64_t* table, uint64_t mask,
-                  Amp* psi, double* mass_part, const int* err) {
+                  Amp* psi, double* mass_part, const uint64_t* keys0,
+                  int64_t n0, int32_t* p0, const int* err) {
   __shared__ double bins[kMaxReal];
   __shared__ uint16_t list[kBlock * kMaxVb];
   if (*err) return;
@@ -681,6 +684,13 @@ __global__ void __launch_bounds__(kBlock)
       }
     }
     c.col[row * D + s] = out;
+  }
+  // rows of the initial states in the new set
+  for (int64_t i = gtid(); i < n0; i += gstride()) {
+    uint64_t kk[W];
+    load_key<W>(keys0, i, kk);
+    const int64_t f = warm_find<W>(table, mask, c.keys, kk, key_hash<W>(m, kk));
+    p0[i] = f >= 0 && kept(c.dist[f], k) ? int32_t(f) : -1;
   }
   if (R > 1) {
     __syncthreads();
@@ -809,17 +819,18 @@ void warm_cap_check(const DevModel& m, const Side& c, int k, StepCtl* ctl,
 int warm_commit(const DevModel& m, int Wi, int prec, const Side& c, int k,
                 StepCtl* ctl, int64_t n_old, int64_t n_found, uint64_t* table,
                 uint64_t mask, const WarmBufs& wb, void* psi,
-                double* mass_part, int* err, hipStream_t s) {
+                double* mass_part, const uint64_t* keys0, int64_t n0,
+                int32_t* p0, int* err, hipStream_t s) {
   const int g = std::min(std::max(sum_grid(n_old, kBlock * 16),
                                   grid_for(n_found * m.D)), kPartBlocks);
   if (prec == 64) {
     PACES_DISPATCH_W(Wi, k_warm_settle<WW, double2><<<g, kBlock, 0, s>>>(
                              m, k, ctl, c, wb.freel, table, mask,
-                             (double2*)psi, mass_part, err));
+                             (double2*)psi, mass_part, keys0, n0, p0, err));
   } else {
     PACES_DISPATCH_W(Wi, k_warm_settle<WW, float2><<<g, kBlock, 0, s>>>(
                              m, k, ctl, c, wb.freel, table, mask,
-                             (float2*)psi, mass_part, err));
+                             (float2*)psi, mass_part, keys0, n0, p0, err));
   }
   return g;
 }
@@ -846,7 +857,7 @@ void rows_at_distance(int Wi, const uint64_t* keys, const uint8_t* dist,
     k_u32_set<<<1, 1, 0, s>>>(count, 0);
     return;
   }
-  const int g = sum_grid(n, kTile);
+  const int g = sum_grid(n, kBlock);
   k_dist_count<<<g, kBlock, 0, s>>>(dist, n, d, sums);
   k_dist_write<<<g, kBlock, 0, s>>>(Wi, keys, dist, n, d, sums, count, out,
                                     rows);

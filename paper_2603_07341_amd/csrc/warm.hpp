@@ -84,11 +84,13 @@ void warm_cap_check(const DevModel& m, const Side& c, int k, StepCtl* ctl,
 // its neighbours' columns toward it -1).  Then the found states: distance
 // r, table entry plain, columns by lookup (also the column of a live
 // neighbour toward them).  Sets ctl->n_new.  Returns the number of partial
-// blocks.  n_found: estimate of the found states, for the grid.
+// blocks.  n_found: estimate of the found states, for the grid.  p0[i]: row
+// of keys0[i], i < n0, or -1.
 int warm_commit(const DevModel& m, int Wi, int prec, const Side& c, int k,
                 StepCtl* ctl, int64_t n_old, int64_t n_found, uint64_t* table,
                 uint64_t mask, const WarmBufs& wb, void* psi,
-                double* mass_part, int* err, hipStream_t s);
+                double* mass_part, const uint64_t* keys0, int64_t n0,
+                int32_t* p0, int* err, hipStream_t s);
 // Before a repeated search: staged and candidate entries of the table back
 // to empty slots, and holes that took a found state back to holes,
 // whatever the latch.
