@@ -181,7 +181,9 @@ int32_t paces_record_doubles(const paces_model* m);
  * records) from the caller's allocator: alloc(bytes, stream, user) returns
  * device memory or NULL, release(ptr, stream, user) frees it; stream is
  * passed as NULL (the library synchronises its stream before it frees).
- * Both NULL restores hipMalloc / hipFree.  Applies to later allocations;
+ * Both NULL restores hipMalloc / hipFree; of blocks from those the library
+ * keeps up to 4 GiB per GPU after they are freed, for its later allocations,
+ * and returns them to the device when an allocation fails.  Applies to later allocations;
  * every block goes back to the allocator that made it, so the functions
  * must stay valid while blocks they made are alive. */
 paces_status paces_set_allocator(void* (*alloc)(size_t bytes, void* stream,

@@ -57,6 +57,14 @@ __global__ void k_clear_err(int* err, StepCtl* ctl) {
   ctl->ticket = 0;
 }
 
+// The number of series terms and the error latch into two words (mapped host
+// memory or device memory).
+__global__ void k_report(const StepCtl* ctl, const int* err, uint32_t* out) {
+  out[0] = ctl->kmax;
+  out[1] = uint32_t(*err);
+  __threadfence_system();
+}
+
 // ---- a given set of states (stateless propagation) --------------------------
 // Canonical keys of W words to the internal width Wi >= W (leading zero
 // words; one realization, so no realization bits).
@@ -1253,6 +1261,11 @@ void mark(int tag, hipStream_t s) { k_mark<<<1, 64, 0, s>>>(tag); }
 
 void clear_latch(StepCtl* ctl, int* err, hipStream_t s) {
   k_clear_err<<<1, 1, 0, s>>>(err, ctl);
+}
+
+void report(const StepCtl* ctl, const int* err, uint32_t* out,
+            hipStream_t s) {
+  k_report<<<1, 1, 0, s>>>(ctl, err, out);
 }
 
 void pad_keys(int W, int Wi, const uint64_t* in, uint64_t* out, int64_t n,

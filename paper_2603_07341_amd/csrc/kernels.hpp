@@ -102,6 +102,8 @@ void fill_u64(uint64_t* p, int64_t n, uint64_t v, hipStream_t s);
 void mark(int tag, hipStream_t s);
 // The error latch (and the arrival counter) cleared on the stream.
 void clear_latch(StepCtl* ctl, int* err, hipStream_t s);
+// ctl->kmax and the latch into out[0] and out[1].
+void report(const StepCtl* ctl, const int* err, uint32_t* out, hipStream_t s);
 // A given set of n states as the rows of a step: keys padded from W to Wi
 // words; control counts with frontier 0 = rows [0, n) and the latch
 // cleared; every key valid and distinct (else kErrInput), after the rows

@@ -122,46 +122,183 @@ void dfree(T*& p) {
 // hipMalloc.  Every allocation of the library goes through here, and each
 // block is returned to the allocator that made it, so the allocator may
 // change while blocks are alive.
+//
+// Blocks from hipMalloc that are freed stay with the library for later
+// allocations of at least four fifths of their size, up to kKeepBytes per
+// GPU (older ones go back to the device first, and all of them when an
+// allocation fails).  A program that makes one sim per trajectory, or calls
+// paces_expmv or the adjoint in a loop, otherwise spends most of a small call
+// in hipMalloc and hipFree, whose times also vary several fold on one machine
+// (a 100-step adjoint pass 124 or 169 ms with the same 92 ms of kernels).
+// hipFree waits for the whole device, and so does dev_free: a block is
+// handed out again only when nothing that was enqueued before its release,
+// on any stream, still runs.
 struct DevAllocator {
   void* (*alloc)(size_t, void*, void*) = nullptr;
   void (*release)(void*, void*, void*) = nullptr;
   void* user = nullptr;
 };
+struct DevBlock {
+  DevAllocator a;
+  size_t bytes = 0;
+  int dev = 0;
+};
+struct KeptBlock {
+  void* p;
+  size_t bytes;
+  int dev;
+};
+constexpr size_t kKeepBytes = size_t(4) << 30;
 DevAllocator g_allocator;
 std::mutex g_blocks_mu;
-std::unordered_map<void*, DevAllocator> g_blocks;  // blocks of an allocator
+std::unordered_map<void*, DevBlock> g_blocks;  // blocks in use
+std::vector<KeptBlock> g_kept;                 // oldest first
+
+// Bytes kept on a device; the caller holds g_blocks_mu.
+size_t kept_bytes(int dev) {
+  size_t t = 0;
+  for (auto& k : g_kept)
+    if (k.dev == dev) t += k.bytes;
+  return t;
+}
+// Give kept blocks of a device back, oldest first, until at most `most`
+// bytes are left; the caller holds g_blocks_mu.
+void trim_kept(int dev, size_t most) {
+  size_t left = kept_bytes(dev);
+  for (size_t i = 0; i < g_kept.size() && left > most;) {
+    if (g_kept[i].dev != dev) {
+      ++i;
+      continue;
+    }
+    left -= g_kept[i].bytes;
+    (void)hipFree(g_kept[i].p);
+    g_kept.erase(g_kept.begin() + i);
+  }
+}
 
 paces_status dev_alloc(void** p, size_t bytes) {
   *p = nullptr;
   const DevAllocator a = g_allocator;
+  DevBlock b;
+  b.a = a;
   if (a.alloc) {
     *p = a.alloc(bytes, nullptr, a.user);
     if (!*p) return fail(PACES_E_OOM, "registered allocator returned NULL");
     std::lock_guard<std::mutex> lk(g_blocks_mu);
-    g_blocks[*p] = a;
+    g_blocks[*p] = b;
+    return PACES_OK;
+  }
+  HIP_TRY(hipGetDevice(&b.dev));
+  const size_t unit = bytes < (size_t(1) << 20) ? size_t(4) << 10 : size_t(2) << 20;
+  b.bytes = (std::max<size_t>(bytes, 1) + unit - 1) / unit * unit;
+  std::lock_guard<std::mutex> lk(g_blocks_mu);
+  size_t best = g_kept.size();
+  for (size_t i = 0; i < g_kept.size(); ++i)
+    if (g_kept[i].dev == b.dev && g_kept[i].bytes >= b.bytes &&
+        g_kept[i].bytes - g_kept[i].bytes / 5 <= b.bytes &&
+        (best == g_kept.size() || g_kept[i].bytes < g_kept[best].bytes))
+      best = i;
+  if (best < g_kept.size()) {
+    *p = g_kept[best].p;
+    b.bytes = g_kept[best].bytes;
+    g_kept.erase(g_kept.begin() + best);
   } else {
-    const hipError_t e = hipMalloc(p, bytes);
-    if (e != hipSuccess)
+    hipError_t e = hipMalloc(p, b.bytes);
+    if (e != hipSuccess && kept_bytes(b.dev) > 0) {
+      (void)hipGetLastError();
+      trim_kept(b.dev, 0);
+      e = hipMalloc(p, b.bytes);
+    }
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      *p = nullptr;
       return fail(PACES_E_OOM, std::string("hipMalloc failed: ") +
                                    hipGetErrorString(e));
+    }
   }
+  g_blocks[*p] = b;
   return PACES_OK;
 }
 void dev_free(void* p) {
   if (!p) return;
-  DevAllocator a;
+  DevBlock b;
   {
     std::lock_guard<std::mutex> lk(g_blocks_mu);
     auto it = g_blocks.find(p);
-    if (it != g_blocks.end()) {
-      a = it->second;
-      g_blocks.erase(it);
+    if (it == g_blocks.end()) return;
+    b = it->second;
+    g_blocks.erase(it);
+  }
+  if (b.a.release) {
+    b.a.release(p, nullptr, b.a.user);
+    return;
+  }
+  int cur = b.dev;
+  (void)hipGetDevice(&cur);
+  if (cur != b.dev) (void)hipSetDevice(b.dev);
+  // nothing that still uses the block may run when it is handed out again; a
+  // device that cannot be waited for (a failed one) gets it back as it is
+  const bool idle = hipDeviceSynchronize() == hipSuccess;
+  {
+    std::lock_guard<std::mutex> lk(g_blocks_mu);
+    if (idle && b.bytes <= kKeepBytes) {
+      trim_kept(b.dev, kKeepBytes - b.bytes);
+      g_kept.push_back({p, b.bytes, b.dev});
+    } else {
+      (void)hipFree(p);
     }
   }
-  if (a.release)
-    a.release(p, nullptr, a.user);
+  if (cur != b.dev) (void)hipSetDevice(cur);
+}
+
+// Pages of pinned host memory for the counts that kernels report: handed out
+// again once freed (at most kKeepPages are kept; the owner has waited for its
+// work by then).
+constexpr size_t kPageBytes = 4096, kKeepPages = 32;
+struct Page {
+  void* host = nullptr;
+  void* dev = nullptr;  // its address on the GPU it was made for
+  int on = 0;
+};
+std::mutex g_pages_mu;
+std::vector<Page> g_pages;
+
+// may_alloc false: only a page that is kept (host null if there is none).
+paces_status page_get(Page* out, bool may_alloc) {
+  *out = Page{};
+  int dev = 0;
+  HIP_TRY(hipGetDevice(&dev));
+  {
+    std::lock_guard<std::mutex> lk(g_pages_mu);
+    for (size_t i = 0; i < g_pages.size(); ++i)
+      if (g_pages[i].on == dev) {
+        *out = g_pages[i];
+        g_pages.erase(g_pages.begin() + i);
+        return PACES_OK;
+      }
+  }
+  if (!may_alloc) return PACES_OK;
+  // coherent mapped memory: kernels write to it directly
+  Page q;
+  q.on = dev;
+  if (hipHostMalloc(&q.host, kPageBytes,
+                    hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess)
+    return fail(PACES_E_OOM, "pinned host allocation failed");
+  if (hipHostGetDevicePointer(&q.dev, q.host, 0) != hipSuccess) {
+    (void)hipHostFree(q.host);
+    return fail(PACES_E_HIP, "no device address for pinned memory");
+  }
+  *out = q;
+  return PACES_OK;
+}
+void page_put(Page& q) {
+  if (!q.host) return;
+  std::lock_guard<std::mutex> lk(g_pages_mu);
+  if (g_pages.size() < kKeepPages)
+    g_pages.push_back(q);
   else
-    (void)hipFree(p);
+    (void)hipHostFree(q.host);
+  q = Page{};
 }
 
 uint64_t splitmix_next(uint64_t& s) {
@@ -186,6 +323,7 @@ struct paces_model {
   int32_t* d_nbr = nullptr;
   double* d_gsq = nullptr;
   double* d_eps = nullptr;
+  int tab_dev = -1;  // device that holds the tables
   DevModel dm{};
 };
 
@@ -403,8 +541,9 @@ struct paces_sim {
   int K_last = 0;
   int k_last = 0;           // neighbour order of the last step
   int latched = 0;
-  StepCtl* h_ctl = nullptr;  // pinned, mapped
-  int* h_err = nullptr;      // pinned, mapped
+  Page page;                 // pinned, mapped: the two below
+  StepCtl* h_ctl = nullptr;
+  int* h_err = nullptr;
   StepCtl* d_hctl = nullptr;  // device addresses of h_ctl / h_err
   int* d_herr = nullptr;
   std::vector<double> pop_host;
@@ -625,6 +764,13 @@ bool fits_device(const paces_sim* s, int64_t cap) {
   const double after =
       block + 8.0 * double(table_size_for(cap, s->tune.table_shift)) + cand +
       (capbuf ? 22.0 * double(cap) : 0.0) + temp;
+  {
+    // freed blocks that are kept go back when an allocation fails
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    std::lock_guard<std::mutex> lk(g_blocks_mu);
+    fr += kept_bytes(dev);
+  }
   const double back = double(s->rows_bytes) + double(s->cand_bytes) +
                       double(s->capb_bytes) + 8.0 * double(s->tmask_alloc + 1);
   return after <= double(fr) + back - margin;
@@ -1977,27 +2123,49 @@ paces_status log_step(paces_sim* s, const char* where, hipStream_t st) {
 }
 
 // Device copies of the model tables, made on first use so that loading a
-// model and the host codec need no GPU.
+// model and the host codec need no GPU; by one thread.
+std::mutex g_tables_mu;
 paces_status ensure_device_tables(paces_model* m) {
+  std::lock_guard<std::mutex> lk(g_tables_mu);
   if (m->d_nbr) return PACES_OK;
-  ST_TRY(dalloc(&m->d_nbr, int64_t(m->nbr.size())));
-  ST_TRY(dalloc(&m->d_gsq, int64_t(m->gsq.size())));
-  ST_TRY(dalloc(&m->d_eps, int64_t(m->R) * m->N));
-  HIP_TRY(hipMemcpy(m->d_nbr, m->nbr.data(), m->nbr.size() * 4,
-                    hipMemcpyHostToDevice));
-  HIP_TRY(hipMemcpy(m->d_gsq, m->gsq.data(), m->gsq.size() * 8,
-                    hipMemcpyHostToDevice));
-  HIP_TRY(hipMemcpy(m->d_eps, m->eps.data(), m->eps.size() * 8,
-                    hipMemcpyHostToDevice));
-  m->dm.nbr = m->d_nbr;
-  m->dm.gsq = m->d_gsq;
-  m->dm.eps = m->d_eps;
+  int dev = 0;
+  HIP_TRY(hipGetDevice(&dev));
+  int32_t* nbr = nullptr;
+  double *gsq = nullptr, *eps = nullptr;
+  paces_status e = dalloc(&nbr, int64_t(m->nbr.size()));
+  if (!e) e = dalloc(&gsq, int64_t(m->gsq.size()));
+  if (!e) e = dalloc(&eps, int64_t(m->R) * m->N);
+  if (!e && (hipMemcpy(nbr, m->nbr.data(), m->nbr.size() * 4,
+                       hipMemcpyHostToDevice) != hipSuccess ||
+             hipMemcpy(gsq, m->gsq.data(), m->gsq.size() * 8,
+                       hipMemcpyHostToDevice) != hipSuccess ||
+             hipMemcpy(eps, m->eps.data(), m->eps.size() * 8,
+                       hipMemcpyHostToDevice) != hipSuccess))
+    e = fail(PACES_E_HIP, "upload of the model tables failed");
+  if (e) {
+    dfree(nbr);
+    dfree(gsq);
+    dfree(eps);
+    return e;
+  }
+  m->dm.gsq = m->d_gsq = gsq;
+  m->dm.eps = m->d_eps = eps;
+  m->dm.nbr = nbr;
+  m->tab_dev = dev;
+  m->d_nbr = nbr;
   return PACES_OK;
+}
+// Whether the current device holds the model's tables.
+bool tables_here(const paces_model* m) {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return false;
+  std::lock_guard<std::mutex> lk(g_tables_mu);
+  return m->d_nbr && m->tab_dev == dev;
 }
 
 // ---- exp(-i H_S dt) phi on a given set (paces_expmv) ------------------------
-// Work memory for n rows: model tables, step control, latch, Chebyshev
-// coefficients, Gershgorin partials, internal keys (when the canonical
+// Work memory for n rows: model tables (used where the device does not hold
+// the model's own), step control, latch, Chebyshev coefficients, Gershgorin partials, internal keys (when the canonical
 // width needs padding), payload and totals, ELL columns, the second
 // Clenshaw vector and the hash table (at least twice the rows).
 struct ExpmvLayout {
@@ -2045,20 +2213,24 @@ paces_status expmv_latch(int e) {
 
 // The propagation of a step on a set given as n canonical keys, with the
 // work memory `work` laid out by expmv_layout.  Synchronises.
+// page (host may be null): pinned memory for the counts the host reads.
 paces_status expmv_run(const paces_model* m, int64_t n, const uint64_t* keys,
                        const void* phi, double dt, void* psi, uint8_t* work,
-                       hipStream_t st) {
+                       const Page& page, hipStream_t st) {
   const ExpmvLayout L = expmv_layout(m, n);
+  const bool here = tables_here(m);  // before the copy of their addresses
   DevModel dm = m->dm;
-  dm.nbr = reinterpret_cast<const int32_t*>(work + L.nbr);
-  dm.gsq = reinterpret_cast<const double*>(work + L.gsq);
-  dm.eps = reinterpret_cast<const double*>(work + L.eps);
-  HIP_TRY(hipMemcpyAsync(work + L.nbr, m->nbr.data(), m->nbr.size() * 4,
-                         hipMemcpyHostToDevice, st));
-  HIP_TRY(hipMemcpyAsync(work + L.gsq, m->gsq.data(), m->gsq.size() * 8,
-                         hipMemcpyHostToDevice, st));
-  HIP_TRY(hipMemcpyAsync(work + L.eps, m->eps.data(), m->eps.size() * 8,
-                         hipMemcpyHostToDevice, st));
+  if (!here) {
+    dm.nbr = reinterpret_cast<const int32_t*>(work + L.nbr);
+    dm.gsq = reinterpret_cast<const double*>(work + L.gsq);
+    dm.eps = reinterpret_cast<const double*>(work + L.eps);
+    HIP_TRY(hipMemcpyAsync(work + L.nbr, m->nbr.data(), m->nbr.size() * 4,
+                           hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(work + L.gsq, m->gsq.data(), m->gsq.size() * 8,
+                           hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(work + L.eps, m->eps.data(), m->eps.size() * 8,
+                           hipMemcpyHostToDevice, st));
+  }
   StepCtl* ctl = reinterpret_cast<StepCtl*>(work + L.ctl);
   int* err = reinterpret_cast<int*>(work + L.err);
   ChebCoef* cc = reinterpret_cast<ChebCoef*>(work + L.cc);
@@ -2083,18 +2255,25 @@ paces_status expmv_run(const paces_model* m, int64_t n, const uint64_t* keys,
               0, nullptr, err, st);
   bounds_and_coef(dm, sd, col, n, n, ctl, dt, 1e-16, kMaxTerms, kMaxTerms,
                   part, cc, err, st);
-  StepCtl hc{};
-  int he = 0;
-  HIP_TRY(hipMemcpyAsync(&hc, ctl, sizeof(StepCtl), hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipMemcpyAsync(&he, err, sizeof(int), hipMemcpyDeviceToHost, st));
+  // the number of terms and the latch, in two words that the kernel writes
+  // to pinned memory, or copies where there is none
+  uint32_t said[2] = {0, 0};
+  uint32_t* dev_said = page.host ? static_cast<uint32_t*>(page.dev)
+                                 : reinterpret_cast<uint32_t*>(part);
+  report(ctl, err, dev_said, st);
+  if (!page.host)
+    HIP_TRY(hipMemcpyAsync(said, dev_said, sizeof(said), hipMemcpyDeviceToHost,
+                           st));
   HIP_TRY(hipStreamSynchronize(st));
-  ST_TRY(expmv_latch(he));
-  for (int kk = std::max(1, int(hc.kmax)) - 1; kk >= 0; --kk)
+  if (page.host) std::memcpy(said, page.host, sizeof(said));
+  ST_TRY(expmv_latch(int(said[1])));
+  // launch indices K - 2 .. 0; nothing latches any more
+  for (int kk = std::max(2, int(said[0])) - 2; kk >= 0; --kk)
     cheb_term(dm, 64, kk, false, false, n, ctl, col, n, sd, cc, phi, psi,
               work + L.b1, nullptr, nullptr, err, nullptr, nullptr, st);
-  HIP_TRY(hipMemcpyAsync(&he, err, sizeof(int), hipMemcpyDeviceToHost, st));
+  HIP_TRY(hipGetLastError());
   HIP_TRY(hipStreamSynchronize(st));
-  return expmv_latch(he);
+  return PACES_OK;
 }
 
 // Work memory of paces_expmv_static: one file-scope array, which every GPU
@@ -2331,12 +2510,16 @@ paces_status paces_expmv(const paces_model* m, int64_t n, const void* dev_keys,
   ST_TRY(expmv_args(m, n, dev_keys, dev_phi, dt, dev_psi));
   if (n == 0) return PACES_OK;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
+  ST_TRY(ensure_device_tables(const_cast<paces_model*>(m)));
   void* work = nullptr;
   ST_TRY(dev_alloc(&work, expmv_layout(m, n).total));
-  const paces_status e =
-      expmv_run(m, n, static_cast<const uint64_t*>(dev_keys), dev_phi, dt,
-                dev_psi, static_cast<uint8_t*>(work), st);
+  Page page;
+  paces_status e = page_get(&page, true);
+  if (!e)
+    e = expmv_run(m, n, static_cast<const uint64_t*>(dev_keys), dev_phi, dt,
+                  dev_psi, static_cast<uint8_t*>(work), page, st);
   (void)hipStreamSynchronize(st);
+  page_put(page);
   dev_free(work);
   return e;
 }
@@ -2355,8 +2538,14 @@ paces_status paces_expmv_static(const paces_model* m, int64_t n,
   void* work = nullptr;
   ST_TRY(static_work(&work));
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  return expmv_run(m, n, static_cast<const uint64_t*>(dev_keys), dev_phi, dt,
-                   dev_psi, static_cast<uint8_t*>(work), st);
+  Page page;  // one that is kept from another call, if any: no allocation
+  ST_TRY(page_get(&page, false));
+  const paces_status e =
+      expmv_run(m, n, static_cast<const uint64_t*>(dev_keys), dev_phi, dt,
+                dev_psi, static_cast<uint8_t*>(work), page, st);
+  if (e) (void)hipStreamSynchronize(st);
+  page_put(page);
+  return e;
 }
 
 paces_status paces_free_model(paces_model* m) {
@@ -2481,19 +2670,15 @@ paces_status paces_init_state(const paces_model* m, const paces_run_params* p,
     paces_free_sim(s);
     return st_;
   };
-  // coherent mapped host memory: the step's last kernel writes the counts
-  // there directly
-  const unsigned hflags = hipHostMallocMapped | hipHostMallocCoherent;
-  if (hipHostMalloc(reinterpret_cast<void**>(&s->h_ctl), sizeof(StepCtl),
-                    hflags) != hipSuccess ||
-      hipHostMalloc(reinterpret_cast<void**>(&s->h_err), 64, hflags) !=
-          hipSuccess)
-    return cleanup(fail(PACES_E_OOM, "pinned host allocation failed"));
-  if (hipHostGetDevicePointer(reinterpret_cast<void**>(&s->d_hctl), s->h_ctl,
-                              0) != hipSuccess ||
-      hipHostGetDevicePointer(reinterpret_cast<void**>(&s->d_herr), s->h_err,
-                              0) != hipSuccess)
-    return cleanup(fail(PACES_E_HIP, "no device address for pinned memory"));
+  // the step's last kernel writes the counts to pinned memory directly
+  if (page_get(&s->page, true)) return cleanup(PACES_E_OOM);
+  static_assert(sizeof(StepCtl) <= kPageBytes - 256, "fits the page");
+  s->h_ctl = static_cast<StepCtl*>(s->page.host);
+  s->d_hctl = static_cast<StepCtl*>(s->page.dev);
+  s->h_err = reinterpret_cast<int*>(static_cast<char*>(s->page.host) +
+                                    kPageBytes - 256);
+  s->d_herr = reinterpret_cast<int*>(static_cast<char*>(s->page.dev) +
+                                     kPageBytes - 256);
   // per-block partials of the row kernels (layouts in kernels.hpp)
   const int64_t blk = R == 1 ? kMaxPartials : int64_t(kPartBlocks) * R;
   const int64_t sz_mass = blk, sz_e = R == 1 ? kMaxPartials : 0,
@@ -2591,8 +2776,7 @@ paces_status paces_free_sim(paces_sim* s) {
     (void)hipEventDestroy(e.a);
     (void)hipEventDestroy(e.b);
   }
-  if (s->h_ctl) (void)hipHostFree(s->h_ctl);
-  if (s->h_err) (void)hipHostFree(s->h_err);
+  page_put(s->page);
   drop_graphs(s);
   if (s->cap_stream) (void)hipStreamDestroy(s->cap_stream);
   delete s->adj;
