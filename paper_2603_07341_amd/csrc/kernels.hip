@@ -1124,9 +1124,29 @@ __device__ __forceinline__ void close_step(StepCtl* ctl, int Rn,
   __threadfence_system();
 }
 
-// Share of block (x, r) in the records: x < N reduces population (r, x),
-// x = N the scalars of realization r with <psi0|psi(t)> over its n0 initial
-// states (rows p0); each folds the per-block partials with a fixed lane
+// Sum of n partials at a stride, eight loads in flight per lane: a block
+// that adds up to 16384 of them waits for memory 8 times instead of 64.
+__device__ __forceinline__ double sum_partials(const double* p, int n,
+                                               int64_t stride) {
+  double a[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  for (int i = threadIdx.x; i < n; i += 8 * kBlock) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int j = i + q * kBlock;
+      if (j < n) a[q] += p[int64_t(j) * stride];
+    }
+  }
+  return block_sum(((a[0] + a[1]) + (a[2] + a[3])) +
+                   ((a[4] + a[5]) + (a[6] + a[7])));
+}
+
+// Blocks of the record per realization beside its N populations: norm and
+// row counts, energy, discarded weight, <psi0|psi(t)>.
+constexpr int kObsBlocks = 4;
+
+// Share of block (x, r) in the records: x < N reduces population (r, x), the
+// others a scalar each of realization r (<psi0|psi(t)> over its n0 initial
+// states, rows p0); each folds the per-block partials with a fixed lane
 // mapping.  Records of one step are stored realization after realization.
 template <typename Amp>
 __device__ __forceinline__ void obs_block(
@@ -1136,28 +1156,38 @@ __device__ __forceinline__ void obs_block(
     int64_t n0, const int32_t* p0, const Amp* psi, const ChebCoef* cc,
     const StepCtl* ctl, const uint32_t* cnt, const double* mass_tot,
     double* ring, int rec_doubles, int* err) {
-  const int r = blockIdx.y;
+  const int r = blockIdx.y, what = int(blockIdx.x) - N;
   double* rec = ring + (int64_t(ctl->nrec) * Rn + r) * rec_doubles;
-  if (int(blockIdx.x) < N) {
-    double s = 0;
-    for (int b = threadIdx.x; b < n_pop; b += blockDim.x)
-      s += pop_part[(int64_t(b) * Rn + r) * N + blockIdx.x];
-    s = block_sum(s);
+  if (what < 0) {
+    const double s = sum_partials(pop_part + int64_t(r) * N + blockIdx.x,
+                                  n_pop, int64_t(Rn) * N);
     if (threadIdx.x == 0) rec[kObsFields + blockIdx.x] = s;
-  } else {
-    double ms = 0, n2 = 0, en = 0, re = 0, im = 0;
-    for (int i = threadIdx.x; i < n_mass; i += blockDim.x)
-      ms += mass_part[int64_t(i) * Rn + r];
-    for (int i = threadIdx.x; i < n_pop; i += blockDim.x)
-      n2 += n2_part[int64_t(i) * Rn + r];
-    if (want_energy) {
-      if (Rn == 1) {
-        for (int i = threadIdx.x; i < n_e; i += blockDim.x) en += e_part[i];
-      } else {
-        for (int i = threadIdx.x; i < n_pop; i += blockDim.x)
-          en += en_part[int64_t(i) * Rn + r];
-      }
+  } else if (what == 0) {
+    const double n2 = sum_partials(n2_part + r, n_pop, Rn);
+    if (threadIdx.x == 0) {
+      rec[0] = ctl->t + dt;
+      rec[1] = n2;
+      rec[7] = double(cnt[Rn + r]);
+      rec[8] = double(cnt[r]);
+      rec[9] = double(cc[r].K);
+      rec[10] = cc[r].emin;
+      rec[11] = cc[r].emax;
+      if (!isfinite(n2)) atomicOr(err, kErrNonFinite);
     }
+  } else if (what == 1) {
+    double en = NAN;
+    if (want_energy)
+      en = Rn == 1 ? sum_partials(e_part, n_e, 1)
+                   : sum_partials(en_part + r, n_pop, Rn);
+    if (threadIdx.x == 0) rec[2] = en;
+  } else if (what == 2) {
+    const double ms = sum_partials(mass_part + r, n_mass, Rn);
+    if (threadIdx.x == 0) {
+      rec[5] = ms;
+      rec[6] = mass_tot[r] + ms;
+    }
+  } else {
+    double re = 0, im = 0;
     const int64_t base = int64_t(r) * n0;
     for (int64_t i = base + threadIdx.x; i < base + n0; i += blockDim.x) {
       const int32_t row = p0[i];
@@ -1167,25 +1197,11 @@ __device__ __forceinline__ void obs_block(
       re += ar * v.x + ai * v.y;  // conj(a0) * v
       im += ar * v.y - ai * v.x;
     }
-    ms = block_sum(ms);
-    n2 = block_sum(n2);
-    en = block_sum(en);
     re = block_sum(re);
     im = block_sum(im);
     if (threadIdx.x == 0) {
-      rec[0] = ctl->t + dt;
-      rec[1] = n2;
-      rec[2] = want_energy ? en : NAN;
       rec[3] = re;
       rec[4] = im;
-      rec[5] = ms;
-      rec[6] = mass_tot[r] + ms;
-      rec[7] = double(cnt[Rn + r]);
-      rec[8] = double(cnt[r]);
-      rec[9] = double(cc[r].K);
-      rec[10] = cc[r].emin;
-      rec[11] = cc[r].emax;
-      if (!isfinite(n2)) atomicOr(err, kErrNonFinite);
     }
   }
 }
@@ -1520,7 +1536,7 @@ void obs_final(int prec, int N, int R, int want_energy, double dt, int n_mass,
                int rec_doubles, int64_t ring_cap, StepCtl* h_ctl_dev,
                int* h_err_dev, int* err, hipStream_t s) {
 #define PACES_OBS(AMP)                                                        \
-  k_obs_final<AMP><<<dim3(N + 1, R), kBlock, 0, s>>>(                         \
+  k_obs_final<AMP><<<dim3(N + kObsBlocks, R), kBlock, 0, s>>>(                \
       N, R, want_energy, dt, n_mass, n_e, n_pop, mass_part, n2_part, e_part,  \
       en_part, pop_part, amps0, n0, p0, (const AMP*)psi, cc, ctl, cnt,        \
       mass_tot, ring, rec_doubles, ring_cap,                                  \
