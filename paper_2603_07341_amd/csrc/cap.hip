@@ -205,7 +205,220 @@ __global__ void __launch_bounds__(kBlock)
     if (status[j] == 1) keep[midx[j]] = 1;
 }
 
+// ---- the cut of one realization -----------------------------------------------
+// Radix select over the complemented weight bits (13, 13, 13, 13 and 12 of
+// them, most significant first): a pass counts the digit of the rows that
+// share the digits decided so far, in LDS (32 KB of bins; the leading digit
+// is the exponent and one mantissa bit, which a heavy-tailed state spreads
+// over some tens of bins), and the block that arrives last finds the digit
+// the cut falls on.  Later passes read 8 bytes per row; a pass that finds
+// the cut between two digits ends the search (three passes for distinct
+// weights), and the rest return at once.  The search took 6-8 passes of 8
+// bits over 21 bytes per row each before, with a host round trip between
+// them: 25-site chain, 24 steps at 1.6e7 rows 14.7 ms of kernels.
+__device__ __forceinline__ int top_shift(int pass) {
+  return pass < 4 ? 51 - 13 * pass : 0;
+}
+
+template <typename Amp>
+__global__ void __launch_bounds__(kBlock)
+    k_top_pass(int pass, const Amp* psi, const uint8_t* dist, int64_t n,
+               int all, double th2, TopState* st, uint64_t* w,
+               uint32_t* hist) {
+  __shared__ uint32_t bins[kTopBins];
+  __shared__ uint64_t prefix;
+  __shared__ int mode;
+  if (threadIdx.x == 0) {
+    prefix = st->prefix;
+    mode = st->mode;
+  }
+  for (int b = threadIdx.x; b < kTopBins; b += kBlock) bins[b] = 0u;
+  __syncthreads();
+  if (mode) return;
+  const int shift = top_shift(pass), width = pass < 4 ? 13 : 12;
+  const uint64_t digit = (uint64_t(1) << width) - 1, pre = prefix;
+  for (int64_t e = gtid(); e < n; e += gstride()) {
+    uint64_t key;
+    if (pass == 0) {
+      const double wt = weight(psi[e]);
+      const bool cand = dist[e] != kHole && (all || wt >= th2);
+      key = cand ? ~uint64_t(__double_as_longlong(wt)) : ~0ull;
+      w[e] = key;
+      if (!cand) continue;
+    } else {
+      key = w[e];
+      if ((key >> shift >> width) != pre) continue;
+      // the last bin of all also holds the rows that are no candidates
+      if (key == ~0ull && (dist[e] == kHole || !(all || th2 <= 0))) continue;
+    }
+    atomicAdd(&bins[(key >> shift) & digit], 1u);
+  }
+  __syncthreads();
+  for (int b = threadIdx.x; b < kTopBins; b += kBlock)
+    if (bins[b]) atomicAdd(&hist[b], bins[b]);
+  if (!last_block(&st->ticket, gridDim.x)) return;
+  constexpr int per = kTopBins / kBlock;
+  const int b0 = threadIdx.x * per;
+  uint32_t h[per], sum = 0;
+#pragma unroll
+  for (int q = 0; q < per; ++q) {
+    h[q] = hist[b0 + q];
+    sum += h[q];
+    hist[b0 + q] = 0u;
+  }
+  uint32_t tot;
+  int64_t below = block_excl_scan(sum, &tot);
+  const int64_t need = st->need;
+  if (below < need && need <= below + sum) {
+    int d = -1;
+    int64_t here = 0;
+#pragma unroll
+    for (int q = 0; q < per; ++q)
+      if (d < 0) {
+        if (below + h[q] >= need) {
+          d = b0 + q;
+          here = h[q];
+        } else {
+          below += h[q];
+        }
+      }
+    const uint64_t now = (pre << width) | uint64_t(d);
+    st->prefix = now;
+    st->need = need - below;
+    if (need - below == here) {
+      st->limit = shift ? ((now + 1) << shift) - 1 : now;
+      st->mode = 1;
+    } else if (pass == kTopPasses - 1) {
+      st->limit = now;
+      st->mode = 2;
+    }
+  }
+}
+
+__global__ void k_top_init(TopState* st, int64_t q) {
+  st->prefix = 0;
+  st->limit = 0;
+  st->need = q;
+  st->nties = 0;
+  st->ticket = 0;
+  st->mode = 0;
+}
+
+// Bits and sums in the layout of the select kernels; the rows equal to the
+// limit in mode 2 are listed.  zeros: a weight of zero can be a candidate's.
+__global__ void __launch_bounds__(kBlock)
+    k_top_bits(const uint64_t* w, const uint8_t* dist, int64_t n, int zeros,
+               TopState* st, uint32_t* ties, uint64_t* bits, uint32_t* sums,
+               const int* err) {
+  if (*err) return;
+  const TileRun run = tile_run(cdiv(n, kBlock), gridDim.x);
+  const uint64_t limit = st->limit;
+  const int mode = st->mode;
+  uint32_t v = 0;
+  for (int64_t t = run.t0; t < run.t1; t += kItems) {
+#pragma unroll
+    for (int q = 0; q < kItems; ++q) {
+      if (t + q >= run.t1) break;
+      const int64_t e = (t + q) * kBlock + threadIdx.x;
+      bool keep = false;
+      if (e < n) {
+        const uint64_t k = w[e];
+        const bool cand = k != ~0ull || (zeros && dist[e] != kHole);
+        keep = cand && (k < limit || (mode == 1 && k == limit));
+        if (mode == 2 && cand && k == limit) {
+          const uint32_t at = atomicAdd(&st->nties, 1u);
+          if (at < kTopTies) ties[at] = uint32_t(e);
+        }
+      }
+      const uint64_t b = __ballot(keep);
+      if ((threadIdx.x & 63) == 0 && e < n) bits[e >> 6] = b;
+      v += keep ? 1u : 0u;
+    }
+  }
+  uint32_t tot;
+  block_excl_scan(v, &tot);
+  if (threadIdx.x == 0) sums[blockIdx.x] = tot;
+}
+
+// One block: the first `need` of the listed rows by (key hash, key) join the
+// selection.  Equal weights come from orbits of a symmetric lattice, a few to
+// a few hundred rows; each is ranked by counting.
+template <int Wi>
+__global__ void __launch_bounds__(kBlock)
+    k_top_ties(DevModel m, int W, const uint64_t* keys, int64_t n, int grid,
+               TopState* st, const uint32_t* ties, uint64_t* bits,
+               uint32_t* sums, int* err) {
+  __shared__ uint64_t hash[kTopTies];
+  if (*err) return;
+  if (st->mode != 2) return;
+  const uint32_t nt = st->nties;
+  const int64_t need = st->need;
+  __syncthreads();
+  if (threadIdx.x == 0) st->nties = 0;
+  if (nt > kTopTies) {
+    if (threadIdx.x == 0) atomicOr(err, kErrTie);
+    return;
+  }
+  for (uint32_t i = threadIdx.x; i < nt; i += kBlock) {
+    uint64_t k[Wi];
+    load_key<Wi>(keys, ties[i], k);
+    uint64_t h = 0;
+    for (int q = 0; q < W; ++q) h = splitmix_mix(h ^ canon_word<Wi>(k, W, m.B, q));
+    hash[i] = h;
+  }
+  __syncthreads();
+  const int64_t per = cdiv(cdiv(n, kBlock), grid);
+  for (uint32_t i = threadIdx.x; i < nt; i += kBlock) {
+    const int64_t row = ties[i];
+    int64_t rank = 0;
+    for (uint32_t j = 0; j < nt; ++j) {
+      bool before = hash[j] < hash[i];
+      if (hash[j] == hash[i] && j != i) {
+        uint64_t a[Wi], b[Wi];
+        load_key<Wi>(keys, ties[j], a);
+        load_key<Wi>(keys, row, b);
+        for (int q = W - 1; q >= 0; --q) {  // the most significant decides
+          const uint64_t x = canon_word<Wi>(a, W, m.B, q);
+          const uint64_t y = canon_word<Wi>(b, W, m.B, q);
+          if (x != y) before = x < y;
+        }
+      }
+      rank += before ? 1 : 0;
+    }
+    if (rank >= need) continue;
+    atomicOr((unsigned long long*)(bits + (row >> 6)), 1ull << (row & 63));
+    atomicAdd(&sums[row / kBlock / per], 1u);
+  }
+}
+
 }  // namespace
+
+void top_select(int prec, const void* psi, const uint8_t* dist, int64_t n,
+                bool all, double th2, int64_t q, const TopBufs& tb,
+                hipStream_t s) {
+  k_top_init<<<1, 1, 0, s>>>(tb.st, q);
+  const int g = std::min(grid_for(cdiv(n, 8)), 1024);
+  for (int p = 0; p < kTopPasses; ++p) {
+    if (prec == 64)
+      k_top_pass<double2><<<g, kBlock, 0, s>>>(p, (const double2*)psi, dist, n,
+                                               all, th2, tb.st, tb.w, tb.hist);
+    else
+      k_top_pass<float2><<<g, kBlock, 0, s>>>(p, (const float2*)psi, dist, n,
+                                              all, th2, tb.st, tb.w, tb.hist);
+  }
+}
+
+int top_bits(const DevModel& m, int Wi, int W, const uint64_t* keys,
+             const uint8_t* dist, int64_t n, bool zeros, const TopBufs& tb,
+             const Sums& sm, int* err, hipStream_t s) {
+  const int g = sum_grid(n, kBlock);
+  k_top_bits<<<g, kBlock, 0, s>>>(tb.w, dist, n, zeros ? 1 : 0, tb.st, tb.ties,
+                                  sm.bits, sm.sel, err);
+  PACES_DISPATCH_W(Wi, k_top_ties<WW><<<1, kBlock, 0, s>>>(
+                           m, W, keys, n, g, tb.st, tb.ties, sm.bits, sm.sel,
+                           err));
+  return g;
+}
 
 void cap_check(const DevModel& m, const StepCtl* ctl, const uint64_t* pay,
                int64_t est, int64_t cap, uint32_t* ball, int* err,

@@ -54,4 +54,35 @@ void cap_apply(const DevModel& m, int Wi, int W, int pass,
 void cap_flags(const uint32_t* midx, int64_t nM, const uint8_t* status,
                uint8_t* keep, int64_t n_old, hipStream_t s);
 
+// ---- the cut of one realization without the host ----------------------------
+// The q heaviest of the candidate rows (live rows; with all false only those
+// with weight >= th2), ties by key hash and key.  top_select finds the weight
+// that the cut falls on by a radix select on 13-bit digits of the weight's
+// bits; top_bits writes the selection's bits and sums (as select_bits does)
+// from it and may be repeated.
+struct TopState {
+  uint64_t prefix;  // digits decided so far
+  uint64_t limit;   // mode 1: rows with key <= limit; mode 2: < limit, and
+                    // need of those equal to it
+  int64_t need;
+  uint32_t nties, ticket;
+  int32_t mode;     // 0 while undecided
+};
+constexpr int kTopBins = 8192, kTopPasses = 5, kTopTies = 2048;
+struct TopBufs {
+  TopState* st;
+  uint32_t* hist;  // [kTopBins], zero between calls
+  uint32_t* ties;  // [kTopTies]
+  uint64_t* w;     // [rows] weight keys
+};
+// q must be positive and below the number of candidates.
+void top_select(int prec, const void* psi, const uint8_t* dist, int64_t n,
+                bool all, double th2, int64_t q, const TopBufs& tb,
+                hipStream_t s);
+// Returns the grid of the sums.  More than kTopTies rows of the weight at the
+// cut latch kErrTie.
+int top_bits(const DevModel& m, int Wi, int W, const uint64_t* keys,
+             const uint8_t* dist, int64_t n, bool zeros, const TopBufs& tb,
+             const Sums& sm, int* err, hipStream_t s);
+
 }  // namespace paces

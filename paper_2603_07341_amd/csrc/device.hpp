@@ -48,6 +48,7 @@ enum : int {
   kErrChunks = 64,     // a round's frontier needs more candidate chunks
   kErrInput = 128,     // a given key is out of range or repeated
   kErrOver = 256,      // the rows found so far already exceed the state cap
+  kErrTie = 512,       // more equal weights at a cut than it can order
 };
 
 // Model constants passed by value to every kernel.

@@ -558,7 +558,7 @@ __global__ void __launch_bounds__(kBlock)
   if (gtid() == 0) {
     ctl->n_new = uint32_t(f1);
     if (max_states > 0) {
-      ball[0] = uint32_t(f1);
+      ctl->n_ball = ball[0] = uint32_t(f1);
       if (f1 > max_states) atomicOr(err, kErrCap);
     }
   }
@@ -577,16 +577,15 @@ __global__ void __launch_bounds__(kBlock)
 // ---- transfer ---------------------------------------------------------------
 
 // Old row i goes to its row of the new set, or counts as discarded weight.
-// skip 1 (threshold selection) and 2 (preset flags keep[i]): rows of M are
-// already in place (insert) and are passed over.
+// Rows whose bit is set in sel (M, already placed by the insert) are passed
+// over.
 template <int W, typename Amp>
 __global__ void __launch_bounds__(kBlock)
     k_transfer(DevModel m, const uint64_t* keys_o, const uint8_t* o_dist,
                const Amp* psi_o,
                const StepCtl* ctl, const uint64_t* table, uint64_t mask,
                const uint64_t* keys_n, Amp* phi, double* mass_part,
-               int32_t* tmap, int skip, double th2, const uint8_t* keep,
-               const int* err) {
+               int32_t* tmap, const uint64_t* sel, const int* err) {
   __shared__ double bins[kMaxReal];
   if (*err) return;
   const int R = m.R;
@@ -601,8 +600,8 @@ __global__ void __launch_bounds__(kBlock)
       if (tmap) tmap[i] = -1;
       continue;
     }
+    if (sel && ((sel[i >> 6] >> (i & 63)) & 1u)) continue;
     const Amp v = psi_o[i];
-    if ((skip == 1 && weight(v) >= th2) || (skip == 2 && keep[i])) continue;
     uint64_t k[W];
     load_key<W>(keys_o, i, k);
     const int64_t r = table_find<W>(table, mask, keys_n, k, key_hash<W>(m, k));
@@ -1404,19 +1403,17 @@ int part_grid(int64_t rows) { return grid_for(rows); }
 int transfer(const DevModel& m, int Wi, int prec, const Side& o,
              const void* psi_o, int64_t n_old, const StepCtl* ctl,
              const uint64_t* table, uint64_t mask, const uint64_t* keys_n,
-             void* phi, double* mass_part, int32_t* tmap, int skip, double th2,
-             const uint8_t* keep, int* err, hipStream_t s) {
+             void* phi, double* mass_part, int32_t* tmap, const uint64_t* sel,
+             int* err, hipStream_t s) {
   const int g = m.R > 1 ? std::min(grid_for(n_old), kPartBlocks) : grid_for(n_old);
   if (prec == 64) {
     PACES_DISPATCH_W(Wi, k_transfer<WW, double2><<<g, kBlock, 0, s>>>(
                              m, o.keys, o.dist, (const double2*)psi_o, ctl, table, mask,
-                             keys_n, (double2*)phi, mass_part, tmap, skip, th2,
-                             keep, err));
+                             keys_n, (double2*)phi, mass_part, tmap, sel, err));
   } else {
     PACES_DISPATCH_W(Wi, k_transfer<WW, float2><<<g, kBlock, 0, s>>>(
                              m, o.keys, o.dist, (const float2*)psi_o, ctl, table, mask,
-                             keys_n, (float2*)phi, mass_part, tmap, skip, th2,
-                             keep, err));
+                             keys_n, (float2*)phi, mass_part, tmap, sel, err));
   }
   return g;
 }

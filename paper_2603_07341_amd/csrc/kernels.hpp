@@ -46,6 +46,8 @@ struct StepCtl {
                                       // round runs (state cap of one
                                       // realization only)
   uint32_t c_max;                     // candidates of the largest round
+  uint32_t n_ball;                    // rows of the new set counted against
+                                      // the state cap (one realization)
   uint32_t kmax;                      // largest K over realizations
   uint32_t nrec;                      // steps recorded (R records each)
   // expansion from the previous step's graph (warm.hpp): states found in
@@ -169,14 +171,14 @@ void lookup_last(const DevModel& m, int Wi, const Side& n, int k,
 // Number of per-block partials written by a kernel over `rows` rows.
 int part_grid(int64_t rows);
 // Returns the number of mass partials written.  tmap (may be null) gets
-// the new row of every old row, -1 if dropped (then skip must be 0).
-// skip: 0 every old row; 1 rows with weight < th2 only; 2 rows with
-// keep[row] == 0 only -- the rows of M, placed by insert_rows.
+// the new row of every old row, -1 if dropped (then sel must be null).
+// sel (may be null): the selection's bits; those rows, placed by insert_rows,
+// are passed over.
 int transfer(const DevModel& m, int Wi, int prec, const Side& o,
              const void* psi_o, int64_t n_old, const StepCtl* ctl,
              const uint64_t* table, uint64_t mask, const uint64_t* keys_n,
-             void* phi, double* mass_part, int32_t* tmap, int skip, double th2,
-             const uint8_t* keep, int* err, hipStream_t s);
+             void* phi, double* mass_part, int32_t* tmap, const uint64_t* sel,
+             int* err, hipStream_t s);
 // Gershgorin bounds + Chebyshev coefficients per realization (cc[R]);
 // latches if some K_r exceeds the launches enqueued.
 void bounds_and_coef(const DevModel& m, const Side& n, const int32_t* col,

@@ -514,7 +514,15 @@ struct paces_sim {
 
   // state cap (max_states per realization)
   uint32_t* ball = nullptr;       // [R] rows of the new set per realization
-  bool cap_active = false;        // the step runs with a cut selection
+  bool cap_active = false;        // the step runs with a cut selection:
+  enum Cut { kFlags, kTop, kWeight } cut = kFlags;  // keep flags, the device
+                                  // cut (topb), or every row of weight
+  double cut_th2 = 0;             // >= cut_th2
+  TopBufs topb{};                 // device cut of one realization
+  void* top_block = nullptr;
+  int64_t top_rows = 0;
+  int64_t rec_nS = 0, rec_nM = 0; // counts of the last record (one
+                                  // realization)
   int64_t cap_buf = 0;            // rows the buffers below hold
   uint8_t* keep = nullptr;        // [rows] selection flags over old rows
   uint32_t* midx_full = nullptr;  // [rows] the step's full selection
@@ -772,7 +780,8 @@ bool fits_device(const paces_sim* s, int64_t cap) {
     fr += kept_bytes(dev);
   }
   const double back = double(s->rows_bytes) + double(s->cand_bytes) +
-                      double(s->capb_bytes) + 8.0 * double(s->tmask_alloc + 1);
+                      double(s->capb_bytes) + 8.0 * double(s->top_rows) +
+                      8.0 * double(s->tmask_alloc + 1);
   return after <= double(fr) + back - margin;
 }
 
@@ -1013,11 +1022,17 @@ void stage_select(paces_sim* s, bool counted, hipStream_t st,
     select_all(s->ctl, s->midx, n_old, st);
     return;
   }
-  if (s->cap_active)
+  const Side& c = s->side[s->cur];
+  if (s->cap_active && s->cut == paces_sim::kFlags)
     s->sel_grid = flag_bits(s->keep, s->ctl, s->sm, n_old, st);
-  else if (!counted)
-    s->sel_grid = select_bits(s->prec, s->vec[s->ipsi], s->side[s->cur].dist,
-                              s->th2, s->ctl, s->sm, n_old, st);
+  else if (s->cap_active && s->cut == paces_sim::kTop)
+    s->sel_grid = top_bits(s->m->dm, s->m->Wi, s->m->W, c.keys, c.dist, s->nS,
+                           s->p.q_nom > 0 || s->fresh || s->th2 <= 0, s->topb,
+                           s->sm, s->err, st);
+  else if (s->cap_active || !counted)
+    s->sel_grid = select_bits(s->prec, s->vec[s->ipsi], c.dist,
+                              s->cap_active ? s->cut_th2 : s->th2, s->ctl,
+                              s->sm, n_old, st);
   if (s->warm_step)
     warm_begin(s->m->dm, s->ctl, s->sm, s->sel_grid, s->side[s->cur], s->wb,
                s->cnt, n_old, s->has_holes, s->err, st);
@@ -1119,12 +1134,12 @@ void stage_transfer(paces_sim* s, hipStream_t st, const FrozenStep* fz,
     return;
   }
   // rows of M were placed with their amplitudes by the insert; the frozen
-  // replay maps every old row
-  const int skip = fz ? 0 : (s->cap_active ? 2 : (s->fresh ? 0 : 1));
+  // replay maps every old row (as does the first step, which has no bits)
+  const bool bits = !fz && (s->cap_active || !s->fresh);
   L.n_mass = transfer(m->dm, m->Wi, s->prec, so, s->vec[s->ipsi],
                           bucket(s->nS), s->ctl, s->table, s->tmask, sn.keys,
                           s->vec[s->iphi], s->mass_part,
-                          fz ? fz->tmap : nullptr, skip, s->th2, s->keep,
+                          fz ? fz->tmap : nullptr, bits ? s->sm.bits : nullptr,
                           s->err, st);
 }
 
@@ -1322,8 +1337,32 @@ paces_status launch_step_graph(paces_sim* s, int64_t est, bool counted,
   return PACES_OK;
 }
 
+// Buffers of the device cut: its state and bins once, the weight keys (which
+// the host-driven cut uses too) for the row capacity.
+paces_status top_buffers(paces_sim* s) {
+  if (!s->topb.st) {
+    uint8_t* q = nullptr;
+    ST_TRY(dalloc(&q, 512 + 4 * (kTopBins + kTopTies)));
+    s->topb.st = reinterpret_cast<TopState*>(q);
+    s->topb.hist = reinterpret_cast<uint32_t*>(q + 512);
+    s->topb.ties = s->topb.hist + kTopBins;
+    HIP_TRY(hipMemset(s->topb.hist, 0, 4 * kTopBins));
+  }
+  if (s->top_rows < s->cap) {
+    if (s->top_block) dev_free(s->top_block);
+    s->top_block = nullptr;
+    s->top_rows = 0;
+    ST_TRY(dev_alloc(&s->top_block, size_t(s->cap) * 8));
+    s->topb.w = static_cast<uint64_t*>(s->top_block);
+    s->top_rows = s->cap;
+  }
+  return PACES_OK;
+}
+
 paces_status cap_buffers(paces_sim* s) {
   const int R = s->m->R;
+  ST_TRY(top_buffers(s));
+  s->cap_w = s->topb.w;
   if (s->cap_buf < s->cap) {
     if (s->cap_block) dev_free(s->cap_block);
     s->cap_block = nullptr;
@@ -1332,7 +1371,6 @@ paces_status cap_buffers(paces_sim* s) {
     Pieces pc;
     pc.add(&s->keep, s->cap);
     pc.add(&s->midx_full, s->cap);
-    pc.add(&s->cap_w, s->cap);
     pc.add(&s->cap_h, s->cap);
     pc.add(&s->cap_status, s->cap);
     ST_TRY(pc.carve(&s->cap_block));
@@ -1350,34 +1388,79 @@ paces_status cap_buffers(paces_sim* s) {
 
 paces_status topq_cut(paces_sim* s, hipStream_t st);
 
+// One realization: M becomes the cap_q[0] heaviest of its cap_nM[0]
+// candidates (all live rows for the fixed size and for the first step's
+// input states, those of weight >= theta^2 otherwise).  Nothing waits.
+paces_status top_cut(paces_sim* s, hipStream_t st) {
+  const bool all = s->p.q_nom > 0 || s->fresh;
+  const int64_t q = std::min(s->cap_q[0], s->cap_nM[0]);
+  s->cap_active = true;
+  if (q == s->cap_nM[0] || q <= 0) {
+    s->cut = paces_sim::kWeight;
+    s->cut_th2 = q <= 0 ? INFINITY : (all ? -1.0 : s->th2);
+    return PACES_OK;
+  }
+  ST_TRY(top_buffers(s));
+  s->cut = paces_sim::kTop;
+  top_select(s->prec, s->vec[s->ipsi], s->side[s->cur].dist, s->nS, all,
+             s->th2, q, s->topb, st);
+  return PACES_OK;
+}
+
+// The candidates of a cut as row indices (midx_full), for the cut that the
+// host decides digit by digit.
+paces_status full_selection(paces_sim* s, hipStream_t st) {
+  const paces_model* m = s->m;
+  const Side& c = s->side[s->cur];
+  ST_TRY(cap_buffers(s));
+  if (s->p.q_nom > 0 || s->fresh) {
+    s->nM_full = s->nlive;
+    if (s->has_holes)
+      rows_at_distance(m->Wi, c.keys, c.dist, s->nS, -1, nullptr, s->midx_full,
+                       s->dcount, s->sm.rows, st);
+    else
+      iota_u32(s->midx_full, s->nS, st);
+    return PACES_OK;
+  }
+  const int g = select_bits(s->prec, s->vec[s->ipsi], c.dist, s->th2, s->ctl,
+                            s->sm, s->nS, st);
+  clear_latch(s->ctl, s->err, st);
+  select_write(s->ctl, s->sm, g, s->midx_full, s->err, st);
+  uint32_t nM = 0;
+  HIP_TRY(hipMemcpyAsync(&nM, &s->ctl->nM, 4, hipMemcpyDeviceToHost, st));
+  HIP_TRY(hipStreamSynchronize(st));
+  s->nM_full = nM;
+  return PACES_OK;
+}
+
+// The cut again, after the rows moved (a growth) or where the device cut met
+// more equal weights than it orders (host true).
+paces_status redo_cut(paces_sim* s, bool host, hipStream_t st) {
+  if (s->m->R == 1 && !host) return top_cut(s, st);
+  ST_TRY(full_selection(s, st));
+  return topq_cut(s, st);
+}
+
 // Fixed-size truncation: M = the q_nom heaviest rows of every
 // realization's set, ties broken as for the state cap.
 paces_status qnom_select(paces_sim* s, hipStream_t st) {
   const paces_model* m = s->m;
   const int R = m->R;
-  ST_TRY(cap_buffers(s));
-  // every live row of the set
-  const Side& c = s->side[s->cur];
-  s->nM_full = s->nlive;
-  if (s->has_holes) {
-    rows_at_distance(m->Wi, c.keys, c.dist, s->nS, -1, nullptr, s->midx_full,
-                     s->dcount, s->sm.rows, st);
-  } else {
-    iota_u32(s->midx_full, s->nS, st);
-  }
-  std::vector<uint32_t> cnt(R, 0);
-  if (R == 1) {
-    cnt[0] = uint32_t(s->nlive);
-  } else {
-    count_per_real(m->dm, c.pay, s->nM_full, s->ball, st,
-                   s->has_holes ? s->midx_full : nullptr);
-    HIP_TRY(hipMemcpyAsync(cnt.data(), s->ball, size_t(R) * 4,
-                           hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
-  }
-  s->cap_nM.assign(cnt.begin(), cnt.end());
   s->cap_on.assign(R, 0);
   s->cap_q.assign(R, s->p.q_nom);
+  if (R == 1) {
+    s->cap_nM.assign(1, s->nlive);
+    s->cap_on[0] = s->nlive > s->p.q_nom;
+    return top_cut(s, st);
+  }
+  ST_TRY(full_selection(s, st));
+  std::vector<uint32_t> cnt(R, 0);
+  count_per_real(m->dm, s->side[s->cur].pay, s->nM_full, s->ball, st,
+                 s->has_holes ? s->midx_full : nullptr);
+  HIP_TRY(hipMemcpyAsync(cnt.data(), s->ball, size_t(R) * 4,
+                         hipMemcpyDeviceToHost, st));
+  HIP_TRY(hipStreamSynchronize(st));
+  s->cap_nM.assign(cnt.begin(), cnt.end());
   for (int r = 0; r < R; ++r) s->cap_on[r] = int64_t(cnt[r]) > s->p.q_nom;
   return topq_cut(s, st);
 }
@@ -1394,6 +1477,24 @@ paces_status cap_select(paces_sim* s, hipStream_t st, bool over) {
   const paces_model* m = s->m;
   const int R = m->R;
   const int64_t cap = s->p.max_states;
+  if (R == 1) {
+    // every count is in the step's mirror
+    if (!s->cap_active) {
+      s->cap_nM.assign(1, s->h_ctl->nM);
+      s->cap_on.assign(1, 0);
+      s->cap_q.assign(1, 0);
+    }
+    if (!s->cap_on[0]) {
+      const bool prev = !s->fresh && s->h.nrec > 0 && s->rec_nS > 0 &&
+                        s->rec_nM > 0;
+      s->cap_on[0] = 1;
+      s->cap_q[0] = prev ? cap * s->rec_nM / s->rec_nS : cap / (m->D + 1);
+    } else {
+      const int64_t qe = std::min(s->cap_q[0], s->cap_nM[0]);
+      s->cap_q[0] = 9 * qe * cap / (10 * int64_t(s->h_ctl->n_ball));
+    }
+    return top_cut(s, st);
+  }
   std::vector<uint32_t> ball(R), cnt(R);
   HIP_TRY(hipMemcpyAsync(ball.data(), s->ball, size_t(R) * 4,
                          hipMemcpyDeviceToHost, st));
@@ -1509,6 +1610,7 @@ paces_status topq_cut(paces_sim* s, hipStream_t st) {
   }
   cap_flags(s->midx_full, s->nM_full, s->cap_status, s->keep, s->nS, st);
   s->cap_active = true;
+  s->cut = paces_sim::kFlags;
   return PACES_OK;
 }
 
@@ -1620,10 +1722,12 @@ void finish_step(paces_sim* s, const FrozenStep* fz) {
   s->last_warm = s->warm_step;
   s->graph_ok = true;
   s->h = c;
+  s->rec_nM = c.nM;
   s->nprev = s->nlive;
   s->nS = c.n_new;
   s->nlive = s->warm_step ? s->nlive + c.n_staged - c.w_drop
                           : int64_t(c.n_new);
+  s->rec_nS = s->nlive;
   s->has_holes = s->nlive < s->nS;
   s->cur = s->nside;
   std::swap(s->ipsi, s->ib0);
@@ -1666,7 +1770,7 @@ bool warm_after_latch(paces_sim* s, int e, hipStream_t st) {
     std::swap(s->ipsi, s->iphi);
     s->swapped = false;
   }
-  if (e != kErrCap && e != kErrOver) s->graph_ok = false;
+  if (e != kErrCap && e != kErrOver && e != kErrTie) s->graph_ok = false;
   return false;
 }
 
@@ -1682,10 +1786,19 @@ bool overflow_over_cap(const paces_sim* s, int e, bool was_warm,
          s->m->R == 1 && s->p.max_states > 0 && s->cap >= s->p.max_states;
 }
 
+// More rows; a growth packs the set, so a cut selection (by row) is made
+// again.
+paces_status grow_cut(paces_sim* s, hipStream_t st) {
+  ST_TRY(grow(s, 2 * s->cap, s->cap + s->cap / 4, st));
+  if (!s->cap_active) return PACES_OK;
+  return redo_cut(s, s->cut == paces_sim::kFlags, st);
+}
+
 // After an attempt that latched e: make the room or the selection the
 // repeated attempt needs, or return the error.
 paces_status handle_latch(paces_sim* s, int e, hipStream_t st) {
   if (e == kErrCap) return cap_select(s, st, false);
+  if (e & kErrTie) return redo_cut(s, true, st);
   if (e & (kErrTerms | kErrNonFinite)) return check_latch_code(s, e);
   if (e & kErrNeedTerms) {
     s->launched = std::min(int(s->h_ctl->kmax) + 2, kMaxTerms);
@@ -1698,10 +1811,10 @@ paces_status handle_latch(paces_sim* s, int e, hipStream_t st) {
       s->tmask = std::min(4 * s->tmask + 3, s->tmask_alloc);
       return PACES_OK;
     }
-    return grow(s, 2 * s->cap, s->cap + s->cap / 4, st);
+    return grow_cut(s, st);
   }
   if (e & kErrChunks) return more_chunks(s, st);
-  if (e & kErrCapacity) return grow(s, 2 * s->cap, s->cap + s->cap / 4, st);
+  if (e & kErrCapacity) return grow_cut(s, st);
   return check_latch_code(s, e);
 }
 
@@ -1793,6 +1906,7 @@ struct Snapshot {
   StepCtl h{};
   bool fresh = false;
   int launched = 0, K_last = 0, k_last = 0;
+  int64_t rec_nS = 0, rec_nM = 0;
   ~Snapshot() {
     dfree(keys);
     dfree(pay);
@@ -1840,6 +1954,8 @@ paces_status take_snapshot(paces_sim* s, Snapshot& z, hipStream_t st) {
   z.h.n_new = uint32_t(z.n);
   z.fresh = s->fresh;
   z.launched = s->launched;
+  z.rec_nS = s->rec_nS;
+  z.rec_nM = s->rec_nM;
   z.K_last = s->K_last;
   z.k_last = s->k_last;
   return PACES_OK;
@@ -1870,6 +1986,8 @@ paces_status restore_snapshot(paces_sim* s, const Snapshot& z,
   s->has_holes = false;
   s->fresh = z.fresh;
   s->launched = z.launched;
+  s->rec_nS = z.rec_nS;
+  s->rec_nM = z.rec_nM;
   s->K_last = z.K_last;
   s->k_last = z.k_last;
   s->have_sets = false;
@@ -2758,6 +2876,8 @@ paces_status paces_free_sim(paces_sim* s) {
   dfree(s->ball);
   dfree(s->dcount);
   dfree(s->sums_block);
+  if (s->topb.st) dev_free(s->topb.st);
+  if (s->top_block) dev_free(s->top_block);
   if (s->cap_block) dev_free(s->cap_block);
   dfree(s->cap_hist);
   dfree(s->cap_mode);
@@ -2833,7 +2953,7 @@ paces_status paces_run_stage(paces_sim* s, int32_t stage, void* hip_stream) {
         if (!e) break;
         drop_pending(s);
         const int retry = kErrTableFull | kErrCapacity | kErrChunks |
-                          kErrCap | kErrOver;
+                          kErrCap | kErrOver | kErrTie;
         if (attempt >= 40 || (e & ~retry)) {
           s->staged_next = 0;
           return check_latch_code(s, e);

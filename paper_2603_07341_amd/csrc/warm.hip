@@ -587,9 +587,10 @@ __global__ void __launch_bounds__(kBlock)
   count_flush(m.R, bins, ball);
 }
 
-__global__ void k_warm_cap_over(int R, int64_t max_states,
+__global__ void k_warm_cap_over(StepCtl* ctl, int R, int64_t max_states,
                                  const uint32_t* ball, int* err) {
   if (*err) return;
+  ctl->n_ball = ball[0];
   for (int r = 0; r < R; ++r)
     if (int64_t(ball[r]) > max_states) atomicOr(err, kErrCap);
 }
@@ -813,7 +814,7 @@ void warm_cap_check(const DevModel& m, const Side& c, int k, StepCtl* ctl,
   // 16 rows per thread and one count added to the total per block
   k_warm_live<<<std::min(grid_for(cdiv(est, 16)), 512), kBlock, 0, s>>>(
       m, k, ctl, c.dist, c.pay, ball, err);
-  k_warm_cap_over<<<1, 1, 0, s>>>(m.R, max_states, ball, err);
+  k_warm_cap_over<<<1, 1, 0, s>>>(ctl, m.R, max_states, ball, err);
 }
 
 int warm_commit(const DevModel& m, int Wi, int prec, const Side& c, int k,
