@@ -16,6 +16,7 @@ LIB = os.path.join(HERE, "libpaces.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 SOURCES = ["kernels.hip", "warm.hip", "adjoint.hip", "cap.hip", "lanczos.hip", "taylor.hip",
+           "small.hip",
            "runtime.cpp"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -49,6 +49,7 @@ enum : int {
   kErrInput = 128,     // a given key is out of range or repeated
   kErrOver = 256,      // the rows found so far already exceed the state cap
   kErrTie = 512,       // more equal weights at a cut than it can order
+  kErrBig = 1024,      // more rows than one block propagates
 };
 
 // Model constants passed by value to every kernel.

@@ -32,6 +32,7 @@
 #include "cap.hpp"
 #include "kernels.hpp"
 #include "lanczos.hpp"
+#include "small.hpp"
 #include "taylor.hpp"
 #include "warm.hpp"
 
@@ -468,6 +469,7 @@ struct paces_sim {
   int64_t gest = 0;        // rows the launches over the new set are sized
                            // for, and candidates those of a round
   int64_t gcand = 0;
+  bool small_step = false;  // one block does the step after its transfer
   int64_t nlive = 0;       // live rows of side cur; nS is its row range
   int64_t nprev = 0;       // live rows before the last step
   bool has_holes = false;  // side cur has holes (nlive < nS)
@@ -1274,12 +1276,83 @@ void stage_observe(paces_sim* s, int64_t est, hipStream_t st,
              s->d_hctl, s->d_herr, st);
 }
 
+// build, propagate and observe of a small set in one launch (small.hpp).
+bool stage_small(paces_sim* s, hipStream_t st, const FrozenStep* fz,
+                 const StepLocals& L) {
+  const Side sn = s->side[s->nside];
+  SmallTail a{};
+  a.m = s->m->dm;
+  a.ctl = s->ctl;
+  a.err = s->err;
+  a.pay = sn.pay;
+  a.dist = sn.dist;
+  a.col = sn.col;
+  a.phi = s->vec[s->iphi];
+  a.psi = s->vec[s->ib0];
+  a.cc = s->cc;
+  a.dt = s->p.dt;
+  a.tol = s->p.tol;
+  a.k_max = s->p.k_max_terms;
+  a.want_energy = (s->p.obs_mask & PACES_OBS_ENERGY) != 0;
+  a.th2 = s->th2;
+  a.mass_part = s->mass_part;
+  a.n_mass = L.n_mass;
+  a.amps0 = s->amps0;
+  a.n0 = s->n0;
+  a.p0 = fz && fz->p0map ? fz->p0map : s->p0_last;
+  a.cnt = s->cnt;
+  a.mass_tot = s->mass_tot;
+  a.ring = s->ring;
+  a.rec_doubles = s->rec_doubles;
+  a.ring_cap = s->ring_cap;
+  a.bits = s->sm.bits;
+  a.sel = s->sm.sel;
+  a.h_ctl = s->d_hctl;
+  a.h_err = s->d_herr;
+  if (!small_tail(a, s->prec, st)) return false;
+  s->sel_grid = 1;
+  return true;
+}
+
+// The in-place step up to its transfer in one launch.
+void stage_small_expand(paces_sim* s, hipStream_t st) {
+  SmallExpand a{};
+  a.m = s->m->dm;
+  a.k = s->p.k;
+  a.ctl = s->ctl;
+  a.err = s->err;
+  a.cnt = s->cnt;
+  a.ball = s->ball;
+  a.c = s->side[s->cur];
+  a.wb = s->wb;
+  a.rb = s->rb;
+  a.table = s->table;
+  a.mask = s->tmask;
+  a.psi = s->vec[s->ipsi];
+  a.th2 = s->th2;
+  a.cap = s->cap;
+  a.row_limit = over_limit(s, nullptr);
+  a.max_states = s->p.max_states;
+  a.mass_part = s->mass_part;
+  a.keys0 = s->keys0;
+  a.n0 = s->n0;
+  a.p0 = s->p0_last;
+  small_expand(a, s->m->Wi, s->prec, st);
+  s->warm_np = 1;
+}
+
 void enqueue_step(paces_sim* s, int64_t est, bool counted, hipStream_t st,
                   const FrozenStep* fz = nullptr) {
   StepLocals L;
-  stage_select(s, counted, st, fz);
-  stage_expand(s, est, st, fz);
+  if (s->small_step && s->warm_step && !s->cap_active && !fz) {
+    stage_small_expand(s, st);
+  } else {
+    stage_select(s, counted, st, fz);
+    stage_expand(s, est, st, fz);
+  }
   stage_transfer(s, st, fz, L);
+  if (s->small_step && stage_small(s, st, fz, L)) return;
+  s->small_step = false;
   stage_build(s, s->gest, st);
   stage_propagate(s, s->gest, st, L);
   stage_observe(s, s->gest, st, fz, L);
@@ -1296,7 +1369,8 @@ paces_status launch_step_graph(paces_sim* s, int64_t est, bool counted,
       s->launched, s->K_last, est, std::min(bucket(s->nS), s->cap),
       int64_t(s->tmask), s->tune.term_rows, s->p.krylov_order,
       s->p.taylor_order, s->chunks, s->warm_step ? 1 : 0,
-      s->has_holes ? 1 : 0, s->gest, s->gcand, s->sel_grid};
+      s->has_holes ? 1 : 0, s->gest, s->gcand, s->sel_grid,
+      s->small_step ? 1 : 0};
   for (auto& g : s->graphs)
     if (g.key == key) {
       g.used = ++s->graph_clock;
@@ -1687,6 +1761,15 @@ paces_status prepare_step(paces_sim* s, hipStream_t st, bool frozen,
   s->gest = s->warm_step ? std::min(est, bucket(s->nS + s->nS / 8 + 512)) : est;
   s->gcand = bucket(s->last_warm ? 2 * int64_t(s->h.c_max) + 2048
                                  : (s->nS + est) * s->m->D);
+  // One block takes the rest of the step where its rows will fit (an eighth
+  // more rows in place, six times as many from scratch, where a young set
+  // grows; more repeat the tail, or the step): at 2500 rows of the 4-site
+  // ring 58 us of kernels in two launches against 135 us in 32, 68 us per
+  // step against 168.  Event timing wants the launches apart.
+  s->small_step =
+      small_shape(s->m->dm) && s->p.krylov_order == 0 &&
+      s->p.taylor_order == 0 && !s->prof &&
+      (s->warm_step ? s->nS + s->nS / 8 + 64 : 6 * s->nS) <= kSmallRows;
   return PACES_OK;
 }
 
@@ -1770,7 +1853,8 @@ bool warm_after_latch(paces_sim* s, int e, hipStream_t st) {
     std::swap(s->ipsi, s->iphi);
     s->swapped = false;
   }
-  if (e != kErrCap && e != kErrOver && e != kErrTie) s->graph_ok = false;
+  if (e != kErrCap && e != kErrOver && e != kErrTie && e != kErrBig)
+    s->graph_ok = false;
   return false;
 }
 
@@ -1799,6 +1883,10 @@ paces_status grow_cut(paces_sim* s, hipStream_t st) {
 paces_status handle_latch(paces_sim* s, int e, hipStream_t st) {
   if (e == kErrCap) return cap_select(s, st, false);
   if (e & kErrTie) return redo_cut(s, true, st);
+  if (e & kErrBig) {
+    s->small_step = false;
+    return PACES_OK;
+  }
   if (e & (kErrTerms | kErrNonFinite)) return check_latch_code(s, e);
   if (e & kErrNeedTerms) {
     s->launched = std::min(int(s->h_ctl->kmax) + 2, kMaxTerms);
@@ -1826,12 +1914,15 @@ paces_status do_step(paces_sim* s, hipStream_t st,
   ST_TRY(prepare_step(s, st, fz != nullptr, &est));
   const bool graph = s->tune.graph && !s->prof && !fz && !s->cap_active;
   bool tail_only = false;  // an in-place step repeats its propagation
+  bool rebuild = false;    // and its build, which one block did not get to
   StepLocals tail;
   for (int attempt = 0; attempt < 40; ++attempt) {
     const bool counted = s->counts_valid && attempt == 0 && !fz &&
                          !s->cap_active;
     if (tail_only) {
       clear_latch(s->ctl, s->err, st);
+      if (rebuild) stage_build(s, s->gest, st);
+      rebuild = false;
       stage_propagate(s, s->gest, st, tail);
       stage_observe(s, s->gest, st, nullptr, tail);
     } else if (graph && attempt == 0) {
@@ -1850,10 +1941,19 @@ paces_status do_step(paces_sim* s, hipStream_t st,
     drop_pending(s);
     const bool was_warm = s->warm_step;
     if (warm_after_latch(s, e, st)) {
-      // committed in place: more series launches are all it can ask for
-      if (e != kErrNeedTerms) {
+      // committed in place: more series launches, or launches for more rows
+      // than one block takes, are all it can ask for
+      if (e != kErrNeedTerms && e != kErrBig) {
         s->latched = e;
         return check_latch_code(s, e);
+      }
+      if (e == kErrBig) {
+        s->small_step = false;
+        rebuild = true;
+        tail_only = true;
+        tail.n_mass = s->warm_nmass;
+        tail.n_e = 0;
+        continue;
       }
       s->launched = std::min(int(s->h_ctl->kmax) + 2, kMaxTerms);
       tail_only = true;
@@ -2371,20 +2471,37 @@ paces_status expmv_run(const paces_model* m, int64_t n, const uint64_t* keys,
   check_set(dm, m->Wi, sd.keys, n, table, mask, err, st);
   lookup_last(dm, m->Wi, sd, 0, ctl, n, table, mask, col, 0, nullptr, nullptr,
               0, nullptr, err, st);
-  bounds_and_coef(dm, sd, col, n, n, ctl, dt, 1e-16, kMaxTerms, kMaxTerms,
-                  part, cc, err, st);
+  // one block takes a small set from here to psi
+  SmallTail one{};
+  one.m = dm;
+  one.ctl = ctl;
+  one.err = err;
+  one.pay = sd.pay;
+  one.col = col;
+  one.phi = phi;
+  one.psi = psi;
+  one.cc = cc;
+  one.dt = dt;
+  one.tol = 1e-16;
+  one.k_max = kMaxTerms;
+  one.said = page.host ? static_cast<uint32_t*>(page.dev)
+                       : reinterpret_cast<uint32_t*>(part);
+  const bool small = n <= kSmallRows && small_shape(dm) && small_tail(one, 64, st);
+  if (!small)
+    bounds_and_coef(dm, sd, col, n, n, ctl, dt, 1e-16, kMaxTerms, kMaxTerms,
+                    part, cc, err, st);
   // the number of terms and the latch, in two words that the kernel writes
   // to pinned memory, or copies where there is none
   uint32_t said[2] = {0, 0};
-  uint32_t* dev_said = page.host ? static_cast<uint32_t*>(page.dev)
-                                 : reinterpret_cast<uint32_t*>(part);
-  report(ctl, err, dev_said, st);
+  if (!small) report(ctl, err, one.said, st);
+  HIP_TRY(hipGetLastError());
   if (!page.host)
-    HIP_TRY(hipMemcpyAsync(said, dev_said, sizeof(said), hipMemcpyDeviceToHost,
+    HIP_TRY(hipMemcpyAsync(said, one.said, sizeof(said), hipMemcpyDeviceToHost,
                            st));
   HIP_TRY(hipStreamSynchronize(st));
   if (page.host) std::memcpy(said, page.host, sizeof(said));
   ST_TRY(expmv_latch(int(said[1])));
+  if (small) return PACES_OK;
   // launch indices K - 2 .. 0; nothing latches any more
   for (int kk = std::max(2, int(said[0])) - 2; kk >= 0; --kk)
     cheb_term(dm, 64, kk, false, false, n, ctl, col, n, sd, cc, phi, psi,
