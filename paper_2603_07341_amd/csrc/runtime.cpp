@@ -997,6 +997,8 @@ struct FrozenStep {
   int k;
   int32_t* tmap;   // [old rows] new row of every old row (may be null)
   int32_t* p0map;  // [n0] rows of the initial states (may be null)
+  int64_t n_new;   // rows of the recorded step's set
+  bool quiet;      // no observables: only the state and the maps are wanted
 };
 
 // Partial results a step hands from one stage to the next.
@@ -1252,12 +1254,13 @@ void stage_observe(paces_sim* s, int64_t est, hipStream_t st,
   const bool want_e = (s->p.obs_mask & PACES_OBS_ENERGY) != 0;
   const bool krylov = s->p.krylov_order > 0;
   Stage sg(s, PACES_STAGE_OBSERVE, st);
-  const int n_pop = pop_norm(s->prec, m->N, R, s->th2, est, s->ctl,
+  int n_pop = 0;
+  if (!(fz && fz->quiet))
+    n_pop = s->sel_grid = pop_norm(s->prec, m->N, R, s->th2, est, s->ctl,
                              s->vec[s->ib0], sn.pay, sn.dist,
                              want_e && R > 1 && !krylov ? s->e_row : nullptr,
                              s->n2_part, s->en_part, s->pop_part, s->sm,
                              s->cnt + R, s->err, st);
-  s->sel_grid = n_pop;
   // the Krylov energy goes into the record after it is written, so the step
   // is closed by a launch of its own there, as it is with several
   // realizations
@@ -1711,8 +1714,9 @@ void cold_table_mask(paces_sim* s, int64_t est) {
 // Host preparation of a step: room for the new set, the record ring, the
 // launch estimate and the part of the table the step probes, and the
 // fixed-size truncation's selection.  Returns the estimate.
-paces_status prepare_step(paces_sim* s, hipStream_t st, bool frozen,
+paces_status prepare_step(paces_sim* s, hipStream_t st, const FrozenStep* fz,
                           int64_t* est_out) {
+  const bool frozen = fz != nullptr;
   // keep room for the new set: growth of the set per step stays well below
   // the factor used here in the workloads; an overflow is caught anyway.
   // Growth to 4 |S| makes the next one due only when the set has doubled.
@@ -1733,8 +1737,10 @@ paces_status prepare_step(paces_sim* s, hipStream_t st, bool frozen,
       (!s->mem_capped || need > s->cap))
     ST_TRY(grow(s, want, need, st));
   ST_TRY(ensure_ring(s, st));
+  // a replayed step's set is known
   const int64_t est = std::min<int64_t>(
-      s->cap, bucket(std::max<int64_t>(s->nS + s->nS / 2, s->nS + 65536)));
+      s->cap, fz ? bucket(std::max(fz->n_new, s->nS) + 256)
+                 : bucket(std::max<int64_t>(s->nS + s->nS / 2, s->nS + 65536)));
   // expand from the previous step's graph when it is there and its table
   // (probed over the same part, tombstones included) has room for a new
   // set up to the estimate at load factor 2^-table_shift
@@ -1824,7 +1830,7 @@ void finish_step(paces_sim* s, const FrozenStep* fz) {
   s->launched = std::max(4, std::min(s->p.taylor_order != 0 ? K + 1 : K,
                                      kMaxTerms));
   s->acc.rows_steps += double(c.n_new);
-  s->counts_valid = true;
+  s->counts_valid = !(fz && fz->quiet);
   s->cap_active = false;
 }
 
@@ -1911,7 +1917,7 @@ paces_status handle_latch(paces_sim* s, int e, hipStream_t st) {
 paces_status do_step(paces_sim* s, hipStream_t st,
                      const FrozenStep* fz = nullptr) {
   int64_t est = 0;
-  ST_TRY(prepare_step(s, st, fz != nullptr, &est));
+  ST_TRY(prepare_step(s, st, fz, &est));
   const bool graph = s->tune.graph && !s->prof && !fz && !s->cap_active;
   bool tail_only = false;  // an in-place step repeats its propagation
   bool rebuild = false;    // and its build, which one block did not get to
@@ -2222,10 +2228,11 @@ paces_status adj_keep_m(paces_sim* s, int64_t nM, hipStream_t st) {
 }
 
 paces_status adj_frozen_step(paces_sim* s, int64_t i, int32_t* tmap,
-                             int32_t* p0map, hipStream_t st) {
+                             int32_t* p0map, bool quiet, hipStream_t st) {
   const AdjRecord& R = *s->adj;
   const AdjStep& a = R.steps[i];
-  const FrozenStep fz{R.mkeys + a.moff * s->m->Wi, a.nM, a.k, tmap, p0map};
+  const FrozenStep fz{R.mkeys + a.moff * s->m->Wi, a.nM, a.k, tmap, p0map,
+                      a.n_new, quiet};
   ST_TRY(do_step(s, st, &fz));
   if (s->nS != a.n_new)
     return fail(PACES_E_STATE, "replay did not reproduce the recorded set");
@@ -3055,7 +3062,7 @@ paces_status paces_run_stage(paces_sim* s, int32_t stage, void* hip_stream) {
   switch (stage) {
     case PACES_STAGE_SELECT: {
       ST_TRY(abandon_staged(s));
-      ST_TRY(prepare_step(s, st, false, &s->staged_est));
+      ST_TRY(prepare_step(s, st, nullptr, &s->staged_est));
       stage_select(s, false, st, nullptr);
       break;
     }
@@ -3517,7 +3524,7 @@ paces_status paces_adjoint_replay(paces_sim* s, const paces_model* model,
   s->m = model;
   const int64_t first = s->h.nrec;
   for (int64_t i = 0; i < R.n && !e; ++i)
-    e = adj_frozen_step(s, i, nullptr, nullptr, st);
+    e = adj_frozen_step(s, i, nullptr, nullptr, false, st);
   if (!e) e = adj_read_a(s, first, R.n, a_out + 2, st);
   s->m = own;
   a_out[0] = R.a[0];
@@ -3630,7 +3637,7 @@ paces_status adjoint_backward(paces_sim* s, const double* gbar, double* grad,
     e = restore_snapshot(s, *R.ck[q], st);
     for (int64_t i = start; i < end && !e; ++i) {
       SegSlot& z = slot[i - start];
-      e = adj_frozen_step(s, i, z.tmap, z.p0, st);
+      e = adj_frozen_step(s, i, z.tmap, z.p0, true, st);
       if (e) break;
       const int64_t n1 = s->nS;
       if (hipMemcpyAsync(z.col, s->side[s->cur].col, size_t(n1) * D * 4,
@@ -3670,7 +3677,7 @@ paces_status adjoint_backward(paces_sim* s, const double* gbar, double* grad,
       // mu = exp(+i H dt) lambda_{i+1}
       adj_set_rows(s->ctl, uint32_t(n1), st);
       adj_conj_coef(z.cc, ccj, st);
-      for (int kk = a.K - 1; kk >= 0; --kk)
+      for (int kk = std::max(a.K - 2, 0); kk >= 0; --kk)
         cheb_term(dm, 64, kk, false, false, n1, s->ctl, z.col, n1, sd, ccj,
                   lamA, b0, b1, nullptr, nullptr, s->err, nullptr, nullptr,
                   st);
@@ -3682,7 +3689,7 @@ paces_status adjoint_backward(paces_sim* s, const double* gbar, double* grad,
       const int nqi = nq[i];
       adj_node_coef(z.cc, s->p.dt, tau + nqi * kMaxNodes, nqi, s->p.tol, cn,
                     s->err, st);
-      for (int kk = 0; kk < a.K; ++kk)
+      for (int kk = 0; kk < std::max(a.K - 1, 1); ++kk)
         adj_nodes(dm, kk, a.K, n1, z.col, z.pay, z.tot, z.cc, cn, nqi, b0,
                   tx1, z.phi, ty1, accx, accy, s->err, st);
       const int nb = adj_contract(dm, n1, z.col, z.pay, z.tot, nqi,
