@@ -795,6 +795,47 @@ struct VecT<float> {
   using T = float2;
 };
 
+// The row's off-diagonal part: hr, hi += sum_s v_s in[col_s].  In complex64
+// every gather is issued before the first is used, a missing neighbour
+// reading the row itself and counting as zero: a middle term of a ring of 16
+// at 8.9e6 rows 116 -> 109 us, of 64 6x6 lattices with 4.07e7 rows together
+// 756 -> 692 us.  In complex128, where the launch is bound by bytes, those
+// reads cost more than they give (ring of 16 at 1.31e7 rows 252 -> 254 us, a
+// 25-site chain at 1.63e7 346 -> 353), so there the gathers stay conditional.
+template <typename R, int ND, int NV, typename Amp>
+__device__ __forceinline__ void gather_row(
+    const Amp* __restrict__ in, int64_t i,
+    const int32_t (&cols)[2 * ND + 2 * NV], const R (&jv)[3],
+    const R (&gv)[NV][2], R& hr, R& hi) {
+  constexpr int D = 2 * ND + 2 * NV;
+  if constexpr (sizeof(R) == 4) {
+    Amp x[D];
+#pragma unroll
+    for (int s = 0; s < D; ++s) x[s] = in[cols[s] >= 0 ? int64_t(cols[s]) : i];
+#pragma unroll
+    for (int s = 0; s < D; ++s) {
+      const R v =
+          s < 2 * ND ? jv[s >> 1] : gv[(s - 2 * ND) >> 1][(s - 2 * ND) & 1];
+      // fused by name: without the branch the diagonal's product could be
+      // fused instead, and a kernel's rounding would depend on its code
+      hr = __builtin_fmaf(v, cols[s] >= 0 ? x[s].x : R(0), hr);
+      hi = __builtin_fmaf(v, cols[s] >= 0 ? x[s].y : R(0), hi);
+    }
+  } else {
+#pragma unroll
+    for (int s = 0; s < D; ++s) {
+      const int32_t c = cols[s];
+      if (c >= 0) {
+        const R v =
+            s < 2 * ND ? jv[s >> 1] : gv[(s - 2 * ND) >> 1][(s - 2 * ND) & 1];
+        const Amp xj = in[c];
+        hr += v * xj.x;
+        hi += v * xj.y;
+      }
+    }
+  }
+}
+
 // MID only names the launches the host expects to be middle terms (neither
 // first nor last for the previous step's K), so that profiles can tell them
 // apart; the code is the same and still decides its role from the device K.
@@ -854,16 +895,7 @@ __global__ void __launch_bounds__(kBlock)
     }
     int32_t cols[D];
     load_cols<D>(col + i * D, cols);
-#pragma unroll
-    for (int s = 0; s < D; ++s) {
-      const int32_t c = cols[s];
-      if (c >= 0) {
-        const R v = s < 2 * ND ? jv[s >> 1] : gv[(s - 2 * ND) >> 1][(s - 2 * ND) & 1];
-        const Amp xj = in[c];
-        hr += v * xj.x;
-        hi += v * xj.y;
-      }
-    }
+    gather_row<R, ND, NV>(in, i, cols, jv, gv, hr, hi);
     if (energy) esum += double(xi.x) * double(hr) + double(xi.y) * double(hi);
     const R tr = alpha * hr + beta * xi.x, ti = alpha * hi + beta * xi.y;
     R yr = sir * tr - sii * ti, yi = sir * ti + sii * tr;
@@ -947,16 +979,7 @@ __global__ void __launch_bounds__(kBlock)
     }
     int32_t cols[D];
     load_cols<D>(col + i * D, cols);
-#pragma unroll
-    for (int s = 0; s < D; ++s) {
-      const int32_t c = cols[s];
-      if (c >= 0) {
-        const R v = s < 2 * ND ? jv[s >> 1] : gv[(s - 2 * ND) >> 1][(s - 2 * ND) & 1];
-        const Amp xj = in[c];
-        hr += v * xj.x;
-        hi += v * xj.y;
-      }
-    }
+    gather_row<R, ND, NV>(in, i, cols, jv, gv, hr, hi);
     if (first && want_energy)
       e_row[i] = double(xi.x) * double(hr) + double(xi.y) * double(hi);
     const R tr = alpha * hr + beta * xi.x, ti = alpha * hi + beta * xi.y;
