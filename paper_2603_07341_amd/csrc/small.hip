@@ -604,8 +604,9 @@ __global__ void __launch_bounds__(kNB) k_small_expand(SmallExpand a) {
     psi[e] = z;
     uint64_t key[W];
     load_key<W>(c.keys, e, key);
+    const uint64_t h = key_hash<W>(m, key);
     const int64_t sl =
-        warm_slot<W>(a.table, a.mask, key, key_hash<W>(m, key), uint32_t(e));
+        warm_slot(a.table, a.mask, h, a.table[h & a.mask], uint32_t(e));
     if (sl >= 0) {
       a.table[sl] = kTomb;
       ++tombs;
@@ -626,7 +627,7 @@ __global__ void __launch_bounds__(kNB) k_small_expand(SmallExpand a) {
     load_key<W>(c.keys, row, par);
     if (s == 0) {
       const uint64_t h = key_hash<W>(m, par);
-      const int64_t sl = warm_slot<W>(a.table, a.mask, par, h,
+      const int64_t sl = warm_slot(a.table, a.mask, h, a.table[h & a.mask],
                                       kStaged | uint32_t(row));
       if (sl >= 0)
         a.table[sl] = (uint64_t(hash_tag(h)) << 32) | uint64_t(row);

@@ -20,12 +20,10 @@ namespace {
 
 // ---- rows by distance byte --------------------------------------------------
 // The search finds its rows by their distance bytes.  A block takes tiles of
-// kBlock * vb rows, vb bytes per lane in one load (vb 16 for sets that fill
-// the chip with tiles of 4096 rows, 4 and 1 below so that every CU has a
-// tile), and collects the matching rows of a tile in LDS in ascending order;
-// then every lane works on a listed row.  With one row per lane and iteration
-// (one byte load each, most of them not matching) the four rounds of a ring16
-// step at 1.5e7 rows took 340 us.
+// kBlock * vb rows, vb bytes per lane in one load, and collects the matching
+// rows of a tile in LDS in ascending order; then every lane works on a listed
+// row.  With one row per lane and iteration (one byte load each, most of them
+// not matching) the four rounds of a ring16 step at 1.5e7 rows took 340 us.
 constexpr int kMaxVb = 16;
 
 // Bit 8b+7 of the result is set where byte b of x equals d.
@@ -73,8 +71,13 @@ __device__ __forceinline__ uint32_t list_rows(const uint8_t* dist, int64_t t,
   return tot;
 }
 
+// vb 16 for sets that put four tiles of 4096 rows on every CU, 4 and 1 below:
+// what a lane does with a listed row is a chain of two or three dependent
+// loads, so the work is spread over as many waves as the chip holds.  (With 16
+// from one tile per CU on, the search of a ring16 step at 1e6..4e6 rows ran on
+// two waves per SIMD.)
 inline int rows_per_lane(int64_t n) {
-  return n >= int64_t(kBlock) * 16 * 256 ? 16 : n >= kBlock * 4 * 128 ? 4 : 1;
+  return n >= int64_t(kBlock) * 16 * 1024 ? 16 : n >= kBlock * 4 * 128 ? 4 : 1;
 }
 
 // ---- start ------------------------------------------------------------------
@@ -217,12 +220,19 @@ __global__ void __launch_bounds__(kBlock)
 // distance r (unless nearer; every writer writes r, and no row at distance
 // r-1 is written in round r), the slots whose neighbour lies outside the set
 // go to wmask and are counted per block.  Holes and found states never match
-// r-1.
+// r-1.  Bound by the latency of a row's chain (listed offset, columns,
+// neighbours' distances): a lane takes U rows at once, and the distances of
+// all their neighbours are asked for before one is looked at (a missing
+// neighbour reads the row itself).  Together with rows_per_lane this took 604
+// of these launches on a ring of 16 (0.5 to 2.3 million rows) from 13.4 to 6.9
+// ms, on 64 6x6 lattices (D = 6) from 58 to 33 us each, on the aggregate (D =
+// 8) from 62 to 33.
 template <int D>
 __global__ void __launch_bounds__(kBlock)
     k_warm_count(DevModel m, int r, int vb, const StepCtl* ctl,
                  const uint64_t* pay, const int32_t* col, uint8_t* dist,
                  uint16_t* wmask, uint32_t* sums, const int* err) {
+  constexpr int U = D <= 4 ? 4 : D <= 8 ? 2 : 1;
   __shared__ uint16_t list[kBlock * kMaxVb];
   if (*err) return;
   const int64_t n = ctl->n_old, tile = int64_t(kBlock) * vb;
@@ -230,23 +240,39 @@ __global__ void __launch_bounds__(kBlock)
   uint32_t cnt = 0;
   for (int64_t t = run.t0; t < run.t1; ++t) {
     const uint32_t tot = list_rows(dist, t, n, vb, uint8_t(r - 1), list);
-    for (uint32_t i = threadIdx.x; i < tot; i += kBlock) {
-      const int64_t e = t * tile + list[i];
-      const uint64_t p = pay[e];
-      int32_t cs[D];
-      load_cols<D>(col + e * D, cs);
-      uint32_t msk = 0;
+    for (uint32_t i = threadIdx.x; i < tot; i += U * kBlock) {
+      int64_t e[U];
+      uint64_t p[U];
+      int32_t cs[U][D];
+      uint8_t ds[U][D];
 #pragma unroll
-      for (int s = 0; s < D; ++s) {
-        const int32_t c = cs[s];
-        if (c >= 0) {
-          if (dist[c] > r) dist[c] = uint8_t(r);
-        } else if (slot_live(m, p, s)) {
-          msk |= 1u << s;
-        }
+      for (int u = 0; u < U; ++u) {
+        const uint32_t x = i + u * kBlock;
+        e[u] = t * tile + list[x < tot ? x : i];
+        p[u] = pay[e[u]];
+        load_cols<D>(col + e[u] * D, cs[u]);
       }
-      wmask[e] = uint16_t(msk);
-      cnt += __popc(msk);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int s = 0; s < D; ++s)
+          ds[u][s] = dist[cs[u][s] >= 0 ? int64_t(cs[u][s]) : e[u]];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (i + u * kBlock >= tot) continue;
+        uint32_t msk = 0;
+#pragma unroll
+        for (int s = 0; s < D; ++s) {
+          const int32_t c = cs[u][s];
+          if (c >= 0) {
+            if (ds[u][s] > r) dist[c] = uint8_t(r);
+          } else if (slot_live(m, p[u], s)) {
+            msk |= 1u << s;
+          }
+        }
+        wmask[e[u]] = uint16_t(msk);
+        cnt += __popc(msk);
+      }
     }
   }
   uint32_t tot;
@@ -502,10 +528,16 @@ __global__ void k_warm_cap_over(StepCtl* ctl, int R, int64_t max_states,
 // set); between two found states both ends write the same values.  The two
 // parts need no order between blocks: a lookup may still find a row that is
 // being dropped, whose distance byte (kFar or kHole) says so, and they write
-// different columns.
+// different columns.  Bound by random access (a table line per dropped and
+// found state, one per slot of a found state) and by the latency of the chains
+// to it: rows and their slots are separate loops, so that a lane's chain is
+// one row's table walk or one slot's neighbour, and a lane keeps U rows or
+// four slots in flight.  On a ring of 16 at about 1e5 rows 17.0 -> 12.0 us, at
+// 0.5 to 2.3 million 23.3 -> 19.3, 64 6x6 lattices 273 -> 246, a 25-site chain
+// 239 -> 222.
 template <int W, typename Amp>
 __global__ void __launch_bounds__(kBlock)
-    k_warm_settle(DevModel m, int k, StepCtl* ctl, Side c,
+    k_warm_settle(DevModel m, int k, int vb, StepCtl* ctl, Side c,
                   const uint32_t* freel, uint64_t* table, uint64_t mask,
                   Amp* psi, double* mass_part, const uint64_t* keys0,
                   int64_t n0, int32_t* p0, const int* err) {
@@ -516,62 +548,104 @@ __global__ void __launch_bounds__(kBlock)
     ctl->w_moved = 1;
     ctl->n_new = uint32_t(new_range(ctl));
   }
-  const int R = m.R, D = m.D;
+  constexpr int U = W <= 4 ? 2 : 1;
+  const int R = m.R;
+  const uint32_t D = uint32_t(m.D);
   if (R > 1) {
     for (int r = threadIdx.x; r < R; r += blockDim.x) bins[r] = 0.0;
     __syncthreads();
   }
   const int64_t nold = ctl->n_old;
-  const TileRun run = tile_run(cdiv(nold, kBlock * 16), gridDim.x);
+  const int64_t tile = int64_t(kBlock) * vb;
+  const TileRun run = tile_run(cdiv(nold, tile), gridDim.x);
   double lost = 0;
   uint32_t tombs = 0, drops = 0;
   for (int64_t t = run.t0; t < run.t1; ++t) {
-    const uint32_t tot = list_rows(c.dist, t, nold, 16, kFar, list);
+    const uint32_t tot = list_rows(c.dist, t, nold, vb, kFar, list);
     drops += tot;
-    for (uint32_t i = threadIdx.x; i < tot; i += kBlock) {
-      const int64_t e = t * kBlock * 16 + list[i];
-      const Amp v = psi[e];
-      if (R > 1)
-        atomicAdd(&bins[pay_real(c.pay[e])], weight(v));
-      else
-        lost += weight(v);
-      Amp z;
-      z.x = 0;
-      z.y = 0;
-      psi[e] = z;
-      uint64_t key[W];
-      load_key<W>(c.keys, e, key);
-      const int64_t sl =
-          warm_slot<W>(table, mask, key, key_hash<W>(m, key), uint32_t(e));
-      if (sl >= 0) {
-        table[sl] = kTomb;
-        ++tombs;
+    for (uint32_t i = threadIdx.x; i < tot; i += U * kBlock) {
+      int64_t e[U];
+      Amp v[U];
+      uint64_t key[U][W], ent[U];
+      int real[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint32_t x = i + u * kBlock;
+        e[u] = t * tile + list[x < tot ? x : i];
+        v[u] = psi[e[u]];
+        load_key<W>(c.keys, e[u], key[u]);
+        real[u] = R > 1 ? pay_real(c.pay[e[u]]) : 0;
       }
-      for (int s = 0; s < D; ++s) {
-        const int32_t nb = c.col[e * D + s];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        ent[u] = table[key_hash<W>(m, key[u]) & mask];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (i + u * kBlock >= tot) continue;
+        if (R > 1)
+          atomicAdd(&bins[real[u]], weight(v[u]));
+        else
+          lost += weight(v[u]);
+        Amp z;
+        z.x = 0;
+        z.y = 0;
+        psi[e[u]] = z;
+        const int64_t sl = warm_slot(table, mask, key_hash<W>(m, key[u]),
+                                     ent[u], uint32_t(e[u]));
+        if (sl >= 0) {
+          table[sl] = kTomb;
+          ++tombs;
+        }
+        c.dist[e[u]] = kHole;
+      }
+    }
+    for (uint32_t i = threadIdx.x; i < tot * D; i += 4 * kBlock) {
+      int64_t e[4];
+      uint32_t sl[4];
+      int32_t nb[4];
+      uint8_t dn[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const uint32_t x = i + u * kBlock < tot * D ? i + u * kBlock : i;
+        const uint32_t q = x / D;
+        e[u] = t * tile + list[q];
+        sl[u] = x - q * D;
+        nb[u] = c.col[e[u] * D + sl[u]];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        dn[u] = c.dist[nb[u] >= 0 ? int64_t(nb[u]) : e[u]];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (i + u * kBlock >= tot * D) continue;
         // a neighbour that stays (within k) loses its column toward e; one
         // dropped too clears its own
-        if (nb >= 0 && c.dist[nb] <= k) c.col[int64_t(nb) * D + (s ^ 1)] = -1;
-        c.col[e * D + s] = -1;
+        if (nb[u] >= 0 && dn[u] <= k)
+          c.col[int64_t(nb[u]) * D + (sl[u] ^ 1u)] = -1;
+        c.col[e[u] * D + sl[u]] = -1;
       }
-      c.dist[e] = kHole;
     }
   }
   const int64_t ns = ctl->n_staged;
-  for (int64_t t = gtid(); t < ns * D; t += gstride()) {
-    const int64_t q = t / D;
-    const int s = int(t % D);
+  for (int64_t q = gtid(); q < ns; q += gstride()) {
+    const int64_t row = found_row(q, ctl, freel);
+    uint64_t key[W];
+    load_key<W>(c.keys, row, key);
+    const uint64_t h = key_hash<W>(m, key);
+    const int64_t sl =
+        warm_slot(table, mask, h, table[h & mask], kStaged | uint32_t(row));
+    if (sl >= 0) table[sl] = (uint64_t(hash_tag(h)) << 32) | uint64_t(row);
+    c.dist[row] = uint8_t(c.dist[row] & ~kNewRow);
+  }
+  for (int64_t t0 = int64_t(blockIdx.x) * kBlock; t0 < ns * D;
+       t0 += gstride()) {
+    if (t0 + threadIdx.x >= ns * D) break;
+    const uint32_t x = uint32_t(t0 % D) + threadIdx.x;
+    const int64_t q = t0 / D + x / D;
+    const int s = int(x % D);
     const int64_t row = found_row(q, ctl, freel);
     uint64_t par[W], kk[W];
     load_key<W>(c.keys, row, par);
-    if (s == 0) {
-      const uint64_t h = key_hash<W>(m, par);
-      const int64_t sl = warm_slot<W>(table, mask, par, h,
-                                      kStaged | uint32_t(row));
-      if (sl >= 0)
-        table[sl] = (uint64_t(hash_tag(h)) << 32) | uint64_t(row);
-      c.dist[row] = uint8_t(c.dist[row] & ~kNewRow);
-    }
     int32_t out = -1;
     if (slot_target<W>(m, par, c.pay[row], s, kk)) {
       const int64_t f = warm_find<W>(table, mask, c.keys, kk, key_hash<W>(m, kk));
@@ -718,15 +792,16 @@ int warm_commit(const DevModel& m, int Wi, int prec, const Side& c, int k,
                 uint64_t mask, const WarmBufs& wb, void* psi,
                 double* mass_part, const uint64_t* keys0, int64_t n0,
                 int32_t* p0, int* err, hipStream_t s) {
-  const int g = std::min(std::max(sum_grid(n_old, kBlock * 16),
+  const int vb = rows_per_lane(n_old);
+  const int g = std::min(std::max(sum_grid(n_old, int64_t(kBlock) * vb),
                                   grid_for(n_found * m.D)), kPartBlocks);
   if (prec == 64) {
     PACES_DISPATCH_W(Wi, k_warm_settle<WW, double2><<<g, kBlock, 0, s>>>(
-                             m, k, ctl, c, wb.freel, table, mask,
+                             m, k, vb, ctl, c, wb.freel, table, mask,
                              (double2*)psi, mass_part, keys0, n0, p0, err));
   } else {
     PACES_DISPATCH_W(Wi, k_warm_settle<WW, float2><<<g, kBlock, 0, s>>>(
-                             m, k, ctl, c, wb.freel, table, mask,
+                             m, k, vb, ctl, c, wb.freel, table, mask,
                              (float2*)psi, mass_part, keys0, n0, p0, err));
   }
   return g;

@@ -71,19 +71,18 @@ __device__ __forceinline__ int64_t warm_find(const uint64_t* table,
   return -1;
 }
 
-// Slot of the table entry of key k whose value is `value`, or -1.
-template <int W>
+// Slot of the table entry with hash h whose value is `value`, or -1; e0: the
+// entry at the hash's own slot, loaded by the caller.
 __device__ __forceinline__ int64_t warm_slot(const uint64_t* table,
-                                             uint64_t mask,
-                                             const uint64_t (&k)[W],
-                                             uint64_t h, uint32_t value) {
-  const uint32_t tag = hash_tag(h);
-  uint64_t i = h & mask;
+                                             uint64_t mask, uint64_t h,
+                                             uint64_t e0, uint32_t value) {
+  const uint64_t want = (uint64_t(hash_tag(h)) << 32) | value;
+  uint64_t i = h & mask, e = e0;
   for (uint64_t probes = 0; probes <= mask && probes < kMaxProbe; ++probes) {
-    const uint64_t e = table[i];
+    if (e == want) return int64_t(i);
     if (e == kEmpty) break;
-    if (uint32_t(e >> 32) == tag && uint32_t(e) == value) return int64_t(i);
     i = (i + 1) & mask;
+    e = table[i];
   }
   return -1;
 }
