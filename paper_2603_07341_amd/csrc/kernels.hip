@@ -635,14 +635,19 @@ __device__ __forceinline__ double dbl_of(long long o) {
 }
 
 // Gershgorin interval per realization: rows stride over a fixed grid; per
-// block the (lo, hi) of each realization go to part[block][r][2].  DT: the
-// slot count at compile time (a row's columns in one vector load), or 0
-// for m.D at run time; the radius sums the slots in order either way.
-template <int DT>
+// block the (lo, hi) of each realization go to part[block][r][2].  A lane
+// takes two rows at once and forms their slots' values without a branch; with
+// each value's load behind a branch of its own a launch waited for one row's
+// chain (24 bytes a row: 25-site chain at 1.5e7 rows 85 -> 55 us, ring of 16
+// at 0.5 to 2.3 million 18.0 -> 13.8).  A wave whose rows are all of one
+// realization folds them first: 64 lanes on one LDS word are served one after
+// the other (with it, 64 6x6 lattices 67 -> 46 us).
+template <int ND, int NV>
 __global__ void __launch_bounds__(kBlock)
     k_bounds(DevModel m, const uint64_t* pay, const uint64_t* tot,
              const uint8_t* dist, const int32_t* col, int64_t cap,
              const StepCtl* ctl, double* part, const int* err) {
+  constexpr int D = 2 * ND + 2 * NV, U = 2;
   __shared__ long long blo[kMaxReal], bhi[kMaxReal];
   if (*err) return;
   const int R = m.R;
@@ -655,27 +660,56 @@ __global__ void __launch_bounds__(kBlock)
   }
   const int64_t n = ctl->n_new;
   double lo = INFINITY, hi = -INFINITY;
-  for (int64_t r = gtid(); r < n; r += gstride()) {
-    if (is_hole(dist, r)) continue;
-    const uint64_t p = ld_stream(pay + r);
-    double rad = 0;
-    if constexpr (DT > 0) {
-      int32_t cs[DT];
-      load_cols<DT>(col + r * DT, cs);
+  for (int64_t r0 = int64_t(blockIdx.x) * kBlock; r0 < n;
+       r0 += U * gstride()) {
+    uint64_t p[U], tt[U];
+    int32_t cs[U][D];
+    bool ok[U];
 #pragma unroll
-      for (int s = 0; s < DT; ++s)
-        if (cs[s] >= 0) rad += fabs(slot_value(m, p, s));
-    } else {
-      for (int s = 0; s < m.D; ++s)
-        if (col[r * m.D + s] >= 0) rad += fabs(slot_value(m, p, s));
+    for (int u = 0; u < U; ++u) {
+      const int64_t r = r0 + u * gstride() + threadIdx.x;
+      ok[u] = r < n && !is_hole(dist, r);
+      const int64_t rc = r < n ? r : n - 1;
+      p[u] = ld_stream(pay + rc);
+      tt[u] = NV > 2 ? tot[rc] : 0;
+      load_cols<D>(col + rc * D, cs[u]);
     }
-    const double d = row_diag(m, p, m.V > 2 ? tot[r] : 0);
-    if (R > 1) {
-      atomicMin(&blo[pay_real(p)], ord_of(d - rad));
-      atomicMax(&bhi[pay_real(p)], ord_of(d + rad));
-    } else {
-      lo = fmin(lo, d - rad);
-      hi = fmax(hi, d + rad);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      double v[D];
+#pragma unroll
+      for (int s = 0; s < 2 * ND; ++s) v[s] = fabs(m.J[s >> 1]);
+#pragma unroll
+      for (int nu = 0; nu < NV; ++nu) {
+        const double* g = m.gsq + nu * kGsqStride + (ok[u] ? pay_occ(p[u], nu) : 0);
+        v[2 * ND + 2 * nu] = fabs(g[0]);
+        v[2 * ND + 2 * nu + 1] = fabs(g[1]);
+      }
+      double rad = 0;
+#pragma unroll
+      for (int s = 0; s < D; ++s) rad += cs[u][s] >= 0 ? v[s] : 0.0;
+      const double d = ok[u] ? row_diag(m, p[u], tt[u]) : 0.0;
+      const double l = ok[u] ? d - rad : INFINITY;
+      const double h = ok[u] ? d + rad : -INFINITY;
+      if (R > 1) {
+        const uint64_t act = __ballot(ok[u]);
+        if (act == 0) continue;
+        const int q = pay_real(p[u]);
+        const int q0 = __shfl(q, __ffsll((unsigned long long)act) - 1);
+        if (__ballot(ok[u] && q != q0) == 0) {
+          const double wl = wave_min(l), wh = wave_max(h);
+          if ((threadIdx.x & 63) == 0) {
+            atomicMin(&blo[q0], ord_of(wl));
+            atomicMax(&bhi[q0], ord_of(wh));
+          }
+        } else if (ok[u]) {
+          atomicMin(&blo[q], ord_of(l));
+          atomicMax(&bhi[q], ord_of(h));
+        }
+      } else {
+        lo = fmin(lo, l);
+        hi = fmax(hi, h);
+      }
     }
   }
   if (R > 1) {
@@ -1009,7 +1043,12 @@ constexpr int kRegBins = 16;
 // Norm, exciton populations, row counts and (batched) energy of psi per
 // realization as per-block partials.  Rows are visited in the select
 // kernels' tile layout, so the same pass also leaves the next step's
-// selection (bits and per-block sums).
+// selection (bits and per-block sums).  A lane reads four rows before it uses
+// the first (25-site chain at 1.5e7 rows 81 -> 73 us).  Batched, a
+// realization's norm is the sum of its populations, and its count and energy
+// are folded by the wave where all its rows are of one realization: 64 6x6
+// lattices 101 -> 53 us, most of which went to lanes waiting for their turn on
+// the same LDS words.
 template <typename R>
 __global__ void __launch_bounds__(kBlock)
     k_pop_norm(int N, int Rn, double th2, const StepCtl* ctl,
@@ -1031,27 +1070,57 @@ __global__ void __launch_bounds__(kBlock)
   for (int q = 0; q < kRegBins; ++q) acc[q] = 0.0;
   const int npop = priv ? N * 64 : Rn * N;
   double* pop_lds = lds;
-  double* n2_lds = lds + npop;          // Rn (batched only)
-  double* en_lds = n2_lds + Rn;         // Rn
+  double* en_lds = lds + npop;  // Rn (batched only)
   uint32_t* cnt_lds = reinterpret_cast<uint32_t*>(en_lds + Rn);  // Rn
   for (int j = threadIdx.x; j < npop; j += blockDim.x) pop_lds[j] = 0.0;
   for (int j = threadIdx.x; j < Rn; j += blockDim.x) {
-    n2_lds[j] = 0.0;
     en_lds[j] = 0.0;
     cnt_lds[j] = 0u;
   }
   __syncthreads();
   double n2 = 0;
   uint32_t rows = 0, kept = 0;
-  for (int64_t t = run.t0; t < run.t1; t += kItems) {
+  constexpr int G = 4;
+  for (int64_t t = run.t0; t < run.t1; t += G) {
+    typename VecT<R>::T a[G];
+    uint64_t pq[G];
+    double er[G];
+    bool ok[G];
 #pragma unroll
-    for (int q = 0; q < kItems; ++q) {
+    for (int q = 0; q < G; ++q) {
+      const int64_t e = (t + q) * kBlock + threadIdx.x;
+      const int64_t ec = e < n ? e : n - 1;
+      a[q] = psi[ec];
+      pq[q] = pay[ec];
+      er[q] = e_row ? e_row[ec] : 0.0;
+      ok[q] = t + q < run.t1 && e < n && !is_hole(dist, ec);
+    }
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
       if (t + q >= run.t1) break;
       const int64_t e = (t + q) * kBlock + threadIdx.x;
       bool keep = false;
-      if (e < n && !is_hole(dist, e)) {
-        const double w = weight(psi[e]);
-        const uint64_t p = pay[e];
+      const uint64_t p = pq[q];
+      const double w = weight(a[q]);
+      if (Rn > 1) {
+        const uint64_t act = __ballot(ok[q]);
+        const int r = pay_real(p);
+        if (ok[q]) atomicAdd(&pop_lds[r * N + pay_site(p)], w);
+        if (act != 0) {
+          const int r0 = __shfl(r, __ffsll((unsigned long long)act) - 1);
+          if (__ballot(ok[q] && r != r0) == 0) {
+            const double ew = e_row ? wave_sum(ok[q] ? er[q] : 0.0) : 0.0;
+            if ((threadIdx.x & 63) == 0) {
+              atomicAdd(&cnt_lds[r0], uint32_t(__popcll(act)));
+              if (e_row) atomicAdd(&en_lds[r0], ew);
+            }
+          } else if (ok[q]) {
+            atomicAdd(&cnt_lds[r], 1u);
+            if (e_row) atomicAdd(&en_lds[r], er[q]);
+          }
+        }
+      }
+      if (ok[q]) {
         keep = w >= th2;
         if (Rn == 1) {
           n2 += w;
@@ -1065,12 +1134,6 @@ __global__ void __launch_bounds__(kBlock)
           } else {
             atomicAdd(&pop_lds[pay_site(p)], w);
           }
-        } else {
-          const int r = pay_real(p);
-          atomicAdd(&n2_lds[r], w);
-          atomicAdd(&cnt_lds[r], 1u);
-          atomicAdd(&pop_lds[r * N + pay_site(p)], w);
-          if (e_row) atomicAdd(&en_lds[r], e_row[e]);
         }
       }
       put_bits(sel_bits, e, n, keep);
@@ -1108,7 +1171,9 @@ __global__ void __launch_bounds__(kBlock)
   } else {
     __syncthreads();
     for (int r = threadIdx.x; r < Rn; r += blockDim.x) {
-      n2_part[int64_t(blockIdx.x) * Rn + r] = n2_lds[r];
+      double n2r = 0;
+      for (int j = 0; j < N; ++j) n2r += pop_lds[r * N + j];
+      n2_part[int64_t(blockIdx.x) * Rn + r] = n2r;
       en_part[int64_t(blockIdx.x) * Rn + r] = en_lds[r];
       if (cnt_lds[r]) atomicAdd(&cnt_s[r], cnt_lds[r]);
     }
@@ -1445,17 +1510,8 @@ namespace {
 void launch_bounds_kernel(const DevModel& m, const Side& n, const int32_t* col,
                           int64_t cap, int g, const StepCtl* ctl, double* part,
                           const int* err, hipStream_t s) {
-#define PACES_BOUNDS(DT) \
-  k_bounds<DT><<<g, kBlock, 0, s>>>(m, n.pay, n.tot, n.dist, col, cap, ctl, part, err)
-  switch (m.D) {
-    case 4: PACES_BOUNDS(4); break;
-    case 6: PACES_BOUNDS(6); break;
-    case 8: PACES_BOUNDS(8); break;
-    case 10: PACES_BOUNDS(10); break;
-    case 12: PACES_BOUNDS(12); break;
-    default: PACES_BOUNDS(0); break;
-  }
-#undef PACES_BOUNDS
+  PACES_DISPATCH_SHAPE(m.ndim, m.V, k_bounds<A, B><<<g, kBlock, 0, s>>>(
+      m, n.pay, n.tot, n.dist, col, cap, ctl, part, err));
 }
 }  // namespace
 
@@ -1521,7 +1577,7 @@ int pop_norm(int prec, int N, int R, double th2, int64_t est,
              double* pop_part, const Sums& sm, uint32_t* cnt_s, int* err,
              hipStream_t s) {
   const bool priv = R == 1 && N <= kPrivBins;
-  const size_t lds = sizeof(double) * ((priv ? N * 64 : R * N) + 3 * R);
+  const size_t lds = sizeof(double) * ((priv ? N * 64 : R * N) + 2 * R);
   // batched partials hold R * N populations per block: fewer blocks
   // a bounded grid: blocks stride over the tiles, so the per-block work
   // (bins cleared and folded, one count added to the total) is amortised
