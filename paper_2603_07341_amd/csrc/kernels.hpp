@@ -106,16 +106,15 @@ void mark(int tag, hipStream_t s);
 void clear_latch(StepCtl* ctl, int* err, hipStream_t s);
 // ctl->kmax and the latch into out[0] and out[1].
 void report(const StepCtl* ctl, const int* err, uint32_t* out, hipStream_t s);
-// A given set of n states as the rows of a step: keys padded from W to Wi
-// words; control counts with frontier 0 = rows [0, n) and the latch
-// cleared; every key valid and distinct (else kErrInput), after the rows
-// are in the table.
+// Keys of a given set of n states padded from W to Wi words.
 void pad_keys(int W, int Wi, const uint64_t* in, uint64_t* out, int64_t n,
               hipStream_t s);
-void set_begin(StepCtl* ctl, int* err, int64_t n, hipStream_t s);
-void check_set(const DevModel& m, int Wi, const uint64_t* keys, int64_t n,
-               const uint64_t* table, uint64_t mask, int* err,
-               hipStream_t s);
+// Counts, payloads, totals, table (mask + 1 slots) and columns of the set given
+// as rows [0, rows) of n.keys; a key out of range or repeated latches
+// kErrInput.
+void build_set(const DevModel& m, int Wi, const Side& n, int64_t rows,
+               StepCtl* ctl, uint64_t* table, uint64_t mask, int32_t* col,
+               int* err, hipStream_t s);
 
 // Start of a step: clear the latch, reset the counters (cnt: 2R
 // per-realization row counts, |M_r| then |S_r|; ball: R).

@@ -2471,13 +2471,7 @@ paces_status expmv_run(const paces_model* m, int64_t n, const uint64_t* keys,
   sd.tot = reinterpret_cast<uint64_t*>(work + L.tot);
   int32_t* col = reinterpret_cast<int32_t*>(work + L.col);
   const uint64_t mask = L.P - 1;
-  set_begin(ctl, err, n, st);
-  row_info(dm, m->Wi, sd.keys, n, sd.pay, sd.tot, st);
-  fill_u64(table, int64_t(L.P), kEmpty, st);
-  rehash_rows(dm, m->Wi, sd, n, table, mask, err, st);
-  check_set(dm, m->Wi, sd.keys, n, table, mask, err, st);
-  lookup_last(dm, m->Wi, sd, 0, ctl, n, table, mask, col, 0, nullptr, nullptr,
-              0, nullptr, err, st);
+  build_set(dm, m->Wi, sd, n, ctl, table, mask, col, err, st);
   // one block takes a small set from here to psi
   SmallTail one{};
   one.m = dm;
