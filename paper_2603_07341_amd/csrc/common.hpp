@@ -279,9 +279,10 @@ constexpr int kSumBlocks = kMaxSums;
 struct TileRun {
   int64_t t0, t1;
 };
-__device__ __forceinline__ TileRun tile_run(int64_t ntiles, int g) {
+__device__ __forceinline__ TileRun tile_run(int64_t ntiles, int g,
+                                            int64_t block = blockIdx.x) {
   const int64_t per = cdiv(ntiles, g);
-  const int64_t a = int64_t(blockIdx.x) * per, b = a + per;
+  const int64_t a = block * per, b = a + per;
   return {a < ntiles ? a : ntiles, b < ntiles ? b : ntiles};
 }
 __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {

@@ -1067,7 +1067,7 @@ void stage_expand_warm(paces_sim* s, int64_t est, hipStream_t st) {
   Stage sg(s, PACES_STAGE_EXPAND, st);
   const int64_t n_old = std::min(bucket(s->nS), s->cap);
   for (int r = 1; r <= k; ++r)
-    warm_round(dm, Wi, s->prec, c, r, s->ctl, s->cap, n_old, s->gcand,
+    warm_round(dm, Wi, s->prec, c, r, k, s->ctl, s->cap, n_old, s->gcand,
                s->table, s->tmask, s->rb, s->wb, s->sm, s->vec[s->ipsi],
                over_limit(s, nullptr), s->err, st);
   if (s->p.max_states > 0)

@@ -4,8 +4,9 @@
 // The search inside the set streams the rows' distance bytes and the
 // columns of the frontier rows; only slots that leave the set, and the slots
 // of states new to it, reach the hash table.  Found states are numbered in
-// the order of their candidates.  A round is four launches; its counts stay
-// per block between them (common.hpp), and every block adds up what it needs.
+// the order of their candidates.  A round is three launches, and one more
+// before the first; its counts stay per block between them (common.hpp), and
+// every block adds up what it needs.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -228,15 +229,14 @@ __global__ void __launch_bounds__(kBlock)
 // ms, on 64 6x6 lattices (D = 6) from 58 to 33 us each, on the aggregate (D =
 // 8) from 62 to 33.
 template <int D>
-__global__ void __launch_bounds__(kBlock)
-    k_warm_count(DevModel m, int r, int vb, const StepCtl* ctl,
-                 const uint64_t* pay, const int32_t* col, uint8_t* dist,
-                 uint16_t* wmask, uint32_t* sums, const int* err) {
+__device__ __forceinline__ void count_part(
+    const DevModel& m, int r, int vb, int block, int grid, const StepCtl* ctl,
+    const uint64_t* pay, const int32_t* col, uint8_t* dist, uint16_t* wmask,
+    uint32_t* sums) {
   constexpr int U = D <= 4 ? 4 : D <= 8 ? 2 : 1;
   __shared__ uint16_t list[kBlock * kMaxVb];
-  if (*err) return;
   const int64_t n = ctl->n_old, tile = int64_t(kBlock) * vb;
-  const TileRun run = tile_run(cdiv(n, tile), gridDim.x);
+  const TileRun run = tile_run(cdiv(n, tile), grid, block);
   uint32_t cnt = 0;
   for (int64_t t = run.t0; t < run.t1; ++t) {
     const uint32_t tot = list_rows(dist, t, n, vb, uint8_t(r - 1), list);
@@ -277,7 +277,17 @@ __global__ void __launch_bounds__(kBlock)
   }
   uint32_t tot;
   block_excl_scan(cnt, &tot);
-  if (threadIdx.x == 0) sums[blockIdx.x] = tot;
+  if (threadIdx.x == 0) sums[block] = tot;
+}
+
+template <int D>
+__global__ void __launch_bounds__(kBlock)
+    k_warm_count(DevModel m, int r, int vb, const StepCtl* ctl,
+                 const uint64_t* pay, const int32_t* col, uint8_t* dist,
+                 uint16_t* wmask, uint32_t* sums, const int* err) {
+  if (*err) return;
+  count_part<D>(m, r, vb, blockIdx.x, gridDim.x, ctl, pay, col, dist, wmask,
+                sums);
 }
 
 // Write pass (same grid): those slots as candidates, in row order.
@@ -426,24 +436,23 @@ __global__ void __launch_bounds__(kBlock)
 // Owners take their rows, numbered by the owners of the blocks before and
 // a scan per tile (same grid as the probe): key, payload, totals, distance
 // kNewRow | r, amplitude 0; their table slot points at the row, staged.
-template <int W, typename Amp>
-__global__ void __launch_bounds__(kBlock)
-    k_warm_commit(DevModel m, int r, StepCtl* ctl, int64_t cap, Side c,
-                  const uint32_t* freel, const uint64_t* wlist,
-                  uint64_t* table, uint64_t mask, const uint32_t* c_slot,
-                  const uint32_t* c_ref, const uint32_t* sums, Amp* psi,
-                  int* err) {
-  if (*err) return;
+template <int W>
+__device__ __forceinline__ void commit_part(
+    const DevModel& m, int r, int block, int grid, StepCtl* ctl, int64_t cap,
+    const Side& c, const uint32_t* freel, const uint64_t* wlist,
+    uint64_t* table, uint64_t mask, const uint32_t* c_slot,
+    const uint32_t* c_ref, const uint32_t* sums, uint64_t* psi, int A8,
+    int* err) {
   const int64_t nc = ctl->r_ncand, noc = ctl->w_noc, f0 = ctl->gstart[r - 1];
-  const TileRun run = tile_run(cdiv(nc, kBlock), gridDim.x);
+  const TileRun run = tile_run(cdiv(nc, kBlock), grid, block);
   uint64_t total;
   int64_t at = ctl->gstart[r] +
-               int64_t(sums_before(sums, gridDim.x, blockIdx.x, &total));
-  if (gtid() == 0) {
+               int64_t(sums_before(sums, grid, block, &total));
+  if (block == 0 && threadIdx.x == 0) {
     ctl->n_staged = uint32_t(ctl->gstart[r] + total);
     ctl->gstart[r + 1] = ctl->n_staged;
   }
-  if (sums[blockIdx.x] == 0) return;
+  if (sums[block] == 0) return;
   for (int64_t tile = run.t0; tile < run.t1; ++tile) {
     const int64_t cand = tile * kBlock + threadIdx.x;
     const bool own = cand < nc && c_ref[cand] == kOwnerW;
@@ -469,11 +478,45 @@ __global__ void __launch_bounds__(kBlock)
     const uint64_t h = key_hash<W>(m, k);
     table[((h & mask) + c_slot[cand]) & mask] =
         (uint64_t(hash_tag(h)) << 32) | uint64_t(kStaged | uint32_t(row));
-    Amp z;
-    z.x = 0;
-    z.y = 0;
-    psi[row] = z;
+    for (int w = 0; w < A8; ++w) psi[row * A8 + w] = 0ull;
   }
+}
+
+template <int W>
+__global__ void __launch_bounds__(kBlock)
+    k_warm_commit(DevModel m, int r, StepCtl* ctl, int64_t cap, Side c,
+                  const uint32_t* freel, const uint64_t* wlist,
+                  uint64_t* table, uint64_t mask, const uint32_t* c_slot,
+                  const uint32_t* c_ref, const uint32_t* sums, uint64_t* psi,
+                  int A8, int* err) {
+  if (*err) return;
+  commit_part<W>(m, r, blockIdx.x, gridDim.x, ctl, cap, c, freel, wlist, table,
+                 mask, c_slot, c_ref, sums, psi, A8, err);
+}
+
+// The commit of round r by blocks [0, grid) beside the count pass of round r +
+// 1 by the others.  The two need nothing of each other: the commit takes rows
+// that no live row's column names, at distances that the count does not
+// match, and the count marks live rows and writes wmask and its own sums, last
+// read by round r's probe.  A launch less per round, and two kernels that wait
+// for memory share the chip: a ring of 16 at 1e3 to 4e5 rows 4.7 + 6.3 us ->
+// 7.0, in complex64 at up to 8e6 5.1 + 9.4 -> 10.8; 64 6x6 lattices 34 + 33 ->
+// 51.
+template <int W, int D>
+__global__ void __launch_bounds__(kBlock)
+    k_warm_turn(DevModel m, int r, int grid, int vb, StepCtl* ctl, int64_t cap,
+                Side c, const uint32_t* freel, const uint64_t* wlist,
+                uint64_t* table, uint64_t mask, const uint32_t* c_slot,
+                const uint32_t* c_ref, const uint32_t* sums, uint64_t* psi,
+                int A8, uint16_t* wmask, uint32_t* old_sums, int* err) {
+  if (*err) return;
+  if (int(blockIdx.x) < grid)
+    commit_part<W>(m, r, blockIdx.x, grid, ctl, cap, c, freel, wlist, table,
+                   mask, c_slot, c_ref, sums, psi, A8, err);
+  else
+    count_part<D>(m, r + 1, vb, int(blockIdx.x) - grid,
+                  int(gridDim.x) - grid, ctl, c.pay, c.col, c.dist, wmask,
+                  old_sums);
 }
 
 // ---- sizes (state cap) --------------------------------------------------------
@@ -739,25 +782,26 @@ void warm_begin(const DevModel& m, StepCtl* ctl, const Sums& sm, int sel_grid,
 }
 
 void warm_round(const DevModel& m, int Wi, int prec, const Side& c, int r,
+                int k,
                 StepCtl* ctl, int64_t cap, int64_t n_old, int64_t n_cand,
                 uint64_t* table, uint64_t mask, const RoundBufs& rb,
                 const WarmBufs& wb, const Sums& sm, void* psi,
                 int64_t row_limit, int* err, hipStream_t s) {
   const int vb = rows_per_lane(n_old);
   const int go = sum_grid(n_old, int64_t(kBlock) * vb);
-#define PACES_WARM_COUNT(DT)                                               \
-  k_warm_count<DT><<<go, kBlock, 0, s>>>(m, r, vb, ctl, c.pay, c.col, c.dist, \
-                                         wb.wmask, sm.old_, err)
-  switch (m.D) {
-    case 4: PACES_WARM_COUNT(4); break;
-    case 6: PACES_WARM_COUNT(6); break;
-    case 8: PACES_WARM_COUNT(8); break;
-    case 10: PACES_WARM_COUNT(10); break;
-    case 12: PACES_WARM_COUNT(12); break;
-    case 14: PACES_WARM_COUNT(14); break;
-    default: break;
+#define PACES_DISPATCH_D(...)                              \
+  switch (m.D) {                                           \
+    case 4: { constexpr int DD = 4; __VA_ARGS__; } break;   \
+    case 6: { constexpr int DD = 6; __VA_ARGS__; } break;   \
+    case 8: { constexpr int DD = 8; __VA_ARGS__; } break;   \
+    case 10: { constexpr int DD = 10; __VA_ARGS__; } break; \
+    case 12: { constexpr int DD = 12; __VA_ARGS__; } break; \
+    case 14: { constexpr int DD = 14; __VA_ARGS__; } break; \
+    default: break;                                        \
   }
-#undef PACES_WARM_COUNT
+  if (r == 1)
+    PACES_DISPATCH_D(k_warm_count<DD><<<go, kBlock, 0, s>>>(
+        m, r, vb, ctl, c.pay, c.col, c.dist, wb.wmask, sm.old_, err));
   k_warm_list<<<go, kBlock, 0, s>>>(r, vb, ctl, c.dist, wb.wmask, sm.old_,
                                     wb.wlist, rb.cand_cap, err);
   const int g = sum_grid(std::min(rb.cand_cap, n_cand), kBlock);
@@ -765,17 +809,20 @@ void warm_round(const DevModel& m, int Wi, int prec, const Side& c, int r,
                            m, r, ctl, row_limit, c, wb.freel, wb.wlist,
                            sm.old_, go, rb.cand_cap, table, mask, rb.c_slot,
                            rb.c_ref, sm.own, err));
-  if (prec == 64) {
-    PACES_DISPATCH_W(Wi, k_warm_commit<WW, double2><<<g, kBlock, 0, s>>>(
+  uint64_t* const psi8 = static_cast<uint64_t*>(psi);
+  const int A8 = prec == 64 ? 2 : 1;
+  if (r == k) {
+    PACES_DISPATCH_W(Wi, k_warm_commit<WW><<<g, kBlock, 0, s>>>(
                              m, r, ctl, cap, c, wb.freel, wb.wlist, table,
-                             mask, rb.c_slot, rb.c_ref, sm.own,
-                             (double2*)psi, err));
+                             mask, rb.c_slot, rb.c_ref, sm.own, psi8, A8,
+                             err));
   } else {
-    PACES_DISPATCH_W(Wi, k_warm_commit<WW, float2><<<g, kBlock, 0, s>>>(
-                             m, r, ctl, cap, c, wb.freel, wb.wlist, table,
-                             mask, rb.c_slot, rb.c_ref, sm.own,
-                             (float2*)psi, err));
+    PACES_DISPATCH_W(Wi, PACES_DISPATCH_D(
+        k_warm_turn<WW, DD><<<g + go, kBlock, 0, s>>>(
+            m, r, g, vb, ctl, cap, c, wb.freel, wb.wlist, table, mask,
+            rb.c_slot, rb.c_ref, sm.own, psi8, A8, wb.wmask, sm.old_, err)));
   }
+#undef PACES_DISPATCH_D
 }
 
 void warm_cap_check(const DevModel& m, const Side& c, int k, StepCtl* ctl,

@@ -57,7 +57,7 @@ struct WarmBufs {
 void warm_begin(const DevModel& m, StepCtl* ctl, const Sums& sm, int sel_grid,
                 const Side& c, const WarmBufs& wb, uint32_t* cnt_m,
                 int64_t n_old, bool holes, int* err, hipStream_t s);
-// Round r (1..k): live rows at distance r-1 mark their neighbours inside
+// Round r of k: live rows at distance r-1 mark their neighbours inside
 // the set at distance r and hand the slots whose neighbour is outside it
 // on as candidates; states found in round r-1 hand on every slot.
 // Candidates already in the set mark it, others are inserted into the
@@ -65,10 +65,12 @@ void warm_begin(const DevModel& m, StepCtl* ctl, const Sums& sm, int sel_grid,
 // else the next row past the range): key, payload, distance kNewRow | r,
 // amplitude 0.  A row past cap latches kErrCapacity; more candidates than
 // the buffers hold latch kErrChunks; M and the found states together
-// beyond row_limit (0: none) latch kErrOver.
+// beyond row_limit (0: none) latch kErrOver.  The rounds are called in order:
+// the last launch of round r < k is also the first of round r + 1.
 // n_old, n_cand: estimates of the rows and of a round's candidates, which
 // only size grids.
 void warm_round(const DevModel& m, int Wi, int prec, const Side& c, int r,
+                int k,
                 StepCtl* ctl, int64_t cap, int64_t n_old, int64_t n_cand,
                 uint64_t* table, uint64_t mask, const RoundBufs& rb,
                 const WarmBufs& wb, const Sums& sm, void* psi,
