@@ -216,6 +216,11 @@ __global__ void __launch_bounds__(kBlock)
 // weights), and the rest return at once.  The search took 6-8 passes of 8
 // bits over 21 bytes per row each before, with a host round trip between
 // them: 25-site chain, 24 steps at 1.6e7 rows 14.7 ms of kernels.
+// Every block adds its bins to the same few counters of the leading digit and
+// takes a ticket of one word, a few ns each, so two blocks per CU run with
+// eight rows in flight per lane: a pass over 7e6 rows 22.5 -> 16 us on average
+// and over 1.6e7 47 -> 35 (1024 blocks, one row in flight; 256 blocks 14 and
+// 38).
 __device__ __forceinline__ int top_shift(int pass) {
   return pass < 4 ? 51 - 13 * pass : 0;
 }
@@ -237,21 +242,46 @@ __global__ void __launch_bounds__(kBlock)
   if (mode) return;
   const int shift = top_shift(pass), width = pass < 4 ? 13 : 12;
   const uint64_t digit = (uint64_t(1) << width) - 1, pre = prefix;
-  for (int64_t e = gtid(); e < n; e += gstride()) {
-    uint64_t key;
-    if (pass == 0) {
-      const double wt = weight(psi[e]);
-      const bool cand = dist[e] != kHole && (all || wt >= th2);
-      key = cand ? ~uint64_t(__double_as_longlong(wt)) : ~0ull;
-      w[e] = key;
-      if (!cand) continue;
-    } else {
-      key = w[e];
-      if ((key >> shift >> width) != pre) continue;
-      // the last bin of all also holds the rows that are no candidates
-      if (key == ~0ull && (dist[e] == kHole || !(all || th2 <= 0))) continue;
+  constexpr int U = 8;  // rows in flight per lane
+  const int64_t step = gstride();
+  if (pass == 0) {
+    for (int64_t e0 = gtid(); e0 < n; e0 += U * step) {
+      Amp a[U];
+      uint8_t d[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t e = e0 + u * step < n ? e0 + u * step : e0;
+        a[u] = psi[e];
+        d[u] = dist[e];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (e0 + u * step >= n) break;
+        const double wt = weight(a[u]);
+        const bool cand = d[u] != kHole && (all || wt >= th2);
+        const uint64_t key =
+            cand ? ~uint64_t(__double_as_longlong(wt)) : ~0ull;
+        w[e0 + u * step] = key;
+        if (cand) atomicAdd(&bins[(key >> shift) & digit], 1u);
+      }
     }
-    atomicAdd(&bins[(key >> shift) & digit], 1u);
+  } else {
+    for (int64_t e0 = gtid(); e0 < n; e0 += U * step) {
+      uint64_t key[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        key[u] = w[e0 + u * step < n ? e0 + u * step : e0];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t e = e0 + u * step;
+        if (e >= n) break;
+        if ((key[u] >> shift >> width) != pre) continue;
+        // the last bin of all also holds the rows that are no candidates
+        if (key[u] == ~0ull && (dist[e] == kHole || !(all || th2 <= 0)))
+          continue;
+        atomicAdd(&bins[(key[u] >> shift) & digit], 1u);
+      }
+    }
   }
   __syncthreads();
   for (int b = threadIdx.x; b < kTopBins; b += kBlock)
@@ -397,7 +427,7 @@ void top_select(int prec, const void* psi, const uint8_t* dist, int64_t n,
                 bool all, double th2, int64_t q, const TopBufs& tb,
                 hipStream_t s) {
   k_top_init<<<1, 1, 0, s>>>(tb.st, q);
-  const int g = std::min(grid_for(cdiv(n, 8)), 1024);
+  const int g = std::min(grid_for(cdiv(n, 8)), 512);
   for (int p = 0; p < kTopPasses; ++p) {
     if (prec == 64)
       k_top_pass<double2><<<g, kBlock, 0, s>>>(p, (const double2*)psi, dist, n,

@@ -192,7 +192,7 @@ __global__ void __launch_bounds__(kBlock)
 
 __global__ void k_begin_step(StepCtl* ctl, int* err, uint32_t* cnt,
                              uint32_t* ball, int R) {
-  for (int i = threadIdx.x; i < 2 * R; i += blockDim.x) cnt[i] = 0u;
+  for (int i = threadIdx.x; i < R; i += blockDim.x) cnt[i] = 0u;
   for (int i = threadIdx.x; i < R; i += blockDim.x) ball[i] = 0u;
   if (threadIdx.x == 0) {
     *err = 0;
@@ -341,7 +341,9 @@ __global__ void __launch_bounds__(kBlock)
 // ---- insert rows into the cleared table -------------------------------------
 // Row i of the new set is row midx[i] of the old one (keys_o given) or is
 // already in place (rehash after growth, keys_o null).  With phi given, the
-// row's amplitude moves along (the transfer then skips rows of M).
+// row's amplitude moves along (the transfer then skips rows of M).  cnt_r: the
+// rows per realization, cleared; with one realization that is nM, and no block
+// adds to it (16384 of them on one counter: 149 -> 139 us at 1.6e7 rows).
 template <int W, typename Amp>
 __global__ void __launch_bounds__(kBlock)
     k_insert_rows(DevModel m, const uint64_t* keys_o, const uint64_t* pay_o,
@@ -364,7 +366,7 @@ __global__ void __launch_bounds__(kBlock)
       pay_n[i] = pay_o[r];
       tot_n[i] = tot_o[r];
       if (phi) phi[i] = psi_o[r];
-      if (cnt_r) atomicAdd(&bins[pay_real(pay_o[r])], 1u);
+      if (cnt_r && m.R > 1) atomicAdd(&bins[pay_real(pay_o[r])], 1u);
     } else {
       load_key<W>(keys_n, i, k);
     }
@@ -384,7 +386,8 @@ __global__ void __launch_bounds__(kBlock)
     }
     if (!done) atomicOr(err, kErrTableFull);
   }
-  if (cnt_r) count_flush(m.R, bins, cnt_r);
+  if (cnt_r && m.R > 1) count_flush(m.R, bins, cnt_r);
+  if (cnt_r && m.R == 1 && gtid() == 0) cnt_r[0] = uint32_t(nM);
 }
 
 // ---- expansion round --------------------------------------------------------
@@ -1119,7 +1122,9 @@ constexpr int kRegBins = 16;
 // realization's norm is the sum of its populations, and its count and energy
 // are folded by the wave where all its rows are of one realization: 64 6x6
 // lattices 101 -> 53 us, most of which went to lanes waiting for their turn on
-// the same LDS words.
+// the same LDS words.  Row counts are left per block like the norms: one
+// counter that 1024 blocks add to is served at about 4 ns each (ring of 16
+// 23.0 -> 19.1 us, in complex64 18.6 -> 14.3).
 template <typename R>
 __global__ void __launch_bounds__(kBlock)
     k_pop_norm(int N, int Rn, double th2, const StepCtl* ctl,
@@ -1127,7 +1132,7 @@ __global__ void __launch_bounds__(kBlock)
                const uint8_t* dist,
                const double* e_row, double* n2_part, double* en_part,
                double* pop_part, uint64_t* sel_bits, uint32_t* sel_sums,
-               uint32_t* cnt_s, const int* err) {
+               const int* err) {
   extern __shared__ double lds[];
   if (*err) return;
   const int64_t n = ctl->n_new;
@@ -1227,7 +1232,7 @@ __global__ void __launch_bounds__(kBlock)
     block_excl_scan(rows, &all);
     if (threadIdx.x == 0) {
       n2_part[blockIdx.x] = n2;
-      if (all) atomicAdd(&cnt_s[0], all);
+      n2_part[kPopBlocks + blockIdx.x] = double(all);
     }
     __syncthreads();
     if (priv) {
@@ -1246,7 +1251,7 @@ __global__ void __launch_bounds__(kBlock)
       for (int j = 0; j < N; ++j) n2r += pop_lds[r * N + j];
       n2_part[int64_t(blockIdx.x) * Rn + r] = n2r;
       en_part[int64_t(blockIdx.x) * Rn + r] = en_lds[r];
-      if (cnt_lds[r]) atomicAdd(&cnt_s[r], cnt_lds[r]);
+      n2_part[int64_t(kPopBlocks + blockIdx.x) * Rn + r] = double(cnt_lds[r]);
     }
     for (int j = threadIdx.x; j < Rn * N; j += blockDim.x)
       pop_part[int64_t(blockIdx.x) * Rn * N + j] = pop_lds[j];
@@ -1282,17 +1287,30 @@ __device__ __forceinline__ void close_step(StepCtl* ctl, int Rn,
   __threadfence_system();
 }
 
-// Sum of n partials at a stride, eight loads in flight per lane: a block
-// that adds up to 16384 of them waits for memory 8 times instead of 64.
+// Sum of n partials at a stride, up to 32 loads in flight per lane: the block
+// that adds up the Clenshaw launch's up to 16384 of them waits for memory
+// twice (with eight in flight 8 times: a record of the 25-site chain 25 -> 9
+// us, of a ring of 16 at 0.5 to 1e7 rows 14.3 -> 8.1).
 __device__ __forceinline__ double sum_partials(const double* p, int n,
                                                int64_t stride) {
   double a[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int i = threadIdx.x; i < n; i += 8 * kBlock) {
+  int i = threadIdx.x;
+  for (; i + 31 * kBlock < n; i += 32 * kBlock) {
+    double v[32];
+#pragma unroll
+    for (int q = 0; q < 32; ++q) v[q] = p[int64_t(i + q * kBlock) * stride];
+#pragma unroll
+    for (int q = 0; q < 32; ++q) a[q & 7] += v[q];
+  }
+  for (; i < n; i += 8 * kBlock) {
+    double v[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
       const int j = i + q * kBlock;
-      if (j < n) a[q] += p[int64_t(j) * stride];
+      v[q] = p[int64_t(j < n ? j : i) * stride];
     }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) a[q] += i + q * kBlock < n ? v[q] : 0.0;
   }
   return block_sum(((a[0] + a[1]) + (a[2] + a[3])) +
                    ((a[4] + a[5]) + (a[6] + a[7])));
@@ -1322,10 +1340,12 @@ __device__ __forceinline__ void obs_block(
     if (threadIdx.x == 0) rec[kObsFields + blockIdx.x] = s;
   } else if (what == 0) {
     const double n2 = sum_partials(n2_part + r, n_pop, Rn);
+    const double rows =
+        sum_partials(n2_part + int64_t(kPopBlocks) * Rn + r, n_pop, Rn);
     if (threadIdx.x == 0) {
       rec[0] = ctl->t + dt;
       rec[1] = n2;
-      rec[7] = double(cnt[Rn + r]);
+      rec[7] = rows;
       rec[8] = double(cnt[r]);
       rec[9] = double(cc[r].K);
       rec[10] = cc[r].emin;
@@ -1647,22 +1667,21 @@ int pop_norm(int prec, int N, int R, double th2, int64_t est,
              const StepCtl* ctl, const void* psi, const uint64_t* pay,
              const uint8_t* dist,
              const double* e_row, double* n2_part, double* en_part,
-             double* pop_part, const Sums& sm, uint32_t* cnt_s, int* err,
-             hipStream_t s) {
+             double* pop_part, const Sums& sm, int* err, hipStream_t s) {
   const bool priv = R == 1 && N <= kPrivBins;
   const size_t lds = sizeof(double) * ((priv ? N * 64 : R * N) + 2 * R);
   // batched partials hold R * N populations per block: fewer blocks
   // a bounded grid: blocks stride over the tiles, so the per-block work
   // (bins cleared and folded, one count added to the total) is amortised
-  const int g = std::min(sum_grid(est, kBlock), 1024);
+  const int g = std::min(sum_grid(est, kBlock), kPopBlocks);
   if (prec == 64)
     k_pop_norm<double><<<g, kBlock, lds, s>>>(
         N, R, th2, ctl, (const double2*)psi, pay, dist, e_row, n2_part, en_part,
-        pop_part, sm.bits, sm.sel, cnt_s, err);
+        pop_part, sm.bits, sm.sel, err);
   else
     k_pop_norm<float><<<g, kBlock, lds, s>>>(
         N, R, th2, ctl, (const float2*)psi, pay, dist, e_row, n2_part, en_part,
-        pop_part, sm.bits, sm.sel, cnt_s, err);
+        pop_part, sm.bits, sm.sel, err);
   return g;
 }
 

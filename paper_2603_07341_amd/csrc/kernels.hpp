@@ -15,7 +15,10 @@ namespace paces {
 
 constexpr int kMaxTerms = 128;   // Chebyshev terms per step, hard limit
 constexpr int kMaxRounds = 30;   // neighbour order per step, hard limit
-constexpr int kPartBlocks = 2048;  // grid of the population reduction
+constexpr int kPartBlocks = 2048;  // largest grid that leaves partials
+// Blocks of the record pass: n2_part holds their norms, and from row
+// kPopBlocks on their row counts.
+constexpr int kPopBlocks = 1024;
 constexpr int kMaxPartials = 1 << 18;  // per-block partials of row kernels
 constexpr int kObsFields = 12;
 constexpr int kMaxReal = 256;      // disorder realizations per sim
@@ -116,8 +119,8 @@ void build_set(const DevModel& m, int Wi, const Side& n, int64_t rows,
                StepCtl* ctl, uint64_t* table, uint64_t mask, int32_t* col,
                int* err, hipStream_t s);
 
-// Start of a step: clear the latch, reset the counters (cnt: 2R
-// per-realization row counts, |M_r| then |S_r|; ball: R).
+// Start of a step: clear the latch, reset the counters (cnt: |M_r| of the R
+// realizations; ball: R).
 void begin_step(StepCtl* ctl, int* err, uint32_t* cnt, uint32_t* ball, int R,
                 hipStream_t s);
 // The selection over rows [0, ctl->n_old) as bits and per-block sums
@@ -206,7 +209,7 @@ int pop_norm(int prec, int N, int R, double th2, int64_t est,
              const StepCtl* ctl, const void* psi, const uint64_t* pay,
              const uint8_t* dist,
              const double* e_row, double* n2_part, double* en_part,
-             double* pop_part, const Sums& sm, uint32_t* cnt_s, int* err,
+             double* pop_part, const Sums& sm, int* err,
              hipStream_t s);
 // Commit a successful step on the device: time, discarded weight per
 // realization, record count and the row count of the current set; then

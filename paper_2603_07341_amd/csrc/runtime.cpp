@@ -487,7 +487,7 @@ struct paces_sim {
          *en_part = nullptr, *pop_part = nullptr, *bnd_part = nullptr;
   double* e_row = nullptr;     // per-row energy terms (batched sims)
   ChebCoef* cc = nullptr;      // [R]
-  uint32_t* cnt = nullptr;     // [2R]: |M_r| then |S_r|
+  uint32_t* cnt = nullptr;     // [R]: |M_r|
   double* mass_tot = nullptr;  // [R] cumulative discarded weight
 
   uint64_t* keys0 = nullptr;
@@ -1260,7 +1260,7 @@ void stage_observe(paces_sim* s, int64_t est, hipStream_t st,
                              s->vec[s->ib0], sn.pay, sn.dist,
                              want_e && R > 1 && !krylov ? s->e_row : nullptr,
                              s->n2_part, s->en_part, s->pop_part, s->sm,
-                             s->cnt + R, s->err, st);
+                             s->err, st);
   // the Krylov energy goes into the record after it is written, so the step
   // is closed by a launch of its own there, as it is with several
   // realizations
@@ -2922,7 +2922,7 @@ paces_status paces_init_state(const paces_model* m, const paces_run_params* p,
   const int64_t nparts = sz_mass + sz_e + sz_bnd + 2 * sz_pop +
                          sz_pop * m->N;
   if (dalloc(&s->ctl, 1) || dalloc(&s->err, 1) || dalloc(&s->parts, nparts) ||
-      dalloc(&s->cc, R) || dalloc(&s->cnt, 2 * R) ||
+      dalloc(&s->cc, R) || dalloc(&s->cnt, R) ||
       dalloc(&s->mass_tot, R) || dalloc(&s->p0_last, nt) ||
       dalloc(&s->ball, R) || dalloc(&s->dcount, 1) ||
       dalloc(&s->sums_block, 5 * kMaxSums) ||
@@ -2957,7 +2957,7 @@ paces_status paces_init_state(const paces_model* m, const paces_run_params* p,
   if (hipMemsetAsync(s->err, 0, 4, st) != hipSuccess ||
       hipMemsetAsync(s->parts, 0, size_t(nparts) * 8, st) != hipSuccess ||
       hipMemsetAsync(s->mass_tot, 0, size_t(R) * 8, st) != hipSuccess ||
-      hipMemsetAsync(s->cnt, 0, size_t(2 * R) * 4, st) != hipSuccess)
+      hipMemsetAsync(s->cnt, 0, size_t(R) * 4, st) != hipSuccess)
     return cleanup(fail(PACES_E_HIP, "memset failed"));
   const int64_t cap0 = std::max<int64_t>({p->cap_states, 4 * nt, 1 << 16});
   paces_status g =

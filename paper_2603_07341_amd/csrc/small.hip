@@ -412,7 +412,6 @@ __global__ void __launch_bounds__(kNB) k_small_expand(SmallExpand a) {
     if (e0 + q < n && ld[e0 + q] == kHole) a.wb.freel[at++] = uint32_t(e0 + q);
   if (threadIdx.x == 0) {
     a.cnt[0] = nM;
-    a.cnt[1] = 0;
     a.ball[0] = 0;
     *a.err = big ? kErrBig : 0;
     latch = big ? kErrBig : 0;
