@@ -470,7 +470,8 @@ def stage_bandwidth(model, A, sprof, srec, n_old0, steps, copy_gbs, wprof,
     committed counter profile of this window, each stage also gets its
     achieved rate: counted HBM bytes (FETCH_SIZE + WRITE_SIZE, calibrated)
     over kernel time, both per step of the window.
-      select        n_old (A + 1) + 4 |M|
+      select        n_old (A + 1) + 4 |M|; in place n_old (1 + 1/8): the bits
+                    left by the observables become distances
       expand+build  |S| (8W + D (8 + 8W + 4) + rho (8W + 16)),
                     rho = net growth of S / |S| (a lower bound on new rows)
       transfer      n_old (16W + 8 + 2A)
@@ -488,7 +489,8 @@ def stage_bandwidth(model, A, sprof, srec, n_old0, steps, copy_gbs, wprof,
           "propagate": 0.0, "observe": 0.0}
     for s in range(steps):
         rho = max(0.0, nS[s] - n_old[s]) / max(nS[s], 1.0)
-        by["select"] += n_old[s] * (A + 1) + 4 * nM[s]
+        by["select"] += (n_old[s] * 1.125 if in_place
+                         else n_old[s] * (A + 1) + 4 * nM[s])
         by["expand+build"] += nS[s] * (8 * W + D * (8 + 8 * W + 4) + rho * (8 * W + 16))
         by["transfer"] += n_old[s] * (16 * W + 8 + 2 * A)
         by["propagate"] += nS[s] * K[s] * (4 * A + 4 * D + 8)
