@@ -359,7 +359,7 @@ __global__ void __launch_bounds__(kBlock)
     if (uint32_t(nc) > ctl->c_max) ctl->c_max = uint32_t(nc);
   }
   const TileRun run = tile_run(cdiv(nc, kBlock), gridDim.x);
-  uint32_t own = 0;
+  uint32_t own = 0, pend = 0;  // pend: not yet in r_own
   int par = 0;
   for (int64_t tile = run.t0; tile < run.t1; ++tile, par ^= 1) {
     const int64_t cand = tile * kBlock + threadIdx.x;
@@ -425,9 +425,13 @@ __global__ void __launch_bounds__(kBlock)
     uint32_t tot;
     block_excl_scan(owner, &tot);
     own += tot;
-    if (threadIdx.x == 0 && row_limit > 0 && tot &&
-        nM + int64_t(atomicAdd(&ctl->r_own, tot)) + tot > row_limit)
-      atomicOr(err, kErrOver);
+    pend += tot;
+    if (threadIdx.x == 0 && row_limit > 0 && pend &&
+        (((tile - run.t0) & 3) == 3 || tile + 1 == run.t1)) {
+      if (nM + int64_t(atomicAdd(&ctl->r_own, pend)) + pend > row_limit)
+        atomicOr(err, kErrOver);
+      pend = 0;
+    }
     if (stop[par]) return;  // written before the scan's barriers
   }
   if (threadIdx.x == 0) sums[blockIdx.x] = own;
