@@ -232,9 +232,11 @@ __global__ void __launch_bounds__(kBlock)
                uint32_t* hist) {
   __shared__ uint32_t bins[kTopBins];
   __shared__ uint64_t prefix;
+  __shared__ int64_t need;  // read here: the lane that decides writes it
   __shared__ int mode;
   if (threadIdx.x == 0) {
     prefix = st->prefix;
+    need = st->need;
     mode = st->mode;
   }
   for (int b = threadIdx.x; b < kTopBins; b += kBlock) bins[b] = 0u;
@@ -298,7 +300,6 @@ __global__ void __launch_bounds__(kBlock)
   }
   uint32_t tot;
   int64_t below = block_excl_scan(sum, &tot);
-  const int64_t need = st->need;
   if (below < need && need <= below + sum) {
     int d = -1;
     int64_t here = 0;

@@ -1,0 +1,46 @@
+"""Order between the waves of a block, read off the kernels' source (no GPU):
+what a run cannot be relied on to show, since the waves of a block usually
+reach a word within a few cycles of each other.  Each test states the order
+that the kernel needs and looks for the statement that makes it."""
+import os
+import re
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                    "paper_2603_07341_amd", "csrc")
+
+
+def source(name):
+    with open(os.path.join(CSRC, name)) as fh:
+        text = fh.read()
+    return re.sub(r"//[^\n]*", "", text)
+
+
+def body(text, name):
+    """Body of the function `name` (its first definition in `text`)."""
+    for m in re.finditer(r"\b%s\s*\(" % name, text):
+        at, depth = m.end(), 1
+        while depth:
+            depth += {"(": 1, ")": -1}.get(text[at], 0)
+            at += 1
+        rest = text[at:]
+        if not rest.lstrip().startswith("{"):
+            continue
+        start = at = at + rest.index("{") + 1
+        depth = 1
+        while depth:
+            depth += {"{": 1, "}": -1}.get(text[at], 0)
+            at += 1
+        return text[start:at - 1]
+    raise AssertionError("no definition of " + name)
+
+
+def test_top_pass_reads_need_before_the_block_that_writes_it():
+    # the lane that finds the digit writes st->need, the waves that have not
+    # searched yet must not read it any more
+    b = body(source("cap.hip"), "k_top_pass")
+    tail = b[b.index("last_block("):]
+    reads = [m for m in re.finditer(r"st->need\b", tail)
+             if not re.match(r"\s*=[^=]", tail[m.end():])]
+    assert not reads, "read of st->need beside the write of the deciding lane"
+    head = b[:b.index("last_block(")]
+    assert "st->need" in head[:head.index("__syncthreads")]
