@@ -174,9 +174,13 @@ __device__ __forceinline__ int64_t gtid_xcd() {
 
 // Arrival of one block at the end of a kernel: true in every lane of the
 // block that arrives last, whose reads then see what the others wrote.  The
-// counter is left at zero for the next kernel that uses it.
+// fence is every lane's: the barrier makes no wave wait for its global stores
+// and adds, so with lane 0's release alone the others' could still be on
+// their way when the ticket is counted.  The counter is left at zero for the
+// next kernel that uses it.
 __device__ __forceinline__ bool last_block(uint32_t* ticket, uint32_t blocks) {
   __shared__ int last;
+  __threadfence();
   __syncthreads();
   if (threadIdx.x == 0) {
     last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_ACQ_REL,

@@ -44,3 +44,10 @@ def test_top_pass_reads_need_before_the_block_that_writes_it():
     assert not reads, "read of st->need beside the write of the deciding lane"
     head = b[:b.index("last_block(")]
     assert "st->need" in head[:head.index("__syncthreads")]
+
+
+def test_last_block_orders_every_wave_before_the_ticket():
+    # a barrier waits for no global store or add of the other waves: each
+    # lane makes its own visible before the one that takes the ticket goes on
+    b = body(source("common.hpp"), "last_block")
+    assert "__threadfence()" in b[:b.index("__syncthreads")]
