@@ -108,8 +108,10 @@ __device__ __forceinline__ void small_observe(const SmallTail& a, int K,
   block_fold(v, red, Add());
   n2 = v[0];
   ms = v[1];
-  const bool room = int64_t(ctl->nrec) + 1 <= a.ring_cap;  // the host keeps it
-  double* rec = a.ring + int64_t(ctl->nrec) * a.rec_doubles;
+  const int64_t nrec = ctl->nrec;
+  const bool room = nrec + 1 <= a.ring_cap;  // the host keeps it
+  double* rec = a.ring + nrec * a.rec_doubles;
+  __syncthreads();  // every wave has its record before lane 0 counts it
   if (room) {
     for (int j = threadIdx.x; j < N; j += kNB) rec[kObsFields + j] = bins[j];
     if (threadIdx.x == 0) {

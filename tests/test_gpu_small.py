@@ -73,3 +73,15 @@ def test_expmv_about_the_limit(n):
     order = np.lexsort(keys.T[::-1])
     assert np.array_equal(k, keys[order])
     assert np.array_equal(a, out[order])
+
+
+@pytest.mark.parametrize("over,steps", [
+    (dict(extent=[65, 1, 1], cutoff=[2], k=1, k_init=1), 10),
+    (dict(extent=[100, 1, 1], cutoff=[2], k=1, k_init=2), 8),
+    (dict(extent=[300, 1, 1], cutoff=[1], k=1, k_init=1, init="local",
+          precision=32), 20),
+])
+def test_small_sets_on_more_sites_than_a_wave(over, steps):
+    # the record's populations come from several waves; each must land in
+    # its own step's record
+    test_steps_equal_the_spread_launches("ring16", over, steps)

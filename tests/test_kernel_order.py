@@ -51,3 +51,12 @@ def test_last_block_orders_every_wave_before_the_ticket():
     # lane makes its own visible before the one that takes the ticket goes on
     b = body(source("common.hpp"), "last_block")
     assert "__threadfence()" in b[:b.index("__syncthreads")]
+
+
+def test_small_record_is_addressed_before_the_count_moves_on():
+    # every wave finds the record by ctl->nrec, lane 0 increments it
+    b = body(source("small.hip"), "small_observe")
+    reads = [m.start() for m in re.finditer(r"ctl->nrec\b", b)]
+    inc = b.index("ctl->nrec += 1")
+    before = max(r for r in reads if r < inc)
+    assert "__syncthreads()" in b[before:inc], "no barrier before the increment"
