@@ -61,7 +61,7 @@ __global__ void __launch_bounds__(kBlock)
     k_adj_node_coef(const ChebCoef* cc, double dt, const double* tau,
                     double tol, double2* cn, int* err) {
   __shared__ double J[kMaxTerms + 1];
-  if (*err) return;
+  if (latched(err)) return;
   const int q = blockIdx.x;
   const double x = cc->a * tau[q] * dt;
   const int kcap = kMaxTerms - 1;

@@ -380,7 +380,7 @@ __global__ void __launch_bounds__(kBlock)
                TopState* st, const uint32_t* ties, uint64_t* bits,
                uint32_t* sums, int* err) {
   __shared__ uint64_t hash[kTopTies];
-  if (*err) return;
+  if (latched(err)) return;
   if (st->mode != 2) return;
   const uint32_t nt = st->nties;
   const int64_t need = st->need;

@@ -191,6 +191,17 @@ __device__ __forceinline__ bool last_block(uint32_t* ticket, uint32_t blocks) {
   return last != 0;
 }
 
+// The latch as the block finds it when it starts, the same for all of its
+// waves.  A kernel whose own blocks latch while others start must not let each
+// wave read it: waves that saw zero would go on into scans and lists of the
+// block with the other waves' parts of them unwritten.
+__device__ __forceinline__ bool latched(const int* err) {
+  __shared__ int seen;
+  if (threadIdx.x == 0) seen = *err;
+  __syncthreads();
+  return seen != 0;
+}
+
 // The error latch as other blocks of the running kernel left it (a plain
 // load may be served from a stale line of this die's cache).
 __device__ __forceinline__ int latch_now(const int* err) {

@@ -353,7 +353,7 @@ __global__ void __launch_bounds__(kBlock)
                   uint64_t* table, uint64_t mask, uint32_t* cnt_r, const Amp* psi_o, Amp* phi,
                   int* err) {
   __shared__ uint32_t bins[kMaxReal];
-  if (*err) return;
+  if (latched(err)) return;
   for (int r = threadIdx.x; r < m.R; r += blockDim.x) bins[r] = 0;
   __syncthreads();
   const int64_t nM = nptr ? int64_t(*nptr) : n_fixed;
@@ -437,7 +437,7 @@ __global__ void __launch_bounds__(kBlock)
                    uint32_t* c_slot, uint32_t* c_ref, uint32_t* tile_base,
                    uint32_t* sums, int32_t* col, int* err) {
   __shared__ int stop[2];  // latch seen at this tile, by parity of the tile
-  if (*err) return;
+  if (latched(err)) return;
   const int D = m.D;
   const int64_t per = cand_cap / D;
   const Chunk ch = round_chunk(ctl, r, chunk, per);
@@ -556,7 +556,7 @@ __global__ void __launch_bounds__(kBlock)
                     const uint32_t* c_ref, const uint32_t* tile_base,
                     const uint32_t* sums, int32_t* col, Amp* phi, int* err) {
   __shared__ uint32_t pre[kSumBlocks];
-  if (*err) return;
+  if (latched(err)) return;
   const int D = m.D;
   const int64_t per = cand_cap / D;
   const Chunk ch = round_chunk(ctl, r, chunk, per);
@@ -815,7 +815,7 @@ __global__ void __launch_bounds__(kBlock)
            int k_max, int launched, ChebCoef* cc_all, StepCtl* ctl,
            int* err) {
   __shared__ double J[kMaxTerms + 1];
-  if (*err) return;
+  if (latched(err)) return;
   const int rr = blockIdx.x;
   ChebCoef* cc = cc_all + rr;
   double lo = INFINITY, hi = -INFINITY;

@@ -209,7 +209,7 @@ __global__ void __launch_bounds__(64)
     k_lz_small(int Rn, double dt, double tol, int k_max, LanczosState* st,
                ChebCoef* cc_all, StepCtl* ctl, int* err) {
   __shared__ double J[kMaxTerms + 1];
-  if (*err) return;
+  if (latched(err)) return;
   const int r = blockIdx.x, l = threadIdx.x;
   LanczosState& s = st[r];
   ChebCoef* cc = cc_all + r;

@@ -78,7 +78,7 @@ __global__ void __launch_bounds__(kBlock)
     k_taylor_plan(int Rn, const double* part, int nparts, double dt, int order,
                   const double* thetas, int k_max, int launched,
                   TaylorPlan* plan, ChebCoef* cc, StepCtl* ctl, int* err) {
-  if (*err) return;
+  if (latched(err)) return;
   const int r = blockIdx.x;
   double lo = INFINITY, hi = -INFINITY;
   for (int i = threadIdx.x; i < nparts; i += blockDim.x) {

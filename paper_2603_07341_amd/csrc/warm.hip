@@ -296,7 +296,7 @@ __global__ void __launch_bounds__(kBlock)
                 const uint16_t* wmask, const uint32_t* sums, uint64_t* wlist,
                 int64_t cand_cap, int* err) {
   __shared__ uint16_t list[kBlock * kMaxVb];
-  if (*err) return;
+  if (latched(err)) return;
   const int64_t n = ctl->n_old, tile = int64_t(kBlock) * vb;
   const TileRun run = tile_run(cdiv(n, tile), gridDim.x);
   uint64_t total;
@@ -344,7 +344,7 @@ __global__ void __launch_bounds__(kBlock)
                  uint64_t* table, uint64_t mask, uint32_t* c_slot,
                  uint32_t* c_ref, uint32_t* sums, int* err) {
   __shared__ int stop[2];  // latch seen at this tile, by parity of the tile
-  if (*err) return;
+  if (latched(err)) return;
   uint64_t total;
   sums_before(old_sums, old_grid, 0, &total);
   const int64_t noc = int64_t(total), f0 = ctl->gstart[r - 1], nM = ctl->nM;
@@ -493,7 +493,7 @@ __global__ void __launch_bounds__(kBlock)
                   uint64_t* table, uint64_t mask, const uint32_t* c_slot,
                   const uint32_t* c_ref, const uint32_t* sums, uint64_t* psi,
                   int A8, int* err) {
-  if (*err) return;
+  if (latched(err)) return;
   commit_part<W>(m, r, blockIdx.x, gridDim.x, ctl, cap, c, freel, wlist, table,
                  mask, c_slot, c_ref, sums, psi, A8, err);
 }
@@ -513,7 +513,7 @@ __global__ void __launch_bounds__(kBlock)
                 uint64_t* table, uint64_t mask, const uint32_t* c_slot,
                 const uint32_t* c_ref, const uint32_t* sums, uint64_t* psi,
                 int A8, uint16_t* wmask, uint32_t* old_sums, int* err) {
-  if (*err) return;
+  if (latched(err)) return;
   if (int(blockIdx.x) < grid)
     commit_part<W>(m, r, blockIdx.x, grid, ctl, cap, c, freel, wlist, table,
                    mask, c_slot, c_ref, sums, psi, A8, err);

@@ -60,3 +60,31 @@ def test_small_record_is_addressed_before_the_count_moves_on():
     inc = b.index("ctl->nrec += 1")
     before = max(r for r in reads if r < inc)
     assert "__syncthreads()" in b[before:inc], "no barrier before the increment"
+
+
+COLLECTIVE = r"__syncthreads|\bblock_\w+\s*\(|\bsums_\w+\s*\(|\blist_rows|_part<"
+
+
+def kernels(text):
+    """(name, parameters, body) of every kernel of a source."""
+    for m in re.finditer(r"__global__\s+void\s+(?:__launch_bounds__\([^)]*\)\s*)?"
+                         r"(k_\w+)\s*\(", text):
+        b = body(text[m.start(1):], m.group(1))
+        yield m.group(1), text[m.end():text.index(b, m.end())], b
+
+
+def test_blocks_that_latch_read_the_latch_once():
+    # kernels that can set the latch (err not const) while other blocks of
+    # theirs start, and that use sums, scans or lists of the whole block
+    seen = []
+    for name in sorted(f for f in os.listdir(CSRC) if f.endswith(".hip")):
+        for k, params, b in kernels(source(name)):
+            if not re.search(r"(?<!const )int\s*\*\s*err\b", params):
+                continue
+            if not re.search(COLLECTIVE, b):
+                continue
+            seen.append(k)
+            assert not re.search(r"if\s*\(\s*\*err\s*\)", b), (name, k)
+            assert re.search(r"latched\(err\)|latch\s*=\s*\*err", b), (name, k)
+    assert {"k_warm_probe", "k_warm_turn", "k_warm_list", "k_expand_probe",
+            "k_expand_commit", "k_obs_final"} <= set(seen)
