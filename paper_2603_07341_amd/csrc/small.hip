@@ -523,7 +523,7 @@ __global__ void __launch_bounds__(kNB) k_small_expand(SmallExpand a) {
           }
           i = (i + 1) & a.mask;
         }
-        if (!done) atomicOr(a.err, kErrTableFull);
+        if (!done) atomicOr(&latch, kErrTableFull);
       }
       a.rb.c_ref[cand] = ref;
     }
@@ -539,7 +539,7 @@ __global__ void __launch_bounds__(kNB) k_small_expand(SmallExpand a) {
       if (!own) continue;
       const int64_t row = found_row(q, ctl, a.wb.freel);
       if (row >= a.cap) {
-        atomicOr(a.err, kErrCapacity);
+        atomicOr(&latch, kErrCapacity);
         continue;
       }
       uint64_t key[W];
@@ -568,12 +568,14 @@ __global__ void __launch_bounds__(kNB) k_small_expand(SmallExpand a) {
       ctl->gstart[r + 1] = num;
       ctl->n_staged = num;
       if (a.row_limit > 0 && int64_t(nM) + num > a.row_limit)
-        atomicOr(a.err, kErrOver);
+        atomicOr(&latch, kErrOver);
     }
     __syncthreads();
-    if (threadIdx.x == 0) latch = latch_now(a.err);
-    __syncthreads();
-    if (latch) return;
+    // (errors gather in LDS: a barrier does not wait for global adds)
+    if (latch) {
+      if (threadIdx.x == 0) *a.err = latch;
+      return;
+    }
   }
   const uint32_t ns = gs[k + 1];
   // state cap: live rows of the new set

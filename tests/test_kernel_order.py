@@ -88,3 +88,12 @@ def test_blocks_that_latch_read_the_latch_once():
             assert re.search(r"latched\(err\)|latch\s*=\s*\*err", b), (name, k)
     assert {"k_warm_probe", "k_warm_turn", "k_warm_list", "k_expand_probe",
             "k_expand_commit", "k_obs_final"} <= set(seen)
+
+
+def test_small_expand_gathers_its_latch_in_lds():
+    # any lane can meet an error, and the block goes on or stops by it: a
+    # global add of another wave need not have landed by the next barrier
+    b = body(source("small.hip"), "k_small_expand")
+    for m in re.finditer(r"atomicOr\(a\.err", b):
+        assert b[:m.start()].rstrip().endswith("if (threadIdx.x == 0)"), b[m.start() - 60:m.end()]
+    assert "latch_now" not in b
