@@ -1416,14 +1416,14 @@ paces_status launch_step_graph(paces_sim* s, int64_t est, bool counted,
 
 // Buffers of the device cut: its state and bins once, the weight keys (which
 // the host-driven cut uses too) for the row capacity.
-paces_status top_buffers(paces_sim* s) {
+paces_status top_buffers(paces_sim* s, hipStream_t st) {
   if (!s->topb.st) {
     uint8_t* q = nullptr;
     ST_TRY(dalloc(&q, 512 + 4 * (kTopBins + kTopTies)));
     s->topb.st = reinterpret_cast<TopState*>(q);
     s->topb.hist = reinterpret_cast<uint32_t*>(q + 512);
     s->topb.ties = s->topb.hist + kTopBins;
-    HIP_TRY(hipMemset(s->topb.hist, 0, 4 * kTopBins));
+    HIP_TRY(hipMemsetAsync(s->topb.hist, 0, 4 * kTopBins, st));
   }
   if (s->top_rows < s->cap) {
     if (s->top_block) dev_free(s->top_block);
@@ -1436,9 +1436,9 @@ paces_status top_buffers(paces_sim* s) {
   return PACES_OK;
 }
 
-paces_status cap_buffers(paces_sim* s) {
+paces_status cap_buffers(paces_sim* s, hipStream_t st) {
   const int R = s->m->R;
-  ST_TRY(top_buffers(s));
+  ST_TRY(top_buffers(s, st));
   s->cap_w = s->topb.w;
   if (s->cap_buf < s->cap) {
     if (s->cap_block) dev_free(s->cap_block);
@@ -1477,7 +1477,7 @@ paces_status top_cut(paces_sim* s, hipStream_t st) {
     s->cut_th2 = q <= 0 ? INFINITY : (all ? -1.0 : s->th2);
     return PACES_OK;
   }
-  ST_TRY(top_buffers(s));
+  ST_TRY(top_buffers(s, st));
   s->cut = paces_sim::kTop;
   top_select(s->prec, s->vec[s->ipsi], s->side[s->cur].dist, s->nS, all,
              s->th2, q, s->topb, st);
@@ -1489,7 +1489,7 @@ paces_status top_cut(paces_sim* s, hipStream_t st) {
 paces_status full_selection(paces_sim* s, hipStream_t st) {
   const paces_model* m = s->m;
   const Side& c = s->side[s->cur];
-  ST_TRY(cap_buffers(s));
+  ST_TRY(cap_buffers(s, st));
   if (s->p.q_nom > 0 || s->fresh) {
     s->nM_full = s->nlive;
     if (s->has_holes)
@@ -1581,7 +1581,7 @@ paces_status cap_select(paces_sim* s, hipStream_t st, bool over) {
   // the ball outgrew the rows: it was not counted, but it is over the cap
   if (over) std::fill(ball.begin(), ball.end(), ~0u);
   if (!s->cap_active) {
-    ST_TRY(cap_buffers(s));
+    ST_TRY(cap_buffers(s, st));
     s->nM_full = s->h_ctl->nM;
     if (s->nM_full > 0 && s->warm_step)
       // an in-place attempt keeps M as the rows at distance 0

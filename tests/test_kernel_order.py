@@ -97,3 +97,9 @@ def test_small_expand_gathers_its_latch_in_lds():
     for m in re.finditer(r"atomicOr\(a\.err", b):
         assert b[:m.start()].rstrip().endswith("if (threadIdx.x == 0)"), b[m.start() - 60:m.end()]
     assert "latch_now" not in b
+
+
+def test_no_clear_runs_on_another_stream():
+    # device memory is cleared on the stream that uses it: the null stream
+    # does not order with the non-blocking streams that callers bring
+    assert not re.search(r"\bhipMemset\s*\(", source("runtime.cpp"))
