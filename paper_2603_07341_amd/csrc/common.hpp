@@ -363,7 +363,7 @@ __device__ __forceinline__ void count_flush(int R, uint32_t* lds,
 }
 
 // J_k(x) by its power series sum_j (-1)^j (x/2)^(2j+k) / (j! (j+k)!); for
-// x <= 2 every term shrinks and no cancellation occurs.  Below 1e-60 the
+// 0 <= x <= 2 every term shrinks and no cancellation occurs.  Below 1e-60 the
 // leading factor (which only shrinks, x / 2 <= 1) is taken as zero: far under
 // every tolerance, and without the up to 128 divisions of the high orders.
 __device__ double bessel_series(double x, int k) {

@@ -833,7 +833,7 @@ __global__ void __launch_bounds__(kBlock)
   double a = 0.5 * (emax - emin);
   const double b = 0.5 * (emax + emin);
   if (!(a > 1e-300)) a = 1e-300;
-  const double x = a * dt;
+  const double x = fabs(a * dt);  // dt < 0: J_k(-x) = (-1)^k J_k(x) below
   const int kcap = k_max < kMaxTerms ? k_max : kMaxTerms;
   // the series needs more than x terms: a spectrum too wide for the step
   // (or not finite) is reported before any Bessel recurrence runs
@@ -880,7 +880,7 @@ __global__ void __launch_bounds__(kBlock)
     cc->phase[1] = -sn;
   }
   for (int k = threadIdx.x; k < K && k < kMaxTerms; k += blockDim.x) {
-    const double v = (k == 0 ? 1.0 : 2.0) * J[k];
+    const double v = (k == 0 ? 1.0 : 2.0) * (dt < 0 && (k & 1) ? -J[k] : J[k]);
     const int q = k & 3;  // (-i)^k
     cc->c[k][0] = (q == 0) ? v : (q == 2 ? -v : 0.0);
     cc->c[k][1] = (q == 1) ? -v : (q == 3 ? v : 0.0);

@@ -213,7 +213,7 @@ __global__ void __launch_bounds__(kNB) k_small_tail(SmallTail a) {
     double wid = 0.5 * (emax - emin);
     const double b = 0.5 * (emax + emin);
     if (!(wid > 1e-300)) wid = 1e-300;
-    const double x = wid * a.dt;
+    const double x = fabs(wid * a.dt);
     const int kcap = a.k_max < kMaxTerms ? a.k_max : kMaxTerms;
     int K = 0;
     if (!(x <= double(kcap))) {
@@ -247,7 +247,8 @@ __global__ void __launch_bounds__(kNB) k_small_tail(SmallTail a) {
         if (threadIdx.x == 0) latch = kErrTerms;
       }
       for (int k = threadIdx.x; k < K && k < kMaxTerms; k += kNB) {
-        const double v = (k == 0 ? 1.0 : 2.0) * J[k];
+        const double v =
+            (k == 0 ? 1.0 : 2.0) * (a.dt < 0 && (k & 1) ? -J[k] : J[k]);
         const int q = k & 3;  // (-i)^k
         coef[k][0] = (q == 0) ? v : (q == 2 ? -v : 0.0);
         coef[k][1] = (q == 1) ? -v : (q == 3 ? v : 0.0);

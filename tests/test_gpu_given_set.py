@@ -64,3 +64,26 @@ def test_columns_of_a_given_set(grown, n):
         with pytest.raises(P.PacesError) as e:
             m.expmv(kd, pd, cfg["dt"])
         assert e.value.status == 1
+
+
+@pytest.mark.parametrize("dt", [-0.01, -0.2, -2.5])
+@pytest.mark.parametrize("n", [2500, 20000])
+def test_backwards_in_time(n, dt):
+    # H is real, so exp(+i H t) phi is the conjugate of exp(-i H t) conj(phi):
+    # the same operations with the imaginary parts negated, hence bit for bit
+    import torch
+    cfg = dict(WL.CONFIGS["ring16"])
+    m = P.Model(WL.model_params(cfg))
+    exc, occ, _ = WL.phonon_ball_state(cfg, 4)
+    rng = np.random.default_rng(n)
+    on = np.sort(rng.permutation(len(exc))[:n])
+    kd = torch.from_numpy(m.pack(exc[on], occ[on]).view(np.int64)).cuda()
+    amps = rng.standard_normal(n) + 1j * rng.standard_normal(n)
+    phi = torch.from_numpy(amps / np.linalg.norm(amps)).cuda()
+    back = m.expmv(kd, phi, dt)
+    ref = m.expmv(kd, phi.conj().resolve_conj(), -dt)
+    assert torch.equal(back, ref.conj().resolve_conj())
+    # and it undoes the step forward (128 u |.|_inf per application)
+    there = m.expmv(kd, back, -dt)
+    bound = 2 * 128 * 2.0 ** -53 * float(phi.abs().max())
+    assert float((there - phi).abs().max()) <= bound * max(1.0, abs(dt) * 40)
