@@ -998,7 +998,6 @@ struct FrozenStep {
   int32_t* tmap;   // [old rows] new row of every old row (may be null)
   int32_t* p0map;  // [n0] rows of the initial states (may be null)
   int64_t n_new;   // rows of the recorded step's set
-  bool quiet;      // no observables: only the state and the maps are wanted
 };
 
 // Partial results a step hands from one stage to the next.
@@ -1254,13 +1253,11 @@ void stage_observe(paces_sim* s, int64_t est, hipStream_t st,
   const bool want_e = (s->p.obs_mask & PACES_OBS_ENERGY) != 0;
   const bool krylov = s->p.krylov_order > 0;
   Stage sg(s, PACES_STAGE_OBSERVE, st);
-  int n_pop = 0;
-  if (!(fz && fz->quiet))
-    n_pop = s->sel_grid = pop_norm(s->prec, m->N, R, s->th2, est, s->ctl,
-                             s->vec[s->ib0], sn.pay, sn.dist,
-                             want_e && R > 1 && !krylov ? s->e_row : nullptr,
-                             s->n2_part, s->en_part, s->pop_part, s->sm,
-                             s->err, st);
+  // (a replayed step writes its record again: the slots are the run's)
+  const int n_pop = s->sel_grid =
+      pop_norm(s->prec, m->N, R, s->th2, est, s->ctl, s->vec[s->ib0], sn.pay,
+               sn.dist, want_e && R > 1 && !krylov ? s->e_row : nullptr,
+               s->n2_part, s->en_part, s->pop_part, s->sm, s->err, st);
   // the Krylov energy goes into the record after it is written, so the step
   // is closed by a launch of its own there, as it is with several
   // realizations
@@ -1830,7 +1827,7 @@ void finish_step(paces_sim* s, const FrozenStep* fz) {
   s->launched = std::max(4, std::min(s->p.taylor_order != 0 ? K + 1 : K,
                                      kMaxTerms));
   s->acc.rows_steps += double(c.n_new);
-  s->counts_valid = !(fz && fz->quiet);
+  s->counts_valid = true;
   s->cap_active = false;
 }
 
@@ -2228,11 +2225,11 @@ paces_status adj_keep_m(paces_sim* s, int64_t nM, hipStream_t st) {
 }
 
 paces_status adj_frozen_step(paces_sim* s, int64_t i, int32_t* tmap,
-                             int32_t* p0map, bool quiet, hipStream_t st) {
+                             int32_t* p0map, hipStream_t st) {
   const AdjRecord& R = *s->adj;
   const AdjStep& a = R.steps[i];
   const FrozenStep fz{R.mkeys + a.moff * s->m->Wi, a.nM, a.k, tmap, p0map,
-                      a.n_new, quiet};
+                      a.n_new};
   ST_TRY(do_step(s, st, &fz));
   if (s->nS != a.n_new)
     return fail(PACES_E_STATE, "replay did not reproduce the recorded set");
@@ -3518,7 +3515,7 @@ paces_status paces_adjoint_replay(paces_sim* s, const paces_model* model,
   s->m = model;
   const int64_t first = s->h.nrec;
   for (int64_t i = 0; i < R.n && !e; ++i)
-    e = adj_frozen_step(s, i, nullptr, nullptr, false, st);
+    e = adj_frozen_step(s, i, nullptr, nullptr, st);
   if (!e) e = adj_read_a(s, first, R.n, a_out + 2, st);
   s->m = own;
   a_out[0] = R.a[0];
@@ -3631,7 +3628,7 @@ paces_status adjoint_backward(paces_sim* s, const double* gbar, double* grad,
     e = restore_snapshot(s, *R.ck[q], st);
     for (int64_t i = start; i < end && !e; ++i) {
       SegSlot& z = slot[i - start];
-      e = adj_frozen_step(s, i, z.tmap, z.p0, true, st);
+      e = adj_frozen_step(s, i, z.tmap, z.p0, st);
       if (e) break;
       const int64_t n1 = s->nS;
       if (hipMemcpyAsync(z.col, s->side[s->cur].col, size_t(n1) * D * 4,

@@ -207,3 +207,24 @@ def test_adjoint_rejects_what_it_does_not_support():
     with pytest.raises(P.PacesError) as ei:
         s.adjoint_forward(3, 2)
     assert ei.value.status == 7
+
+
+def test_records_survive_the_backward_sweep():
+    # the backward sweep replays every step on the sim; its records are
+    # afterwards those of the run: sets, counts, K and the interval exactly,
+    # sums over the replay's row order within 4 n u of their terms' sum (at
+    # most 1, or the spectrum's width for the energy)
+    cfg, p, run, init, gm, gs, a, steps, ckpt = setup("ring12")
+    before, last = gs.series().copy(), gs.observe()
+    assert before[:, 7].max() > 3072  # more rows than one block propagates
+    gs.adjoint_backward(a - target(a))
+    after = gs.series()
+    exact = [0, 7, 8, 9, 10, 11]  # t, n_S, n_M, K, E_min, E_max
+    assert np.array_equal(after[:, exact], before[:, exact])
+    tol = 4 * before[:, 7].max() * 2.0 ** -53
+    width = before[:, 11] - before[:, 10]
+    assert np.all(np.abs(after[:, 2] - before[:, 2]) <= tol * width)
+    rest = [1, 3, 4, 5, 6] + list(range(12, before.shape[1]))
+    assert np.all(np.abs(after[:, rest] - before[:, rest]) <= tol)
+    now = gs.observe()
+    assert now["n_S"] == last["n_S"] and abs(now["norm2"] - last["norm2"]) <= tol
