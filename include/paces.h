@@ -276,8 +276,9 @@ paces_status paces_run_stage(paces_sim* s, int32_t stage, void* hip_stream);
  * Models with one realization only (else PACES_E_UNSUPPORTED).  A key out
  * of range or repeated is found on the device and returns PACES_E_ARG.
  * Work memory (about 60-120 bytes per row) comes from the library's
- * allocator for the call.  Runs on hip_stream and synchronises it before
- * returning. */
+ * allocator for the call; with hipMalloc the model's tables stay on the
+ * device for later calls, until paces_free_model.  Runs on hip_stream and
+ * synchronises it before returning. */
 paces_status paces_expmv(const paces_model* m, int64_t n, const void* dev_keys,
                          const void* dev_phi, double dt, void* dev_psi,
                          void* hip_stream);

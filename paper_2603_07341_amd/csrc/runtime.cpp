@@ -326,6 +326,14 @@ struct paces_model {
   double* d_eps = nullptr;
   int tab_dev = -1;  // device that holds the tables
   DevModel dm{};
+  // tables that paces_expmv keeps for its later calls, one set per device
+  // (the sims' tables above are made by the first sim, on its device)
+  struct GivenTables {
+    int dev;
+    int32_t* nbr;
+    double *gsq, *eps;
+  };
+  mutable std::vector<GivenTables> given;
 };
 
 namespace {
@@ -2344,8 +2352,31 @@ paces_status log_step(paces_sim* s, const char* where, hipStream_t st) {
   return PACES_OK;
 }
 
-// Device copies of the model tables, made on first use so that loading a
-// model and the host codec need no GPU; by one thread.
+// Copies of the model tables on the current device.
+paces_status upload_tables(const paces_model* m, int32_t** nbr, double** gsq,
+                           double** eps) {
+  *nbr = nullptr;
+  *gsq = *eps = nullptr;
+  paces_status e = dalloc(nbr, int64_t(m->nbr.size()));
+  if (!e) e = dalloc(gsq, int64_t(m->gsq.size()));
+  if (!e) e = dalloc(eps, int64_t(m->R) * m->N);
+  if (!e && (hipMemcpy(*nbr, m->nbr.data(), m->nbr.size() * 4,
+                       hipMemcpyHostToDevice) != hipSuccess ||
+             hipMemcpy(*gsq, m->gsq.data(), m->gsq.size() * 8,
+                       hipMemcpyHostToDevice) != hipSuccess ||
+             hipMemcpy(*eps, m->eps.data(), m->eps.size() * 8,
+                       hipMemcpyHostToDevice) != hipSuccess))
+    e = fail(PACES_E_HIP, "upload of the model tables failed");
+  if (e) {
+    dfree(*nbr);
+    dfree(*gsq);
+    dfree(*eps);
+  }
+  return e;
+}
+
+// The sims' tables, made on first use so that loading a model and the host
+// codec need no GPU; by one thread.
 std::mutex g_tables_mu;
 paces_status ensure_device_tables(paces_model* m) {
   std::lock_guard<std::mutex> lk(g_tables_mu);
@@ -2354,22 +2385,7 @@ paces_status ensure_device_tables(paces_model* m) {
   HIP_TRY(hipGetDevice(&dev));
   int32_t* nbr = nullptr;
   double *gsq = nullptr, *eps = nullptr;
-  paces_status e = dalloc(&nbr, int64_t(m->nbr.size()));
-  if (!e) e = dalloc(&gsq, int64_t(m->gsq.size()));
-  if (!e) e = dalloc(&eps, int64_t(m->R) * m->N);
-  if (!e && (hipMemcpy(nbr, m->nbr.data(), m->nbr.size() * 4,
-                       hipMemcpyHostToDevice) != hipSuccess ||
-             hipMemcpy(gsq, m->gsq.data(), m->gsq.size() * 8,
-                       hipMemcpyHostToDevice) != hipSuccess ||
-             hipMemcpy(eps, m->eps.data(), m->eps.size() * 8,
-                       hipMemcpyHostToDevice) != hipSuccess))
-    e = fail(PACES_E_HIP, "upload of the model tables failed");
-  if (e) {
-    dfree(nbr);
-    dfree(gsq);
-    dfree(eps);
-    return e;
-  }
+  ST_TRY(upload_tables(m, &nbr, &gsq, &eps));
   m->dm.gsq = m->d_gsq = gsq;
   m->dm.eps = m->d_eps = eps;
   m->dm.nbr = nbr;
@@ -2377,19 +2393,39 @@ paces_status ensure_device_tables(paces_model* m) {
   m->d_nbr = nbr;
   return PACES_OK;
 }
-// Whether the current device holds the model's tables.
-bool tables_here(const paces_model* m) {
+
+// The model for a propagation on a given set, with tables that the current
+// device holds (the sims' or those kept here; with may_keep they are made, but
+// not from a caller's allocator, whose blocks are for the call).  False: the
+// device holds none.
+bool given_model(const paces_model* m, bool may_keep, DevModel* dm) {
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return false;
+  const bool known = hipGetDevice(&dev) == hipSuccess;
   std::lock_guard<std::mutex> lk(g_tables_mu);
-  return m->d_nbr && m->tab_dev == dev;
+  *dm = m->dm;
+  if (!known) return false;
+  if (m->d_nbr && m->tab_dev == dev) return true;
+  paces_model::GivenTables t{dev, nullptr, nullptr, nullptr};
+  for (const auto& g : m->given)
+    if (g.dev == dev) t = g;
+  if (!t.nbr) {
+    if (!may_keep || g_allocator.alloc ||
+        upload_tables(m, &t.nbr, &t.gsq, &t.eps))
+      return false;
+    m->given.push_back(t);
+  }
+  dm->nbr = t.nbr;
+  dm->gsq = t.gsq;
+  dm->eps = t.eps;
+  return true;
 }
 
 // ---- exp(-i H_S dt) phi on a given set (paces_expmv) ------------------------
-// Work memory for n rows: model tables (used where the device does not hold
-// the model's own), step control, latch, Chebyshev coefficients, Gershgorin partials, internal keys (when the canonical
-// width needs padding), payload and totals, ELL columns, the second
-// Clenshaw vector and the hash table (at least twice the rows).
+// Work memory for n rows: model tables (used where the device holds none of
+// the model), step control, latch, Chebyshev coefficients, Gershgorin
+// partials, internal keys (when the canonical width needs padding), payload
+// and totals, ELL columns, the second Clenshaw vector and the hash table (at
+// least twice the rows).
 struct ExpmvLayout {
   size_t nbr = 0, gsq = 0, eps = 0, ctl = 0, err = 0, cc = 0, part = 0;
   size_t keys = 0, pay = 0, tot = 0, col = 0, b1 = 0, table = 0, total = 0;
@@ -2436,13 +2472,13 @@ paces_status expmv_latch(int e) {
 // The propagation of a step on a set given as n canonical keys, with the
 // work memory `work` laid out by expmv_layout.  Synchronises.
 // page (host may be null): pinned memory for the counts the host reads.
+// may_keep: the model's tables may be kept on the device for later calls.
 paces_status expmv_run(const paces_model* m, int64_t n, const uint64_t* keys,
                        const void* phi, double dt, void* psi, uint8_t* work,
-                       const Page& page, hipStream_t st) {
+                       const Page& page, bool may_keep, hipStream_t st) {
   const ExpmvLayout L = expmv_layout(m, n);
-  const bool here = tables_here(m);  // before the copy of their addresses
-  DevModel dm = m->dm;
-  if (!here) {
+  DevModel dm;
+  if (!given_model(m, may_keep, &dm)) {
     dm.nbr = reinterpret_cast<const int32_t*>(work + L.nbr);
     dm.gsq = reinterpret_cast<const double*>(work + L.gsq);
     dm.eps = reinterpret_cast<const double*>(work + L.eps);
@@ -2743,14 +2779,13 @@ paces_status paces_expmv(const paces_model* m, int64_t n, const void* dev_keys,
   ST_TRY(expmv_args(m, n, dev_keys, dev_phi, dt, dev_psi));
   if (n == 0) return PACES_OK;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  ST_TRY(ensure_device_tables(const_cast<paces_model*>(m)));
   void* work = nullptr;
   ST_TRY(dev_alloc(&work, expmv_layout(m, n).total));
   Page page;
   paces_status e = page_get(&page, true);
   if (!e)
     e = expmv_run(m, n, static_cast<const uint64_t*>(dev_keys), dev_phi, dt,
-                  dev_psi, static_cast<uint8_t*>(work), page, st);
+                  dev_psi, static_cast<uint8_t*>(work), page, true, st);
   (void)hipStreamSynchronize(st);
   page_put(page);
   dev_free(work);
@@ -2775,7 +2810,7 @@ paces_status paces_expmv_static(const paces_model* m, int64_t n,
   ST_TRY(page_get(&page, false));
   const paces_status e =
       expmv_run(m, n, static_cast<const uint64_t*>(dev_keys), dev_phi, dt,
-                dev_psi, static_cast<uint8_t*>(work), page, st);
+                dev_psi, static_cast<uint8_t*>(work), page, false, st);
   if (e) (void)hipStreamSynchronize(st);
   page_put(page);
   return e;
@@ -2786,6 +2821,11 @@ paces_status paces_free_model(paces_model* m) {
   dfree(m->d_nbr);
   dfree(m->d_gsq);
   dfree(m->d_eps);
+  for (auto& g : m->given) {
+    dfree(g.nbr);
+    dfree(g.gsq);
+    dfree(g.eps);
+  }
   delete m;
   return PACES_OK;
 }

@@ -127,3 +127,29 @@ def test_capacity_beyond_the_device_is_cut_to_fit():
     ref.close()
     assert np.array_equal(kb, kr)
     assert np.array_equal(ab, ar)
+
+
+def small_expmv():
+    cfg = WL.CONFIGS["ring4"]
+    m = P.Model(WL.model_params(cfg))
+    exc, occ, coef = WL.phonon_ball_state(cfg, 3)
+    kd = torch.from_numpy(m.pack(exc, occ).view(np.int64)).cuda()
+    pd = torch.from_numpy(coef.view(np.complex128).copy()).cuda()
+    return m, kd, pd, torch.empty_like(pd)
+
+
+def test_expmv_keeps_no_block_of_a_registered_allocator():
+    # its work memory is for the call
+    m, kd, pd, out = small_expmv()
+    gc.collect()
+    torch.cuda.synchronize()
+    before = torch.cuda.memory_allocated()
+    P.use_torch_allocator(True)
+    try:
+        m.expmv(kd, pd, 0.01, out=out)
+        torch.cuda.synchronize()
+        assert torch.cuda.memory_allocated() == before
+    finally:
+        P.use_torch_allocator(False)
+    ref = m.expmv(kd, pd, 0.01)
+    assert torch.equal(out, ref)
