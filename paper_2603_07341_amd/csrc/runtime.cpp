@@ -2504,6 +2504,12 @@ paces_status expmv_run(const paces_model* m, int64_t n, const uint64_t* keys,
   sd.tot = reinterpret_cast<uint64_t*>(work + L.tot);
   int32_t* col = reinterpret_cast<int32_t*>(work + L.col);
   const uint64_t mask = L.P - 1;
+  // the host reads two words that a kernel writes to pinned memory, or copies
+  // where there is none; words that nothing wrote show a launch that failed
+  // (the thread's last HIP error may be of another call of the program's)
+  constexpr uint32_t kUnsaid = ~0u;
+  uint32_t said[2] = {0, kUnsaid};
+  if (page.host) std::memcpy(page.host, said, sizeof(said));
   build_set(dm, m->Wi, sd, n, ctl, table, mask, col, err, st);
   // one block takes a small set from here to psi
   SmallTail one{};
@@ -2524,23 +2530,20 @@ paces_status expmv_run(const paces_model* m, int64_t n, const uint64_t* keys,
   if (!small)
     bounds_and_coef(dm, sd, col, n, n, ctl, dt, 1e-16, kMaxTerms, kMaxTerms,
                     part, cc, err, st);
-  // the number of terms and the latch, in two words that the kernel writes
-  // to pinned memory, or copies where there is none
-  uint32_t said[2] = {0, 0};
+  // the number of terms and the latch
   if (!small) report(ctl, err, one.said, st);
-  HIP_TRY(hipGetLastError());
   if (!page.host)
     HIP_TRY(hipMemcpyAsync(said, one.said, sizeof(said), hipMemcpyDeviceToHost,
                            st));
   HIP_TRY(hipStreamSynchronize(st));
   if (page.host) std::memcpy(said, page.host, sizeof(said));
+  if (said[1] == kUnsaid) return fail(PACES_E_HIP, "kernel launch failed");
   ST_TRY(expmv_latch(int(said[1])));
   if (small) return PACES_OK;
   // launch indices K - 2 .. 0; nothing latches any more
   for (int kk = std::max(2, int(said[0])) - 2; kk >= 0; --kk)
     cheb_term(dm, 64, kk, false, false, n, ctl, col, n, sd, cc, phi, psi,
               work + L.b1, nullptr, nullptr, err, nullptr, nullptr, st);
-  HIP_TRY(hipGetLastError());
   HIP_TRY(hipStreamSynchronize(st));
   return PACES_OK;
 }

@@ -153,3 +153,27 @@ def test_expmv_keeps_no_block_of_a_registered_allocator():
         P.use_torch_allocator(False)
     ref = m.expmv(kd, pd, 0.01)
     assert torch.equal(out, ref)
+
+
+def test_expmv_beside_an_error_of_the_callers():
+    # a HIP call of the program's own that failed before is not this call's
+    import ctypes
+    path = next(ln.split()[-1] for ln in open("/proc/self/maps")
+                if "libamdhip64" in ln)
+    hip = ctypes.CDLL(path)
+    m, kd, pd, out = small_expmv()
+    ref = m.expmv(kd, pd, 0.01).cpu()
+    big = WL.phonon_ball_state(WL.CONFIGS["ring16"], 3)
+    mb = P.Model(WL.model_params(WL.CONFIGS["ring16"]))
+    kb = torch.from_numpy(mb.pack(big[0], big[1]).view(np.int64)).cuda()
+    pb = torch.from_numpy(big[2].view(np.complex128).copy()).cuda()
+    ob = torch.empty_like(pb)
+    torch.cuda.synchronize()
+    try:
+        assert hip.hipSetDevice(4096) != 0  # refused by the runtime
+        m.expmv(kd, pd, 0.01, out=out)
+        mb.expmv(kb, pb, 0.01, out=ob)
+        m.expmv_static(kd, pd, 0.01, out=out)
+    finally:
+        hip.hipGetLastError()
+    assert torch.equal(out.cpu(), ref)
