@@ -1034,6 +1034,9 @@ void stage_select(paces_sim* s, bool counted, hipStream_t st,
     return;
   }
   const Side& c = s->side[s->cur];
+  // a cut's bits take the place of the threshold's: the next attempt, or the
+  // next step if this one is given up, selects anew
+  if (s->cap_active) s->counts_valid = false;
   if (s->cap_active && s->cut == paces_sim::kFlags)
     s->sel_grid = flag_bits(s->keep, s->ctl, s->sm, n_old, st);
   else if (s->cap_active && s->cut == paces_sim::kTop)
@@ -1504,6 +1507,7 @@ paces_status full_selection(paces_sim* s, hipStream_t st) {
       iota_u32(s->midx_full, s->nS, st);
     return PACES_OK;
   }
+  s->counts_valid = false;
   const int g = select_bits(s->prec, s->vec[s->ipsi], c.dist, s->th2, s->ctl,
                             s->sm, s->nS, st);
   clear_latch(s->ctl, s->err, st);

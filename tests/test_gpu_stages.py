@@ -181,3 +181,30 @@ def test_expmv_refuses_bad_sets():
         gm.expmv(kd, pd, 0.01, out=pd)
     e = torch.zeros(0, dtype=torch.complex128, device="cuda")
     gm.expmv(torch.zeros((0, gm.W), dtype=torch.int64, device="cuda"), e, 0.01)
+
+
+def test_abandoned_capped_step_leaves_the_threshold_selection():
+    """A staged step whose expansion cut its selection under the state cap is
+    abandoned; the next step, with a model that couples nothing (its set is
+    the selection itself), takes every row above the threshold again, as the same run without the staged step."""
+    cfg = dict(WL.CONFIGS["ring16"], k=1, k_init=1, max_states=5000)
+    p, run, init = WL.model_params(cfg), WL.run_params(cfg), WL.initial_state(cfg)
+    still = dict(p, J=[0.0, 0.0, 0.0], g=[0.0, 0.0, 0.0, 0.0])
+    sims = []
+    for staged in (False, True):
+        s = P.Sim(P.Model(p), run, *init)
+        s.set_tuning(warm=0)
+        s.step(40)
+        above = int((np.abs(s.state()[1]) >= cfg["theta"]).sum())
+        if staged:
+            s.run_stage("select")
+            s.run_stage("expand")
+        s.set_model(P.Model(still))
+        s.step(1)
+        sims.append(s)
+    a, b = sims
+    ra, rb = a.series(), b.series()
+    assert ra[39, 8] < above  # the cap cuts the full coupling's step
+    assert ra[40, 8] == above
+    assert np.array_equal(ra[40, 7:12], rb[40, 7:12])
+    assert np.array_equal(sort_rows(*a.state())[0], sort_rows(*b.state())[0])
