@@ -1103,6 +1103,7 @@ void stage_expand(paces_sim* s, int64_t est, hipStream_t st,
   const int k = step_order(s, fz);
   const Side so = s->side[s->cur], sn = s->side[1 - s->cur];
   Stage sg(s, PACES_STAGE_EXPAND, st);
+  s->graph_ok = false;  // the table is the set's no more, until the step ends
   fill_u64(s->table, int64_t(s->tmask + 1), kEmpty, st);
   if (fz) {
     if (fz->nM > 0)

@@ -208,3 +208,24 @@ def test_abandoned_capped_step_leaves_the_threshold_selection():
     assert ra[40, 8] == above
     assert np.array_equal(ra[40, 7:12], rb[40, 7:12])
     assert np.array_equal(sort_rows(*a.state())[0], sort_rows(*b.state())[0])
+
+
+def test_abandoned_step_from_scratch_leaves_no_graph_behind():
+    """A staged step from scratch that is abandoned after its expansion has
+    rebuilt the hash table for a set that is not the sim's: the next step
+    must not search it in place."""
+    cfg = dict(WL.CONFIGS["ring16"], k=2, k_init=2)
+    p, run, init = WL.model_params(cfg), WL.run_params(cfg), WL.initial_state(cfg)
+    a, b = (P.Sim(P.Model(p), run, *init) for _ in range(2))
+    for s in (a, b):
+        s.set_tuning(warm=0)
+        s.step(20)
+    b.run_stage("select")
+    b.run_stage("expand")
+    for s in (a, b):
+        s.set_tuning(warm=2)
+        s.step(3)
+    ka, va = sort_rows(*a.state())
+    kb, vb = sort_rows(*b.state())
+    assert np.array_equal(ka, kb) and np.array_equal(va, vb)
+    assert np.array_equal(a.series()[:, 7:10], b.series()[:, 7:10])
