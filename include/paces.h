@@ -183,14 +183,18 @@ int32_t paces_record_doubles(const paces_model* m);
  * passed as NULL (the library synchronises its stream before it frees).
  * Both NULL restores hipMalloc / hipFree; of blocks from those the library
  * keeps up to 4 GiB per GPU after they are freed, for its later allocations,
- * and returns them to the device when an allocation fails.  Applies to later allocations;
- * every block goes back to the allocator that made it, so the functions
- * must stay valid while blocks they made are alive. */
+ * and returns them to the device when one of its allocations fails, when an
+ * allocator is registered and by paces_trim_memory.  Applies to later
+ * allocations; every block goes back to the allocator that made it, so the
+ * functions must stay valid while blocks they made are alive. */
 paces_status paces_set_allocator(void* (*alloc)(size_t bytes, void* stream,
                                                 void* user),
                                  void (*release)(void* ptr, void* stream,
                                                  void* user),
                                  void* user);
+/* Return the freed blocks and pinned pages that the library keeps to the
+ * device (all GPUs), for programs whose own allocations need that memory. */
+paces_status paces_trim_memory(void);
 
 /* Load a model: validates the description and builds the neighbour table,
  * the key layout and the g*sqrt(n) table on the host.  The tables are copied

@@ -41,6 +41,7 @@ EXPORTS = [
     "paces_model_key_words", "paces_series_field", "paces_set_model",
     "paces_run_stage", "paces_adjoint_forward_dev", "paces_adjoint_backward_dev",
     "paces_profile_mark", "paces_expmv", "paces_expmv_static",
+    "paces_trim_memory",
 ]
 
 
@@ -132,6 +133,12 @@ def use_torch_allocator(on=True):
     refs = (_ALLOC_FN(_alloc), _FREE_FN(_free))
     _check(lib().paces_set_allocator(refs[0], refs[1], None))
     _allocator_refs.append(refs)
+
+
+def trim_memory():
+    """Return the device memory that the library keeps of freed sims and calls
+    (up to 4 GiB per GPU) to the device."""
+    _check(lib().paces_trim_memory())
 
 
 def _check(rc):

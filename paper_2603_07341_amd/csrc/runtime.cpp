@@ -127,7 +127,8 @@ void dfree(T*& p) {
 // Blocks from hipMalloc that are freed stay with the library for later
 // allocations of at least four fifths of their size, up to kKeepBytes per
 // GPU (older ones go back to the device first, and all of them when an
-// allocation fails).  A program that makes one sim per trajectory, or calls
+// allocation fails, when the caller registers an allocator and by
+// paces_trim_memory).  A program that makes one sim per trajectory, or calls
 // paces_expmv or the adjoint in a loop, otherwise spends most of a small call
 // in hipMalloc and hipFree, whose times also vary several fold on one machine
 // (a 100-step adjoint pass 124 or 169 ms with the same 92 ms of kernels).
@@ -155,26 +156,36 @@ std::mutex g_blocks_mu;
 std::unordered_map<void*, DevBlock> g_blocks;  // blocks in use
 std::vector<KeptBlock> g_kept;                 // oldest first
 
-// Bytes kept on a device; the caller holds g_blocks_mu.
-size_t kept_bytes(int dev) {
-  size_t t = 0;
+// Kept blocks of a device (dev < 0: of every device) to be given back, oldest
+// first, until at most `most` bytes are left there; the caller holds
+// g_blocks_mu, and frees them without it (hipFree waits for the device, which
+// threads on other devices need not).
+std::vector<void*> take_kept(int dev, size_t most) {
+  size_t left = 0;
   for (auto& k : g_kept)
-    if (k.dev == dev) t += k.bytes;
-  return t;
-}
-// Give kept blocks of a device back, oldest first, until at most `most`
-// bytes are left; the caller holds g_blocks_mu.
-void trim_kept(int dev, size_t most) {
-  size_t left = kept_bytes(dev);
+    if (dev < 0 || k.dev == dev) left += k.bytes;
+  std::vector<void*> out;
   for (size_t i = 0; i < g_kept.size() && left > most;) {
-    if (g_kept[i].dev != dev) {
+    if (dev >= 0 && g_kept[i].dev != dev) {
       ++i;
       continue;
     }
     left -= g_kept[i].bytes;
-    (void)hipFree(g_kept[i].p);
+    out.push_back(g_kept[i].p);
     g_kept.erase(g_kept.begin() + i);
   }
+  return out;
+}
+// Give every kept block of a device (dev < 0: of all) back; whether there
+// was one.
+bool release_kept(int dev) {
+  std::vector<void*> out;
+  {
+    std::lock_guard<std::mutex> lk(g_blocks_mu);
+    out = take_kept(dev, 0);
+  }
+  for (void* q : out) (void)hipFree(q);
+  return !out.empty();
 }
 
 paces_status dev_alloc(void** p, size_t bytes) {
@@ -192,31 +203,34 @@ paces_status dev_alloc(void** p, size_t bytes) {
   HIP_TRY(hipGetDevice(&b.dev));
   const size_t unit = bytes < (size_t(1) << 20) ? size_t(4) << 10 : size_t(2) << 20;
   b.bytes = (std::max<size_t>(bytes, 1) + unit - 1) / unit * unit;
-  std::lock_guard<std::mutex> lk(g_blocks_mu);
-  size_t best = g_kept.size();
-  for (size_t i = 0; i < g_kept.size(); ++i)
-    if (g_kept[i].dev == b.dev && g_kept[i].bytes >= b.bytes &&
-        g_kept[i].bytes - g_kept[i].bytes / 5 <= b.bytes &&
-        (best == g_kept.size() || g_kept[i].bytes < g_kept[best].bytes))
-      best = i;
-  if (best < g_kept.size()) {
-    *p = g_kept[best].p;
-    b.bytes = g_kept[best].bytes;
-    g_kept.erase(g_kept.begin() + best);
-  } else {
-    hipError_t e = hipMalloc(p, b.bytes);
-    if (e != hipSuccess && kept_bytes(b.dev) > 0) {
-      (void)hipGetLastError();
-      trim_kept(b.dev, 0);
-      e = hipMalloc(p, b.bytes);
-    }
-    if (e != hipSuccess) {
-      (void)hipGetLastError();
-      *p = nullptr;
-      return fail(PACES_E_OOM, std::string("hipMalloc failed: ") +
-                                   hipGetErrorString(e));
+  {
+    std::lock_guard<std::mutex> lk(g_blocks_mu);
+    size_t best = g_kept.size();
+    for (size_t i = 0; i < g_kept.size(); ++i)
+      if (g_kept[i].dev == b.dev && g_kept[i].bytes >= b.bytes &&
+          g_kept[i].bytes - g_kept[i].bytes / 5 <= b.bytes &&
+          (best == g_kept.size() || g_kept[i].bytes < g_kept[best].bytes))
+        best = i;
+    if (best < g_kept.size()) {
+      *p = g_kept[best].p;
+      b.bytes = g_kept[best].bytes;
+      g_kept.erase(g_kept.begin() + best);
+      g_blocks[*p] = b;
+      return PACES_OK;
     }
   }
+  hipError_t e = hipMalloc(p, b.bytes);
+  if (e != hipSuccess && release_kept(b.dev)) {
+    (void)hipGetLastError();
+    e = hipMalloc(p, b.bytes);
+  }
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    *p = nullptr;
+    return fail(PACES_E_OOM, std::string("hipMalloc failed: ") +
+                                 hipGetErrorString(e));
+  }
+  std::lock_guard<std::mutex> lk(g_blocks_mu);
   g_blocks[*p] = b;
   return PACES_OK;
 }
@@ -240,15 +254,15 @@ void dev_free(void* p) {
   // nothing that still uses the block may run when it is handed out again; a
   // device that cannot be waited for (a failed one) gets it back as it is
   const bool idle = hipDeviceSynchronize() == hipSuccess;
-  {
+  std::vector<void*> back;
+  if (idle && b.bytes <= kKeepBytes) {
     std::lock_guard<std::mutex> lk(g_blocks_mu);
-    if (idle && b.bytes <= kKeepBytes) {
-      trim_kept(b.dev, kKeepBytes - b.bytes);
-      g_kept.push_back({p, b.bytes, b.dev});
-    } else {
-      (void)hipFree(p);
-    }
+    back = take_kept(b.dev, kKeepBytes - b.bytes);
+    g_kept.push_back({p, b.bytes, b.dev});
+  } else {
+    back.push_back(p);
   }
+  for (void* q : back) (void)hipFree(q);
   if (cur != b.dev) (void)hipSetDevice(cur);
 }
 
@@ -787,7 +801,8 @@ bool fits_device(const paces_sim* s, int64_t cap) {
     int dev = 0;
     (void)hipGetDevice(&dev);
     std::lock_guard<std::mutex> lk(g_blocks_mu);
-    fr += kept_bytes(dev);
+    for (auto& k : g_kept)
+      if (k.dev == dev) fr += k.bytes;
   }
   const double back = double(s->rows_bytes) + double(s->cand_bytes) +
                       double(s->capb_bytes) + 8.0 * double(s->top_rows) +
@@ -3404,6 +3419,18 @@ paces_status paces_set_allocator(void* (*alloc)(size_t, void*, void*),
   g_allocator.alloc = alloc;
   g_allocator.release = release;
   g_allocator.user = user;
+  if (alloc) (void)release_kept(-1);  // the memory is the allocator's now
+  return PACES_OK;
+}
+
+paces_status paces_trim_memory(void) {
+  (void)release_kept(-1);
+  std::vector<Page> out;
+  {
+    std::lock_guard<std::mutex> lk(g_pages_mu);
+    out.swap(g_pages);
+  }
+  for (auto& q : out) (void)hipHostFree(q.host);
   return PACES_OK;
 }
 

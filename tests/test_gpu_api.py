@@ -177,3 +177,24 @@ def test_expmv_beside_an_error_of_the_callers():
     finally:
         hip.hipGetLastError()
     assert torch.equal(out.cpu(), ref)
+
+
+@pytest.mark.parametrize("how", ["trim", "allocator"])
+def test_kept_memory_is_given_back(how):
+    # a freed sim's blocks stay with the library for its next one, and go
+    # back to the device where the program asks for the memory
+    P.trim_memory()
+    gc.collect()
+    torch.cuda.synchronize()
+    free0 = torch.cuda.mem_get_info()[0]
+    _, s, _, _ = run_ring(12)
+    s.close()
+    kept = free0 - torch.cuda.mem_get_info()[0]
+    assert kept > (8 << 20)
+    if how == "trim":
+        P.trim_memory()
+    else:
+        P.use_torch_allocator(True)
+        P.use_torch_allocator(False)
+    assert free0 - torch.cuda.mem_get_info()[0] < kept // 4
+    _, s, _, _ = run_ring(12)  # and the library allocates anew
