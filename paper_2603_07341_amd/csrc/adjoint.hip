@@ -69,16 +69,16 @@ __global__ void __launch_bounds__(kBlock)
     if (threadIdx.x == 0) atomicOr(err, kErrTerms);
     return;
   }
+  const double thresh = ldexp(tol, -2);
   if (x <= 2.0) {
     for (int k = threadIdx.x; k <= kcap; k += blockDim.x)
-      J[k] = bessel_series(x, k);
+      J[k] = bessel_series(x, k, thresh);
   } else if (threadIdx.x == 0) {
     bessel_miller(x, kcap, J);
   }
   __syncthreads();
   // the step's own rule (omitted tail within tol): a node's x is at most
   // the step's, so its term count is too
-  const double thresh = ldexp(tol, -2);
   double last = 0;
   for (int k = threadIdx.x; k <= kcap; k += blockDim.x)
     if (fabs(J[k]) > thresh) last = fmax(last, double(k));

@@ -363,16 +363,19 @@ __device__ __forceinline__ void count_flush(int R, uint32_t* lds,
 }
 
 // J_k(x) by its power series sum_j (-1)^j (x/2)^(2j+k) / (j! (j+k)!); for
-// 0 <= x <= 2 every term shrinks and no cancellation occurs.  Below 1e-60 the
-// leading factor (which only shrinks, x / 2 <= 1) is taken as zero: far under
-// every tolerance, and without the up to 128 divisions of the high orders.
-__device__ double bessel_series(double x, int k) {
+// 0 <= x <= 2 every term shrinks and no cancellation occurs.  Where the leading
+// factor (which bounds |J_k| and only shrinks, x / 2 <= 1) falls below 1e-60
+// and below a quarter of thresh, the size from which the caller counts orders,
+// it is taken as zero: without the up to 128 divisions of the high orders.
+__device__ double bessel_series(double x, int k, double thresh) {
+  const double tiny = fmin(1e-60, 0.25 * thresh);
   const double h = 0.5 * x, h2 = h * h;
   double lead = 1.0;
   for (int q = 1; q <= k; ++q) {
     lead *= h / q;
-    if (lead < 1e-60) return 0.0;
+    if (lead < tiny) return 0.0;
   }
+  if (lead == 0.0) return 0.0;
   double term = lead, sum = lead;
   for (int j = 1; j < 60; ++j) {
     term *= -h2 / (double(j) * double(j + k));

@@ -841,9 +841,10 @@ __global__ void __launch_bounds__(kBlock)
     if (threadIdx.x == 0) atomicOr(err, isfinite(x) ? kErrTerms : kErrNonFinite);
     return;
   }
+  const double thresh = ldexp(tol, -2);
   if (x <= 2.0) {
     for (int k = threadIdx.x; k <= kcap; k += blockDim.x)
-      J[k] = bessel_series(x, k);
+      J[k] = bessel_series(x, k, thresh);
   } else if (threadIdx.x == 0) {
     bessel_miller(x, kcap, J);
   }
@@ -852,7 +853,6 @@ __global__ void __launch_bounds__(kBlock)
   // below half the one before (J_{k+1} / J_k < x / (2k + 2) before the
   // first zero of J_k), so the omitted tail sum_{k>=K} |c_k| =
   // 2 sum |J_k| <= 4 |J_K| stays within tol (|T_k| <= 1 on the interval)
-  const double thresh = ldexp(tol, -2);
   double last = 0;
   for (int k = threadIdx.x; k <= kcap; k += blockDim.x)
     if (fabs(J[k]) > thresh) last = fmax(last, double(k));

@@ -243,14 +243,14 @@ __global__ void __launch_bounds__(64)
     if (l == 0) atomicOr(err, isfinite(x) ? kErrTerms : kErrNonFinite);
     return;
   }
+  const double thresh = ldexp(tol, -2);
   if (x <= 2.0) {
-    for (int k = l; k <= kcap; k += 64) J[k] = bessel_series(x, k);
+    for (int k = l; k <= kcap; k += 64) J[k] = bessel_series(x, k, thresh);
   } else if (l == 0) {
     bessel_miller(x, kcap, J);
   }
   __syncthreads();
   // the Clenshaw step's rule: terms up to the last |J_k| above tol / 4
-  const double thresh = ldexp(tol, -2);
   double last = 0;
   for (int k = l; k <= kcap; k += 64)
     if (fabs(J[k]) > thresh) last = fmax(last, double(k));

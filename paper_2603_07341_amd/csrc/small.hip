@@ -220,8 +220,10 @@ __global__ void __launch_bounds__(kNB) k_small_tail(SmallTail a) {
       if (threadIdx.x == 0) latch = isfinite(x) ? kErrTerms : kErrNonFinite;
       __syncthreads();
     } else {
+      const double thresh = ldexp(a.tol, -2);
       if (x <= 2.0) {
-        for (int k = threadIdx.x; k <= kcap; k += kNB) J[k] = bessel_series(x, k);
+        for (int k = threadIdx.x; k <= kcap; k += kNB)
+          J[k] = bessel_series(x, k, thresh);
       } else if (threadIdx.x == 0) {
         bessel_miller(x, kcap, J);
       }
@@ -232,7 +234,6 @@ __global__ void __launch_bounds__(kNB) k_small_tail(SmallTail a) {
         phase[1] = -sn;
       }
       __syncthreads();
-      const double thresh = ldexp(a.tol, -2);
       double last = 0;
       for (int k = threadIdx.x; k <= kcap; k += kNB)
         if (fabs(J[k]) > thresh) last = fmax(last, double(k));

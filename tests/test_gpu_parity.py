@@ -216,3 +216,26 @@ def test_non_finite_inputs_and_overflow_latch():
         s.step(1)
     assert ei.value.status == 7
     s.set_state(keys, amps, 0.0)  # clears the latch
+
+
+@pytest.mark.parametrize("tol", [1e-16, 1e-59, 1e-70, 1e-120])
+@pytest.mark.parametrize("name", ["ring4", "ring16"])
+def test_term_count_follows_the_tolerance(name, tol):
+    # K = 1 + the last k with |J_k(x)| > tol / 4, x the half width times dt
+    # (power series; no |J_k| of these x lies within rounding of tol / 4)
+    import math
+    cfg = dict(WL.CONFIGS[name])
+    s = P.Sim(P.Model(WL.model_params(cfg)), WL.run_params(cfg),
+              *WL.initial_state(cfg), tol=tol)
+    s.step(9)
+    for rec in s.series():
+        x = 0.5 * (rec[11] - rec[10]) * cfg["dt"]
+        last = 0
+        for k in range(129):
+            term = total = math.exp(k * math.log(x / 2) - math.lgamma(k + 1))
+            for j in range(1, 30):
+                term *= -(x / 2) ** 2 / (j * (j + k))
+                total += term
+            if abs(total) > tol / 4:
+                last = k
+        assert rec[9] == last + 1
