@@ -53,8 +53,9 @@ STAGE_START = [("k_begin_step", "select"), ("k_fill_u64", "expand+build"),
 def source_hash():
     """Hash of the step kernels' code, comments and blank lines ignored."""
     h = hashlib.sha256()
-    for f in ["kernels.hip", "warm.hip", "device.hpp", "kernels.hpp",
-              "warm.hpp", "warm_device.hpp", "common.hpp"]:
+    for f in ["kernels.hip", "warm.hip", "small.hip", "cap.hip", "device.hpp",
+              "kernels.hpp", "warm.hpp", "warm_device.hpp", "small.hpp",
+              "cap.hpp", "common.hpp"]:
         with open(os.path.join(HERE, "csrc", f)) as fh:
             for line in fh:
                 code = line.split("//")[0].rstrip()

@@ -104,3 +104,22 @@ def test_stage_bandwidth_reports_in_place_transfer_with_the_expansion():
     plain = bench.stage_bandwidth(M, A, {"ms": ms}, srec, 900.0, 2, 5000.0,
                                   None, in_place=False)
     assert plain["transfer"]["effective"] > 0
+
+
+def test_source_hash_covers_every_launch_of_a_step(tmp_path, monkeypatch):
+    # a change in any source that a series-propagated step runs, the one-block
+    # launches and the cuts among them, makes a committed profile stale
+    import shutil
+    shutil.copytree(os.path.join(ps.HERE, "csrc"), tmp_path / "csrc")
+    monkeypatch.setattr(ps, "HERE", str(tmp_path))
+    base = ps.source_hash()
+    for f in ("kernels.hip", "warm.hip", "small.hip", "cap.hip", "device.hpp",
+              "kernels.hpp", "warm.hpp", "warm_device.hpp", "small.hpp",
+              "cap.hpp", "common.hpp"):
+        path = tmp_path / "csrc" / f
+        text = path.read_text()
+        path.write_text(text + "\n// a comment changes nothing\n")
+        assert ps.source_hash() == base, f
+        path.write_text(text + "\nint changed;\n")
+        assert ps.source_hash() != base, f
+        path.write_text(text)
