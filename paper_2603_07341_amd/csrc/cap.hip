@@ -60,10 +60,6 @@ __global__ void __launch_bounds__(kBlock)
   __shared__ uint32_t bins[kMaxReal];
   if (*err) return;
   const int64_t n = ctl->n_new;
-  if (m.R == 1) {
-    if (gtid() == 0) ball[0] = uint32_t(n);
-    return;
-  }
   for (int r = threadIdx.x; r < m.R; r += blockDim.x) bins[r] = 0;
   __syncthreads();
   for (int64_t i = gtid(); i < n; i += gstride())
@@ -455,7 +451,7 @@ void cap_check(const DevModel& m, const StepCtl* ctl, const uint64_t* pay,
                int64_t est, int64_t cap, uint32_t* ball, int* err,
                hipStream_t s) {
   k_cap_zero<<<1, kBlock, 0, s>>>(ball, m.R, err);
-  const int g = m.R == 1 ? 1 : std::min(grid_for(est), 2048);
+  const int g = std::min(grid_for(est), 2048);
   k_cap_count<<<g, kBlock, 0, s>>>(m, ctl, pay, ball, err);
   k_cap_over<<<1, kBlock, 0, s>>>(ball, m.R, cap, err);
 }

@@ -15,8 +15,8 @@ namespace paces {
 // Passes of the radix select for W canonical key words.
 inline int cap_passes(int W) { return 16 + 8 * W; }
 
-// Rows of the new set per realization into ball[R]; latches kErrCap when
-// one exceeds cap.
+// Rows of the new set per realization into ball[R] (with one realization the
+// last lookup counts them); latches kErrCap when one exceeds cap.
 void cap_check(const DevModel& m, const StepCtl* ctl, const uint64_t* pay,
                int64_t est, int64_t cap, uint32_t* ball, int* err,
                hipStream_t s);

@@ -51,7 +51,6 @@ constexpr int kItems = 8;  // tiles of kBlock rows in flight per block
 // to exit, and with grids sized from a row estimate they cost the
 // expansion rounds about a sixth of their time.
 constexpr int kMaxGrid = 16384;
-constexpr int kFold = 256;  // blocks of the second reduction level
 
 __host__ __device__ inline int64_t cdiv(int64_t a, int64_t b) {
   return (a + b - 1) / b;

@@ -1676,9 +1676,8 @@ int pop_norm(int prec, int N, int R, double th2, int64_t est,
              double* pop_part, const Sums& sm, int* err, hipStream_t s) {
   const bool priv = R == 1 && N <= kPrivBins;
   const size_t lds = sizeof(double) * ((priv ? N * 64 : R * N) + 2 * R);
-  // batched partials hold R * N populations per block: fewer blocks
-  // a bounded grid: blocks stride over the tiles, so the per-block work
-  // (bins cleared and folded, one count added to the total) is amortised
+  // a bounded grid: blocks stride over the tiles, so the per-block work (bins
+  // cleared and folded, R * N partials written) is amortised
   const int g = std::min(sum_grid(est, kBlock), kPopBlocks);
   if (prec == 64)
     k_pop_norm<double><<<g, kBlock, lds, s>>>(

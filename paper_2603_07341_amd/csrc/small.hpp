@@ -57,8 +57,9 @@ bool small_tail(const SmallTail& a, int prec, hipStream_t s);
 // kSmallRows rows (range included) selected by threshold: what begin_step,
 // warm_begin, the k rounds, the state-cap check and warm_commit do, with the
 // same results.  Writes one partial of the dropped weight.  Latches as those
-// do (kErrBig where the set or a round's candidates are too many), and until
-// its commit changes nothing of the set but what warm_unstage restores.
+// do (kErrChunks where a round's candidates are too many) and kErrBig for a
+// larger set, and until its commit changes nothing of the set but what
+// warm_unstage restores.
 struct SmallExpand {
   DevModel m;
   int k;
