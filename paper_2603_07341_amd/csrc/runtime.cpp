@@ -2047,7 +2047,9 @@ struct Snapshot {
   }
 };
 
-paces_status take_snapshot(paces_sim* s, Snapshot& z, hipStream_t st) {
+// p0 (may be null): rows of the initial states in the snapshot's rows.
+paces_status take_snapshot(paces_sim* s, Snapshot& z, hipStream_t st,
+                           int32_t* p0 = nullptr) {
   const paces_model* m = s->m;
   const int64_t n = std::max<int64_t>(s->nlive, 1);
   ST_TRY(dalloc(&z.keys, n * m->Wi));
@@ -2065,9 +2067,14 @@ paces_status take_snapshot(paces_sim* s, Snapshot& z, hipStream_t st) {
                      s->dcount, s->sm.rows, st);
     gather_rows(m->Wi, s->A, c, s->vec[s->ipsi], idx, s->nlive, z.keys,
                 z.pay, z.tot, z.psi, st);
+    if (p0) rank_rows(idx, s->nlive, s->p0_last, p0, m->R * s->n0, st);
     HIP_TRY(hipStreamSynchronize(st));
     dfree(idx);
-  } else if (s->nS > 0) {
+  } else if (p0) {
+    HIP_TRY(hipMemcpyAsync(p0, s->p0_last, size_t(m->R * s->n0) * 4,
+                           hipMemcpyDeviceToDevice, st));
+  }
+  if (!s->has_holes && s->nS > 0) {
     HIP_TRY(hipMemcpyAsync(z.keys, c.keys, size_t(s->nS) * m->Wi * 8,
                            hipMemcpyDeviceToDevice, st));
     HIP_TRY(hipMemcpyAsync(z.pay, c.pay, size_t(s->nS) * 8,
@@ -3511,10 +3518,10 @@ paces_status paces_adjoint_forward(paces_sim* s, int64_t n_steps,
     if (i % R.C == 0) {
       Snapshot* z = new Snapshot();
       R.ck.push_back(z);
-      paces_status e = take_snapshot(s, *z, st);
       int32_t* p0 = nullptr;
-      if (!e) e = dalloc(&p0, s->n0);
+      paces_status e = dalloc(&p0, s->n0);
       R.ck_p0.push_back(p0);
+      if (!e) e = take_snapshot(s, *z, st, i ? p0 : nullptr);
       if (e) return bail(e);
       if (i == 0) {
         // the initial state sits in input order
@@ -3523,9 +3530,6 @@ paces_status paces_adjoint_forward(paces_sim* s, int64_t n_steps,
         if (hipMemcpy(p0, id.data(), id.size() * 4, hipMemcpyHostToDevice) !=
             hipSuccess)
           return bail(fail(PACES_E_HIP, "upload failed"));
-      } else if (hipMemcpyAsync(p0, s->p0_last, size_t(s->n0) * 4,
-                                hipMemcpyDeviceToDevice, st) != hipSuccess) {
-        return bail(fail(PACES_E_HIP, "copy failed"));
       }
     }
     paces_status e = do_step(s, st);

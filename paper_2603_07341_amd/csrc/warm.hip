@@ -770,6 +770,23 @@ __global__ void __launch_bounds__(kBlock)
   }
 }
 
+__global__ void __launch_bounds__(kBlock)
+    k_rank_rows(const uint32_t* idx, int64_t n, const int32_t* rows,
+                int32_t* out, int64_t n0) {
+  for (int64_t i = gtid(); i < n0; i += gstride()) {
+    const int64_t r = rows[i];
+    int64_t lo = 0, hi = r < 0 ? 0 : n;  // first listed row >= r
+    while (lo < hi) {
+      const int64_t mid = (lo + hi) / 2;
+      if (int64_t(idx[mid]) < r)
+        lo = mid + 1;
+      else
+        hi = mid;
+    }
+    out[i] = r >= 0 && lo < n && int64_t(idx[lo]) == r ? int32_t(lo) : -1;
+  }
+}
+
 }  // namespace
 
 // ---- host wrappers ----------------------------------------------------------
@@ -893,6 +910,12 @@ void gather_rows(int Wi, size_t A, const Side& c, const void* psi,
   k_gather_rows<<<grid_for(n), kBlock, 0, s>>>(
       Wi, int(A / 8), c.keys, c.pay, c.tot, static_cast<const uint64_t*>(psi),
       idx, n, keys, pay, tot, static_cast<uint64_t*>(amps));
+}
+
+void rank_rows(const uint32_t* idx, int64_t n, const int32_t* rows,
+               int32_t* out, int64_t n0, hipStream_t s) {
+  if (n0 <= 0) return;
+  k_rank_rows<<<grid_for(n0), kBlock, 0, s>>>(idx, n, rows, out, n0);
 }
 
 }  // namespace paces

@@ -114,4 +114,9 @@ void gather_rows(int Wi, size_t A, const Side& c, const void* psi,
                  const uint32_t* idx, int64_t n, uint64_t* keys,
                  uint64_t* pay, uint64_t* tot, void* amps, hipStream_t s);
 
+// out[i] = position of row rows[i] in the ascending list idx[0, n), or -1
+// (rows[i] < 0, or not listed); i < n0.
+void rank_rows(const uint32_t* idx, int64_t n, const int32_t* rows,
+               int32_t* out, int64_t n0, hipStream_t s);
+
 }  // namespace paces

@@ -228,3 +228,26 @@ def test_records_survive_the_backward_sweep():
     assert np.all(np.abs(after[:, rest] - before[:, rest]) <= tol)
     now = gs.observe()
     assert now["n_S"] == last["n_S"] and abs(now["norm2"] - last["norm2"]) <= tol
+
+
+@pytest.mark.parametrize("over,steps,ckpt", [
+    # the cap drops initial states and neighbours every step: checkpoints are
+    # taken of sets with holes, before and among the initial states' rows
+    (dict(extent=[40, 1, 1], cutoff=[7], k=2, k_init=3, max_states=400), 10, 2),
+    (dict(extent=[12, 1, 1], cutoff=[3], k=1, k_init=2, max_states=90), 17, 3),
+    # a threshold near the amplitudes themselves
+    (dict(extent=[16, 1, 1], cutoff=[4], k=1, k_init=1, theta=2e-3), 20, 4),
+])
+def test_gradient_from_checkpoints_with_holes(over, steps, ckpt):
+    cfg = dict(WL.CONFIGS["ring12"], **over)
+    p, run, init = WL.model_params(cfg), WL.run_params(cfg), WL.initial_state(cfg)
+    gs = P.Sim(P.Model(p), run, *init)
+    a = gs.adjoint_forward(steps, ckpt)
+    om = O.Model(p)
+    f = O.Frozen(om, run, *init, steps)
+    oa = f.eval(om)
+    assert np.max(np.abs(a - oa)) <= 1e-10
+    gbar = oa - target(oa)
+    g = gs.adjoint_backward(gbar)
+    _, ref = f.grad(om, gbar)
+    assert np.max(np.abs(g - ref)) <= 1e-8 * np.max(np.abs(ref))
