@@ -171,15 +171,23 @@ __device__ __forceinline__ int64_t gtid_xcd() {
   return int64_t(b) * blockDim.x + threadIdx.x;
 }
 
+// Waits until the wave's own global stores and adds have been performed in the
+// L2, which all waves of a block share.
+__device__ __forceinline__ void stores_performed() {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
 // Arrival of one block at the end of a kernel: true in every lane of the
 // block that arrives last, whose reads then see what the others wrote.  The
-// fence is every lane's: the barrier makes no wave wait for its global stores
-// and adds, so with lane 0's release alone the others' could still be on
-// their way when the ticket is counted.  The counter is left at zero for the
-// next kernel that uses it.
+// barrier makes no wave wait for its global stores and adds (they could still
+// be on their way when lane 0's ticket is counted), so every wave waits for
+// its own before it; lane 0's release then writes the L2 back for the block.
+// With a fence at agent scope in every lane each wave wrote the L2 back: a
+// pass of the device cut over 7e6 rows took 29 us instead of 15.  The counter is left at
+// zero for the next kernel that uses it.
 __device__ __forceinline__ bool last_block(uint32_t* ticket, uint32_t blocks) {
   __shared__ int last;
-  __threadfence();
+  stores_performed();
   __syncthreads();
   if (threadIdx.x == 0) {
     last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_ACQ_REL,

@@ -48,9 +48,12 @@ def test_top_pass_reads_need_before_the_block_that_writes_it():
 
 def test_last_block_orders_every_wave_before_the_ticket():
     # a barrier waits for no global store or add of the other waves: each
-    # lane makes its own visible before the one that takes the ticket goes on
-    b = body(source("common.hpp"), "last_block")
-    assert "__threadfence()" in b[:b.index("__syncthreads")]
+    # wave waits for its own before the one that takes the ticket goes on
+    text = source("common.hpp")
+    b = body(text, "last_block")
+    assert "stores_performed()" in b[:b.index("__syncthreads")]
+    assert "vmcnt(0)" in body(text, "stores_performed")
+    assert "__ATOMIC_ACQ_REL" in b and "MEMORY_SCOPE_AGENT" in b
 
 
 def test_small_record_is_addressed_before_the_count_moves_on():
