@@ -277,6 +277,7 @@ paces_status paces_run_stage(paces_sim* s, int32_t stage, void* hip_stream);
  *             dev_keys
  *   dev_psi   device complex128 [n] output, same order; must not alias
  *             dev_phi
+ *   dt        any finite number (negative: backwards in time)
  * Models with one realization only (else PACES_E_UNSUPPORTED).  A key out
  * of range or repeated is found on the device and returns PACES_E_ARG.
  * Work memory (about 60-120 bytes per row) comes from the library's
