@@ -183,8 +183,8 @@ __device__ __forceinline__ void stores_performed() {
 // be on their way when lane 0's ticket is counted), so every wave waits for
 // its own before it; lane 0's release then writes the L2 back for the block.
 // With a fence at agent scope in every lane each wave wrote the L2 back: a
-// pass of the device cut over 7e6 rows took 29 us instead of 15.  The counter is left at
-// zero for the next kernel that uses it.
+// pass of the device cut over 7e6 rows took 29 us instead of 15.  The counter
+// is left at zero for the next kernel that uses it.
 __device__ __forceinline__ bool last_block(uint32_t* ticket, uint32_t blocks) {
   __shared__ int last;
   stores_performed();
